@@ -2,7 +2,7 @@
 // (Section III-C compresses each layer's dense fp16 gradient as soon as the backward pass has
 // produced it; Section VI-C, on the compute overhead of that compression, names fusing that
 // compression into the backward kernels as the way to remove it).  dW = dY^T X is a dense
-// contraction over the tokens: MFMA 32x32x16 fp16 with fp32 accumulation, operands staged through
+// contraction over the tokens: fp16 MFMA with fp32 accumulation, operands staged through
 // LDS; the epilogue rounds each accumulator once to fp16 — the value the dense gradient tensor
 // would have held — and stores only the entries the layer's index keeps.  The dense gradient is
 // never written to or read back from HBM.
@@ -10,28 +10,39 @@
 // How the operands travel.  They arrive tokens-outer (dY is tokens x out, X is tokens x in) and go
 // global -> LDS without passing registers (global_load_lds_dwordx4: each lane names 16 bytes of
 // global memory, the wave's 1 KiB lands contiguously in LDS at a base held in M0), in the layout
-// they have in memory — per token, a run of X features then a run of dY features.  An MFMA lane
-// wants 8 tokens of one feature; the transposing LDS read ds_read_b64_tr_b16 forms that: within
-// each group of 16 lanes, lanes 4r .. 4r+3 name the 16 features of token r (r = 0..3), and lane i
-// receives feature i of those four tokens.  No transposes on the vector ALU and no registers for
-// bytes in flight: a ring of four stages, three on their way while the fourth is multiplied.
-// The compiler cannot know which LDS reads alias a copy in flight and would wait for all of them
-// before every read, so the copies are issued from inline assembly and the kernels count their
-// outstanding copies themselves: every stage is exactly 4 copies per wave, the partial last stage
-// included (rows past the last token are copied from a row of zeros).
+// they have in memory — per token, a run of features.  An MFMA lane wants 8 tokens of one feature;
+// the transposing LDS read ds_read_b64_tr_b16 forms that: within each group of 16 lanes, lanes
+// 4r .. 4r+3 name the 16 features of token r (r = 0..3), and lane i receives feature i of those four
+// tokens.  Which tokens a lane gets does not matter as long as both operands agree.  No transposes on
+// the vector ALU and no registers for bytes in flight: a ring of four stages, three on their way
+// while the fourth is multiplied.  The compiler cannot know which LDS reads alias a copy in flight
+// and would wait for all of them before every read, so the copies are issued from inline assembly
+// and the kernels count their outstanding copies themselves: every stage is exactly 4 copies per
+// wave, the partial last stage included (rows past the last token are copied from a row of zeros).
 //
-// Two tile shapes, both 8 waves with two waves per SIMD — with one wave per SIMD nothing covers a
-// wave's LDS reads and barrier waits, with two the other wave's MFMAs do (measured: 0.167 ms with
-// 4 waves of 128 x 128, 0.144 ms with 8 waves of 64 x 128, FC1 of the GPT-3 2.7B shape at 2048
-// tokens):
-//   256 x 256, waves as 4 x 2 of 64 x 128 (128 accumulators), 32 tokens per stage;
+// Two tile shapes, both 8 waves with two waves per SIMD, in two groups of four (waves 0-3, 4-7: one
+// of each group per SIMD):
+//   256 x 256, 32 tokens per stage, 64 (out) x 128 (in) per wave, 128 accumulators;
 //   128 x 128 for what is left of a layer after whole rounds of large tiles, where that is at
-//   most half a round (so also for every layer of up to 128 large tiles): two
-//   groups of four waves, each group covers the whole tile with 64 x 64 per wave (64 accumulators)
-//   and multiplies half of the tokens of every 64-token stage; group 1 hands its sums to group 0
-//   through LDS at the end.
+//   most half a round (so also for every layer of up to 128 large tiles): each group covers the whole
+//   tile with 64 x 64 per wave (64 accumulators) and multiplies half of the tokens of every 64-token
+//   stage; group 1 hands its sums to group 0 through LDS at the end.
+//
+// What bounds the large tile: power, and the overlap of its parts.  Per 32-token stage of a
+// 256 x 256 tile (all compute units, ordinary fp16 values), in cycles: the matrix instructions
+// alone 1054, the copies alone 760, the LDS reads alone 515 — but copies and multiplications
+// issued by all waves in step take 2240 (1760 interleaved), because a wave whose copies queue up
+// issues no matrix instructions and its partner on the SIMD queues up at the same moment.  So the two
+// groups run half a stage apart: while one multiplies, the other reads its fragments and issues its
+// copies, and they change places at a barrier: 1230 cycles.  From registers alone the chip sustains
+// 1655 TFLOP/s (1.70 GHz) with the 32x32x16 instruction and 1930 (1.97 GHz) with 16x16x32, which
+// touches half as many accumulators per flop: the clock gives way under the matrix units' power.
+// 16x16x32, and an order in which consecutive instructions share an operand (1.5 % over row order).
+// A 4096 x 4096 layer, before (32x32x16, all waves in step) and after: 8192 tokens 0.273 -> 0.207 ms
+// (1007 -> 1329 TFLOP/s), 2048 tokens 0.083 -> 0.066 ms.
 #include <atomic>
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 
@@ -42,17 +53,21 @@ namespace {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 
 constexpr int kWgThreads = 512;
 constexpr int kRowPitch = 1024 + 64;                 // an LDS row is one copy instruction's 1 KiB; the pad spreads rows over the banks
+constexpr int kBigPitch = 1024 + 32;                 // ... eight consecutive rows, 32 bytes of each, cover the 64 banks once
 constexpr int kStageRows = 32;
 constexpr int kStageBytes = kStageRows * kRowPitch;  // 34816
 constexpr int kStages = 4;
 constexpr int kLdsBytes = kStages * kStageBytes;     // 139264: one workgroup per CU
-constexpr int kBigTile = 256, kBigTokens = 32;       // tokens per stage: one per LDS row
-constexpr int kSmallTile = 128, kSmallTokens = 64;   // two per LDS row
+constexpr int kBigTile = 256, kBigTokens = 32;       // an LDS row holds two tokens of one operand
+constexpr int kBigStageBytes = kStageRows * kBigPitch;
+constexpr int kSmallTile = 128, kSmallTokens = 64;   // an LDS row holds two tokens of both operands
+static_assert(kStages * kBigStageBytes <= kLdsBytes, "the ring of the large tile fits");
 
 // What a workgroup knows of the layer its tile belongs to.
 struct WgradArgs {
@@ -92,6 +107,25 @@ __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] =
 __device__ __forceinline__ void dma16(const void *g, unsigned lds_byte_addr)
 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte_addr) : "memory");
+}
+
+// The same with the global addresses as a scalar base plus a 32-bit offset per lane.  A scalar
+// register that a vector instruction has written (the compiler may have parked the base in one) must
+// not be read by a memory instruction for five cycles: the wait states in front cover that.
+__device__ __forceinline__ void dma16_from(const void *base, unsigned lane_offset, unsigned lds_byte_addr)
+{
+    asm volatile("s_nop 3\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_offset), "s"(base), "s"(lds_byte_addr)
+                 : "memory");
+}
+
+// 8 tokens of one feature for an MFMA lane, from LDS rows that hold two tokens each, 512 bytes apart:
+// two transposing reads, the first tokens of four rows and their second tokens.
+__device__ __forceinline__ half8 read_pair_fragment(const unsigned char *p)
+{
+    const short4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)p);
+    const short4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)(p + 512));
+    const short8v q = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    return __builtin_bit_cast(half8, q);
 }
 
 // 8 tokens of one feature for an MFMA lane: two transposing reads of 4 tokens (LDS rows) each.
@@ -214,7 +248,7 @@ __device__ __forceinline__ int bound_settle(const WgradArgs &A, Bound b, const W
     return b.lo;
 }
 
-// The main loop both kernels share.  At the top of stage s the copies of stages s+1 and s+2 may
+// The main loop of the 128 x 128 kernel.  At the top of stage s the copies of stages s+1 and s+2 may
 // still be outstanding (8 per wave), those of stage s may not; the barrier also tells every wave
 // that the slot of stage s-1 has been read and may take stage s+3.  The 8 loads of bound_window
 // sit between the copies of stages 2 and 3 in the same counter: they are older than every stage
@@ -278,7 +312,35 @@ __device__ __forceinline__ void gather_pass(const WgradArgs &A, const _Float16 *
     }
 }
 
-// 256 x 256 tile.  LDS row j of a stage: token j as 256 X features then 256 dY features.
+// Waits until at most `younger` stages' copies of this wave are outstanding (and every LDS read has returned).
+__device__ __forceinline__ void wait_copies(int64_t younger)
+{
+    if (younger >= 2) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    else if (younger == 1) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// A bare workgroup barrier: what has to be complete before it is waited for explicitly.
+__device__ __forceinline__ void meet()
+{
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// 256 x 256 tile.  A stage is 32 LDS rows: row j < 16 tokens 2j and 2j+1 of X (256 features each),
+// row 16 + j the same two tokens of dY.  Waves 0-3 (group 0) copy X and multiply the first 128
+// columns of the tile, waves 4-7 (group 1) copy dY and multiply the others.
+//
+// The groups' half stages, b(i) the barriers all eight waves meet at:
+//   group 0:  b(0) fetch 0  b(1) multiply 0  b(2) fetch 1  b(3) multiply 1 ...
+//   group 1:  b(0)          b(1) fetch 0     b(2) multiply 0  b(3) fetch 1 ...
+// fetch s reads the stage's fragments into registers and issues the copies of stage s + 3 into the ring
+// slot of stage s - 1: group 1, the later one, has finished reading that slot before b(2s).  Stage
+// s + 1 is read from b(2s + 2) on, so every wave waits for its own copies of it before that barrier —
+// group 0 at the end of multiply s, group 1 at the end of fetch s — when the copies of stages s + 2
+// and s + 3 are the only younger ones.  The 8 loads of bound_window sit between the copies of stages 2
+// and 3 in the same counter: they are older than every stage whose wait could mistake them for its own
+// copies, so they can only make the first waits longer than needed, never shorter.
 template <int OUT>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBatch B)
 {
@@ -294,68 +356,109 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     // thread t < 256: the first bound of tile row t; thread 256 + t: its second
     const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile);
 
-    // Copy role of a lane: lanes 0-31 bring 8 features of X each, lanes 32-63 8 features of dY; one
-    // instruction of a wave moves one token.  Wave w owns rows 4w .. 4w+3 of every stage.
-    const bool is_y = lane >= 32;
-    const int features = is_y ? A.out : A.in;
-    const int f = (is_y ? row0 : col0) + (lane & 31) * 8;
+    // Copy role: one instruction of a wave moves two tokens of its group's operand, lanes 0-31 the 256
+    // features of the first, 32-63 those of the second.  Wave w owns rows 4w .. 4w+3 of every stage.
+    const int group = wave >> 2;
+    const int features = group ? A.out : A.in;
+    const int f0 = group ? row0 : col0;
     const int64_t row_bytes = (int64_t)features * 2;
-    const unsigned char *gbase = reinterpret_cast<const unsigned char *>(is_y ? A.dy : A.x) + (int64_t)(f < features ? f : 0) * 2;
-    const unsigned lds_base = (unsigned)(size_t)(LDS_AS unsigned char *)lds;
+    const unsigned f_bytes = (unsigned)(f0 + (lane & 31) * 8 < features ? (lane & 31) * 8 : 0) * 2;
+    const unsigned lane_offset = (unsigned)(lane >> 5) * (unsigned)row_bytes + f_bytes;
+    const unsigned char *gbase = reinterpret_cast<const unsigned char *>(group ? A.dy : A.x) + (int64_t)f0 * 2;
+    const unsigned lds_rows = (unsigned)(size_t)(LDS_AS unsigned char *)lds + (unsigned)(wave * 4) * kBigPitch;
     const int64_t stages = (A.tokens + kBigTokens - 1) / kBigTokens;
+    const int64_t full = A.tokens / kBigTokens;              // stages without rows past the last token
+    const int first_token = (wave & 3) * 8;                  // of the wave's rows in a stage
     auto issue_stage = [&](int64_t s) {
-        const unsigned dst = lds_base + (unsigned)(s % kStages) * kStageBytes + (unsigned)(wave * 4) * kRowPitch;
-        const int64_t token = s * kBigTokens + wave * 4;
+        const unsigned dst = lds_rows + (unsigned)(s % kStages) * kBigStageBytes;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            dma16(token + i < A.tokens ? gbase + (token + i) * row_bytes : wgrad_zero_row, dst + i * kRowPitch);
-    };
-
-    const int wo = wave & 3, wi = wave >> 2;
-    const int l32 = lane & 31, khalf = lane >> 5;
-    f32x16 acc[2][4];
-#pragma unroll
-    for (int bo = 0; bo < 2; ++bo)
-#pragma unroll
-        for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[bo][bi][r] = 0.f;
-    const int x_off = tr_lane_offset(lane) + (wi * 128) * 2, y_off = tr_lane_offset(lane) + 512 + (wo * 64) * 2;
-    auto multiply_stage = [&](const unsigned char *cur) {
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            half8 xa[4], yb[2];
-#pragma unroll
-            for (int bi = 0; bi < 4; ++bi) xa[bi] = read_tr_fragment(cur + x_off + kk * 16 * kRowPitch + bi * 64);
-#pragma unroll
-            for (int bo = 0; bo < 2; ++bo) yb[bo] = read_tr_fragment(cur + y_off + kk * 16 * kRowPitch + bo * 64);
-#pragma unroll
-            for (int bo = 0; bo < 2; ++bo)
-#pragma unroll
-                for (int bi = 0; bi < 4; ++bi)
-                    acc[bo][bi] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        for (int i = 0; i < 4; ++i) {
+            const int64_t token = s * kBigTokens + first_token + 2 * i + (lane >> 5);
+            dma16(token < A.tokens ? gbase + token * row_bytes + f_bytes : wgrad_zero_row, dst + i * kBigPitch);
         }
     };
 
+    const int wo = wave & 3, wi = group;
+    const int l16 = lane & 15, quarter = lane >> 4;
+    f32x4 acc[4][8];
+#pragma unroll
+    for (int bo = 0; bo < 4; ++bo)
+#pragma unroll
+        for (int bi = 0; bi < 8; ++bi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[bo][bi][r] = 0.f;
+    // 16 lanes read four rows, 16 features: the lane groups take rows 0-3, 4-7, 8-11, 12-15
+    const int lane_read = (lane >> 2) * kBigPitch + (lane & 3) * 8;
+    const int x_off = lane_read + wi * 128 * 2, y_off = lane_read + 16 * kBigPitch + wo * 64 * 2;
+
     for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
     const Window window = bound_window(A, open);
-    run_stages(stages, lds, issue_stage, multiply_stage);
+    wait_copies(stages - 1);
+    meet();                                                  // b(0)
+    if (group == 1) meet();                                  // half a stage behind from here on
+
+    unsigned slot = 0;                                       // LDS offset of the stage being read
+    const unsigned char *gnext = gbase + (3 * kBigTokens + first_token) * row_bytes;     // the wave's rows three stages ahead
+    auto stage = [&](int64_t s, auto steady_loop) {
+        constexpr bool kSteady = decltype(steady_loop)::value;      // stage s + 3 exists and is full
+        const unsigned char *cur = lds + slot;
+        const unsigned dst = lds_rows + (slot >= kBigStageBytes ? slot - kBigStageBytes : slot + 3 * kBigStageBytes);
+        auto copy = [&](int i) {
+            __builtin_amdgcn_sched_barrier(0);               // the copies stay spread between the LDS reads
+            if (kSteady) dma16_from(gnext + 2 * i * row_bytes, lane_offset, dst + i * kBigPitch);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        half8 xa[8], yb[4];
+#pragma unroll
+        for (int bo = 0; bo < 4; ++bo) yb[bo] = read_pair_fragment(cur + y_off + bo * 32);
+        copy(0);
+#pragma unroll
+        for (int bi = 0; bi < 8; ++bi) {
+            xa[bi] = read_pair_fragment(cur + x_off + bi * 32);
+            if (bi == 2) copy(1);
+            if (bi == 5) copy(2);
+        }
+        copy(3);
+        if (!kSteady && s + 3 < stages) issue_stage(s + 3);
+        if (group == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else wait_copies(kSteady ? 2 : stages - 2 - s);
+        __builtin_amdgcn_sched_barrier(0);
+        meet();
+        __builtin_amdgcn_s_setprio(1);                       // the multiplying wave first: the other one's reads fit in between
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 32; ++q) {
+            const int bi = q / 4, bo = (bi & 1) ? 3 - q % 4 : q % 4;
+            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        if (group == 0) wait_copies(kSteady ? 2 : stages - 2 - s);
+        meet();
+        gnext += kBigTokens * row_bytes;
+        slot = slot == (kStages - 1) * kBigStageBytes ? 0 : slot + kBigStageBytes;
+    };
+    int64_t s = 0;
+    for (; s + 3 < full; ++s) stage(s, std::true_type{});
+    for (; s < stages; ++s) stage(s, std::false_type{});
+    if (group == 0) meet();
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
     bounds[t] = bound_settle(A, open, window);
 
+    // accumulator layout: lane l holds dW[.. + (l & 15)][.. + 4 * (l >> 4) + r], r = 0..3
     _Float16 *img = reinterpret_cast<_Float16 *>(lds);
     static_assert(kTile * kEpiPitch * 2 <= kLdsBytes, "the whole tile's image fits in the stages");
 #pragma unroll
-    for (int bo = 0; bo < 2; ++bo)
+    for (int bo = 0; bo < 4; ++bo)
 #pragma unroll
-        for (int bi = 0; bi < 4; ++bi)
+        for (int bi = 0; bi < 8; ++bi) {
+            half4 h;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                half4 h;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[bo][bi][q * 4 + e];   // round to nearest even
-                const int col = wi * 128 + bi * 32 + q * 8 + khalf * 4;
-                *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 32 + l32) * kEpiPitch + col) = h;
-            }
+            for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[bo][bi][e];           // round to nearest even
+            const int col = wi * 128 + bi * 16 + quarter * 4;
+            *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + l16) * kEpiPitch + col) = h;
+        }
     __syncthreads();
     gather_pass<OUT, kTile>(A, img, kEpiPitch, bounds, bounds + kTile, row0, col0);
 }

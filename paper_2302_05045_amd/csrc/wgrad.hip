@@ -39,7 +39,8 @@
 // touches half as many accumulators per flop: the clock gives way under the matrix units' power.
 // 16x16x32, and an order in which consecutive instructions share an operand (1.5 % over row order).
 // A 4096 x 4096 layer, before (32x32x16, all waves in step) and after: 8192 tokens 0.273 -> 0.207 ms
-// (1007 -> 1329 TFLOP/s), 2048 tokens 0.083 -> 0.066 ms.
+// (1007 -> 1329 TFLOP/s), 2048 tokens 0.083 -> 0.066 ms.  The 128 x 128 tile on a 1024 x 4096 layer: 8192
+// tokens 0.087 -> 0.072 ms, 2048 tokens 0.0279 -> 0.0248.
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
@@ -58,16 +59,16 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 
 constexpr int kWgThreads = 512;
-constexpr int kRowPitch = 1024 + 64;                 // an LDS row is one copy instruction's 1 KiB; the pad spreads rows over the banks
-constexpr int kBigPitch = 1024 + 32;                 // ... eight consecutive rows, 32 bytes of each, cover the 64 banks once
+constexpr int kRowPitch = 1024 + 32;                 // an LDS row is one copy instruction's 1 KiB; with the pad eight consecutive
+                                                     // rows, 32 bytes of each, cover the 64 banks once
 constexpr int kStageRows = 32;
-constexpr int kStageBytes = kStageRows * kRowPitch;  // 34816
+constexpr int kStageBytes = kStageRows * kRowPitch;  // 33792
 constexpr int kStages = 4;
-constexpr int kLdsBytes = kStages * kStageBytes;     // 139264: one workgroup per CU
-constexpr int kBigTile = 256, kBigTokens = 32;       // an LDS row holds two tokens of one operand
-constexpr int kBigStageBytes = kStageRows * kBigPitch;
-constexpr int kSmallTile = 128, kSmallTokens = 64;   // an LDS row holds two tokens of both operands
-static_assert(kStages * kBigStageBytes <= kLdsBytes, "the ring of the large tile fits");
+constexpr int kLdsBytes = kStages * kStageBytes;     // 135168: one workgroup per CU
+constexpr int kBigTile = 256, kSmallTile = 128;
+// Tokens of one operand in an LDS row, and in a stage (16 rows of each operand).
+constexpr int row_tokens(int tile) { return 512 / tile; }
+constexpr int stage_tokens(int tile) { return 16 * row_tokens(tile); }       // 32, 64
 
 // What a workgroup knows of the layer its tile belongs to.
 struct WgradArgs {
@@ -118,32 +119,14 @@ __device__ __forceinline__ void dma16_from(const void *base, unsigned lane_offse
                  : "memory");
 }
 
-// 8 tokens of one feature for an MFMA lane, from LDS rows that hold two tokens each, 512 bytes apart:
-// two transposing reads, the first tokens of four rows and their second tokens.
-__device__ __forceinline__ half8 read_pair_fragment(const unsigned char *p)
+// 8 tokens of one feature for an MFMA lane: two transposing reads of one token of four LDS rows each,
+// the rows' tokens `step` bytes apart.
+__device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 {
     const short4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)p);
-    const short4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)(p + 512));
+    const short4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)(p + step));
     const short8v q = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     return __builtin_bit_cast(half8, q);
-}
-
-// 8 tokens of one feature for an MFMA lane: two transposing reads of 4 tokens (LDS rows) each.
-__device__ __forceinline__ half8 read_tr_fragment(const unsigned char *p)
-{
-    const short4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)p);
-    const short4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS short4v *)(LDS_AS unsigned char *)(p + 4 * kRowPitch));
-    const short8v q = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    return __builtin_bit_cast(half8, q);
-}
-
-// Byte offset, inside a stage, of a lane's first transposing read for a 32-feature block that
-// starts at byte 0 of the rows: group of 16 lanes g, lane j of the group reads LDS row
-// 8*(g>>1) + (j>>2), features 16*(g&1) + 4*(j&3) .. +3.
-__device__ __forceinline__ int tr_lane_offset(int lane)
-{
-    const int g = lane >> 4, j = lane & 15;
-    return (8 * (g >> 1) + (j >> 2)) * kRowPitch + (16 * (g & 1) + 4 * (j & 3)) * 2;
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs: each XCD gets a contiguous run of tiles so
@@ -248,27 +231,128 @@ __device__ __forceinline__ int bound_settle(const WgradArgs &A, Bound b, const W
     return b.lo;
 }
 
-// The main loop of the 128 x 128 kernel.  At the top of stage s the copies of stages s+1 and s+2 may
-// still be outstanding (8 per wave), those of stage s may not; the barrier also tells every wave
-// that the slot of stage s-1 has been read and may take stage s+3.  The 8 loads of bound_window
-// sit between the copies of stages 2 and 3 in the same counter: they are older than every stage
-// whose wait could mistake them for its own copies, so they can only make the waits of stages 0
-// to 2 longer than needed, never shorter.
-template <typename Issue, typename Multiply>
-__device__ __forceinline__ void run_stages(int64_t stages, unsigned char *lds, Issue issue_stage, Multiply multiply_stage)
+// Waits until at most `younger` stages' copies of this wave are outstanding (and every LDS read has returned).
+__device__ __forceinline__ void wait_copies(int64_t younger)
 {
-    for (int64_t s = 0; s < stages; ++s) {
-        const int64_t younger = stages - 1 - s < 2 ? stages - 1 - s : 2;
-        if (younger == 2) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-        else if (younger == 1) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (s + 3 < stages) issue_stage(s + 3);
-        multiply_stage(lds + (s % kStages) * kStageBytes);
-    }
+    if (younger >= 2) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    else if (younger == 1) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// A bare workgroup barrier: what has to be complete before it is waited for explicitly.
+__device__ __forceinline__ void meet()
+{
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The main loop: acc += the wave's OB x IB blocks of 16 x 16 of a tile.  A stage is 32 LDS rows, row j < 16
+// row_tokens(TILE) consecutive tokens of X (TILE features each), row 16 + j the same tokens of dY.
+// Waves 0-3 (group 0) copy X, waves 4-7 (group 1) dY.  x_at / y_at: byte offset, within a row, of the
+// wave's first feature of the first of the two tokens it multiplies per row.
+//
+// The groups' half stages, b(i) the barriers all eight waves meet at:
+//   group 0:  b(0) fetch 0  b(1) multiply 0  b(2) fetch 1  b(3) multiply 1 ...
+//   group 1:  b(0)          b(1) fetch 0     b(2) multiply 0  b(3) fetch 1 ...
+// fetch s reads the stage's fragments into registers and issues the copies of stage s + 3 into the ring
+// slot of stage s - 1: group 1, the later one, has finished reading that slot before b(2s).  Stage
+// s + 1 is read from b(2s + 2) on, so every wave waits for its own copies of it before that barrier —
+// group 0 at the end of multiply s, group 1 at the end of fetch s — when the copies of stages s + 2
+// and s + 3 are the only younger ones.  The 8 loads of bound_window sit between the copies of stages 2
+// and 3 in the same counter: they are older than every stage whose wait could mistake them for its own
+// copies, so they can only make the first waits longer than needed, never shorter.
+template <int TILE, int OB, int IB>
+__device__ __forceinline__ Window multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
+                                                const Bound &open, f32x4 (&acc)[OB][IB])
+{
+    constexpr int kRowTokens = row_tokens(TILE), kTokens = stage_tokens(TILE), kTokenLanes = 64 / kRowTokens;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int group = wave >> 2;
+    // Copy role: one instruction of a wave moves one row, kTokenLanes lanes per token.  Wave w owns rows 4w .. 4w+3.
+    const int features = group ? A.out : A.in;
+    const int f0 = group ? row0 : col0;
+    const int64_t row_bytes = (int64_t)features * 2;
+    const int f = lane % kTokenLanes * 8;
+    const unsigned f_bytes = (unsigned)(f0 + f < features ? f : 0) * 2;
+    const int sub = lane / kTokenLanes;
+    const unsigned lane_offset = (unsigned)sub * (unsigned)row_bytes + f_bytes;      // below 2^27: a row has at most 2^24 features
+    const unsigned char *gbase = reinterpret_cast<const unsigned char *>(group ? A.dy : A.x) + (int64_t)f0 * 2;
+    const unsigned lds_rows = (unsigned)(size_t)(LDS_AS unsigned char *)lds + (unsigned)(wave * 4) * kRowPitch;
+    const int64_t stages = (A.tokens + kTokens - 1) / kTokens;
+    const int64_t full = A.tokens / kTokens;                 // stages without rows past the last token
+    const int first_token = (wave & 3) * 4 * kRowTokens;     // of the wave's rows in a stage
+    auto issue_stage = [&](int64_t s) {
+        const unsigned dst = lds_rows + (unsigned)(s % kStages) * kStageBytes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t token = s * kTokens + first_token + kRowTokens * i + sub;
+            dma16(token < A.tokens ? gbase + token * row_bytes + f_bytes : wgrad_zero_row, dst + i * kRowPitch);
+        }
+    };
+#pragma unroll
+    for (int bo = 0; bo < OB; ++bo)
+#pragma unroll
+        for (int bi = 0; bi < IB; ++bi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[bo][bi][r] = 0.f;
+    // 16 lanes read four rows, 16 features: the lane groups take rows 0-3, 4-7, 8-11, 12-15
+    const int lane_read = (lane >> 2) * kRowPitch + (lane & 3) * 8;
+    const int x_off = lane_read + x_at, y_off = lane_read + 16 * kRowPitch + y_at;
+
+    for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
+    const Window window = bound_window(A, open);
+    wait_copies(stages - 1);
+    meet();                                                  // b(0)
+    if (group == 1) meet();                                  // half a stage behind from here on
+
+    unsigned slot = 0;                                       // LDS offset of the stage being read
+    const unsigned char *gnext = gbase + (3 * kTokens + first_token) * row_bytes;    // the wave's rows three stages ahead
+    auto stage = [&](int64_t s, auto steady_loop) {
+        constexpr bool kSteady = decltype(steady_loop)::value;      // stage s + 3 exists and is full
+        const unsigned char *cur = lds + slot;
+        const unsigned dst = lds_rows + (slot >= kStageBytes ? slot - kStageBytes : slot + 3 * kStageBytes);
+        auto copy = [&](int i) {
+            __builtin_amdgcn_sched_barrier(0);               // the copies stay spread between the LDS reads
+            if (kSteady) dma16_from(gnext + kRowTokens * i * row_bytes, lane_offset, dst + i * kRowPitch);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        half8 xa[IB], yb[OB];
+#pragma unroll
+        for (int bo = 0; bo < OB; ++bo) yb[bo] = read_fragment(cur + y_off + bo * 32, TILE * 2);
+        copy(0);
+#pragma unroll
+        for (int bi = 0; bi < IB; ++bi) {
+            xa[bi] = read_fragment(cur + x_off + bi * 32, TILE * 2);
+            if (bi == IB / 3) copy(1);
+            if (bi == 2 * IB / 3) copy(2);
+        }
+        copy(3);
+        if (!kSteady && s + 3 < stages) issue_stage(s + 3);
+        if (group == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else wait_copies(kSteady ? 2 : stages - 2 - s);
+        __builtin_amdgcn_sched_barrier(0);
+        meet();
+        __builtin_amdgcn_s_setprio(1);                       // the multiplying wave first: the other one's reads fit in between
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < OB * IB; ++q) {
+            const int bi = q / OB, bo = (bi & 1) ? OB - 1 - q % OB : q % OB;
+            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        if (group == 0) wait_copies(kSteady ? 2 : stages - 2 - s);
+        meet();
+        gnext += kTokens * row_bytes;
+        slot = slot == (kStages - 1) * kStageBytes ? 0 : slot + kStageBytes;
+    };
+    int64_t s = 0;
+    for (; s + 3 < full; ++s) stage(s, std::true_type{});
+    for (; s < stages; ++s) stage(s, std::false_type{});
+    if (group == 0) meet();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
+    return window;
 }
 
 // Epilogue over the ROWS rows of a tile held as an fp16 image in LDS: each of the 16 half-waves
@@ -312,35 +396,7 @@ __device__ __forceinline__ void gather_pass(const WgradArgs &A, const _Float16 *
     }
 }
 
-// Waits until at most `younger` stages' copies of this wave are outstanding (and every LDS read has returned).
-__device__ __forceinline__ void wait_copies(int64_t younger)
-{
-    if (younger >= 2) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-    else if (younger == 1) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-}
-
-// A bare workgroup barrier: what has to be complete before it is waited for explicitly.
-__device__ __forceinline__ void meet()
-{
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// 256 x 256 tile.  A stage is 32 LDS rows: row j < 16 tokens 2j and 2j+1 of X (256 features each),
-// row 16 + j the same two tokens of dY.  Waves 0-3 (group 0) copy X and multiply the first 128
-// columns of the tile, waves 4-7 (group 1) copy dY and multiply the others.
-//
-// The groups' half stages, b(i) the barriers all eight waves meet at:
-//   group 0:  b(0) fetch 0  b(1) multiply 0  b(2) fetch 1  b(3) multiply 1 ...
-//   group 1:  b(0)          b(1) fetch 0     b(2) multiply 0  b(3) fetch 1 ...
-// fetch s reads the stage's fragments into registers and issues the copies of stage s + 3 into the ring
-// slot of stage s - 1: group 1, the later one, has finished reading that slot before b(2s).  Stage
-// s + 1 is read from b(2s + 2) on, so every wave waits for its own copies of it before that barrier —
-// group 0 at the end of multiply s, group 1 at the end of fetch s — when the copies of stages s + 2
-// and s + 3 are the only younger ones.  The 8 loads of bound_window sit between the copies of stages 2
-// and 3 in the same counter: they are older than every stage whose wait could mistake them for its own
-// copies, so they can only make the first waits longer than needed, never shorter.
+// 256 x 256 tile: 64 (out) x 128 (in) per wave, waves as 4 x 2; both groups multiply every token.
 template <int OUT>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBatch B)
 {
@@ -355,95 +411,9 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     // thread t < 256: the first bound of tile row t; thread 256 + t: its second
     const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile);
-
-    // Copy role: one instruction of a wave moves two tokens of its group's operand, lanes 0-31 the 256
-    // features of the first, 32-63 those of the second.  Wave w owns rows 4w .. 4w+3 of every stage.
-    const int group = wave >> 2;
-    const int features = group ? A.out : A.in;
-    const int f0 = group ? row0 : col0;
-    const int64_t row_bytes = (int64_t)features * 2;
-    const unsigned f_bytes = (unsigned)(f0 + (lane & 31) * 8 < features ? (lane & 31) * 8 : 0) * 2;
-    const unsigned lane_offset = (unsigned)(lane >> 5) * (unsigned)row_bytes + f_bytes;
-    const unsigned char *gbase = reinterpret_cast<const unsigned char *>(group ? A.dy : A.x) + (int64_t)f0 * 2;
-    const unsigned lds_rows = (unsigned)(size_t)(LDS_AS unsigned char *)lds + (unsigned)(wave * 4) * kBigPitch;
-    const int64_t stages = (A.tokens + kBigTokens - 1) / kBigTokens;
-    const int64_t full = A.tokens / kBigTokens;              // stages without rows past the last token
-    const int first_token = (wave & 3) * 8;                  // of the wave's rows in a stage
-    auto issue_stage = [&](int64_t s) {
-        const unsigned dst = lds_rows + (unsigned)(s % kStages) * kBigStageBytes;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t token = s * kBigTokens + first_token + 2 * i + (lane >> 5);
-            dma16(token < A.tokens ? gbase + token * row_bytes + f_bytes : wgrad_zero_row, dst + i * kBigPitch);
-        }
-    };
-
-    const int wo = wave & 3, wi = group;
-    const int l16 = lane & 15, quarter = lane >> 4;
+    const int wo = wave & 3, wi = wave >> 2;
     f32x4 acc[4][8];
-#pragma unroll
-    for (int bo = 0; bo < 4; ++bo)
-#pragma unroll
-        for (int bi = 0; bi < 8; ++bi)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[bo][bi][r] = 0.f;
-    // 16 lanes read four rows, 16 features: the lane groups take rows 0-3, 4-7, 8-11, 12-15
-    const int lane_read = (lane >> 2) * kBigPitch + (lane & 3) * 8;
-    const int x_off = lane_read + wi * 128 * 2, y_off = lane_read + 16 * kBigPitch + wo * 64 * 2;
-
-    for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
-    const Window window = bound_window(A, open);
-    wait_copies(stages - 1);
-    meet();                                                  // b(0)
-    if (group == 1) meet();                                  // half a stage behind from here on
-
-    unsigned slot = 0;                                       // LDS offset of the stage being read
-    const unsigned char *gnext = gbase + (3 * kBigTokens + first_token) * row_bytes;     // the wave's rows three stages ahead
-    auto stage = [&](int64_t s, auto steady_loop) {
-        constexpr bool kSteady = decltype(steady_loop)::value;      // stage s + 3 exists and is full
-        const unsigned char *cur = lds + slot;
-        const unsigned dst = lds_rows + (slot >= kBigStageBytes ? slot - kBigStageBytes : slot + 3 * kBigStageBytes);
-        auto copy = [&](int i) {
-            __builtin_amdgcn_sched_barrier(0);               // the copies stay spread between the LDS reads
-            if (kSteady) dma16_from(gnext + 2 * i * row_bytes, lane_offset, dst + i * kBigPitch);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        half8 xa[8], yb[4];
-#pragma unroll
-        for (int bo = 0; bo < 4; ++bo) yb[bo] = read_pair_fragment(cur + y_off + bo * 32);
-        copy(0);
-#pragma unroll
-        for (int bi = 0; bi < 8; ++bi) {
-            xa[bi] = read_pair_fragment(cur + x_off + bi * 32);
-            if (bi == 2) copy(1);
-            if (bi == 5) copy(2);
-        }
-        copy(3);
-        if (!kSteady && s + 3 < stages) issue_stage(s + 3);
-        if (group == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        else wait_copies(kSteady ? 2 : stages - 2 - s);
-        __builtin_amdgcn_sched_barrier(0);
-        meet();
-        __builtin_amdgcn_s_setprio(1);                       // the multiplying wave first: the other one's reads fit in between
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < 32; ++q) {
-            const int bi = q / 4, bo = (bi & 1) ? 3 - q % 4 : q % 4;
-            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
-        if (group == 0) wait_copies(kSteady ? 2 : stages - 2 - s);
-        meet();
-        gnext += kBigTokens * row_bytes;
-        slot = slot == (kStages - 1) * kBigStageBytes ? 0 : slot + kBigStageBytes;
-    };
-    int64_t s = 0;
-    for (; s + 3 < full; ++s) stage(s, std::true_type{});
-    for (; s < stages; ++s) stage(s, std::false_type{});
-    if (group == 0) meet();
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
+    const Window window = multiply_tile<kTile>(A, row0, col0, wi * 128 * 2, wo * 64 * 2, lds, open, acc);
     bounds[t] = bound_settle(A, open, window);
 
     // accumulator layout: lane l holds dW[.. + (l & 15)][.. + 4 * (l >> 4) + r], r = 0..3
@@ -456,15 +426,14 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
             half4 h;
 #pragma unroll
             for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[bo][bi][e];           // round to nearest even
-            const int col = wi * 128 + bi * 16 + quarter * 4;
-            *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + l16) * kEpiPitch + col) = h;
+            const int col = wi * 128 + bi * 16 + (lane >> 4) * 4;
+            *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
         }
     __syncthreads();
     gather_pass<OUT, kTile>(A, img, kEpiPitch, bounds, bounds + kTile, row0, col0);
 }
 
-// 128 x 128 tile.  LDS row j of a stage: token j and token j + 32, each as 128 X features then
-// 128 dY features; wave group g multiplies the tokens in slot g of the rows.
+// 128 x 128 tile: 64 x 64 per wave, the waves of a group as 2 x 2; group g multiplies tokens 2g and 2g + 1 of every row.
 template <int OUT>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradBatch B)
 {
@@ -480,55 +449,11 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     // thread t < 128: the first bound of tile row t; thread 128 + t: its second; the rest: none
     const Bound open = t < 2 * kTile ? bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile) : Bound{0, 0, 0};
-
-    // Copy role of a lane: token row + 32 * (lane >> 5); of its 32 lanes the first 16 bring 8
-    // features of X each, the other 16 8 features of dY.  Wave w owns rows 4w .. 4w+3.
-    const bool is_y = (lane & 16) != 0;
-    const int features = is_y ? A.out : A.in;
-    const int f = (is_y ? row0 : col0) + (lane & 15) * 8;
-    const int64_t row_bytes = (int64_t)features * 2;
-    const unsigned char *gbase = reinterpret_cast<const unsigned char *>(is_y ? A.dy : A.x) + (int64_t)(f < features ? f : 0) * 2;
-    const int lane_token = wave * 4 + 32 * (lane >> 5);
-    const unsigned lds_base = (unsigned)(size_t)(LDS_AS unsigned char *)lds;
-    const int64_t stages = (A.tokens + kSmallTokens - 1) / kSmallTokens;
-    auto issue_stage = [&](int64_t s) {
-        const unsigned dst = lds_base + (unsigned)(s % kStages) * kStageBytes + (unsigned)(wave * 4) * kRowPitch;
-        const int64_t token = s * kSmallTokens + lane_token;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            dma16(token + i < A.tokens ? gbase + (token + i) * row_bytes : wgrad_zero_row, dst + i * kRowPitch);
-    };
-
-    const int half = wave >> 2;                   // which 32 tokens of a stage
+    const int half = wave >> 2;
     const int wo = wave & 1, wi = (wave >> 1) & 1;
-    const int l32 = lane & 31, khalf = lane >> 5;
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int bo = 0; bo < 2; ++bo)
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[bo][bi][r] = 0.f;
-    const int x_off = tr_lane_offset(lane) + half * 512 + (wi * 64) * 2, y_off = tr_lane_offset(lane) + half * 512 + 256 + (wo * 64) * 2;
-    auto multiply_stage = [&](const unsigned char *cur) {
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            half8 xa[2], yb[2];
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi) xa[bi] = read_tr_fragment(cur + x_off + kk * 16 * kRowPitch + bi * 64);
-#pragma unroll
-            for (int bo = 0; bo < 2; ++bo) yb[bo] = read_tr_fragment(cur + y_off + kk * 16 * kRowPitch + bo * 64);
-#pragma unroll
-            for (int bo = 0; bo < 2; ++bo)
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
-                    acc[bo][bi] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
-        }
-    };
-
-    for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
-    const Window window = bound_window(A, open);
-    run_stages(stages, lds, issue_stage, multiply_stage);
+    f32x4 acc[4][4];
+    const int tokens_at = half * 2 * kTile * 2;
+    const Window window = multiply_tile<kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
     const int closed = bound_settle(A, open, window);
     if (t < 2 * kTile) bounds[t] = closed;
 
@@ -538,33 +463,26 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     _Float16 *img = reinterpret_cast<_Float16 *>(lds + kTile * kSumPitch * 4);
     if (half == 1) {
 #pragma unroll
-        for (int bo = 0; bo < 2; ++bo)
+        for (int bo = 0; bo < 4; ++bo)
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = wi * 64 + bi * 32 + q * 8 + khalf * 4;
-                    *reinterpret_cast<float4 *>(sums + (wo * 64 + bo * 32 + l32) * kSumPitch + col) =
-                        make_float4(acc[bo][bi][q * 4], acc[bo][bi][q * 4 + 1], acc[bo][bi][q * 4 + 2], acc[bo][bi][q * 4 + 3]);
-                }
+            for (int bi = 0; bi < 4; ++bi) {
+                const int col = wi * 64 + bi * 16 + (lane >> 4) * 4;
+                *reinterpret_cast<f32x4 *>(sums + (wo * 64 + bo * 16 + (lane & 15)) * kSumPitch + col) = acc[bo][bi];
+            }
     }
     __syncthreads();
     if (half == 0) {
 #pragma unroll
-        for (int bo = 0; bo < 2; ++bo)
+        for (int bo = 0; bo < 4; ++bo)
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
+            for (int bi = 0; bi < 4; ++bi) {
+                const int col = wi * 64 + bi * 16 + (lane >> 4) * 4;
+                const f32x4 o = *reinterpret_cast<const f32x4 *>(sums + (wo * 64 + bo * 16 + (lane & 15)) * kSumPitch + col);
+                half4 h;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = wi * 64 + bi * 32 + q * 8 + khalf * 4;
-                    const float4 o = *reinterpret_cast<const float4 *>(sums + (wo * 64 + bo * 32 + l32) * kSumPitch + col);
-                    half4 h;                                                 // round to nearest even
-                    h[0] = (_Float16)(acc[bo][bi][q * 4] + o.x);
-                    h[1] = (_Float16)(acc[bo][bi][q * 4 + 1] + o.y);
-                    h[2] = (_Float16)(acc[bo][bi][q * 4 + 2] + o.z);
-                    h[3] = (_Float16)(acc[bo][bi][q * 4 + 3] + o.w);
-                    *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 32 + l32) * kEpiPitch + col) = h;
-                }
+                for (int e = 0; e < 4; ++e) h[e] = (_Float16)(acc[bo][bi][e] + o[e]);   // round to nearest even
+                *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
+            }
     }
     __syncthreads();
     gather_pass<OUT, kTile>(A, img, kEpiPitch, bounds, bounds + kTile, row0, col0);

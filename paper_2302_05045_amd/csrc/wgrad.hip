@@ -91,12 +91,12 @@ struct WgradArgs {
 struct WgradBatch {
     WgradJob job[kWgradMaxJobs];
     int tiles_out[kWgradMaxJobs], tiles_in[kWgradMaxJobs];
-    int64_t first_tile[kWgradMaxJobs + 1];
+    int first_tile[kWgradMaxJobs + 1];       // 32 bits: a layer of less than 2^31 elements, sides up to 2^24, has about 10^5 tiles at most
     int jobs;
     float inv_scale;
     int accumulate;
     int quadrants;
-    int64_t first, tiles;
+    int first, tiles;
 };
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
@@ -137,27 +137,27 @@ __device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 // that lies outside the matrix.
 __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, int &row0, int &col0)
 {
-    const int64_t blocks = B.quadrants ? B.tiles * 4 : B.tiles;
-    const int64_t per_xcd = (blocks + 7) / 8;
-    const int64_t local = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int blocks = B.quadrants ? B.tiles * 4 : B.tiles;
+    const int per_xcd = (blocks + 7) / 8;
+    const int local = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (local >= blocks) return false;
-    const int64_t listed = B.first + (B.quadrants ? local >> 2 : local);
+    const int listed = B.first + (B.quadrants ? local >> 2 : local);
     int j = 0;
     while (j + 1 < B.jobs && listed >= B.first_tile[j + 1]) ++j;
     const WgradJob &J = B.job[j];
     A.dy = J.dy; A.x = J.x; A.tokens = J.tokens; A.out = J.out; A.in = J.in;
     A.idx = J.idx; A.seg_ptr = J.seg_ptr; A.nnz = J.nnz; A.gc = J.gc;
     A.inv_scale = B.inv_scale; A.accumulate = B.accumulate;
-    const int64_t tile = listed - B.first_tile[j];
+    const int tile = listed - B.first_tile[j];
     const int tiles_out = B.tiles_out[j], tiles_in = B.tiles_in[j];
-    const int group = (int)(tile / (4 * tiles_in));
-    const int in_group = (int)(tile - (int64_t)group * 4 * tiles_in);
+    const int group = tile / (4 * tiles_in);
+    const int in_group = tile - group * 4 * tiles_in;
     const int group_rows = tiles_out - group * 4 < 4 ? tiles_out - group * 4 : 4;
     row0 = (group * 4 + in_group % group_rows) * kBigTile;   // first row of dW (feature of dY)
     col0 = (in_group / group_rows) * kBigTile;               // first column of dW (feature of X)
     if (B.quadrants) {
-        row0 += (int)(local & 1) * kSmallTile;
-        col0 += (int)((local >> 1) & 1) * kSmallTile;
+        row0 += (local & 1) * kSmallTile;
+        col0 += ((local >> 1) & 1) * kSmallTile;
     }
     return row0 < A.out && col0 < A.in;
 }
@@ -165,7 +165,7 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
 // The kept entries of a tile row are a run of idx between two bounds: the first kept position at
 // or after the row's first column in the tile, and the first one at or after the column where the
 // tile ends.  A bound is searched in three steps with the tile's other work between them:
-// bound_open reads the segment's range from seg_ptr, bound_window requests a few entries of idx
+// bound_open reads the segment's range from seg_ptr, bound_window requests the entries of idx around
 // where the bound should be, bound_settle decides.
 struct Bound {
     int lo, hi, key;
@@ -186,42 +186,55 @@ __device__ __forceinline__ Bound bound_open(const WgradArgs &A, int row, int col
     return b;
 }
 
-// First a guess by interpolation inside the segment (kept elements spread evenly over it would
-// put the bound at lo + (hi - lo) * offset / 1024) and a look at the 8 entries around it — on
-// masks without structure that settles it in one round trip; then bisection of what is left.
-// The look is requested by bound_window and used by bound_settle, which a kernel calls after its
-// main loop: the entries travel while the tile is multiplied.
+// The guess is an interpolation inside the segment (kept elements spread evenly over it would put the
+// bound at lo + (hi - lo) * offset / 1024), the look takes the 32 entries around it as eight vectors:
+// on masks without structure the bound of a segment with k kept of 1024 is within sqrt(k (1 - k / 1024)) / 2
+// of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %), so a look of 32 misses hardly
+// ever, where one of 8 left a third of the bounds of a 10 % mask to a bisection of six dependent loads
+// (2.2 us per tile).  What is left after a miss is bisected.
+// The look is requested by bound_window near the end of the main loop and used by bound_settle after it.
+constexpr int kLook = 32;
+typedef int Look __attribute__((ext_vector_type(4), aligned(4)));
 struct Window {
-    int w0, wn;
-    int v[8];
+    int w0, wn;              // entries w0 .. w0 + wn - 1; wn = 0: nothing was requested
+    Look v[kLook / 4];
 };
+
+// First entry of vector i of a window: the last ones of a short range overlap, every vector lies inside it.
+__device__ __forceinline__ int look_start(const Window &w, int i)
+{
+    return w.w0 + (4 * i + 4 <= w.wn ? 4 * i : w.wn - 4);
+}
 
 __device__ __forceinline__ Window bound_window(const WgradArgs &A, const Bound &b)
 {
     Window w;
     w.w0 = 0; w.wn = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w.v[i] = 0;
-    if (b.lo < b.hi) {
+    for (int i = 0; i < kLook / 4; ++i) w.v[i] = Look{0, 0, 0, 0};
+    if (b.hi - b.lo >= 4) {
         const int guess = b.lo + (int)(((int64_t)(b.hi - b.lo) * (b.key & (kSeg - 1))) >> 10);
-        w.w0 = guess - 4 > b.lo ? guess - 4 : b.lo;
-        if (w.w0 + 8 > b.hi) w.w0 = b.hi - 8 > b.lo ? b.hi - 8 : b.lo;
-        w.wn = b.hi - w.w0 < 8 ? b.hi - w.w0 : 8;
+        w.w0 = guess - kLook / 2 > b.lo ? guess - kLook / 2 : b.lo;
+        if (w.w0 + kLook > b.hi) w.w0 = b.hi - kLook > b.lo ? b.hi - kLook : b.lo;
+        w.wn = b.hi - w.w0 < kLook ? b.hi - w.w0 : kLook;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w.v[i] = A.idx[w.w0 + (i < w.wn ? i : w.wn - 1)];
+        for (int i = 0; i < kLook / 4; ++i) w.v[i] = *reinterpret_cast<const Look *>(A.idx + look_start(w, i));
     }
     return w;
 }
 
 __device__ __forceinline__ int bound_settle(const WgradArgs &A, Bound b, const Window &w)
 {
-    if (b.lo < b.hi) {
-        int below = 0;
+    if (w.wn > 0) {
+        int at = w.w0;                                           // after the last entry of the look that is below the key
 #pragma unroll
-        for (int i = 0; i < 8; ++i) below += (i < w.wn && w.v[i] < b.key) ? 1 : 0;
-        if (below == 0) b.hi = w.w0;                             // the bound is at or before the window
-        else if (below == w.wn) b.lo = w.w0 + w.wn;              // at or after its end
-        else b.lo = b.hi = w.w0 + below;                         // inside
+        for (int i = 0; i < kLook / 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (w.v[i][e] < b.key) at = look_start(w, i) + e + 1;
+        if (at == w.w0) b.hi = w.w0;                             // the bound is at or before the look
+        else if (at == w.w0 + w.wn) b.lo = at;                   // at or after its end
+        else b.lo = b.hi = at;                                   // inside
     }
     while (b.lo < b.hi) {
         const int mid = (b.lo + b.hi) >> 1;
@@ -249,7 +262,8 @@ __device__ __forceinline__ void meet()
 // The main loop: acc += the wave's OB x IB blocks of 16 x 16 of a tile.  A stage is 32 LDS rows, row j < 16
 // row_tokens(TILE) consecutive tokens of X (TILE features each), row 16 + j the same tokens of dY.
 // Waves 0-3 (group 0) copy X, waves 4-7 (group 1) dY.  x_at / y_at: byte offset, within a row, of the
-// wave's first feature of the first of the two tokens it multiplies per row.
+// wave's first feature of the first of the two tokens it multiplies per row.  Returns the thread's bound;
+// the ring is free after the next __syncthreads.
 //
 // The groups' half stages, b(i) the barriers all eight waves meet at:
 //   group 0:  b(0) fetch 0  b(1) multiply 0  b(2) fetch 1  b(3) multiply 1 ...
@@ -258,11 +272,12 @@ __device__ __forceinline__ void meet()
 // slot of stage s - 1: group 1, the later one, has finished reading that slot before b(2s).  Stage
 // s + 1 is read from b(2s + 2) on, so every wave waits for its own copies of it before that barrier —
 // group 0 at the end of multiply s, group 1 at the end of fetch s — when the copies of stages s + 2
-// and s + 3 are the only younger ones.  The 8 loads of bound_window sit between the copies of stages 2
-// and 3 in the same counter: they are older than every stage whose wait could mistake them for its own
-// copies, so they can only make the first waits longer than needed, never shorter.
+// and s + 3 are the only younger ones.  The loads of bound_open are older than every copy.  Those of
+// bound_window are requested when the last full stage is on its way: the wait for bound_open's results
+// is a wait for every copy in flight, once, where only one or two stages are; after it they can only make
+// the waits of the last stages longer than needed, never shorter.
 template <int TILE, int OB, int IB>
-__device__ __forceinline__ Window multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
+__device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
                                                 const Bound &open, f32x4 (&acc)[OB][IB])
 {
     constexpr int kRowTokens = row_tokens(TILE), kTokens = stage_tokens(TILE), kTokenLanes = 64 / kRowTokens;
@@ -300,7 +315,6 @@ __device__ __forceinline__ Window multiply_tile(const WgradArgs &A, int row0, in
     const int x_off = lane_read + x_at, y_off = lane_read + 16 * kRowPitch + y_at;
 
     for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
-    const Window window = bound_window(A, open);
     wait_copies(stages - 1);
     meet();                                                  // b(0)
     if (group == 1) meet();                                  // half a stage behind from here on
@@ -348,53 +362,85 @@ __device__ __forceinline__ Window multiply_tile(const WgradArgs &A, int row0, in
     };
     int64_t s = 0;
     for (; s + 3 < full; ++s) stage(s, std::true_type{});
+    const Window window = bound_window(A, open);
     for (; s < stages; ++s) stage(s, std::false_type{});
     if (group == 0) meet();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-    return window;
+    return bound_settle(A, open, window);
 }
 
 // Epilogue over the ROWS rows of a tile held as an fp16 image in LDS: each of the 16 half-waves
 // takes every 16th row, all of them at once; per row, idx between the row's two bounds is read
 // coalesced, the values are picked from the image and the compressed gradient is written
-// coalesced.
+// coalesced, 32 entries of every row a step.  What a step needs from memory (idx, and the old values where it
+// accumulates) is requested for kAhead steps together; the first kAhead steps' idx is requested by
+// begin(), before the image exists, and travels while it is written; the old values by request_old(), when
+// the accumulators' registers are free.
 template <int OUT, int ROWS>
-__device__ __forceinline__ void gather_pass(const WgradArgs &A, const _Float16 *img, int pitch, const int *first, const int *last,
-                                            int first_row, int col0)
-{
-    constexpr int kRows = ROWS / (kWgThreads / 32);
-    const int hw = threadIdx.x >> 5, l32 = threadIdx.x & 31;
-    int lo[kRows], hi[kRows], longest = 0;
+struct GatherPass {
+    static constexpr int kRows = ROWS / (kWgThreads / 32), kAhead = 2;
+    int lo[kRows], hi[kRows], longest;
+    int pos[kAhead][kRows];                  // -1: past the end of the row's run
+    _Float16 old[kAhead][kRows];
+
+    __device__ __forceinline__ void request_idx(const WgradArgs &A, int step)
+    {
+        const int l32 = threadIdx.x & 31;
 #pragma unroll
-    for (int it = 0; it < kRows; ++it) {
-        lo[it] = first[it * 16 + hw];
-        hi[it] = last[it * 16 + hw];
-        longest = hi[it] - lo[it] > longest ? hi[it] - lo[it] : longest;
-    }
-    for (int off_k = l32; off_k - l32 < longest; off_k += 32) {
-        int pos[kRows];
+        for (int a = 0; a < kAhead; ++a)
 #pragma unroll
-        for (int it = 0; it < kRows; ++it) {
-            const int k = lo[it] + off_k;
-            pos[it] = k < hi[it] ? (A.idx ? A.idx[k] : k) : -1;
-        }
-#pragma unroll
-        for (int it = 0; it < kRows; ++it) {
-            if (pos[it] < 0) continue;
-            const int k = lo[it] + off_k;
-            const int rl = it * 16 + hw;
-            const int64_t base = (int64_t)(first_row + rl) * A.in + col0;
-            const _Float16 v = img[rl * pitch + (int)(pos[it] - base)];
-            if (OUT == kOutF32) {
-                reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
-            } else {
-                _Float16 *dst = reinterpret_cast<_Float16 *>(A.gc) + k;
-                *dst = A.accumulate ? (_Float16)(*dst + v) : v;
+            for (int it = 0; it < kRows; ++it) {
+                const int k = lo[it] + (step + a) * 32 + l32;
+                pos[a][it] = k < hi[it] ? (A.idx ? A.idx[k] : k) : -1;
             }
+    }
+    __device__ __forceinline__ void request_old(const WgradArgs &A, int step)
+    {
+        if (OUT != kOutF16 || !A.accumulate) return;
+        const int l32 = threadIdx.x & 31;
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) {
+                const int k = lo[it] + (step + a) * 32 + l32;
+                old[a][it] = k < hi[it] ? reinterpret_cast<const _Float16 *>(A.gc)[k] : (_Float16)0.f;
+            }
+    }
+    __device__ __forceinline__ void begin(const WgradArgs &A, const int *first, const int *last)
+    {
+        const int hw = threadIdx.x >> 5;
+        longest = 0;
+#pragma unroll
+        for (int it = 0; it < kRows; ++it) {
+            lo[it] = first[it * 16 + hw];
+            hi[it] = last[it * 16 + hw];
+            longest = hi[it] - lo[it] > longest ? hi[it] - lo[it] : longest;
+        }
+        request_idx(A, 0);
+    }
+    __device__ __forceinline__ void finish(const WgradArgs &A, const _Float16 *img, int pitch, int first_row, int col0)
+    {
+        const int hw = threadIdx.x >> 5, l32 = threadIdx.x & 31;
+        for (int step = 0; step * 32 < longest; step += kAhead) {
+            if (step > 0) {
+                request_idx(A, step);
+                request_old(A, step);
+            }
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+                for (int it = 0; it < kRows; ++it) {
+                    if (pos[a][it] < 0) continue;
+                    const int k = lo[it] + (step + a) * 32 + l32;
+                    const int rl = it * 16 + hw;
+                    // positions of a layer fit 32 bits
+                    const _Float16 v = img[rl * pitch + (pos[a][it] - ((first_row + rl) * A.in + col0))];
+                    if (OUT == kOutF32) reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
+                    else reinterpret_cast<_Float16 *>(A.gc)[k] = A.accumulate ? (_Float16)(old[a][it] + v) : v;
+                }
         }
     }
-}
+};
 
 // 256 x 256 tile: 64 (out) x 128 (in) per wave, waves as 4 x 2; both groups multiply every token.
 template <int OUT>
@@ -413,8 +459,10 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile);
     const int wo = wave & 3, wi = wave >> 2;
     f32x4 acc[4][8];
-    const Window window = multiply_tile<kTile>(A, row0, col0, wi * 128 * 2, wo * 64 * 2, lds, open, acc);
-    bounds[t] = bound_settle(A, open, window);
+    bounds[t] = multiply_tile<kTile>(A, row0, col0, wi * 128 * 2, wo * 64 * 2, lds, open, acc);
+    __syncthreads();
+    GatherPass<OUT, kTile> gather;
+    gather.begin(A, bounds, bounds + kTile);
 
     // accumulator layout: lane l holds dW[.. + (l & 15)][.. + 4 * (l >> 4) + r], r = 0..3
     _Float16 *img = reinterpret_cast<_Float16 *>(lds);
@@ -429,8 +477,9 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
             const int col = wi * 128 + bi * 16 + (lane >> 4) * 4;
             *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
         }
+    gather.request_old(A, 0);
     __syncthreads();
-    gather_pass<OUT, kTile>(A, img, kEpiPitch, bounds, bounds + kTile, row0, col0);
+    gather.finish(A, img, kEpiPitch, row0, col0);
 }
 
 // 128 x 128 tile: 64 x 64 per wave, the waves of a group as 2 x 2; group g multiplies tokens 2g and 2g + 1 of every row.
@@ -453,9 +502,11 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     const int wo = wave & 1, wi = (wave >> 1) & 1;
     f32x4 acc[4][4];
     const int tokens_at = half * 2 * kTile * 2;
-    const Window window = multiply_tile<kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
-    const int closed = bound_settle(A, open, window);
+    const int closed = multiply_tile<kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
     if (t < 2 * kTile) bounds[t] = closed;
+    __syncthreads();
+    GatherPass<OUT, kTile> gather;
+    gather.begin(A, bounds, bounds + kTile);
 
     // group 1's sums -> LDS as fp32; group 0 adds them to its own, rounds once to fp16 and writes
     // the image behind them
@@ -484,8 +535,9 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
                 *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
             }
     }
+    gather.request_old(A, 0);
     __syncthreads();
-    gather_pass<OUT, kTile>(A, img, kEpiPitch, bounds, bounds + kTile, row0, col0);
+    gather.finish(A, img, kEpiPitch, row0, col0);
 }
 
 // What the matrix units sustain with nothing to fetch: every wave issues eight independent
@@ -565,7 +617,7 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
         b.job[k] = jobs[j];
         b.tiles_out[k] = (int)ceil_div(jobs[j].out, kBigTile);
         b.tiles_in[k] = (int)ceil_div(jobs[j].in, kBigTile);
-        b.first_tile[k + 1] = b.first_tile[k] + (int64_t)b.tiles_out[k] * b.tiles_in[k];
+        b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
     }
     if (b.jobs == 0) return hipSuccess;
     for (int k = b.jobs; k < kWgradMaxJobs; ++k) {
@@ -573,14 +625,14 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
     }
     int cus = 0;
     if (hipError_t e = configure_once(&cus)) return e;
-    const int64_t big_tiles = b.first_tile[b.jobs];
+    const int big_tiles = b.first_tile[b.jobs];
     const int force = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
     const int round = knob(SAMO_KNOB_WGRAD_ROUND, 0);          // test aid: tiles per round in place of the CU count
     if (round > 0) cus = round;
     // Large tiles in whole rounds of the compute units; what is left over after the last whole
     // round goes to the small shape when that is the quicker way to finish it: up to half a round
     // of large tiles is at most two rounds of small ones, and a small round takes 0.4 of a large.
-    int64_t as_big = big_tiles, as_small = 0;
+    int as_big = big_tiles, as_small = 0;
     if (force == kSmallTile) as_big = 0, as_small = big_tiles;
     else if (force != kBigTile && cus > 0 && big_tiles % cus != 0 && big_tiles % cus <= cus / 2) {
         as_small = big_tiles % cus;

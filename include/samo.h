@@ -172,6 +172,19 @@ typedef struct {
     int64_t *nnz;
 } samo_index_job;
 samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_jobs, void *stream);
+/* Counting and filling as two calls that read the mask once, for callers that allocate the index
+ * in between.  samo_index_flags_bytes: the size of a device buffer (16-byte aligned) that holds one flag
+ * bit per element of a layer, rounded up to whole groups of segments.
+ * samo_count_flags_batched: what samo_build_index_batched does for jobs that only count (idx and
+ * idx_capacity are ignored), and every job's flag bits are left in h_flags[j], a HOST array of
+ * DEVICE pointers.
+ * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
+ * flag bits and the seg_ptr such a call left, later on the same stream; the mask is not read. */
+samo_status samo_index_flags_bytes(int64_t n, size_t *bytes);
+samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,
+                                     void *stream);
+samo_status samo_fill_index_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,
+                                    void *stream);
 /* seg_ptr for an index that came from elsewhere (e.g. straight from a pruner). */
 samo_status samo_build_seg_ptr(const int32_t *d_idx, int64_t nnz, int64_t n,
                                int32_t *d_seg_ptr, void *stream);

@@ -105,6 +105,11 @@ _SIGNATURES = {
     "samo_build_index": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64,
                                           ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "samo_build_index_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.c_int32, ctypes.c_void_p]),
+    "samo_index_flags_bytes": (ctypes.c_int32, [ctypes.c_int64, ctypes.POINTER(ctypes.c_size_t)]),
+    "samo_count_flags_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.POINTER(ctypes.c_void_p),
+                                                  ctypes.c_int32, ctypes.c_void_p]),
+    "samo_fill_index_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.POINTER(ctypes.c_void_p),
+                                                 ctypes.c_int32, ctypes.c_void_p]),
     "samo_build_seg_ptr": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
                                             ctypes.c_void_p]),
     "samo_validate_index": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
@@ -209,6 +214,12 @@ def samo_index_workspace_bytes(n: int) -> int:
     return out.value
 
 
+def samo_index_flags_bytes(n: int) -> int:
+    out = ctypes.c_size_t()
+    _check(lib().samo_index_flags_bytes(int(n), ctypes.byref(out)), "samo_index_flags_bytes")
+    return out.value
+
+
 def status_string(status: int) -> str:
     return lib().samo_status_string(int(status)).decode()
 
@@ -269,16 +280,36 @@ def samo_build_index(mask: torch.Tensor) -> Index:
 
     Reads the count back to size the index (one host synchronisation; the index is built
     once per pruning, not per iteration)."""
-    n = mask.numel()
-    seg_ptr = torch.empty(samo_seg_ptr_len(n), dtype=torch.int32, device=mask.device)
-    nnz_out = torch.empty(1, dtype=torch.int64, device=mask.device)
-    samo_count_nonzero(mask, seg_ptr, nnz_out)
-    nnz = int(nnz_out.item())
-    if nnz < 0:
-        raise SamoError(SAMO_ERR_INDEX, "samo_count_nonzero (the device-side scan gave up)")
-    idx = torch.empty(nnz, dtype=torch.int32, device=mask.device)
-    samo_build_index_into(mask, idx, seg_ptr, nnz_out)
-    return Index(idx, seg_ptr, nnz, n)
+    return _build_indices([mask], "samo_build_index")[0]
+
+
+def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
+    """Index of every mask: one batched count that reads the masks and leaves their flag bits, one read-back
+    of the counts to size the indices, one batched fill from the flag bits."""
+    dev, k = masks[0].device, len(masks)
+    jobs, flags, sizes = (IndexJob * k)(), (ctypes.c_void_p * k)(), []
+    nnz_out = torch.empty(k, dtype=torch.int64, device=dev)
+    seg_ptrs, at = [], 0
+    for m in masks:
+        sizes.append(samo_index_flags_bytes(m.numel()))
+    flag_buf = torch.empty(max(sum(sizes), 1), dtype=torch.uint8, device=dev)      # used and freed in stream order
+    for i, m in enumerate(masks):
+        n = m.numel()
+        seg_ptrs.append(torch.empty(samo_seg_ptr_len(n), dtype=torch.int32, device=dev))
+        jobs[i] = IndexJob(_dev(m, torch.uint8, "mask"), n, None, 0, seg_ptrs[i].data_ptr(), nnz_out.data_ptr() + 8 * i)
+        flags[i] = flag_buf.data_ptr() + at
+        at += sizes[i]
+    _check(lib().samo_count_flags_batched(jobs, flags, k, _stream()), where)
+    counts = nnz_out.cpu().tolist()
+    if any(c < 0 for c in counts):
+        raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
+    out = []
+    for i, (m, c) in enumerate(zip(masks, counts)):
+        idx = torch.empty(c, dtype=torch.int32, device=dev)
+        jobs[i].idx, jobs[i].idx_capacity = (idx.data_ptr() if c else None), c
+        out.append(Index(idx, seg_ptrs[i], c, m.numel()))
+    _check(lib().samo_fill_index_batched(jobs, flags, k, _stream()), where)
+    return out
 
 
 def samo_build_index_into(mask: torch.Tensor, idx: torch.Tensor, seg_ptr: torch.Tensor,
@@ -324,19 +355,10 @@ def samo_build_index_batched(masks: Sequence[torch.Tensor], idxs: Sequence[Optio
 
 def samo_build_index_many(masks: Sequence[torch.Tensor]) -> list:
     """Index of every mask with a handful of launches: batched count, one read-back of the
-    counts to size the indices, batched count + fill."""
+    counts to size the indices, batched fill."""
     if not masks:
         return []
-    dev = masks[0].device
-    seg_ptrs = [torch.empty(samo_seg_ptr_len(m.numel()), dtype=torch.int32, device=dev) for m in masks]
-    nnz_out = torch.empty(len(masks), dtype=torch.int64, device=dev)
-    samo_build_index_batched(masks, [None] * len(masks), seg_ptrs, nnz_out)
-    counts = nnz_out.cpu().tolist()
-    if any(c < 0 for c in counts):
-        raise SamoError(SAMO_ERR_INDEX, "samo_build_index_batched (the device-side scan gave up)")
-    idxs = [torch.empty(c, dtype=torch.int32, device=dev) for c in counts]
-    samo_build_index_batched(masks, idxs, seg_ptrs, nnz_out)
-    return [Index(i, s, c, m.numel()) for i, s, c, m in zip(idxs, seg_ptrs, counts, masks)]
+    return _build_indices(masks, "samo_build_index_many")
 
 
 def samo_build_seg_ptr(idx: torch.Tensor, n: int) -> torch.Tensor:

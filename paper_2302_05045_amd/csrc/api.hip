@@ -182,18 +182,30 @@ int64_t samo_seg_ptr_len(int64_t n)
     return ceil_div(n, kSeg) + 1;
 }
 
-samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_jobs, void *stream)
+}  // extern "C"
+
+namespace {
+
+samo_status check_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, bool need_flags, int32_t num_jobs)
 {
     if (num_jobs < 0) return SAMO_ERR_SIZE;
-    if (num_jobs > 0 && !h_jobs) return SAMO_ERR_NULL;
-    for (int32_t j = 0; j < num_jobs; ++j) {                      // validate everything before any launch
+    if (num_jobs > 0 && (!h_jobs || (need_flags && !h_flags))) return SAMO_ERR_NULL;
+    for (int32_t j = 0; j < num_jobs; ++j) {
         const samo_index_job &J = h_jobs[j];
         if (J.n < 0 || J.n > kMaxN || J.idx_capacity < 0) return SAMO_ERR_SIZE;
         if ((!J.mask && J.n > 0) || !J.seg_ptr || !J.nnz || (!J.idx && J.idx_capacity > 0)) return SAMO_ERR_NULL;
-        if (misaligned(J.mask) || misaligned(J.seg_ptr) || misaligned(J.idx) ||
+        if (need_flags && !h_flags[j] && J.n > 0) return SAMO_ERR_NULL;
+        if (misaligned(J.mask) || misaligned(J.seg_ptr) || misaligned(J.idx) || (need_flags && misaligned(h_flags[j])) ||
             (reinterpret_cast<uintptr_t>(J.nnz) & 7u))
             return SAMO_ERR_ALIGN;
     }
+    return SAMO_OK;
+}
+
+// Launches the jobs in groups of up to kIndexBatchJobs: counting (and filling, where a job has room for
+// positions), leaving the flag words where h_flags says so.
+samo_status run_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)
+{
     const int cus = compute_units();
     for (int32_t j0 = 0; j0 < num_jobs;) {
         IndexBatch batch;
@@ -221,17 +233,69 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
             batch.wg_start[i] = (int)wgs;
             batch.mask[i] = J.mask;
             batch.n[i] = J.n;
-            batch.idx[i] = J.idx;
-            batch.cap[i] = J.idx_capacity;
+            batch.idx[i] = h_flags ? nullptr : J.idx;
+            batch.cap[i] = h_flags ? 0 : J.idx_capacity;
             batch.seg_ptr[i] = J.seg_ptr;
             batch.nnz[i] = J.nnz;
-            fill |= J.idx_capacity > 0;
+            batch.flags[i] = h_flags ? reinterpret_cast<uint4 *>(h_flags[j0 + i]) : nullptr;
+            fill |= batch.cap[i] > 0;
             if (w > 0) batch.ticket = J.nnz;
             wgs += w;
         }
         batch.wg_start[k] = (int)wgs;
         if (launch_index_batch(batch, fill, as_stream(stream)) != hipSuccess) return SAMO_ERR_HIP;
         j0 += k;
+    }
+    return SAMO_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_jobs, void *stream)
+{
+    if (samo_status s = check_index_jobs(h_jobs, nullptr, false, num_jobs)) return s;     // everything before any launch
+    return run_index_jobs(h_jobs, nullptr, num_jobs, stream);
+}
+
+samo_status samo_index_flags_bytes(int64_t n, size_t *bytes)
+{
+    if (!bytes) return SAMO_ERR_NULL;
+    if (n < 0 || n > kMaxN) return SAMO_ERR_SIZE;
+    *bytes = (size_t)ceil_div(ceil_div(n, kSeg), kFlagGroupSegs) * 64 * sizeof(uint4);
+    return SAMO_OK;
+}
+
+samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)
+{
+    if (samo_status s = check_index_jobs(h_jobs, h_flags, true, num_jobs)) return s;
+    return run_index_jobs(h_jobs, h_flags, num_jobs, stream);
+}
+
+samo_status samo_fill_index_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)
+{
+    if (samo_status s = check_index_jobs(h_jobs, h_flags, true, num_jobs)) return s;
+    for (int32_t j = 0; j < num_jobs;) {
+        IndexBatch batch;
+        std::memset(&batch, 0, sizeof(batch));
+        int64_t wgs = 0;
+        for (; batch.num < kIndexBatchJobs && j < num_jobs; ++j) {
+            const samo_index_job &J = h_jobs[j];
+            if (J.idx_capacity <= 0) continue;                       // nothing to write
+            const int64_t w = index_fill_workgroups(J.n);
+            if (batch.num > 0 && wgs + w > kMaxN) break;
+            const int i = batch.num++;
+            batch.wg_start[i] = (int)wgs;
+            batch.n[i] = J.n;
+            batch.idx[i] = J.idx;
+            batch.cap[i] = J.idx_capacity;
+            batch.seg_ptr[i] = J.seg_ptr;
+            batch.flags[i] = reinterpret_cast<uint4 *>(h_flags[j]);
+            wgs += w;
+        }
+        batch.wg_start[batch.num] = (int)wgs;
+        if (launch_index_fill(batch, as_stream(stream)) != hipSuccess) return SAMO_ERR_HIP;
     }
     return SAMO_OK;
 }

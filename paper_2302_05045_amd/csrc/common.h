@@ -100,6 +100,7 @@ int knob(int which, int dflt);
 
 // Up to kIndexBatchJobs index-build jobs, passed to the kernels by value (kernel argument segment).
 constexpr int kIndexBatchJobs = 48;
+constexpr int kFlagGroupSegs = 8;          // segments whose flag words are one group of 64 uint4 (1 KiB), a lane's four words adjacent
 constexpr int kIndexSpinLimit = 1 << 20;   // about a second of polling
 struct IndexBatch {
     int num;
@@ -110,6 +111,7 @@ struct IndexBatch {
     int64_t cap[kIndexBatchJobs];
     int32_t *seg_ptr[kIndexBatchJobs];
     int64_t *nnz[kIndexBatchJobs];
+    uint4 *flags[kIndexBatchJobs];       // NULL, or where a counting launch leaves the flag words and the fill launch reads them
     int passes;                          // 64 KiB passes a workgroup makes over its block: 1, 2 or 4
     int spin_limit;                      // polls of a missing predecessor before a workgroup gives up
     int64_t *ticket;                     // the nnz of the job that owns the last workgroup: zero before the
@@ -121,7 +123,9 @@ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) -----------------------
 hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s);
+hipError_t launch_index_fill(const IndexBatch &batch, hipStream_t s);
 int64_t index_job_workgroups(int64_t n, int passes);
+int64_t index_fill_workgroups(int64_t n);
 int index_passes_for(int64_t mask_bytes, int compute_units);
 hipError_t launch_seg_ptr_from_idx(const int32_t *idx, int64_t nnz, int64_t n, int32_t *seg_ptr,
                                    hipStream_t s);

@@ -5,13 +5,18 @@
 // SAMO_SEG_ELEMS = 1024 mask bytes, taken in passes of 64; in a pass a wavefront takes eight of
 // them, every lane loading 16 bytes of each, so a segment is one coalesced 1 KiB access and eight
 // are in flight per lane.  The kept bytes are counted per lane (popcount of a 16-bit flag word)
-// and scanned across the wave, which gives every lane its offset within the segment and the
-// segment its total; the number of kept elements in front of the workgroup then comes from a
-// chained scan across workgroups (each publishes its own count at once and the running total as
-// soon as it knows it; a successor sums the counts back to the nearest running total); finally
-// the ascending int32 positions are produced from the flag words still held in registers,
-// collected per segment in LDS and stored as contiguous runs.  All integer work: one read of the
-// mask plus the write of the index, about 100 vector-ALU instructions per segment and wave.
+// and scanned across the wave, which gives the segments their totals; the number of kept elements in
+// front of the workgroup then comes from a chained scan across workgroups (each publishes its own count
+// at once and the running total as soon as it knows it; a successor sums the counts back to the nearest
+// running total); finally
+// the ascending int32 positions are produced from the flag bits still held in registers,
+// collected per pair of segments in LDS and stored as contiguous runs.  All integer work: one read of the
+// mask plus the write of the index.
+//
+// A caller that has to know the count before it can allocate the index makes two calls.  The second
+// need not read the mask again: the first can leave its flag words (an eighth of the mask's size) in a
+// buffer of the caller, and fill_kernel makes the positions from those and from seg_ptr.  Seven layers of the
+// 2.7B shape (550 M mask bytes, 10 % kept): counting 117 us and a whole second build 160 before, 133 and 63 now.
 //
 // The chain lives in seg_ptr itself: seg_ptr[e], e the end of a workgroup's block of segments, is
 // the number of kept elements up to there — exactly the running total the next workgroup needs.
@@ -34,7 +39,7 @@ __device__ __forceinline__ uint32_t nonzero_byte_flags(uint32_t x)
     return (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
 }
 
-// 16-bit flag word for the 16 mask bytes owned by this lane; bytes at or beyond n read as 0.
+// 16 flag bits for 16 mask bytes; bytes at or beyond n read as 0.
 __device__ __forceinline__ uint32_t lane_flags(const uint8_t *__restrict__ mask, int64_t n, int64_t first)
 {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
@@ -99,13 +104,19 @@ __device__ __forceinline__ int find_job(const IndexBatch &batch, int wg)
 
 // A workgroup takes its block in PASSES passes of 64 KiB: in a pass every wave loads eight
 // consecutive segments — all eight 16-byte loads of a lane in flight before anything is reduced —
-// and keeps only their flag words (two to a register) for the fill.  The per-lane counts travel
+// and keeps only their flag bits (two segments to a register) for the fill.  The per-lane counts travel
 // through the wave scans packed two to a register: a count is at most 1024, a 16-bit field is
 // enough.  What a workgroup pays once whatever its block's size — drawing the ticket, waiting for
 // its predecessors in the chain — is a dozen microseconds, against less than two for a pass, so a
 // launch with enough mask to keep the compute units busy takes four passes per workgroup (256 KiB
 // blocks), smaller ones two or one.
+// The fill takes the segments in pairs, 32 consecutive elements to a lane: a pair's positions are one
+// contiguous run of idx, and the loop that turns a lane's flag word into positions runs as often as the
+// fullest lane of the wave has kept elements, about 8 times for a pair at 10 % kept, where two words of 16
+// took 5 to 6 each.
 constexpr int kSegsPerPass = 8;           // per wave
+constexpr int kPairs = kSegsPerPass / 2;
+static_assert(kFlagGroupSegs == kSegsPerPass && kPairs == 4, "a lane's flag words of a pass are one 16-byte vector");
 constexpr int kMaxPasses = 4;
 __host__ __device__ constexpr int segs_per_wg(int passes) { return kSegsPerPass * kWavesPerWg * passes; }
 
@@ -181,6 +192,52 @@ __device__ __forceinline__ int kept_before_block(const int32_t *seg_ptr, int64_t
     return prefix;
 }
 
+// From 16 elements of either segment of every pair (as the mask is loaded: 1 KiB of one segment per
+// instruction; lanes that load 32 bytes apart read 17 % slower) to 32 consecutive elements of the pair, by
+// way of the wave's LDS area.
+__device__ __forceinline__ void pair_words(const uint32_t (&halves)[kPairs], uint32_t (&word)[kPairs], int32_t *stage, int lane)
+{
+    uint16_t *to = reinterpret_cast<uint16_t *>(stage) + (lane >> 1) * 2 * kPairs + (lane & 1);
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        to[2 * j] = (uint16_t)halves[j];                                 // word (lane / 2) of the pair's first segment
+        to[32 * 2 * kPairs + 2 * j] = (uint16_t)(halves[j] >> 16);       // ... of its second
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint4 w = reinterpret_cast<const uint4 *>(stage)[lane];
+    word[0] = w.x; word[1] = w.y; word[2] = w.z; word[3] = w.w;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Writes the positions of one pair of segments: lane l holds the flag word of elements first .. first + 31,
+// first = 32 l behind the pair's start; idx[out0 ..] takes them in order, nothing at or beyond cap.  The
+// positions go to LDS (the wave's own kSeg ints: no workgroup barrier), then leave as contiguous 256-byte
+// stores; a pair with more than kSeg of them goes in two halves.
+__device__ __forceinline__ void emit_pair(uint32_t word, int first, int64_t out0, int64_t cap, int32_t *__restrict__ idx,
+                                          int32_t *stage, int lane)
+{
+    const int cnt = __popc(word);
+    const int incl = wave_inclusive_scan(cnt, lane);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int lower = __builtin_amdgcn_readlane(incl, 31);
+    const bool halves = total > kSeg;
+    for (int h = 0; h < (halves ? 2 : 1); ++h) {
+        const int from = h ? lower : 0, to = (halves && !h) ? lower : total;
+        int32_t *at = stage + (incl - cnt - from);
+        uint32_t bits = (!halves || (lane >> 5) == h) ? word : 0u;
+        while (bits) {
+            *at++ = first + __builtin_ctz(bits);
+            bits &= bits - 1;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t room = cap - out0 - from;
+        const int count = room < to - from ? (int)room : to - from;      // not positive where the room has run out
+        int32_t *__restrict__ out = idx + out0 + from;
+        for (int o = lane; o < count; o += 64) out[o] = stage[o];
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 template <int PASSES>
 __global__ void __launch_bounds__(kIndexThreads)
 index_kernel(const IndexBatch batch, int fill)
@@ -191,27 +248,27 @@ index_kernel(const IndexBatch batch, int fill)
     __shared__ int sh_ticket;
     __shared__ int sh_seg[kSegsPerWg];        // kept elements per segment, then in front of it within the block
     __shared__ int sh_base;                   // kept elements in front of the block, or kPoison
-    __shared__ int32_t sh_stage[kWavesPerWg][kSeg];   // positions of one segment per wave, on their way out
+    __shared__ __attribute__((aligned(16))) int32_t sh_stage[kWavesPerWg][kSeg];   // positions of a pair per wave, on their way out
     if (threadIdx.x == 0) sh_ticket = (int)atomicAdd(reinterpret_cast<unsigned long long *>(batch.ticket), 1ull);
     __syncthreads();
-    const int ticket = sh_ticket;
+    const int ticket = __builtin_amdgcn_readfirstlane(sh_ticket);
     const int job = find_job(batch, ticket);
     const int blk = ticket - batch.wg_start[job];
     const int64_t n = batch.n[job];
     const int64_t nseg = (n + kSeg - 1) / kSeg;
     int32_t *__restrict__ seg_ptr = batch.seg_ptr[job];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t seg0 = ((int64_t)blk * kWavesPerWg + wave) * kSegsPerWave;     // segments beyond nseg read as empty
 
-    uint32_t fp[PASSES][kSegsPerPass / 2];    // flag words of segments 2j (low half) and 2j + 1 (high half) of a pass
+    uint32_t fp[PASSES][kPairs];              // flag bits of segments 2j (low half) and 2j + 1 (high half) of a pass
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
-        uint32_t f[kSegsPerPass];
+        uint32_t f[2 * kPairs];
 #pragma unroll
-        for (int q = 0; q < kSegsPerPass; ++q)
+        for (int q = 0; q < 2 * kPairs; ++q)
             f[q] = lane_flags(batch.mask[job], n, (seg0 + p * kSegsPerPass + q) * kSeg + lane * 16);
 #pragma unroll
-        for (int j = 0; j < kSegsPerPass / 2; ++j) {
+        for (int j = 0; j < kPairs; ++j) {
             const int incl = wave_inclusive_scan(__popc(f[2 * j]) | (__popc(f[2 * j + 1]) << 16), lane);
             if (lane == 63) {                  // the last lane's inclusive prefixes are the segment totals
                 int *dst = sh_seg + wave * kSegsPerWave + p * kSegsPerPass + 2 * j;
@@ -219,6 +276,13 @@ index_kernel(const IndexBatch batch, int fill)
                 dst[1] = incl >> 16;
             }
             fp[p][j] = f[2 * j] | (f[2 * j + 1] << 16);
+        }
+        // the lane's flag bits of the pass, one vector: what fill_kernel reads instead of the mask (past the
+        // caches: a whole 2.7B model is counted in 0.56 instead of 0.59 ms, 0.47 without the bits)
+        if (batch.flags[job] != nullptr && seg0 + p * kSegsPerPass < nseg) {
+            typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+            __builtin_nontemporal_store((u32x4){fp[p][0], fp[p][1], fp[p][2], fp[p][3]},
+                                        reinterpret_cast<u32x4 *>(batch.flags[job] + (seg0 / kSegsPerPass + p) * 64 + lane));
         }
         asm volatile("" ::: "memory");        // the next pass's loads are requested after this pass's flag words exist
     }
@@ -250,7 +314,7 @@ index_kernel(const IndexBatch batch, int fill)
         }
     }
     __syncthreads();
-    const int base = sh_base;
+    const int base = __builtin_amdgcn_readfirstlane(sh_base);
     if (base == kPoison) return;
 
     // seg_ptr entries strictly inside the block (its first is the predecessor's chain entry)
@@ -260,37 +324,46 @@ index_kernel(const IndexBatch batch, int fill)
 
     const int64_t cap = batch.cap[job];
     if (!fill || cap <= 0 || seg0 >= nseg) return;
-    int32_t *__restrict__ idx = batch.idx[job];
-    int32_t *stage = sh_stage[wave];           // this wave's own staging area: no workgroup barrier needed
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
+        uint32_t word[kPairs];
+        pair_words(fp[p], word, sh_stage[wave], lane);
 #pragma unroll
-        for (int j = 0; j < kSegsPerPass / 2; ++j) {
-            const uint32_t pair[2] = {fp[p][j] & 0xffffu, fp[p][j] >> 16};
-            const int cnt = __popc(pair[0]) | (__popc(pair[1]) << 16);
-            const int incl = wave_inclusive_scan(cnt, lane);          // formed again: cheaper than keeping it
-            const int ex = incl - cnt, tt = __builtin_amdgcn_readlane(incl, 63);
-            const int excl[2] = {ex & 0xffff, ex >> 16}, tot[2] = {tt & 0xffff, tt >> 16};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                // the segment's positions go to LDS in order, then leave as contiguous 256-byte stores
-                const int sq = p * kSegsPerPass + 2 * j + h;
-                const int first = (int)((seg0 + sq) * kSeg) + lane * 16;     // a layer's flat size fits int32
-                int at = excl[h];
-                uint32_t bits = pair[h];
-                while (bits) {
-                    const int b = __ffs(bits) - 1;
-                    bits &= bits - 1;
-                    stage[at++] = first + b;
-                }
-                __builtin_amdgcn_wave_barrier();
-                const int64_t out0 = (int64_t)base + sh_seg[wave * kSegsPerWave + sq];
-                for (int o = lane; o < tot[h]; o += 64)
-                    if (out0 + o < cap) idx[out0 + o] = stage[o];
-                __builtin_amdgcn_wave_barrier();
-            }
+        for (int j = 0; j < kPairs; ++j) {
+            const int sq = p * kSegsPerPass + 2 * j;
+            emit_pair(word[j], (int)((seg0 + sq) * kSeg) + lane * 32,           // a layer's flat size fits int32
+                      (int64_t)base + __builtin_amdgcn_readfirstlane(sh_seg[wave * kSegsPerWave + sq]), cap, batch.idx[job], sh_stage[wave], lane);
         }
     }
+}
+
+// The positions from the flag words and the seg_ptr a counting launch left: a wave takes a group of eight
+// segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
+// What bounds it: the loop over a lane's kept elements (7 vector instructions and an LDS store a trip, 8 trips
+// a pair at 10 % kept) beside the index written, 4 bytes per kept element: 4.6 TB/s at 10 % kept.
+constexpr int kFillWaves = 4;
+
+__global__ void __launch_bounds__(kFillWaves * 64)
+fill_kernel(const IndexBatch batch)
+{
+    __shared__ __attribute__((aligned(16))) int32_t sh_stage[kFillWaves][kSeg];
+    const int job = find_job(batch, (int)blockIdx.x);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t nseg = (batch.n[job] + kSeg - 1) / kSeg;
+    const int64_t group = (int64_t)((int)blockIdx.x - batch.wg_start[job]) * kFillWaves + wave;
+    const int64_t seg0 = group * kFlagGroupSegs;
+    if (seg0 >= nseg) return;                 // whole waves leave; nothing below is a workgroup barrier
+    const uint4 w = batch.flags[job][group * 64 + lane];
+    const uint32_t halves[kPairs] = {w.x, w.y, w.z, w.w};
+    uint32_t word[kPairs];
+    pair_words(halves, word, sh_stage[wave], lane);
+    const int32_t *__restrict__ seg_ptr = batch.seg_ptr[job];
+    int start[kPairs];
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) start[j] = seg_ptr[seg0 + 2 * j < nseg ? seg0 + 2 * j : nseg];
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j)
+        emit_pair(word[j], (int)((seg0 + 2 * j) * kSeg) + lane * 32, start[j], batch.cap[job], batch.idx[job], sh_stage[wave], lane);
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -348,6 +421,15 @@ hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
     }
     return hipGetLastError();
 }
+
+hipError_t launch_index_fill(const IndexBatch &batch, hipStream_t s)
+{
+    const int wgs = batch.num > 0 ? batch.wg_start[batch.num] : 0;
+    if (wgs > 0) fill_kernel<<<dim3((unsigned)wgs), dim3(kFillWaves * 64), 0, s>>>(batch);
+    return hipGetLastError();
+}
+
+int64_t index_fill_workgroups(int64_t n) { return ceil_div(ceil_div(n, kSeg), kFlagGroupSegs * kFillWaves); }
 
 int64_t index_job_workgroups(int64_t n, int passes) { return ceil_div(ceil_div(n, kSeg), segs_per_wg(passes)); }
 

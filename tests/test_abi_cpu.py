@@ -282,3 +282,28 @@ def test_host_side_of_the_library_under_sanitizers(tmp_path):
                          env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0:protect_shadow_gap=0"))
     assert out.returncode == 0, (out.stdout + out.stderr)[-3000:]
     assert "all rejected as documented" in out.stdout
+
+
+def test_two_call_index_build_rejects_bad_arguments():
+    import ctypes
+    L = samo.lib()
+    size = ctypes.c_size_t()
+    for n, want in ((0, 0), (1, 1024), (8192, 1024), (8193, 2048), (2 ** 31 - 1, 262144 * 1024)):
+        assert L.samo_index_flags_bytes(n, ctypes.byref(size)) == samo.SAMO_OK and size.value == want
+    assert L.samo_index_flags_bytes(-1, ctypes.byref(size)) == samo.SAMO_ERR_SIZE
+    assert L.samo_index_flags_bytes(8, None) == samo.SAMO_ERR_NULL
+    for entry in (L.samo_count_flags_batched, L.samo_fill_index_batched):
+        def call(flags=FAKE, mask=FAKE, n=8, idx=FAKE, cap=8, seg=FAKE, nnz=FAKE, num=1):
+            jobs = (samo.IndexJob * 1)(samo.IndexJob(mask, n, idx, cap, seg, nnz))
+            return entry(jobs, (ctypes.c_void_p * 1)(flags), num, None)
+        assert call(flags=None) == samo.SAMO_ERR_NULL
+        assert call(mask=None) == samo.SAMO_ERR_NULL
+        assert call(seg=None) == samo.SAMO_ERR_NULL
+        assert call(nnz=None) == samo.SAMO_ERR_NULL
+        assert call(idx=None) == samo.SAMO_ERR_NULL
+        assert call(flags=FAKE + 8) == samo.SAMO_ERR_ALIGN
+        assert call(n=-1) == samo.SAMO_ERR_SIZE
+        assert call(num=-1) == samo.SAMO_ERR_SIZE
+        assert entry(None, (ctypes.c_void_p * 1)(FAKE), 1, None) == samo.SAMO_ERR_NULL
+        assert entry((samo.IndexJob * 1)(), None, 1, None) == samo.SAMO_ERR_NULL
+        assert entry(None, None, 0, None) == samo.SAMO_OK

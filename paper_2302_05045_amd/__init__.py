@@ -229,7 +229,7 @@ def _check(status: int, where: str) -> None:
         raise SamoError(status, where)
 
 
-def _dev(t: Optional[torch.Tensor], dtype: torch.dtype, name: str, length: Optional[int] = None) -> Optional[int]:
+def _dev_python(t: Optional[torch.Tensor], dtype: torch.dtype, name: str, length: Optional[int] = None) -> Optional[int]:
     """Device pointer of a contiguous 1-D CUDA tensor of the given dtype (None passes NULL)."""
     if t is None:
         return None
@@ -242,8 +242,36 @@ def _dev(t: Optional[torch.Tensor], dtype: torch.dtype, name: str, length: Optio
     return t.data_ptr() if t.numel() else None
 
 
+def _dev_matrix_python(t: torch.Tensor, name: str) -> tuple:
+    """(device pointer, rows, columns) of a contiguous 2-D fp16 CUDA tensor."""
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+        raise TypeError("%s must be a tensor on the GPU" % name)
+    if t.dtype != _F16 or t.dim() != 2 or not t.is_contiguous():
+        raise TypeError("%s must be a contiguous 2-D float16 tensor" % name)
+    return (t.data_ptr() if t.numel() else None), t.shape[0], t.shape[1]
+
+
+# The same two in native code (csrc/marshal.cpp): the checks of the seven tensors of a step take 0.7 instead of 7 us,
+# and a small layer's kernel runs for 5.  They call back the functions above for everything that is no plain tensor.
+try:
+    from . import _marshal
+except ImportError:                          # not built: the Python checks serve every call
+    _dev, _dev_matrix = _dev_python, _dev_matrix_python
+else:
+    _marshal.use(_dev_python, _dev_matrix_python)
+    _dev, _dev_matrix = _marshal.vector, _marshal.matrix
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current device's current stream.  The first call goes through torch's public function, which
+    initialises the runtime; the raw query that serves the later ones makes no Python object per call."""
+    global _stream
+    handle = torch.cuda.current_stream().cuda_stream
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        def _stream() -> int:
+            return raw(device())
+    return handle
 
 
 _F16 = torch.float16
@@ -255,10 +283,10 @@ def adam_cfg(step: int, lr: float = 1e-4, beta1: float = 0.9, beta2: float = 0.9
 
 
 def samo_seg_ptr_len(n: int) -> int:
-    r = lib().samo_seg_ptr_len(int(n))
-    if r < 0:
+    n = int(n)
+    if n < 0 or n > 2147483647:                               # as samo_seg_ptr_len of the library, without the call
         raise SamoError(SAMO_ERR_SIZE, "samo_seg_ptr_len")
-    return r
+    return (n + SEG_ELEMS - 1) // SEG_ELEMS + 1
 
 
 class Index(NamedTuple):
@@ -287,27 +315,30 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     """Index of every mask: one batched count that reads the masks and leaves their flag bits, one read-back
     of the counts to size the indices, one batched fill from the flag bits."""
     dev, k = masks[0].device, len(masks)
-    jobs, flags, sizes = (IndexJob * k)(), (ctypes.c_void_p * k)(), []
+    sizes = [m.numel() for m in masks]
+    seg_lens = [samo_seg_ptr_len(n) for n in sizes]
+    flag_bytes = [(s + 6) // 8 * 1024 for s in seg_lens]                 # samo_index_flags_bytes: 1 KiB per eight segments
+    flag_buf = torch.empty(max(sum(flag_bytes), 1), dtype=torch.uint8, device=dev)      # used and freed in stream order
     nnz_out = torch.empty(k, dtype=torch.int64, device=dev)
-    seg_ptrs, at = [], 0
-    for m in masks:
-        sizes.append(samo_index_flags_bytes(m.numel()))
-    flag_buf = torch.empty(max(sum(sizes), 1), dtype=torch.uint8, device=dev)      # used and freed in stream order
+    jobs, flags = (IndexJob * k)(), (ctypes.c_void_p * k)()
+    seg_ptrs = []
+    nnz_at, flags_at = nnz_out.data_ptr(), flag_buf.data_ptr()
     for i, m in enumerate(masks):
-        n = m.numel()
-        seg_ptrs.append(torch.empty(samo_seg_ptr_len(n), dtype=torch.int32, device=dev))
-        jobs[i] = IndexJob(_dev(m, torch.uint8, "mask"), n, None, 0, seg_ptrs[i].data_ptr(), nnz_out.data_ptr() + 8 * i)
-        flags[i] = flag_buf.data_ptr() + at
-        at += sizes[i]
+        seg_ptr = torch.empty(seg_lens[i], dtype=torch.int32, device=dev)
+        seg_ptrs.append(seg_ptr)
+        jobs[i] = IndexJob(_dev(m, torch.uint8, "mask"), sizes[i], None, 0, seg_ptr.data_ptr(), nnz_at + 8 * i)
+        flags[i] = flags_at
+        flags_at += flag_bytes[i]
     _check(lib().samo_count_flags_batched(jobs, flags, k, _stream()), where)
     counts = nnz_out.cpu().tolist()
     if any(c < 0 for c in counts):
         raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
     out = []
-    for i, (m, c) in enumerate(zip(masks, counts)):
+    for i, c in enumerate(counts):
         idx = torch.empty(c, dtype=torch.int32, device=dev)
-        jobs[i].idx, jobs[i].idx_capacity = (idx.data_ptr() if c else None), c
-        out.append(Index(idx, seg_ptrs[i], c, m.numel()))
+        job = jobs[i]
+        job.idx, job.idx_capacity = (idx.data_ptr() if c else None), c
+        out.append(Index(idx, seg_ptrs[i], c, sizes[i]))
     _check(lib().samo_fill_index_batched(jobs, flags, k, _stream()), where)
     return out
 
@@ -397,15 +428,6 @@ def samo_gather_grads_fp16(g: torch.Tensor, idx: Optional[torch.Tensor], gc16: t
     _check(lib().samo_gather_grads_fp16(_dev(g, _F16, "g"), n, _dev(idx, torch.int32, "idx", nnz), nnz,
                                         _dev(gc16, _F16, "gc16"), int(bool(accumulate)), _stream()),
            "samo_gather_grads_fp16")
-
-
-def _dev_matrix(t: torch.Tensor, name: str) -> tuple:
-    """(device pointer, rows, columns) of a contiguous 2-D fp16 CUDA tensor."""
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise TypeError("%s must be a tensor on the GPU" % name)
-    if t.dtype != _F16 or t.dim() != 2 or not t.is_contiguous():
-        raise TypeError("%s must be a contiguous 2-D float16 tensor" % name)
-    return (t.data_ptr() if t.numel() else None), t.shape[0], t.shape[1]
 
 
 def _wgrad_args(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Tensor], seg_ptr: Optional[torch.Tensor],

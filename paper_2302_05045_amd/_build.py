@@ -1,8 +1,9 @@
-"""Builds libsamo.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libsamo.so (HIP, gfx950 only) and the binding's native argument marshalling in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -30,5 +31,24 @@ def build(verbose: bool = False, extra_flags: list | None = None, out: str | Non
     return out
 
 
+def build_marshal(verbose: bool = False, out: str | None = None) -> str:
+    """_marshal.so, a CPython extension against the installed torch's headers (host code only)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    out = out or os.path.join(PKG, "_marshal.so")
+    tmp = out + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
+           "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_marshal(verbose=True))

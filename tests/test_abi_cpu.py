@@ -307,3 +307,31 @@ def test_two_call_index_build_rejects_bad_arguments():
         assert entry(None, (ctypes.c_void_p * 1)(FAKE), 1, None) == samo.SAMO_ERR_NULL
         assert entry((samo.IndexJob * 1)(), None, 1, None) == samo.SAMO_ERR_NULL
         assert entry(None, None, 0, None) == samo.SAMO_OK
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_argument_marshalling_native_and_python_agree(native):
+    """Both forms refuse the same arguments with the same words (a GPU is not needed to be refused)."""
+    import torch
+    if native:
+        from paper_2302_05045_amd import _marshal
+        vector, matrix = _marshal.vector, _marshal.matrix
+    else:
+        vector, matrix = samo._dev_python, samo._dev_matrix_python
+
+    class Sub(torch.Tensor):
+        pass
+    plain = torch.zeros(4)
+    for bad in (plain, plain.as_subclass(Sub), torch.nn.Parameter(plain), 3, "x", [1.0], plain.numpy()):
+        with pytest.raises(TypeError, match="^p must be a tensor on the GPU$"):
+            vector(bad, torch.float32, "p")
+        with pytest.raises(TypeError, match="^m must be a tensor on the GPU$"):
+            matrix(bad, "m")
+    assert vector(None, torch.float32, "p") is None and vector(None, torch.float32, "p", 7) is None
+    with pytest.raises(TypeError):
+        matrix(None, "m")
+    for n in (-1, 2 ** 31):
+        with pytest.raises(samo.SamoError):
+            samo.samo_seg_ptr_len(n)
+    for n in (0, 1, 1023, 1024, 1025, 2 ** 31 - 1):
+        assert samo.samo_seg_ptr_len(n) == samo.lib().samo_seg_ptr_len(n)

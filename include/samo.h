@@ -431,6 +431,18 @@ samo_status samo_wgrad_gather_batched(int32_t count, const samo_wgrad_job *h_job
 samo_status samo_wgrad_gather_fp16_batched(int32_t count, const samo_wgrad_job *h_jobs,
                                            int32_t accumulate, void *stream);
 
+/* The same with a device workspace (16-byte aligned).  Layers too small to occupy the device then have
+ * their tokens split over several workgroups per tile, whose fp32 sums meet in the workspace: the
+ * sums are formed in another order, within the bound above, and deterministic.
+ * samo_wgrad_workspace_bytes reports the size worth providing for these jobs on the current device, 0 where
+ * the call would not be split; a NULL or smaller workspace gives the unsplit call.  The workspace is in
+ * use until the stream has passed the call. */
+samo_status samo_wgrad_workspace_bytes(int32_t count, const samo_wgrad_job *h_jobs, size_t *bytes);
+samo_status samo_wgrad_gather_batched_ws(int32_t count, const samo_wgrad_job *h_jobs, float inv_loss_scale,
+                                         void *d_workspace, size_t workspace_bytes, void *stream);
+samo_status samo_wgrad_gather_fp16_batched_ws(int32_t count, const samo_wgrad_job *h_jobs, int32_t accumulate,
+                                              void *d_workspace, size_t workspace_bytes, void *stream);
+
 /* ---------------------------------------------------------------- byte accounting (Section III-D, Eq. 1-5)  [host only]
  * paper_default = 20 * n_total; paper_samo = 24 * nnz_total + 2 * n_total;
  * resident = what this library's fused pipeline keeps allocated:
@@ -472,6 +484,9 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *                        compute units and 128 x 128 for a remainder of at most half a round).
  *   SAMO_KNOB_WGRAD_ROUND  test aid: the number of tiles taken as one round in that rule, in
  *                        place of the device's compute-unit count.
+ *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace; 1: never split.  Applies to
+ *                        calls of at most half a round of large tiles, with the tile shape SAMO_KNOB_WGRAD_TILE names
+ *                        (default there: 128 x 128).
  *   SAMO_KNOB_TILE_COST    the weight of a plan's tiles in units of 1024 (6 .. 96; default 32, or 48 for a
  *                        model that keeps under 7 % of its elements; 48 there with an fp32 dense side).
  *                        Read by samo_plan_workspace_bytes and samo_plan_init: set it before both.
@@ -489,7 +504,8 @@ enum {
     SAMO_KNOB_WGRAD_ROUND = 9,
     SAMO_KNOB_INDEX_PASSES = 10,
     SAMO_KNOB_TILE_COST = 11,
-    SAMO_KNOB_COUNT = 12
+    SAMO_KNOB_WGRAD_SPLIT = 12,
+    SAMO_KNOB_COUNT = 13
 };
 #define SAMO_KNOB_DEFAULT (-1)
 samo_status samo_debug_set(int32_t knob, int32_t value);

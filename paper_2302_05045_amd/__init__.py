@@ -31,7 +31,7 @@ SAMO_OK = 0
 # samo_debug_set knobs
 (KNOB_OCC_TILE_STEP, KNOB_OCC_TILE_STEP32, KNOB_OCC_TILE_DECOMP, KNOB_OCC_TILE_C16, KNOB_OCC_FLAT_GATHER,
  KNOB_OCC_FLAT_STATS, KNOB_OCC_FLAT_STEP, KNOB_INDEX_SPIN_LIMIT, KNOB_WGRAD_TILE, KNOB_WGRAD_ROUND,
- KNOB_INDEX_PASSES, KNOB_TILE_COST) = range(12)
+ KNOB_INDEX_PASSES, KNOB_TILE_COST, KNOB_WGRAD_SPLIT) = range(13)
 KNOB_DEFAULT = -1
 
 
@@ -174,6 +174,12 @@ _SIGNATURES = {
                                                    ctypes.c_void_p]),
     "samo_wgrad_gather_fp16_batched": (ctypes.c_int32, [ctypes.c_int32, ctypes.POINTER(WgradJob), ctypes.c_int32,
                                                         ctypes.c_void_p]),
+    "samo_wgrad_workspace_bytes": (ctypes.c_int32, [ctypes.c_int32, ctypes.POINTER(WgradJob),
+                                                    ctypes.POINTER(ctypes.c_size_t)]),
+    "samo_wgrad_gather_batched_ws": (ctypes.c_int32, [ctypes.c_int32, ctypes.POINTER(WgradJob), ctypes.c_float,
+                                                      ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]),
+    "samo_wgrad_gather_fp16_batched_ws": (ctypes.c_int32, [ctypes.c_int32, ctypes.POINTER(WgradJob), ctypes.c_int32,
+                                                           ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]),
     "samo_stream_copy": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]),
     "samo_mfma_rate_probe": (ctypes.c_int32, [ctypes.c_int64, ctypes.c_void_p, ctypes.c_int32,
                                               ctypes.POINTER(ctypes.c_double), ctypes.c_void_p]),
@@ -445,41 +451,71 @@ def samo_wgrad_gather(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Ten
                       inv_loss_scale: float, gc: torch.Tensor) -> None:
     """gc = the weight gradient dy^T x (tokens x out, tokens x in -> out x in), rounded to fp16, at idx,
     times inv_loss_scale."""
-    nnz = gc.numel()
-    _check(lib().samo_wgrad_gather(*_wgrad_args(dy, x, idx, seg_ptr, nnz), float(inv_loss_scale),
-                                   _dev(gc, torch.float32, "gc"), _stream()), "samo_wgrad_gather")
+    jobs = (WgradJob * 1)()
+    large = _wgrad_job(jobs, 0, dy, x, idx, seg_ptr, gc, torch.float32, "gc")
+    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, gc)
+    _check(lib().samo_wgrad_gather_batched_ws(1, jobs, float(inv_loss_scale), _ptr(ws), ws_bytes, _stream()),
+           "samo_wgrad_gather")
 
 
 def samo_wgrad_gather_fp16(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Tensor],
                            seg_ptr: Optional[torch.Tensor], gc16: torch.Tensor, accumulate: bool = False) -> None:
     """gc16 = that weight gradient, rounded to fp16, at idx; added to gc16 (in fp16) if accumulate."""
-    nnz = gc16.numel()
-    _check(lib().samo_wgrad_gather_fp16(*_wgrad_args(dy, x, idx, seg_ptr, nnz), _dev(gc16, _F16, "gc16"),
-                                        int(bool(accumulate)), _stream()), "samo_wgrad_gather_fp16")
+    jobs = (WgradJob * 1)()
+    large = _wgrad_job(jobs, 0, dy, x, idx, seg_ptr, gc16, _F16, "gc16")
+    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, gc16)
+    _check(lib().samo_wgrad_gather_fp16_batched_ws(1, jobs, int(bool(accumulate)), _ptr(ws), ws_bytes, _stream()),
+           "samo_wgrad_gather_fp16")
+
+
+def _wgrad_job(arr, j: int, dy, x, idx, seg_ptr, gc, dtype, name: str) -> int:
+    """Fills job j; returns its number of 256 x 256 tiles."""
+    nnz = gc.numel()
+    dy_ptr, x_ptr, tokens, out_features, in_features, idx_ptr, seg, _ = _wgrad_args(dy, x, idx, seg_ptr, nnz)
+    arr[j] = WgradJob(dy_ptr, x_ptr, tokens, out_features, in_features, idx_ptr, seg, nnz, _dev(gc, dtype, name))
+    return ((out_features + 255) >> 8) * ((in_features + 255) >> 8)
+
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
+
+
+def _wgrad_workspace(jobs, count: int, tiles: int, gc: torch.Tensor):
+    """(workspace, bytes) for layers too small to occupy the device, freed in stream order; (None, 0) where the library
+    would not split the call (it never does above half a round of large tiles: no need to ask)."""
+    if tiles > 160:
+        return None, 0
+    need = ctypes.c_size_t()
+    _check(lib().samo_wgrad_workspace_bytes(count, jobs, ctypes.byref(need)), "samo_wgrad_workspace_bytes")
+    if not need.value:
+        return None, 0
+    return torch.empty(need.value, dtype=torch.uint8, device=gc.device), need.value
 
 
 def _wgrad_jobs(jobs, dtype, name: str):
-    """A samo_wgrad_job array from (dy, x, idx, seg_ptr, gc) tuples."""
+    """(samo_wgrad_job array, its large tiles) from (dy, x, idx, seg_ptr, gc) tuples."""
     arr = (WgradJob * max(len(jobs), 1))()
+    tiles = 0
     for j, (dy, x, idx, seg_ptr, gc) in enumerate(jobs):
-        nnz = gc.numel()
-        dy_ptr, x_ptr, tokens, out_features, in_features, idx_ptr, seg, _ = _wgrad_args(dy, x, idx, seg_ptr, nnz)
-        arr[j] = WgradJob(dy_ptr, x_ptr, tokens, out_features, in_features, idx_ptr, seg, nnz,
-                          _dev(gc, dtype, "%s of job %d" % (name, j)))
-    return arr
+        tiles += _wgrad_job(arr, j, dy, x, idx, seg_ptr, gc, dtype, "%s of job %d" % (name, j))
+    return arr, tiles
 
 
 def samo_wgrad_gather_batched(jobs, inv_loss_scale: float) -> None:
     """samo_wgrad_gather for every (dy, x, idx, seg_ptr, gc) of jobs (at most SAMO_WGRAD_MAX_JOBS), the
     layers' tiles dealt to the compute units as one list."""
-    _check(lib().samo_wgrad_gather_batched(len(jobs), _wgrad_jobs(jobs, torch.float32, "gc"), float(inv_loss_scale),
-                                           _stream()), "samo_wgrad_gather_batched")
+    arr, tiles = _wgrad_jobs(jobs, torch.float32, "gc")
+    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, jobs[0][4]) if jobs else (None, 0)
+    _check(lib().samo_wgrad_gather_batched_ws(len(jobs), arr, float(inv_loss_scale), _ptr(ws), ws_bytes, _stream()),
+           "samo_wgrad_gather_batched")
 
 
 def samo_wgrad_gather_fp16_batched(jobs, accumulate: bool = False) -> None:
     """samo_wgrad_gather_fp16 for every (dy, x, idx, seg_ptr, gc16) of jobs."""
-    _check(lib().samo_wgrad_gather_fp16_batched(len(jobs), _wgrad_jobs(jobs, _F16, "gc16"), int(bool(accumulate)),
-                                                _stream()), "samo_wgrad_gather_fp16_batched")
+    arr, tiles = _wgrad_jobs(jobs, _F16, "gc16")
+    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, jobs[0][4]) if jobs else (None, 0)
+    _check(lib().samo_wgrad_gather_fp16_batched_ws(len(jobs), arr, int(bool(accumulate)), _ptr(ws), ws_bytes, _stream()),
+           "samo_wgrad_gather_fp16_batched")
 
 
 def sgd_cfg(lr: float, momentum: float = 0.9, weight_decay: float = 0.0) -> SgdCfg:

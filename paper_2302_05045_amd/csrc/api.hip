@@ -471,19 +471,26 @@ samo_status check_wgrad(const void *d_dy, const void *d_x, int64_t tokens, int64
 }  // namespace
 
 namespace {
-samo_status wgrad_batched(int out_kind, int32_t count, const samo_wgrad_job *h_jobs, float inv_scale, int accumulate,
-                          void *stream)
+samo_status make_wgrad_jobs(int32_t count, const samo_wgrad_job *h_jobs, WgradJob *jobs)
 {
     if (count < 0 || count > SAMO_WGRAD_MAX_JOBS) return SAMO_ERR_SIZE;
     if (count > 0 && !h_jobs) return SAMO_ERR_NULL;
-    WgradJob jobs[SAMO_WGRAD_MAX_JOBS];
     for (int j = 0; j < count; ++j) {
         const samo_wgrad_job &h = h_jobs[j];
         if (samo_status s = check_wgrad(h.d_dy, h.d_x, h.tokens, h.out, h.in, h.d_idx, h.d_seg_ptr, h.nnz, h.d_gc)) return s;
         jobs[j] = {reinterpret_cast<const _Float16 *>(h.d_dy), reinterpret_cast<const _Float16 *>(h.d_x), h.tokens,
                    (int)h.out, (int)h.in, h.d_idx, h.d_seg_ptr, h.nnz, h.d_gc};
     }
-    return hip_status(launch_wgrad(out_kind, jobs, count, inv_scale, accumulate, as_stream(stream)));
+    return SAMO_OK;
+}
+
+samo_status wgrad_batched(int out_kind, int32_t count, const samo_wgrad_job *h_jobs, float inv_scale, int accumulate,
+                          void *ws, size_t ws_bytes, void *stream)
+{
+    WgradJob jobs[SAMO_WGRAD_MAX_JOBS];
+    if (samo_status s = make_wgrad_jobs(count, h_jobs, jobs)) return s;
+    if (misaligned(ws)) return SAMO_ERR_ALIGN;
+    return hip_status(launch_wgrad(out_kind, jobs, count, inv_scale, accumulate, ws, ws_bytes, as_stream(stream)));
 }
 }  // namespace
 
@@ -503,15 +510,35 @@ samo_status samo_wgrad_gather_fp16(const uint16_t *d_dy, const uint16_t *d_x, in
     return samo_wgrad_gather_fp16_batched(1, &job, accumulate, stream);
 }
 
+samo_status samo_wgrad_workspace_bytes(int32_t count, const samo_wgrad_job *h_jobs, size_t *bytes)
+{
+    if (!bytes) return SAMO_ERR_NULL;
+    WgradJob jobs[SAMO_WGRAD_MAX_JOBS];
+    if (samo_status s = make_wgrad_jobs(count, h_jobs, jobs)) return s;
+    return hip_status(wgrad_workspace(jobs, count, bytes));
+}
+
 samo_status samo_wgrad_gather_batched(int32_t count, const samo_wgrad_job *h_jobs, float inv_loss_scale, void *stream)
 {
-    if (samo_status s = check_scale(inv_loss_scale)) return s;
-    return wgrad_batched(kOutF32, count, h_jobs, inv_loss_scale, 0, stream);
+    return samo_wgrad_gather_batched_ws(count, h_jobs, inv_loss_scale, nullptr, 0, stream);
 }
 
 samo_status samo_wgrad_gather_fp16_batched(int32_t count, const samo_wgrad_job *h_jobs, int32_t accumulate, void *stream)
 {
-    return wgrad_batched(kOutF16, count, h_jobs, 1.f, accumulate != 0, stream);
+    return samo_wgrad_gather_fp16_batched_ws(count, h_jobs, accumulate, nullptr, 0, stream);
+}
+
+samo_status samo_wgrad_gather_batched_ws(int32_t count, const samo_wgrad_job *h_jobs, float inv_loss_scale,
+                                         void *d_workspace, size_t workspace_bytes, void *stream)
+{
+    if (samo_status s = check_scale(inv_loss_scale)) return s;
+    return wgrad_batched(kOutF32, count, h_jobs, inv_loss_scale, 0, d_workspace, workspace_bytes, stream);
+}
+
+samo_status samo_wgrad_gather_fp16_batched_ws(int32_t count, const samo_wgrad_job *h_jobs, int32_t accumulate,
+                                              void *d_workspace, size_t workspace_bytes, void *stream)
+{
+    return wgrad_batched(kOutF16, count, h_jobs, 1.f, accumulate != 0, d_workspace, workspace_bytes, stream);
 }
 
 samo_status samo_adam_step(float *d_p, float *d_m, float *d_v, const float *d_gc, int64_t nnz,

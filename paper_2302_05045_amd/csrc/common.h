@@ -186,7 +186,10 @@ struct WgradJob {
     int64_t nnz;
     void *gc;
 };
-hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv_scale, int accumulate, hipStream_t s);
+// With a workspace (wgrad_workspace bytes) the tokens of small layers are split over several workgroups.
+hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv_scale, int accumulate, void *ws,
+                        size_t ws_bytes, hipStream_t s);
+hipError_t wgrad_workspace(const WgradJob *jobs, int count, size_t *bytes);
 // Function attributes of the weight-gradient kernels and the compute-unit count of the current device (once per device).
 hipError_t wgrad_configure(int *cus);
 constexpr int kMfmaRateWaves = 8;          // waves per workgroup of launch_mfma_rate, 8 MFMAs of 32 x 32 x 16 each per iteration

@@ -97,7 +97,14 @@ struct WgradBatch {
     int accumulate;
     int quadrants;
     int first, tiles;
+    // splits > 1: that many workgroups share a tile, each multiplies split_tokens[j] tokens and leaves its fp32
+    // sums at the kept positions in partial[j] + split * partial_stride[j]; wgrad_sum_kernel adds them up.
+    int splits;
+    int64_t split_tokens[kWgradMaxJobs];
+    float *partial[kWgradMaxJobs];
+    int64_t partial_stride[kWgradMaxJobs];
 };
+constexpr int kOutPartial = 3;
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
 
@@ -137,10 +144,13 @@ __device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 // that lies outside the matrix.
 __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, int &row0, int &col0)
 {
-    const int blocks = B.quadrants ? B.tiles * 4 : B.tiles;
+    const int shares = B.quadrants ? B.tiles * 4 : B.tiles;      // workgroups of one split
+    const int blocks = shares * B.splits;
     const int per_xcd = (blocks + 7) / 8;
-    const int local = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    int local = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (local >= blocks) return false;
+    const int split = B.splits > 1 ? local / shares : 0;         // the tiles of one split stay together
+    local -= split * shares;
     const int listed = B.first + (B.quadrants ? local >> 2 : local);
     int j = 0;
     while (j + 1 < B.jobs && listed >= B.first_tile[j + 1]) ++j;
@@ -148,6 +158,15 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
     A.dy = J.dy; A.x = J.x; A.tokens = J.tokens; A.out = J.out; A.in = J.in;
     A.idx = J.idx; A.seg_ptr = J.seg_ptr; A.nnz = J.nnz; A.gc = J.gc;
     A.inv_scale = B.inv_scale; A.accumulate = B.accumulate;
+    if (B.splits > 1) {
+        const int64_t begin = split * B.split_tokens[j], left = J.tokens - begin;
+        A.tokens = left < B.split_tokens[j] ? (left > 0 ? left : 0) : B.split_tokens[j];
+        if (left > 0) {
+            A.dy += begin * J.out;
+            A.x += begin * J.in;
+        }
+        A.gc = B.partial[j] + split * B.partial_stride[j];
+    }
     const int tile = listed - B.first_tile[j];
     const int tiles_out = B.tiles_out[j], tiles_in = B.tiles_in[j];
     const int group = tile / (4 * tiles_in);
@@ -369,7 +388,7 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
     return bound_settle(A, open, window);
 }
 
-// Epilogue over the ROWS rows of a tile held as an fp16 image in LDS: each of the 16 half-waves
+// Epilogue over the ROWS rows of a tile held as an image in LDS (fp16; fp32 sums for kOutPartial): each of the 16 half-waves
 // takes every 16th row, all of them at once; per row, idx between the row's two bounds is read
 // coalesced, the values are picked from the image and the compressed gradient is written
 // coalesced, 32 entries of every row a step.  What a step needs from memory (idx, and the old values where it
@@ -418,7 +437,8 @@ struct GatherPass {
         }
         request_idx(A, 0);
     }
-    __device__ __forceinline__ void finish(const WgradArgs &A, const _Float16 *img, int pitch, int first_row, int col0)
+    template <typename Pixel>
+    __device__ __forceinline__ void finish(const WgradArgs &A, const Pixel *img, int pitch, int first_row, int col0)
     {
         const int hw = threadIdx.x >> 5, l32 = threadIdx.x & 31;
         for (int step = 0; step * 32 < longest; step += kAhead) {
@@ -434,8 +454,9 @@ struct GatherPass {
                     const int k = lo[it] + (step + a) * 32 + l32;
                     const int rl = it * 16 + hw;
                     // positions of a layer fit 32 bits
-                    const _Float16 v = img[rl * pitch + (pos[a][it] - ((first_row + rl) * A.in + col0))];
-                    if (OUT == kOutF32) reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
+                    const Pixel v = img[rl * pitch + (pos[a][it] - ((first_row + rl) * A.in + col0))];
+                    if (OUT == kOutPartial) reinterpret_cast<float *>(A.gc)[k] = (float)v;
+                    else if (OUT == kOutF32) reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
                     else reinterpret_cast<_Float16 *>(A.gc)[k] = A.accumulate ? (_Float16)(old[a][it] + v) : v;
                 }
         }
@@ -461,6 +482,28 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     f32x4 acc[4][8];
     bounds[t] = multiply_tile<kTile>(A, row0, col0, wi * 128 * 2, wo * 64 * 2, lds, open, acc);
     __syncthreads();
+    if constexpr (OUT == kOutPartial) {                      // fp32 sums: the ring holds half of the rows at a time
+        constexpr int kHalf = kTile / 2, kSumPitch = kTile + 4;
+        static_assert(kHalf * kSumPitch * 4 <= kLdsBytes, "half of the tile's sums fit in the stages");
+        float *sums = reinterpret_cast<float *>(lds);
+        for (int half = 0; half < 2; ++half) {
+            GatherPass<OUT, kHalf> gather;
+            gather.begin(A, bounds + half * kHalf, bounds + kTile + half * kHalf);
+            if (wo >> 1 == half) {
+#pragma unroll
+                for (int bo = 0; bo < 4; ++bo)
+#pragma unroll
+                    for (int bi = 0; bi < 8; ++bi) {
+                        const int col = wi * 128 + bi * 16 + (lane >> 4) * 4;
+                        *reinterpret_cast<f32x4 *>(sums + ((wo & 1) * 64 + bo * 16 + (lane & 15)) * kSumPitch + col) = acc[bo][bi];
+                    }
+            }
+            __syncthreads();
+            gather.finish(A, sums, kSumPitch, row0 + half * kHalf, col0);
+            __syncthreads();
+        }
+        return;
+    }
     GatherPass<OUT, kTile> gather;
     gather.begin(A, bounds, bounds + kTile);
 
@@ -528,7 +571,15 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
 #pragma unroll
             for (int bi = 0; bi < 4; ++bi) {
                 const int col = wi * 64 + bi * 16 + (lane >> 4) * 4;
-                const f32x4 o = *reinterpret_cast<const f32x4 *>(sums + (wo * 64 + bo * 16 + (lane & 15)) * kSumPitch + col);
+                f32x4 *at = reinterpret_cast<f32x4 *>(sums + (wo * 64 + bo * 16 + (lane & 15)) * kSumPitch + col);
+                const f32x4 o = *at;
+                if (OUT == kOutPartial) {
+                    f32x4 sum;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] = acc[bo][bi][e] + o[e];
+                    *at = sum;
+                    continue;
+                }
                 half4 h;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) h[e] = (_Float16)(acc[bo][bi][e] + o[e]);   // round to nearest even
@@ -537,7 +588,30 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     }
     gather.request_old(A, 0);
     __syncthreads();
-    gather.finish(A, img, kEpiPitch, row0, col0);
+    if constexpr (OUT == kOutPartial) gather.finish(A, sums, kSumPitch, row0, col0);
+    else gather.finish(A, img, kEpiPitch, row0, col0);
+}
+
+// Adds the splits' sums of every kept element in split order, rounds once to fp16 and stores as the
+// unsplit kernels do.  One workgroup row (blockIdx.y) per job.
+constexpr int kSumThreads = 256;
+
+template <int OUT>
+__global__ void __launch_bounds__(kSumThreads) wgrad_sum_kernel(const WgradBatch B)
+{
+    const int j = blockIdx.y;
+    const int64_t nnz = B.job[j].nnz, stride = B.partial_stride[j];
+    const float *__restrict__ part = B.partial[j];
+    for (int64_t k = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; k < nnz; k += (int64_t)gridDim.x * kSumThreads) {
+        float sum = part[k];
+        for (int s = 1; s < B.splits; ++s) sum += part[s * stride + k];
+        const _Float16 h = (_Float16)sum;                        // round to nearest even
+        if (OUT == kOutF32) reinterpret_cast<float *>(B.job[j].gc)[k] = (float)h * B.inv_scale;
+        else {
+            _Float16 *dst = reinterpret_cast<_Float16 *>(B.job[j].gc) + k;
+            *dst = B.accumulate ? (_Float16)(*dst + h) : h;
+        }
+    }
 }
 
 // What the matrix units sustain with nothing to fetch: every wave issues eight independent
@@ -581,7 +655,9 @@ hipError_t configure_once(int *cus)
     if (hipError_t e = hipGetDevice(&device)) return e;
     const uint64_t bit = 1ull << (device & 63);
     if (!(configured.load(std::memory_order_acquire) & bit)) {
-        const void *kernels[4] = {reinterpret_cast<const void *>(&wgrad_big_kernel<kOutF32>),
+        const void *kernels[6] = {reinterpret_cast<const void *>(&wgrad_big_kernel<kOutPartial>),
+                                  reinterpret_cast<const void *>(&wgrad_small_kernel<kOutPartial>),
+                                  reinterpret_cast<const void *>(&wgrad_big_kernel<kOutF32>),
                                   reinterpret_cast<const void *>(&wgrad_big_kernel<kOutF16>),
                                   reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF32>),
                                   reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF16>)};
@@ -606,10 +682,60 @@ hipError_t launch_mfma_rate(int64_t iters, float *sink, int workgroups, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv_scale, int accumulate, hipStream_t s)
+namespace {
+
+// Whether, and how, the tiles of a call are shared by several workgroups each: `splits` workgroups per tile
+// of the shape `small` says; splits == 1: not at all.
+struct SplitPlan {
+    int splits;
+    bool small;
+};
+
+// A call whose large tiles would fill less than half of the compute units has its tokens split over
+// workgroups.  Times in us (measured, one MI355X): a 32-token stage of a large tile 0.62 and 8 around it, a
+// 64-token stage of a small tile 0.50 and 6 around it; the splits' sums are written and read at 4.5 TB/s, by
+// one more launch (3).  A split is taken where it saves a tenth of the call.  Unsplit and split, 10 % kept, us:
+// 512 x 512, 2048 tokens 22.0 -> 16.1, 8192 tokens 63.5 -> 19.6; 1024 x 1024, 8192 tokens 61.4 -> 31.1;
+// 2560 x 2560, 2048 tokens 44.6 -> 37.4, 8192 tokens 138 -> 107; 1024 x 4096, 8192 tokens 78.2 -> 64.9, and
+// 24.7 unsplit at 2048 tokens, where four splits of the large shape take 28.7.
+SplitPlan plan_split(const WgradBatch &b, int cus)
 {
-    WgradBatch b;
-    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate;
+    SplitPlan best = {1, true};
+    const int tiles = b.first_tile[b.jobs];
+    if (tiles * 2 > cus) return best;
+    const int forced = knob(SAMO_KNOB_WGRAD_SPLIT, 0), shape = knob(SAMO_KNOB_WGRAD_TILE, 0);
+    int64_t stages = 0, nnz = 0, quarters = 0;
+    for (int j = 0; j < b.jobs; ++j) {
+        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
+        stages = s > stages ? s : stages;
+        nnz += b.job[j].nnz;
+        quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
+    }
+    if (forced > 1) return {stages > 0 ? (int)(forced < stages ? forced : stages) : 1, shape != kBigTile};
+    if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || stages < 8) return best;
+    double least = 1e30;
+    for (int small = 1; small >= 0; --small) {
+        const int64_t units = small ? quarters : tiles;
+        const double stage_us = small ? 0.25 : 0.62, around = small ? 6.0 : 8.0;
+        for (int s = 1; s <= 16 && s * 4 <= stages; ++s) {
+            if (s == 1 && !small) continue;                      // the rule without splits takes the small shape here
+            const double rounds = (double)ceil_div(units * s, (int64_t)cus);
+            double us = rounds * ((double)ceil_div(stages, (int64_t)s) * stage_us + around);
+            if (s > 1) us = (us + 3.0 + 8.0 * s * (double)nnz / 4.5e6) / 0.9;
+            if (us < least) {
+                least = us;
+                best = {s, small != 0};
+            }
+        }
+    }
+    return best;
+}
+
+// The call's job list with its tiles; false if there is nothing to write.
+bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate, WgradBatch *out)
+{
+    WgradBatch &b = *out;
+    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate; b.splits = 1;
     b.first_tile[0] = 0;
     for (int j = 0; j < count && b.jobs < kWgradMaxJobs; ++j) {
         if (jobs[j].out <= 0 || jobs[j].in <= 0 || jobs[j].nnz <= 0) continue;     // nothing to write
@@ -619,13 +745,75 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
         b.tiles_in[k] = (int)ceil_div(jobs[j].in, kBigTile);
         b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
     }
-    if (b.jobs == 0) return hipSuccess;
+    if (b.jobs == 0) return false;
     for (int k = b.jobs; k < kWgradMaxJobs; ++k) {
         b.job[k] = b.job[0]; b.tiles_out[k] = b.tiles_in[k] = 1; b.first_tile[k + 1] = b.first_tile[b.jobs];
     }
+    return true;
+}
+
+// Places the splits' sums in the workspace (or only adds up its size, with ws == NULL); returns the bytes.
+size_t place_partials(WgradBatch *b, const SplitPlan &plan, unsigned char *ws)
+{
+    const int64_t unit = stage_tokens(plan.small ? kSmallTile : kBigTile);
+    size_t at = 0;
+    b->splits = plan.splits;
+    for (int j = 0; j < kWgradMaxJobs; ++j) {
+        const int64_t stages = ceil_div(b->job[j].tokens, unit);
+        b->split_tokens[j] = ceil_div(stages, (int64_t)plan.splits) * unit;
+        b->partial_stride[j] = ceil_div(b->job[j].nnz, (int64_t)64) * 64;
+        b->partial[j] = reinterpret_cast<float *>(ws + at);
+        if (j < b->jobs) at += (size_t)b->partial_stride[j] * plan.splits * sizeof(float);
+    }
+    return at;
+}
+
+template <int OUT>
+void launch_tiles(const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
+{
+    const unsigned grid = (blocks + 7) / 8 * 8;                 // whole rounds of the 8 XCDs; the surplus exits at once
+    if (small) wgrad_small_kernel<OUT><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
+    else wgrad_big_kernel<OUT><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
+}
+
+}  // namespace
+
+// Bytes launch_wgrad can use to split these jobs' tokens over workgroups (0: it would not split them).
+hipError_t wgrad_workspace(const WgradJob *jobs, int count, size_t *bytes)
+{
+    *bytes = 0;
+    WgradBatch b;
+    if (!list_tiles(jobs, count, 1.f, 0, &b)) return hipSuccess;
+    int cus = 0;
+    if (hipError_t e = configure_once(&cus)) return e;
+    const SplitPlan plan = plan_split(b, cus);
+    if (plan.splits > 1) *bytes = place_partials(&b, plan, nullptr);
+    return hipSuccess;
+}
+
+hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv_scale, int accumulate, void *ws,
+                        size_t ws_bytes, hipStream_t s)
+{
+    WgradBatch b;
+    if (!list_tiles(jobs, count, inv_scale, accumulate, &b)) return hipSuccess;
     int cus = 0;
     if (hipError_t e = configure_once(&cus)) return e;
     const int big_tiles = b.first_tile[b.jobs];
+    if (ws) {
+        const SplitPlan plan = plan_split(b, cus);
+        if (plan.splits > 1 && place_partials(&b, plan, static_cast<unsigned char *>(ws)) <= ws_bytes) {
+            b.quadrants = plan.small ? 1 : 0; b.first = 0; b.tiles = big_tiles;
+            launch_tiles<kOutPartial>(b, plan.small, (unsigned)(big_tiles * plan.splits * (plan.small ? 4 : 1)), s);
+            int64_t most = 0;
+            for (int j = 0; j < b.jobs; ++j) most = b.job[j].nnz > most ? b.job[j].nnz : most;
+            const int64_t wgs = ceil_div(most, (int64_t)kSumThreads);
+            const dim3 grid((unsigned)(wgs < 4096 ? wgs : 4096), (unsigned)b.jobs);
+            if (out_kind == kOutF32) wgrad_sum_kernel<kOutF32><<<grid, dim3(kSumThreads), 0, s>>>(b);
+            else wgrad_sum_kernel<kOutF16><<<grid, dim3(kSumThreads), 0, s>>>(b);
+            return hipGetLastError();
+        }
+        b.splits = 1;
+    }
     const int force = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
     const int round = knob(SAMO_KNOB_WGRAD_ROUND, 0);          // test aid: tiles per round in place of the CU count
     if (round > 0) cus = round;
@@ -639,14 +827,8 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
         as_big = big_tiles - as_small;
     }
     auto launch = [&](bool small, unsigned blocks) {
-        const unsigned grid = (blocks + 7) / 8 * 8;             // whole rounds of the 8 XCDs; the surplus exits at once
-        if (small) {
-            if (out_kind == kOutF32) wgrad_small_kernel<kOutF32><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
-            else wgrad_small_kernel<kOutF16><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
-        } else {
-            if (out_kind == kOutF32) wgrad_big_kernel<kOutF32><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
-            else wgrad_big_kernel<kOutF16><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
-        }
+        if (out_kind == kOutF32) launch_tiles<kOutF32>(b, small, blocks, s);
+        else launch_tiles<kOutF16>(b, small, blocks, s);
     };
     if (as_big > 0) {
         b.quadrants = 0; b.first = 0; b.tiles = as_big;

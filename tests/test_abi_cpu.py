@@ -335,3 +335,31 @@ def test_argument_marshalling_native_and_python_agree(native):
             samo.samo_seg_ptr_len(n)
     for n in (0, 1, 1023, 1024, 1025, 2 ** 31 - 1):
         assert samo.samo_seg_ptr_len(n) == samo.lib().samo_seg_ptr_len(n)
+
+
+def test_weight_gradient_workspace_entries_reject_bad_arguments():
+    import ctypes
+    L = samo.lib()
+    size = ctypes.c_size_t()
+
+    def job(**kw):
+        v = dict(dy=FAKE, x=FAKE, tokens=64, out=8, in_=16, idx=None, seg=None, nnz=128, gc=FAKE)
+        v.update(kw)
+        return (samo.WgradJob * 1)(samo.WgradJob(v["dy"], v["x"], v["tokens"], v["out"], v["in_"], v["idx"], v["seg"], v["nnz"], v["gc"]))
+    calls = (lambda j, n=1: L.samo_wgrad_workspace_bytes(n, j, ctypes.byref(size)),
+             lambda j, n=1: L.samo_wgrad_gather_batched_ws(n, j, 1.0, FAKE, 1 << 20, None),
+             lambda j, n=1: L.samo_wgrad_gather_fp16_batched_ws(n, j, 0, FAKE, 1 << 20, None))
+    for call in calls:
+        assert call(job(in_=12, nnz=96)) == samo.SAMO_ERR_SIZE
+        assert call(job(nnz=90)) == samo.SAMO_ERR_NULL
+        assert call(job(idx=FAKE, nnz=90)) == samo.SAMO_ERR_NULL
+        assert call(job(dy=None)) == samo.SAMO_ERR_NULL
+        assert call(job(x=FAKE + 8)) == samo.SAMO_ERR_ALIGN
+        assert call(job(), samo.SAMO_WGRAD_MAX_JOBS + 1) == samo.SAMO_ERR_SIZE
+        assert call(None) == samo.SAMO_ERR_NULL
+        assert call(None, 0) == samo.SAMO_OK
+        assert call(job(nnz=0, gc=None)) == samo.SAMO_OK
+    assert size.value == 0
+    assert L.samo_wgrad_workspace_bytes(0, None, None) == samo.SAMO_ERR_NULL
+    assert L.samo_wgrad_gather_batched_ws(1, job(), 1.0, FAKE + 4, 1 << 20, None) == samo.SAMO_ERR_ALIGN
+    assert L.samo_wgrad_gather_batched_ws(1, job(), 0.0, FAKE, 1 << 20, None) == samo.SAMO_ERR_ARG

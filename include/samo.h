@@ -487,6 +487,8 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace; 1: never split.  Applies to
  *                        calls of at most half a round of large tiles, with the tile shape SAMO_KNOB_WGRAD_TILE names
  *                        (default there: 128 x 128).
+ *   SAMO_KNOB_WGRAD_COLS   test aid: 128, 160 or 192 columns of a 256-row tile, whatever the rule says (the default
+ *                        takes such tiles for calls of less than a round of 256 x 256 ones where they fill it better).
  *   SAMO_KNOB_TILE_COST    the weight of a plan's tiles in units of 1024 (6 .. 96; default 32, or 48 for a
  *                        model that keeps under 7 % of its elements; 48 there with an fp32 dense side).
  *                        Read by samo_plan_workspace_bytes and samo_plan_init: set it before both.
@@ -505,7 +507,8 @@ enum {
     SAMO_KNOB_INDEX_PASSES = 10,
     SAMO_KNOB_TILE_COST = 11,
     SAMO_KNOB_WGRAD_SPLIT = 12,
-    SAMO_KNOB_COUNT = 13
+    SAMO_KNOB_WGRAD_COLS = 13,
+    SAMO_KNOB_COUNT = 14
 };
 #define SAMO_KNOB_DEFAULT (-1)
 samo_status samo_debug_set(int32_t knob, int32_t value);

@@ -97,6 +97,7 @@ struct WgradBatch {
     int accumulate;
     int quadrants;
     int first, tiles;
+    int tile_cols;                           // columns of a tile that is not quartered: 256, or 128, 160 or 192
     // splits > 1: that many workgroups share a tile, each multiplies split_tokens[j] tokens and leaves its fp32
     // sums at the kept positions in partial[j] + split * partial_stride[j]; wgrad_sum_kernel adds them up.
     int splits;
@@ -105,6 +106,7 @@ struct WgradBatch {
     int64_t partial_stride[kWgradMaxJobs];
 };
 constexpr int kOutPartial = 3;
+constexpr int64_t kMaxGrid = 1 << 24;       // far above any call: the tile lists stay 32-bit
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
 
@@ -173,7 +175,7 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
     const int in_group = tile - group * 4 * tiles_in;
     const int group_rows = tiles_out - group * 4 < 4 ? tiles_out - group * 4 : 4;
     row0 = (group * 4 + in_group % group_rows) * kBigTile;   // first row of dW (feature of dY)
-    col0 = (in_group / group_rows) * kBigTile;               // first column of dW (feature of X)
+    col0 = (in_group / group_rows) * B.tile_cols;            // first column of dW (feature of X)
     if (B.quadrants) {
         row0 += (local & 1) * kSmallTile;
         col0 += ((local >> 1) & 1) * kSmallTile;
@@ -278,8 +280,9 @@ __device__ __forceinline__ void meet()
     asm volatile("" ::: "memory");
 }
 
-// The main loop: acc += the wave's OB x IB blocks of 16 x 16 of a tile.  A stage is 32 LDS rows, row j < 16
-// row_tokens(TILE) consecutive tokens of X (TILE features each), row 16 + j the same tokens of dY.
+// The main loop: acc += the wave's OB x IB blocks of 16 x 16 of a tile of COLS <= TILE columns.  A stage is 32
+// LDS rows, row j < 16 row_tokens(TILE) consecutive tokens of X (room for TILE features each), row 16 + j
+// the same tokens of dY.
 // Waves 0-3 (group 0) copy X, waves 4-7 (group 1) dY.  x_at / y_at: byte offset, within a row, of the
 // wave's first feature of the first of the two tokens it multiplies per row.  Returns the thread's bound;
 // the ring is free after the next __syncthreads.
@@ -295,7 +298,7 @@ __device__ __forceinline__ void meet()
 // bound_window are requested when the last full stage is on its way: the wait for bound_open's results
 // is a wait for every copy in flight, once, where only one or two stages are; after it they can only make
 // the waits of the last stages longer than needed, never shorter.
-template <int TILE, int OB, int IB>
+template <int TILE, int COLS, int OB, int IB>
 __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
                                                 const Bound &open, f32x4 (&acc)[OB][IB])
 {
@@ -307,7 +310,8 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
     const int f0 = group ? row0 : col0;
     const int64_t row_bytes = (int64_t)features * 2;
     const int f = lane % kTokenLanes * 8;
-    const unsigned f_bytes = (unsigned)(f0 + f < features ? f : 0) * 2;
+    const bool wanted = f0 + f < features && (COLS == TILE || group || f < COLS);   // else: the first feature again
+    const unsigned f_bytes = (unsigned)(wanted ? f : 0) * 2;
     const int sub = lane / kTokenLanes;
     const unsigned lane_offset = (unsigned)sub * (unsigned)row_bytes + f_bytes;      // below 2^27: a row has at most 2^24 features
     const unsigned char *gbase = reinterpret_cast<const unsigned char *>(group ? A.dy : A.x) + (int64_t)f0 * 2;
@@ -463,11 +467,12 @@ struct GatherPass {
     }
 };
 
-// 256 x 256 tile: 64 (out) x 128 (in) per wave, waves as 4 x 2; both groups multiply every token.
-template <int OUT>
+// 256 x (32 IB) tile, IB = 8 or fewer for calls of less than a round: 64 (out) x 16 IB (in) per wave, waves as 4 x 2;
+// both groups multiply every token.
+template <int OUT, int IB>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBatch B)
 {
-    constexpr int kTile = kBigTile, kEpiPitch = kTile + 8;
+    constexpr int kTile = kBigTile, kCols = 32 * IB, kEpiPitch = kCols + 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ int bounds[2 * kTile];
     WgradArgs A;
@@ -477,13 +482,13 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     // thread t < 256: the first bound of tile row t; thread 256 + t: its second
-    const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile);
+    const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kCols);
     const int wo = wave & 3, wi = wave >> 2;
-    f32x4 acc[4][8];
-    bounds[t] = multiply_tile<kTile>(A, row0, col0, wi * 128 * 2, wo * 64 * 2, lds, open, acc);
+    f32x4 acc[4][IB];
+    bounds[t] = multiply_tile<kTile, kCols>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, open, acc);
     __syncthreads();
     if constexpr (OUT == kOutPartial) {                      // fp32 sums: the ring holds half of the rows at a time
-        constexpr int kHalf = kTile / 2, kSumPitch = kTile + 4;
+        constexpr int kHalf = kTile / 2, kSumPitch = kCols + 4;
         static_assert(kHalf * kSumPitch * 4 <= kLdsBytes, "half of the tile's sums fit in the stages");
         float *sums = reinterpret_cast<float *>(lds);
         for (int half = 0; half < 2; ++half) {
@@ -493,8 +498,8 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
 #pragma unroll
                 for (int bo = 0; bo < 4; ++bo)
 #pragma unroll
-                    for (int bi = 0; bi < 8; ++bi) {
-                        const int col = wi * 128 + bi * 16 + (lane >> 4) * 4;
+                    for (int bi = 0; bi < IB; ++bi) {
+                        const int col = wi * (kCols / 2) + bi * 16 + (lane >> 4) * 4;
                         *reinterpret_cast<f32x4 *>(sums + ((wo & 1) * 64 + bo * 16 + (lane & 15)) * kSumPitch + col) = acc[bo][bi];
                     }
             }
@@ -513,11 +518,11 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
 #pragma unroll
     for (int bo = 0; bo < 4; ++bo)
 #pragma unroll
-        for (int bi = 0; bi < 8; ++bi) {
+        for (int bi = 0; bi < IB; ++bi) {
             half4 h;
 #pragma unroll
             for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[bo][bi][e];           // round to nearest even
-            const int col = wi * 128 + bi * 16 + (lane >> 4) * 4;
+            const int col = wi * (kCols / 2) + bi * 16 + (lane >> 4) * 4;
             *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
         }
     gather.request_old(A, 0);
@@ -545,7 +550,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     const int wo = wave & 1, wi = (wave >> 1) & 1;
     f32x4 acc[4][4];
     const int tokens_at = half * 2 * kTile * 2;
-    const int closed = multiply_tile<kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
+    const int closed = multiply_tile<kTile, kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
     if (t < 2 * kTile) bounds[t] = closed;
     __syncthreads();
     GatherPass<OUT, kTile> gather;
@@ -645,6 +650,24 @@ __global__ void __launch_bounds__(kWgThreads, 2) mfma_rate_kernel(int64_t iters,
     if (threadIdx.x == 0) sink[blockIdx.x] = sum;
 }
 
+// The 256-row kernel of a width of 32 * blocks columns.
+typedef void (*TileKernel)(const WgradBatch);
+template <int OUT>
+TileKernel tile_kernel_of(int blocks)
+{
+    switch (blocks) {
+    case 4: return &wgrad_big_kernel<OUT, 4>;
+    case 5: return &wgrad_big_kernel<OUT, 5>;
+    case 6: return &wgrad_big_kernel<OUT, 6>;
+    default: return &wgrad_big_kernel<OUT, 8>;
+    }
+}
+const void *big_kernel(int out, int blocks)
+{
+    if (out == kOutPartial) return reinterpret_cast<const void *>(&wgrad_big_kernel<kOutPartial, 8>);
+    return reinterpret_cast<const void *>(out == kOutF32 ? tile_kernel_of<kOutF32>(blocks) : tile_kernel_of<kOutF16>(blocks));
+}
+
 // The LDS size above 64 KiB is a per-device attribute of a kernel: set once per device, where the
 // device's number of compute units is read too.
 hipError_t configure_once(int *cus)
@@ -655,12 +678,11 @@ hipError_t configure_once(int *cus)
     if (hipError_t e = hipGetDevice(&device)) return e;
     const uint64_t bit = 1ull << (device & 63);
     if (!(configured.load(std::memory_order_acquire) & bit)) {
-        const void *kernels[6] = {reinterpret_cast<const void *>(&wgrad_big_kernel<kOutPartial>),
-                                  reinterpret_cast<const void *>(&wgrad_small_kernel<kOutPartial>),
-                                  reinterpret_cast<const void *>(&wgrad_big_kernel<kOutF32>),
-                                  reinterpret_cast<const void *>(&wgrad_big_kernel<kOutF16>),
-                                  reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF32>),
-                                  reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF16>)};
+        const void *kernels[] = {big_kernel(kOutPartial, 8), reinterpret_cast<const void *>(&wgrad_small_kernel<kOutPartial>),
+                                 reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF32>),
+                                 reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF16>),
+                                 big_kernel(kOutF32, 8), big_kernel(kOutF32, 6), big_kernel(kOutF32, 5), big_kernel(kOutF32, 4),
+                                 big_kernel(kOutF16, 8), big_kernel(kOutF16, 6), big_kernel(kOutF16, 5), big_kernel(kOutF16, 4)};
         for (const void *k : kernels)
             if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes)) return e;
         int n = 0;
@@ -712,7 +734,8 @@ SplitPlan plan_split(const WgradBatch &b, int cus)
         quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
     }
     if (forced > 1) return {stages > 0 ? (int)(forced < stages ? forced : stages) : 1, shape != kBigTile};
-    if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || stages < 8) return best;
+    if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || knob(SAMO_KNOB_WGRAD_COLS, 0) > 0 || stages < 8)
+        return best;
     double least = 1e30;
     for (int small = 1; small >= 0; --small) {
         const int64_t units = small ? quarters : tiles;
@@ -735,7 +758,7 @@ SplitPlan plan_split(const WgradBatch &b, int cus)
 bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate, WgradBatch *out)
 {
     WgradBatch &b = *out;
-    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate; b.splits = 1;
+    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate; b.splits = 1; b.tile_cols = kBigTile;
     b.first_tile[0] = 0;
     for (int j = 0; j < count && b.jobs < kWgradMaxJobs; ++j) {
         if (jobs[j].out <= 0 || jobs[j].in <= 0 || jobs[j].nnz <= 0) continue;     // nothing to write
@@ -768,12 +791,66 @@ size_t place_partials(WgradBatch *b, const SplitPlan &plan, unsigned char *ws)
     return at;
 }
 
-template <int OUT>
-void launch_tiles(const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
+void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
 {
-    const unsigned grid = (blocks + 7) / 8 * 8;                 // whole rounds of the 8 XCDs; the surplus exits at once
-    if (small) wgrad_small_kernel<OUT><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
-    else wgrad_big_kernel<OUT><<<dim3(grid), dim3(kWgThreads), kLdsBytes, s>>>(b);
+    const dim3 grid((blocks + 7) / 8 * 8), threads(kWgThreads);  // whole rounds of the 8 XCDs; the surplus exits at once
+    if (small) {
+        if (out_kind == kOutPartial) wgrad_small_kernel<kOutPartial><<<grid, threads, kLdsBytes, s>>>(b);
+        else if (out_kind == kOutF32) wgrad_small_kernel<kOutF32><<<grid, threads, kLdsBytes, s>>>(b);
+        else wgrad_small_kernel<kOutF16><<<grid, threads, kLdsBytes, s>>>(b);
+    } else if (out_kind == kOutPartial) wgrad_big_kernel<kOutPartial, 8><<<grid, threads, kLdsBytes, s>>>(b);
+    else if (out_kind == kOutF32) tile_kernel_of<kOutF32>(b.tile_cols / 32)<<<grid, threads, kLdsBytes, s>>>(b);
+    else tile_kernel_of<kOutF16>(b.tile_cols / 32)<<<grid, threads, kLdsBytes, s>>>(b);
+}
+
+// How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the
+// last `quarters` large tiles of the list as small ones (blocks is 8 then).
+struct TilePlan {
+    int wide, quarters, blocks;
+};
+
+// Large tiles in whole rounds of the compute units; what is left over after the last whole
+// round goes to the small shape when that is the quicker way to finish it: up to half a round
+// of large tiles is at most two rounds of small ones, and a small round takes 0.4 of a large.
+// A call of less than a round leaves compute units idle, and narrower tiles that fill the round
+// better are quicker: by the times (us, one MI355X) of a 32-token stage of a tile and of what is around it,
+// 0.70 and 9 for 256 columns, 0.70 * (IB + 1) / 9 and 8 for 32 IB (a narrower tile brings fewer results per byte
+// copied), against 0.25 and 6 for a round of small ones.  3072 x 3072 (144 large tiles, 228 of 160
+// columns): 2048 tokens 47.5 -> 43.8 us, 512 tokens 21.5 -> 18.9; 2560 x 2560 without a workspace (100, or 200 of 128
+// columns) 42.1 -> 38.4.  Behind whole rounds the same (the last columns of the largest layer in narrower tiles
+// that make one full round) gains nothing: with all compute units busy the chip is at its power limit, and
+// idle ones let the others run faster (400 tiles 107.1 -> 103.6 us, but 102.4 -> 106.1 for the
+// transposed layer and 104.1 -> 110.0 for 432 tiles).
+TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
+{
+    const int tiles = b.first_tile[b.jobs];
+    const int shape = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
+    if (shape == kSmallTile) return {0, tiles, 8};
+    if (shape == kBigTile || cus <= 0) return {tiles, 0, 8};
+    const int forced_cols = knob(SAMO_KNOB_WGRAD_COLS, 0);     // test aid: narrow tiles whatever they cost
+    const int left = tiles % cus;
+    TilePlan plan = {tiles, 0, 8};
+    if (left != 0 && left <= cus / 2) plan = {tiles - left, left, 8};
+    if (forced_cols == 0 && (tiles >= cus || round_forced)) return plan;
+    int64_t stages = 0;
+    for (int j = 0; j < b.jobs; ++j) {
+        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
+        stages = s > stages ? s : stages;
+    }
+    const double n = (double)stages;
+    double least = plan.quarters ? (double)ceil_div((int64_t)left * 4, (int64_t)cus) * (0.25 * n + 6.0) : 0.70 * n + 9.0;
+    if (forced_cols) least = 1e30;
+    for (int blocks = 4; blocks <= 6; ++blocks) {
+        if (forced_cols && forced_cols != 32 * blocks) continue;
+        int64_t narrow = 0;
+        for (int j = 0; j < b.jobs; ++j) narrow += b.tiles_out[j] * ceil_div((int64_t)b.job[j].in, (int64_t)(32 * blocks));
+        const double us = (double)ceil_div(narrow, (int64_t)cus) * (0.70 * (blocks + 1) / 9.0 * n + 8.0);
+        if (narrow <= kMaxGrid && us < least) {
+            least = us;
+            plan = {(int)narrow, 0, blocks};
+        }
+    }
+    return plan;
 }
 
 }  // namespace
@@ -803,7 +880,7 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
         const SplitPlan plan = plan_split(b, cus);
         if (plan.splits > 1 && place_partials(&b, plan, static_cast<unsigned char *>(ws)) <= ws_bytes) {
             b.quadrants = plan.small ? 1 : 0; b.first = 0; b.tiles = big_tiles;
-            launch_tiles<kOutPartial>(b, plan.small, (unsigned)(big_tiles * plan.splits * (plan.small ? 4 : 1)), s);
+            launch_tiles(kOutPartial, b, plan.small, (unsigned)(big_tiles * plan.splits * (plan.small ? 4 : 1)), s);
             int64_t most = 0;
             for (int j = 0; j < b.jobs; ++j) most = b.job[j].nnz > most ? b.job[j].nnz : most;
             const int64_t wgs = ceil_div(most, (int64_t)kSumThreads);
@@ -814,29 +891,22 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
         }
         b.splits = 1;
     }
-    const int force = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
     const int round = knob(SAMO_KNOB_WGRAD_ROUND, 0);          // test aid: tiles per round in place of the CU count
-    if (round > 0) cus = round;
-    // Large tiles in whole rounds of the compute units; what is left over after the last whole
-    // round goes to the small shape when that is the quicker way to finish it: up to half a round
-    // of large tiles is at most two rounds of small ones, and a small round takes 0.4 of a large.
-    int as_big = big_tiles, as_small = 0;
-    if (force == kSmallTile) as_big = 0, as_small = big_tiles;
-    else if (force != kBigTile && cus > 0 && big_tiles % cus != 0 && big_tiles % cus <= cus / 2) {
-        as_small = big_tiles % cus;
-        as_big = big_tiles - as_small;
+    const TilePlan plan = plan_tiles(b, round > 0 ? round : cus, round > 0);
+    if (plan.wide > 0) {
+        b.quadrants = 0; b.first = 0; b.tiles = plan.wide;
+        if (plan.blocks != 8) {
+            b.tile_cols = 32 * plan.blocks;
+            for (int k = 0; k < b.jobs; ++k) {
+                b.tiles_in[k] = (int)ceil_div(b.job[k].in, b.tile_cols);
+                b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
+            }
+        }
+        launch_tiles(out_kind, b, false, (unsigned)plan.wide, s);
     }
-    auto launch = [&](bool small, unsigned blocks) {
-        if (out_kind == kOutF32) launch_tiles<kOutF32>(b, small, blocks, s);
-        else launch_tiles<kOutF16>(b, small, blocks, s);
-    };
-    if (as_big > 0) {
-        b.quadrants = 0; b.first = 0; b.tiles = as_big;
-        launch(false, (unsigned)as_big);
-    }
-    if (as_small > 0) {
-        b.quadrants = 1; b.first = as_big; b.tiles = as_small;
-        launch(true, (unsigned)(as_small * 4));
+    if (plan.quarters > 0) {
+        b.quadrants = 1; b.first = plan.wide; b.tiles = plan.quarters;
+        launch_tiles(out_kind, b, true, (unsigned)(plan.quarters * 4), s);
     }
     return hipGetLastError();
 }

@@ -115,6 +115,7 @@ __device__ __forceinline__ int find_job(const IndexBatch &batch, int wg)
 // fullest lane of the wave has kept elements, about 8 times for a pair at 10 % kept, where two words of 16
 // took 5 to 6 each.
 constexpr int kSegsPerPass = 8;           // per wave
+constexpr int kCountLdsPad = 22000;       // beside the kernel's 33 KB: two workgroups to a compute unit's 160 KB
 constexpr int kPairs = kSegsPerPass / 2;
 static_assert(kFlagGroupSegs == kSegsPerPass && kPairs == 4, "a lane's flag words of a pass are one 16-byte vector");
 constexpr int kMaxPasses = 4;
@@ -415,9 +416,13 @@ hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
     index_init_kernel<<<dim3((unsigned)ceil_div(init_threads, kThreads)), dim3(kThreads), 0, s>>>(batch);
     if (wgs > 0) {
         const dim3 grid((unsigned)wgs), block(kIndexThreads);
-        if (batch.passes == 4) index_kernel<4><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
-        else if (batch.passes == 2) index_kernel<2><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
-        else index_kernel<1><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
+        // A launch that only counts reads as fast as the memory lets it and runs best with two workgroups per
+        // compute unit, not four (with the flag bits of 32 and 7 layers of the 2.7B shape 537 and 128 us against
+        // 558 and 133, without them 462 against 466); one that fills as well needs the waves (765 against 757).
+        const int pad = fill ? 0 : kCountLdsPad;
+        if (batch.passes == 4) index_kernel<4><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
+        else if (batch.passes == 2) index_kernel<2><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
+        else index_kernel<1><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
     }
     return hipGetLastError();
 }

@@ -91,6 +91,7 @@ struct WgradArgs {
 struct WgradBatch {
     WgradJob job[kWgradMaxJobs];
     int tiles_out[kWgradMaxJobs], tiles_in[kWgradMaxJobs];
+    uint32_t per_group[kWgradMaxJobs];       // 2^32 / (4 * tiles_in), rounded up
     int first_tile[kWgradMaxJobs + 1];       // 32 bits: a layer of less than 2^31 elements, sides up to 2^24, has about 10^5 tiles at most
     int jobs;
     float inv_scale;
@@ -154,9 +155,18 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
     const int split = B.splits > 1 ? local / shares : 0;         // the tiles of one split stay together
     local -= split * shares;
     const int listed = B.first + (B.quadrants ? local >> 2 : local);
-    int j = 0;
-    while (j + 1 < B.jobs && listed >= B.first_tile[j + 1]) ++j;
-    const WgradJob &J = B.job[j];
+    // The workgroup's first copies wait for this function, and what it reads comes from the kernel arguments by way of
+    // cold caches: a single job's descriptor is read at fixed places, all at once, and only a list of
+    // several is searched.
+    WgradJob J = B.job[0];
+    int j = 0, first = 0, tiles_out = B.tiles_out[0], tiles_in = B.tiles_in[0];
+    uint32_t per_group = B.per_group[0];
+    if (B.jobs > 1) {
+        while (j + 1 < B.jobs && listed >= B.first_tile[j + 1]) ++j;
+        J = B.job[j];
+        first = B.first_tile[j]; tiles_out = B.tiles_out[j]; tiles_in = B.tiles_in[j];
+        per_group = B.per_group[j];
+    }
     A.dy = J.dy; A.x = J.x; A.tokens = J.tokens; A.out = J.out; A.in = J.in;
     A.idx = J.idx; A.seg_ptr = J.seg_ptr; A.nnz = J.nnz; A.gc = J.gc;
     A.inv_scale = B.inv_scale; A.accumulate = B.accumulate;
@@ -169,13 +179,15 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
         }
         A.gc = B.partial[j] + split * B.partial_stride[j];
     }
-    const int tile = listed - B.first_tile[j];
-    const int tiles_out = B.tiles_out[j], tiles_in = B.tiles_in[j];
-    const int group = tile / (4 * tiles_in);
+    const int tile = listed - first;
+    // tile / (4 * tiles_in) by the reciprocal the host prepared (2^32 over it, rounded up: one too many at most)
+    int group = (int)(((uint64_t)(uint32_t)tile * per_group) >> 32);
+    if (group * 4 * tiles_in > tile) --group;
     const int in_group = tile - group * 4 * tiles_in;
     const int group_rows = tiles_out - group * 4 < 4 ? tiles_out - group * 4 : 4;
-    row0 = (group * 4 + in_group % group_rows) * kBigTile;   // first row of dW (feature of dY)
-    col0 = (in_group / group_rows) * B.tile_cols;            // first column of dW (feature of X)
+    const int across = group_rows == 4 ? in_group >> 2 : in_group / group_rows;
+    row0 = (group * 4 + in_group - across * group_rows) * kBigTile;   // first row of dW (feature of dY)
+    col0 = across * B.tile_cols;                             // first column of dW (feature of X)
     if (B.quadrants) {
         row0 += (local & 1) * kSmallTile;
         col0 += ((local >> 1) & 1) * kSmallTile;
@@ -754,6 +766,8 @@ SplitPlan plan_split(const WgradBatch &b, int cus)
     return best;
 }
 
+uint32_t per_group_of(int tiles_in) { return (uint32_t)((1ull << 32) / (4u * (uint32_t)tiles_in) + 1u); }
+
 // The call's job list with its tiles; false if there is nothing to write.
 bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate, WgradBatch *out)
 {
@@ -767,10 +781,12 @@ bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate
         b.tiles_out[k] = (int)ceil_div(jobs[j].out, kBigTile);
         b.tiles_in[k] = (int)ceil_div(jobs[j].in, kBigTile);
         b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
+        b.per_group[k] = per_group_of(b.tiles_in[k]);
     }
     if (b.jobs == 0) return false;
     for (int k = b.jobs; k < kWgradMaxJobs; ++k) {
         b.job[k] = b.job[0]; b.tiles_out[k] = b.tiles_in[k] = 1; b.first_tile[k + 1] = b.first_tile[b.jobs];
+        b.per_group[k] = per_group_of(1);
     }
     return true;
 }
@@ -900,6 +916,7 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
             for (int k = 0; k < b.jobs; ++k) {
                 b.tiles_in[k] = (int)ceil_div(b.job[k].in, b.tile_cols);
                 b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
+                b.per_group[k] = per_group_of(b.tiles_in[k]);
             }
         }
         launch_tiles(out_kind, b, false, (unsigned)plan.wide, s);

@@ -409,7 +409,7 @@ samo_status samo_wgrad_gather_fp16(const uint16_t *d_dy, const uint16_t *d_x, in
 /* The same for several layers in one call: the tiles of all the jobs' layers are dealt to the
  * compute units as one list, so that a layer whose own tiles would end in a partly filled round
  * shares that round with the next layer (the four matrices of a GPT-3 2.7B transformer layer at
- * 2048 tokens: 0.35 ms in one call against 0.42 ms in four).  The caller holds dY and X of all
+ * 2048 tokens: 0.30 ms in one call against 0.39 ms in four).  The caller holds dY and X of all
  * the jobs' layers until the call — it trades that memory for the time.  Each job is one layer
  * with the arguments of samo_wgrad_gather / samo_wgrad_gather_fp16 (d_gc: fp32 for
  * samo_wgrad_gather_batched, fp16 for samo_wgrad_gather_fp16_batched; tokens may differ between
@@ -479,9 +479,9 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *                        workgroup; default: 4 for launches with at least a dozen blocks of that size per
  *                        compute unit, else 2 or 1).
  *   SAMO_KNOB_WGRAD_TILE   128 or 256: forces the tile shape of the weight-gradient entries
- *                        (default: 128 x 128 for layers of at most 128 tiles of 256 x 256, which
- *                        would leave compute units idle, else 256 x 256 in whole rounds of the
- *                        compute units and 128 x 128 for a remainder of at most half a round).
+ *                        (default: 256 x 256 in whole rounds of the compute units and 128 x 128 for a
+ *                        remainder of at most half a round; calls of less than a round take 128 x 128
+ *                        or narrower tiles of 256 rows, whichever fills the device better).
  *   SAMO_KNOB_WGRAD_ROUND  test aid: the number of tiles taken as one round in that rule, in
  *                        place of the device's compute-unit count.
  *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace; 1: never split.  Applies to

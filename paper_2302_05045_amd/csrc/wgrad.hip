@@ -20,13 +20,15 @@
 // and the kernels count their outstanding copies themselves: every stage is exactly 4 copies per
 // wave, the partial last stage included (rows past the last token are copied from a row of zeros).
 //
-// Two tile shapes, both 8 waves with two waves per SIMD, in two groups of four (waves 0-3, 4-7: one
+// Tile shapes, all 8 waves with two waves per SIMD, in two groups of four (waves 0-3, 4-7: one
 // of each group per SIMD):
 //   256 x 256, 32 tokens per stage, 64 (out) x 128 (in) per wave, 128 accumulators;
-//   128 x 128 for what is left of a layer after whole rounds of large tiles, where that is at
-//   most half a round (so also for every layer of up to 128 large tiles): each group covers the whole
-//   tile with 64 x 64 per wave (64 accumulators) and multiplies half of the tokens of every 64-token
-//   stage; group 1 hands its sums to group 0 through LDS at the end.
+//   256 rows x 128, 160 or 192 columns for calls that large tiles would not fill a round with;
+//   128 x 128 for smaller calls, and for what is left of a call after whole rounds of large tiles where
+//   that is at most half a round: each group covers the whole tile with 64 x 64 per wave (64
+//   accumulators) and multiplies half of the tokens of every 64-token stage; group 1 hands its sums to
+//   group 0 through LDS at the end.
+// Calls of few tiles may have their tokens split over several workgroups per tile (plan_split).
 //
 // What bounds the large tile: power, and the overlap of its parts.  Per 32-token stage of a
 // 256 x 256 tile (all compute units, ordinary fp16 values), in cycles: the matrix instructions

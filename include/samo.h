@@ -179,7 +179,8 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
  * idx_capacity are ignored), and every job's flag bits are left in h_flags[j], a HOST array of
  * DEVICE pointers.
  * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
- * flag bits and the seg_ptr such a call left, later on the same stream; the mask is not read. */
+ * flag bits, the seg_ptr and the nnz such a call left, later on the same stream; the mask is not read.
+ * A job whose count gave up (*nnz = -1) is left without positions. */
 samo_status samo_index_flags_bytes(int64_t n, size_t *bytes);
 samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,
                                      void *stream);

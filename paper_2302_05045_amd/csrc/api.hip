@@ -291,6 +291,7 @@ samo_status samo_fill_index_batched(const samo_index_job *h_jobs, void *const *h
             batch.idx[i] = J.idx;
             batch.cap[i] = J.idx_capacity;
             batch.seg_ptr[i] = J.seg_ptr;
+            batch.nnz[i] = J.nnz;
             batch.flags[i] = reinterpret_cast<uint4 *>(h_flags[j]);
             wgs += w;
         }

@@ -119,6 +119,14 @@ struct IndexBatch {
 };
 static_assert(sizeof(IndexBatch) <= 3072, "the job table must fit the kernel argument segment");
 
+// Of `count` positions on their way to idx[at ..], how many may be stored where idx has room for cap: those
+// inside [0, cap) from `at` on, none if `at` is not an offset into it.
+__host__ __device__ inline int storable(int64_t cap, int64_t at, int count)
+{
+    if (at < 0 || at >= cap) return 0;
+    return cap - at < count ? (int)(cap - at) : count;
+}
+
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) -----------------------

@@ -231,8 +231,7 @@ __device__ __forceinline__ void emit_pair(uint32_t word, int first, int64_t out0
             bits &= bits - 1;
         }
         __builtin_amdgcn_wave_barrier();
-        const int64_t room = cap - out0 - from;
-        const int count = room < to - from ? (int)room : to - from;      // not positive where the room has run out
+        const int count = storable(cap, out0 + from, to - from);
         int32_t *__restrict__ out = idx + out0 + from;
         for (int o = lane; o < count; o += 64) out[o] = stage[o];
         __builtin_amdgcn_wave_barrier();
@@ -340,6 +339,8 @@ index_kernel(const IndexBatch batch, int fill)
 
 // The positions from the flag words and the seg_ptr a counting launch left: a wave takes a group of eight
 // segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
+// A count that gave up left *nnz = -1 and a seg_ptr that is no table of offsets (chain states, entries never
+// written): nothing is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
 // What bounds it: the loop over a lane's kept elements (7 vector instructions and an LDS store a trip, 8 trips
 // a pair at 10 % kept) beside the index written, 4 bytes per kept element: 4.6 TB/s at 10 % kept.
 constexpr int kFillWaves = 4;
@@ -353,7 +354,7 @@ fill_kernel(const IndexBatch batch)
     const int64_t nseg = (batch.n[job] + kSeg - 1) / kSeg;
     const int64_t group = (int64_t)((int)blockIdx.x - batch.wg_start[job]) * kFillWaves + wave;
     const int64_t seg0 = group * kFlagGroupSegs;
-    if (seg0 >= nseg) return;                 // whole waves leave; nothing below is a workgroup barrier
+    if (seg0 >= nseg || *batch.nnz[job] < 0) return;      // whole waves leave; nothing below is a workgroup barrier
     const uint4 w = batch.flags[job][group * 64 + lane];
     const uint32_t halves[kPairs] = {w.x, w.y, w.z, w.w};
     uint32_t word[kPairs];

@@ -309,6 +309,34 @@ def test_two_call_index_build_rejects_bad_arguments():
         assert entry(None, None, 0, None) == samo.SAMO_OK
 
 
+def test_positions_are_stored_inside_the_index_whatever_the_offset(tmp_path):
+    """The bound that every store of the index build goes through (storable, common.h), on the host: offsets a table
+    may hold after a count that gave up (chain states are -1 - count and INT32_MIN + 1) and around the capacity."""
+    import subprocess
+    from paper_2302_05045_amd import _build
+    src, exe = tmp_path / "storable.hip", tmp_path / "storable"
+    src.write_text("""
+        #include <cstdio>
+        #include "common.h"
+        int main() {
+            const int64_t caps[] = {0, 1, 700, 1000000, 2147483647};
+            const int64_t ats[] = {INT64_MIN, -2147483648ll, -2147483647ll, -1025, -1, 0, 1, 699, 700, 701, 999500, 2147483600, 2147483647, 4294967296ll};
+            const int counts[] = {0, 1, 64, 1024, 2048};
+            for (int64_t cap : caps) for (int64_t at : ats) for (int count : counts) {
+                const int got = samo::storable(cap, at, count);
+                int want = 0;
+                for (int i = 0; i < count; ++i) want += at >= 0 && at + i < cap;
+                if (got != want) { std::printf("cap %lld at %lld count %d: %d, not %d\\n", (long long)cap, (long long)at, count, got, want); return 1; }
+            }
+            return 0;
+        }""")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.check_call([hipcc, "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                           "-w", "-I", os.path.join(ROOT, "include"), "-I", _build.CSRC, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+
+
 @pytest.mark.parametrize("native", [True, False])
 def test_argument_marshalling_native_and_python_agree(native):
     """Both forms refuse the same arguments with the same words (a GPU is not needed to be refused)."""

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 SIZES = [1, 31, 32, 33, 1024, 1025, 2047, 2048, 2049, 8191, 8192, 8193, 32768, 32769, 5 * 32768 + 4097]
 
 
-def _two_calls(masks, caps):
+def _two_calls(masks, caps, between=None):
     k = len(masks)
     seg = [torch.full((samo.samo_seg_ptr_len(m.numel()),), -7, dtype=torch.int32, device=DEV) for m in masks]
     sizes = [samo.samo_index_flags_bytes(m.numel()) for m in masks]
@@ -36,6 +36,8 @@ def _two_calls(masks, caps):
     assert all((i == -1).all() for i in idx), "counting wrote positions"
     for s, f in zip(sizes, flags):
         assert (f[s:] == 0xA5).all(), "flag bits past their buffer"
+    if between is not None:
+        between(nnz)
     assert samo.lib().samo_fill_index_batched(jobs, ptrs, k, stream) == samo.SAMO_OK
     torch.cuda.synchronize()
     return seg, idx, nnz.cpu().tolist()
@@ -78,3 +80,16 @@ def test_fill_stops_at_the_capacity(n, keep, cap):
     assert nnz[0] == ref.shape[0]
     assert np.array_equal(idx[0][:cap].cpu().numpy(), ref[:cap])
     assert (idx[0][cap:] == -1).all()
+
+
+def test_fill_after_a_count_that_gave_up_writes_nothing():
+    """Such a count reports -1.  The report alone is planted here (seg_ptr stays the valid one): the other job is filled."""
+    masks = [si.bernoulli_mask(n, 0.3, n) for n in (50000, 50001)]
+    refs = [oracle.build_index(m) for m in masks]
+
+    def give_up(nnz):
+        nnz[0] = -1
+    seg, idx, nnz = _two_calls([dev_u8(m) for m in masks], [r.shape[0] for r in refs], give_up)
+    assert nnz == [-1, refs[1].shape[0]]
+    assert (idx[0] == -1).all()
+    assert np.array_equal(idx[1][:refs[1].shape[0]].cpu().numpy(), refs[1])

@@ -1,10 +1,13 @@
 """Python binding of libsamo — the SAMO compressed-parameter pipeline for MI355X.
 
-Argument marshalling only: every function takes torch tensors that already live
+Argument marshalling: every function takes torch tensors that already live
 on the GPU, passes their device pointers and the current HIP stream through the
 C ABI declared in ``include/samo.h``, and returns.  All arithmetic and data
-movement happens in the library's HIP kernels.  There is no CPU fallback: if the
-shared library has not been built, importing the first symbol raises.
+movement happens in the library's HIP kernels.  Memory is allocated where results are
+returned (the index build) and, as scratch given back in stream order, by the index
+build (an eighth of the masks) and by weight gradients of small layers that are given
+no workspace.  There is no CPU fallback: if the shared library has not been built,
+importing the first symbol raises.
 
 Names and semantics follow ``samo.h`` one to one (Section III of the paper):
 ``samo_build_index``, ``samo_decompress``, ``samo_gather_grads``,
@@ -448,22 +451,26 @@ def _wgrad_args(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Tensor], 
 
 
 def samo_wgrad_gather(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Tensor], seg_ptr: Optional[torch.Tensor],
-                      inv_loss_scale: float, gc: torch.Tensor) -> None:
+                      inv_loss_scale: float, gc: torch.Tensor, workspace: Optional[torch.Tensor] = None) -> None:
     """gc = the weight gradient dy^T x (tokens x out, tokens x in -> out x in), rounded to fp16, at idx,
-    times inv_loss_scale."""
+    times inv_loss_scale.
+
+    workspace (uint8, samo_wgrad_workspace_bytes of them; an empty one: none) is in use until the stream has passed
+    the call.  Without one a small layer's call takes it from torch's allocator (_wgrad_workspace)."""
     jobs = (WgradJob * 1)()
     large = _wgrad_job(jobs, 0, dy, x, idx, seg_ptr, gc, torch.float32, "gc")
-    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, gc)
+    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, workspace)
     _check(lib().samo_wgrad_gather_batched_ws(1, jobs, float(inv_loss_scale), _ptr(ws), ws_bytes, _stream()),
            "samo_wgrad_gather")
 
 
 def samo_wgrad_gather_fp16(dy: torch.Tensor, x: torch.Tensor, idx: Optional[torch.Tensor],
-                           seg_ptr: Optional[torch.Tensor], gc16: torch.Tensor, accumulate: bool = False) -> None:
+                           seg_ptr: Optional[torch.Tensor], gc16: torch.Tensor, accumulate: bool = False,
+                           workspace: Optional[torch.Tensor] = None) -> None:
     """gc16 = that weight gradient, rounded to fp16, at idx; added to gc16 (in fp16) if accumulate."""
     jobs = (WgradJob * 1)()
     large = _wgrad_job(jobs, 0, dy, x, idx, seg_ptr, gc16, _F16, "gc16")
-    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, gc16)
+    ws, ws_bytes = _wgrad_workspace(jobs, 1, large, workspace)
     _check(lib().samo_wgrad_gather_fp16_batched_ws(1, jobs, int(bool(accumulate)), _ptr(ws), ws_bytes, _stream()),
            "samo_wgrad_gather_fp16")
 
@@ -477,19 +484,57 @@ def _wgrad_job(arr, j: int, dy, x, idx, seg_ptr, gc, dtype, name: str) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
-    return None if t is None else t.data_ptr()
+    return None if t is None or not t.numel() else t.data_ptr()
 
 
-def _wgrad_workspace(jobs, count: int, tiles: int, gc: torch.Tensor):
-    """(workspace, bytes) for layers too small to occupy the device, freed in stream order; (None, 0) where the library
-    would not split the call (it never does above half a round of large tiles: no need to ask)."""
-    if tiles > 160:
-        return None, 0
+def samo_wgrad_workspace_bytes(jobs) -> int:
+    """Size of the workspace worth passing to the weight gradient of these (dy, x, idx, seg_ptr, gc) on the
+    current device; 0 where the call would not use one."""
+    arr = (WgradJob * max(len(jobs), 1))()
+    for j, (dy, x, idx, seg_ptr, gc) in enumerate(jobs):
+        _wgrad_job(arr, j, dy, x, idx, seg_ptr, gc, gc.dtype, "gc of job %d" % j)
+    return _wgrad_need(arr, len(jobs))
+
+
+def _wgrad_need(jobs, count: int) -> int:
     need = ctypes.c_size_t()
     _check(lib().samo_wgrad_workspace_bytes(count, jobs, ctypes.byref(need)), "samo_wgrad_workspace_bytes")
-    if not need.value:
+    return need.value
+
+
+def _wgrad_workspace(jobs, count: int, tiles: int, given: Optional[torch.Tensor]):
+    """(workspace, bytes) of a call: what the caller gave, or, for layers too small to occupy the device, scratch memory
+    for the length of the call; (None, 0) where the library would not split the call (it never does above half a
+    round of large tiles: no need to ask)."""
+    if given is not None:
+        _dev(given, torch.uint8, "workspace")
+        return given, given.numel()
+    if tiles > 160:
         return None, 0
-    return torch.empty(need.value, dtype=torch.uint8, device=gc.device), need.value
+    need = _wgrad_need(jobs, count)
+    ws = _scratch(need) if need else None
+    return ws, (need if ws is not None else 0)
+
+
+def _scratch(nbytes: int) -> Optional[torch.Tensor]:
+    """Scratch memory for the kernels that the current call enqueues, given back in stream order when the call returns.
+    It belongs to the device and the stream that the launches go to, wherever the arguments live.  None where there is
+    no memory for it, and where the memory would have to outlive the call: a capture replays the kernels later, so
+    while one is under way only memory of the graph's own pool will do.  torch's captures allocate from
+    such a pool; in a capture begun any other way the allocator's ordinary blocks would be handed to somebody else."""
+    try:
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    except torch.OutOfMemoryError:
+        return None
+    if torch.cuda.is_current_stream_capturing() and not _in_private_pool(t):
+        return None
+    return t
+
+
+def _in_private_pool(t: torch.Tensor) -> bool:
+    at = t.data_ptr()
+    return any(seg["address"] <= at < seg["address"] + seg["total_size"] and tuple(seg.get("segment_pool_id", (0, 0))) != (0, 0)
+               for seg in torch.cuda.memory_snapshot())
 
 
 def _wgrad_jobs(jobs, dtype, name: str):
@@ -501,19 +546,19 @@ def _wgrad_jobs(jobs, dtype, name: str):
     return arr, tiles
 
 
-def samo_wgrad_gather_batched(jobs, inv_loss_scale: float) -> None:
+def samo_wgrad_gather_batched(jobs, inv_loss_scale: float, workspace: Optional[torch.Tensor] = None) -> None:
     """samo_wgrad_gather for every (dy, x, idx, seg_ptr, gc) of jobs (at most SAMO_WGRAD_MAX_JOBS), the
     layers' tiles dealt to the compute units as one list."""
     arr, tiles = _wgrad_jobs(jobs, torch.float32, "gc")
-    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, jobs[0][4]) if jobs else (None, 0)
+    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, workspace)
     _check(lib().samo_wgrad_gather_batched_ws(len(jobs), arr, float(inv_loss_scale), _ptr(ws), ws_bytes, _stream()),
            "samo_wgrad_gather_batched")
 
 
-def samo_wgrad_gather_fp16_batched(jobs, accumulate: bool = False) -> None:
+def samo_wgrad_gather_fp16_batched(jobs, accumulate: bool = False, workspace: Optional[torch.Tensor] = None) -> None:
     """samo_wgrad_gather_fp16 for every (dy, x, idx, seg_ptr, gc16) of jobs."""
     arr, tiles = _wgrad_jobs(jobs, _F16, "gc16")
-    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, jobs[0][4]) if jobs else (None, 0)
+    ws, ws_bytes = _wgrad_workspace(arr, len(jobs), tiles, workspace)
     _check(lib().samo_wgrad_gather_fp16_batched_ws(len(jobs), arr, int(bool(accumulate)), _ptr(ws), ws_bytes, _stream()),
            "samo_wgrad_gather_fp16_batched")
 

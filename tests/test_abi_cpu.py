@@ -391,3 +391,11 @@ def test_weight_gradient_workspace_entries_reject_bad_arguments():
     assert L.samo_wgrad_workspace_bytes(0, None, None) == samo.SAMO_ERR_NULL
     assert L.samo_wgrad_gather_batched_ws(1, job(), 1.0, FAKE + 4, 1 << 20, None) == samo.SAMO_ERR_ALIGN
     assert L.samo_wgrad_gather_batched_ws(1, job(), 0.0, FAKE, 1 << 20, None) == samo.SAMO_ERR_ARG
+
+
+def test_python_weight_gradient_entries_take_a_workspace():
+    import inspect
+    for f in (samo.samo_wgrad_gather, samo.samo_wgrad_gather_fp16, samo.samo_wgrad_gather_batched, samo.samo_wgrad_gather_fp16_batched):
+        p = inspect.signature(f).parameters
+        assert list(p)[-1] == "workspace" and p["workspace"].default is None
+    assert samo.samo_wgrad_workspace_bytes([]) == 0

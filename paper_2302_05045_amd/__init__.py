@@ -322,23 +322,27 @@ def samo_build_index(mask: torch.Tensor) -> Index:
 
 def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     """Index of every mask: one batched count that reads the masks and leaves their flag bits, one read-back
-    of the counts to size the indices, one batched fill from the flag bits."""
+    of the counts to size the indices, one batched fill from the flag bits.  Without memory for those
+    (an eighth of the masks) the second call reads the masks again."""
     dev, k = masks[0].device, len(masks)
     sizes = [m.numel() for m in masks]
     seg_lens = [samo_seg_ptr_len(n) for n in sizes]
     flag_bytes = [(s + 6) // 8 * 1024 for s in seg_lens]                 # samo_index_flags_bytes: 1 KiB per eight segments
-    flag_buf = torch.empty(max(sum(flag_bytes), 1), dtype=torch.uint8, device=dev)      # used and freed in stream order
+    flag_buf = _scratch(max(sum(flag_bytes), 1))
     nnz_out = torch.empty(k, dtype=torch.int64, device=dev)
     jobs, flags = (IndexJob * k)(), (ctypes.c_void_p * k)()
     seg_ptrs = []
-    nnz_at, flags_at = nnz_out.data_ptr(), flag_buf.data_ptr()
+    nnz_at, flags_at = nnz_out.data_ptr(), flag_buf.data_ptr() if flag_buf is not None else 0
     for i, m in enumerate(masks):
         seg_ptr = torch.empty(seg_lens[i], dtype=torch.int32, device=dev)
         seg_ptrs.append(seg_ptr)
         jobs[i] = IndexJob(_dev(m, torch.uint8, "mask"), sizes[i], None, 0, seg_ptr.data_ptr(), nnz_at + 8 * i)
         flags[i] = flags_at
         flags_at += flag_bytes[i]
-    _check(lib().samo_count_flags_batched(jobs, flags, k, _stream()), where)
+    if flag_buf is not None:
+        _check(lib().samo_count_flags_batched(jobs, flags, k, _stream()), where)
+    else:
+        _check(lib().samo_build_index_batched(jobs, k, _stream()), where)                # no room for positions: counts only
     counts = nnz_out.cpu().tolist()
     if any(c < 0 for c in counts):
         raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
@@ -348,7 +352,10 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
         job = jobs[i]
         job.idx, job.idx_capacity = (idx.data_ptr() if c else None), c
         out.append(Index(idx, seg_ptrs[i], c, sizes[i]))
-    _check(lib().samo_fill_index_batched(jobs, flags, k, _stream()), where)
+    if flag_buf is not None:
+        _check(lib().samo_fill_index_batched(jobs, flags, k, _stream()), where)
+    else:
+        _check(lib().samo_build_index_batched(jobs, k, _stream()), where)
     return out
 
 

@@ -93,3 +93,20 @@ def test_fill_after_a_count_that_gave_up_writes_nothing():
     assert nnz == [-1, refs[1].shape[0]]
     assert (idx[0] == -1).all()
     assert np.array_equal(idx[1][:refs[1].shape[0]].cpu().numpy(), refs[1])
+
+
+def test_build_without_memory_for_the_flag_bits(monkeypatch):
+    masks = [si.bernoulli_mask(n, keep, n) for n, keep in ((70001, 0.1), (1, 1.0), (33000, 0.9), (2048, 0.0))]
+    real = torch.empty
+
+    def no_scratch(*a, dtype=None, **kw):
+        if dtype == torch.uint8:
+            raise torch.OutOfMemoryError("no memory")
+        return real(*a, dtype=dtype, **kw)
+    dev = [dev_u8(m) for m in masks]
+    monkeypatch.setattr(torch, "empty", no_scratch)
+    built = samo.samo_build_index_many(dev) + [samo.samo_build_index(dev[0])]
+    for m, ix in zip(masks + masks[:1], built):
+        ref = oracle.build_index(m)
+        assert ix.nnz == ref.shape[0] and np.array_equal(ix.idx.cpu().numpy(), ref)
+        assert np.array_equal(ix.seg_ptr.cpu().numpy(), ref_seg_ptr(ref, m.shape[0]))

@@ -29,6 +29,7 @@
 //   accumulators) and multiplies half of the tokens of every 64-token stage; group 1 hands its sums to
 //   group 0 through LDS at the end.
 // Calls of few tiles may have their tokens split over several workgroups per tile (plan_split).
+// Short calls go through the stages with all waves in step (loop_apart).
 //
 // What bounds the large tile: power, and the overlap of its parts.  Per 32-token stage of a
 // 256 x 256 tile (all compute units, ordinary fp16 values), in cycles: the matrix instructions
@@ -312,7 +313,14 @@ __device__ __forceinline__ void meet()
 // bound_window are requested when the last full stage is on its way: the wait for bound_open's results
 // is a wait for every copy in flight, once, where only one or two stages are; after it they can only make
 // the waits of the last stages longer than needed, never shorter.
-template <int TILE, int COLS, int OB, int IB>
+//
+// Not APART, all waves take a stage together, one barrier each: fetch s and multiply s are one step, the copies of stage
+// s + 3 go into the slot of stage s - 1, which every wave has finished reading before the barrier of step s.  That
+// saves the half stage at either end and the second barrier, and is quicker where a call has few stages
+// (loop_apart).  bound_window comes first in the small tile, whose registers allow it, and travels under the whole
+// loop; the large tile requests it where the other loop does.  Its wait for every copy in flight is
+// made explicit and remembered.
+template <int TILE, int COLS, bool APART, int OB, int IB>
 __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
                                                 const Bound &open, f32x4 (&acc)[OB][IB])
 {
@@ -352,12 +360,55 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
     const int x_off = lane_read + x_at, y_off = lane_read + 16 * kRowPitch + y_at;
 
     for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
+    unsigned slot = 0;                                       // LDS offset of the stage being read
+    const unsigned char *gnext = gbase + (3 * kTokens + first_token) * row_bytes;    // the wave's rows three stages ahead
+    auto multiply = [&](const half8 (&xa)[IB], const half8 (&yb)[OB]) {
+#pragma unroll
+        for (int q = 0; q < OB * IB; ++q) {
+            const int bi = q / OB, bo = (bi & 1) ? OB - 1 - q % OB : q % OB;
+            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        }
+    };
+    auto advance = [&]() {
+        gnext += kTokens * row_bytes;
+        slot = slot == (kStages - 1) * kStageBytes ? 0 : slot + kStageBytes;
+    };
+    if constexpr (!APART) {
+        Window window;
+        window.w0 = 0; window.wn = 0;
+        const int64_t look = TILE == kSmallTile || full <= 3 ? 0 : full - 3;
+        int64_t arrived = 0;                                 // stages whose copies are known to be there
+        for (int64_t s = 0; s < stages; ++s) {
+            if (s == look) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                window = bound_window(A, open);
+                arrived = s + 3;
+            }
+            if (s < arrived) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            else wait_copies(stages - 1 - s);
+            meet();
+            const unsigned char *cur = lds + slot;
+            const unsigned dst = lds_rows + (slot >= kStageBytes ? slot - kStageBytes : slot + 3 * kStageBytes);
+            if (s + 3 < full) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dma16_from(gnext + kRowTokens * i * row_bytes, lane_offset, dst + i * kRowPitch);
+            } else if (s + 3 < stages) issue_stage(s + 3);
+            half8 xa[IB], yb[OB];
+#pragma unroll
+            for (int bo = 0; bo < OB; ++bo) yb[bo] = read_fragment(cur + y_off + bo * 32, TILE * 2);
+#pragma unroll
+            for (int bi = 0; bi < IB; ++bi) xa[bi] = read_fragment(cur + x_off + bi * 32, TILE * 2);
+            multiply(xa, yb);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            advance();
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        return bound_settle(A, open, window);
+    }
     wait_copies(stages - 1);
     meet();                                                  // b(0)
     if (group == 1) meet();                                  // half a stage behind from here on
 
-    unsigned slot = 0;                                       // LDS offset of the stage being read
-    const unsigned char *gnext = gbase + (3 * kTokens + first_token) * row_bytes;    // the wave's rows three stages ahead
     auto stage = [&](int64_t s, auto steady_loop) {
         constexpr bool kSteady = decltype(steady_loop)::value;      // stage s + 3 exists and is full
         const unsigned char *cur = lds + slot;
@@ -385,17 +436,12 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
         meet();
         __builtin_amdgcn_s_setprio(1);                       // the multiplying wave first: the other one's reads fit in between
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < OB * IB; ++q) {
-            const int bi = q / OB, bo = (bi & 1) ? OB - 1 - q % OB : q % OB;
-            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
-        }
+        multiply(xa, yb);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
         if (group == 0) wait_copies(kSteady ? 2 : stages - 2 - s);
         meet();
-        gnext += kTokens * row_bytes;
-        slot = slot == (kStages - 1) * kStageBytes ? 0 : slot + kStageBytes;
+        advance();
     };
     int64_t s = 0;
     for (; s + 3 < full; ++s) stage(s, std::true_type{});
@@ -483,7 +529,7 @@ struct GatherPass {
 
 // 256 x (32 IB) tile, IB = 8 or fewer for calls of less than a round: 64 (out) x 16 IB (in) per wave, waves as 4 x 2;
 // both groups multiply every token.
-template <int OUT, int IB>
+template <int OUT, int IB, bool APART>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBatch B)
 {
     constexpr int kTile = kBigTile, kCols = 32 * IB, kEpiPitch = kCols + 8;
@@ -499,7 +545,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kCols);
     const int wo = wave & 3, wi = wave >> 2;
     f32x4 acc[4][IB];
-    bounds[t] = multiply_tile<kTile, kCols>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, open, acc);
+    bounds[t] = multiply_tile<kTile, kCols, APART>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, open, acc);
     __syncthreads();
     if constexpr (OUT == kOutPartial) {                      // fp32 sums: the ring holds half of the rows at a time
         constexpr int kHalf = kTile / 2, kSumPitch = kCols + 4;
@@ -545,7 +591,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
 }
 
 // 128 x 128 tile: 64 x 64 per wave, the waves of a group as 2 x 2; group g multiplies tokens 2g and 2g + 1 of every row.
-template <int OUT>
+template <int OUT, bool APART>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradBatch B)
 {
     constexpr int kTile = kSmallTile, kEpiPitch = kTile + 8, kSumPitch = kTile + 4;
@@ -564,7 +610,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     const int wo = wave & 1, wi = (wave >> 1) & 1;
     f32x4 acc[4][4];
     const int tokens_at = half * 2 * kTile * 2;
-    const int closed = multiply_tile<kTile, kTile>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
+    const int closed = multiply_tile<kTile, kTile, APART>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
     if (t < 2 * kTile) bounds[t] = closed;
     __syncthreads();
     GatherPass<OUT, kTile> gather;
@@ -664,22 +710,30 @@ __global__ void __launch_bounds__(kWgThreads, 2) mfma_rate_kernel(int64_t iters,
     if (threadIdx.x == 0) sink[blockIdx.x] = sum;
 }
 
-// The 256-row kernel of a width of 32 * blocks columns.
+// Whether the two wave groups of a launch run half a stage apart (multiply_tile).  In step a short call is over
+// earlier, apart a long one is faster per stage.  In us, in step and apart: 128 x 128 tiles, 1024 x 1024, 100 / 300 / 500 /
+// 700 / 1003 / 1500 tokens 7.8 / 9.5 / 10.9 / 12.3 / 15.5 / 19.7 and 8.4 / 10.3 / 11.5 / 12.8 / 15.0 / 18.3; 256 x 256 tiles,
+// 4096 x 4096, 64 / 100 / 160 / 200 / 300 tokens 11.4 / 13.2 / 14.2 / 16.3 / 18.8 and 12.4 / 14.1 / 14.6 / 16.2 / 17.9.  Tiles
+// of 128 to 192 columns and the splits of a call have the one loop only.
+bool loop_apart(int64_t tokens, bool small) { return tokens > (small ? 11 * stage_tokens(kSmallTile) : 6 * stage_tokens(kBigTile)); }
+
+// The kernel of a tile shape: 32 * blocks columns of a 256-row tile, or the small one.
 typedef void (*TileKernel)(const WgradBatch);
 template <int OUT>
-TileKernel tile_kernel_of(int blocks)
+TileKernel tile_kernel_of(bool small, int blocks, bool apart)
 {
+    if (small) return apart ? &wgrad_small_kernel<OUT, true> : &wgrad_small_kernel<OUT, false>;
     switch (blocks) {
-    case 4: return &wgrad_big_kernel<OUT, 4>;
-    case 5: return &wgrad_big_kernel<OUT, 5>;
-    case 6: return &wgrad_big_kernel<OUT, 6>;
-    default: return &wgrad_big_kernel<OUT, 8>;
+    case 4: return &wgrad_big_kernel<OUT, 4, true>;
+    case 5: return &wgrad_big_kernel<OUT, 5, true>;
+    case 6: return &wgrad_big_kernel<OUT, 6, true>;
+    default: return apart ? &wgrad_big_kernel<OUT, 8, true> : &wgrad_big_kernel<OUT, 8, false>;
     }
 }
-const void *big_kernel(int out, int blocks)
+TileKernel tile_kernel(int out, bool small, int blocks, bool apart)
 {
-    if (out == kOutPartial) return reinterpret_cast<const void *>(&wgrad_big_kernel<kOutPartial, 8>);
-    return reinterpret_cast<const void *>(out == kOutF32 ? tile_kernel_of<kOutF32>(blocks) : tile_kernel_of<kOutF16>(blocks));
+    if (out == kOutPartial) return small ? &wgrad_small_kernel<kOutPartial, true> : &wgrad_big_kernel<kOutPartial, 8, true>;
+    return out == kOutF32 ? tile_kernel_of<kOutF32>(small, blocks, apart) : tile_kernel_of<kOutF16>(small, blocks, apart);
 }
 
 // The LDS size above 64 KiB is a per-device attribute of a kernel: set once per device, where the
@@ -692,13 +746,12 @@ hipError_t configure_once(int *cus)
     if (hipError_t e = hipGetDevice(&device)) return e;
     const uint64_t bit = 1ull << (device & 63);
     if (!(configured.load(std::memory_order_acquire) & bit)) {
-        const void *kernels[] = {big_kernel(kOutPartial, 8), reinterpret_cast<const void *>(&wgrad_small_kernel<kOutPartial>),
-                                 reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF32>),
-                                 reinterpret_cast<const void *>(&wgrad_small_kernel<kOutF16>),
-                                 big_kernel(kOutF32, 8), big_kernel(kOutF32, 6), big_kernel(kOutF32, 5), big_kernel(kOutF32, 4),
-                                 big_kernel(kOutF16, 8), big_kernel(kOutF16, 6), big_kernel(kOutF16, 5), big_kernel(kOutF16, 4)};
-        for (const void *k : kernels)
-            if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes)) return e;
+        for (int out : {(int)kOutF32, (int)kOutF16, kOutPartial})
+            for (int shape = 3; shape <= 8; ++shape)                             // 3: the small tile
+                for (bool apart : {false, true}) {
+                    const void *k = reinterpret_cast<const void *>(tile_kernel(out, shape == 3, shape, apart));
+                    if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes)) return e;
+                }
         int n = 0;
         if (hipError_t e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device)) return e;
         cus_of[device & 63] = n;
@@ -812,13 +865,9 @@ size_t place_partials(WgradBatch *b, const SplitPlan &plan, unsigned char *ws)
 void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
 {
     const dim3 grid((blocks + 7) / 8 * 8), threads(kWgThreads);  // whole rounds of the 8 XCDs; the surplus exits at once
-    if (small) {
-        if (out_kind == kOutPartial) wgrad_small_kernel<kOutPartial><<<grid, threads, kLdsBytes, s>>>(b);
-        else if (out_kind == kOutF32) wgrad_small_kernel<kOutF32><<<grid, threads, kLdsBytes, s>>>(b);
-        else wgrad_small_kernel<kOutF16><<<grid, threads, kLdsBytes, s>>>(b);
-    } else if (out_kind == kOutPartial) wgrad_big_kernel<kOutPartial, 8><<<grid, threads, kLdsBytes, s>>>(b);
-    else if (out_kind == kOutF32) tile_kernel_of<kOutF32>(b.tile_cols / 32)<<<grid, threads, kLdsBytes, s>>>(b);
-    else tile_kernel_of<kOutF16>(b.tile_cols / 32)<<<grid, threads, kLdsBytes, s>>>(b);
+    int64_t tokens = 0;
+    for (int j = 0; j < b.jobs; ++j) tokens = b.job[j].tokens > tokens ? b.job[j].tokens : tokens;
+    tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small))<<<grid, threads, kLdsBytes, s>>>(b);
 }
 
 // How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the

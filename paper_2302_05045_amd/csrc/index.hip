@@ -210,32 +210,42 @@ __device__ __forceinline__ void pair_words(const uint32_t (&halves)[kPairs], uin
     __builtin_amdgcn_wave_barrier();
 }
 
-// Writes the positions of one pair of segments: lane l holds the flag word of elements first .. first + 31,
-// first = 32 l behind the pair's start; idx[out0 ..] takes them in order, nothing at or beyond cap.  The
-// positions go to LDS (the wave's own kSeg ints: no workgroup barrier), then leave as contiguous 256-byte
-// stores; a pair with more than kSeg of them goes in two halves.
-__device__ __forceinline__ void emit_pair(uint32_t word, int first, int64_t out0, int64_t cap, int32_t *__restrict__ idx,
-                                          int32_t *stage, int lane)
+// Writes the positions of one pair of segments, base the pair's first element; idx[out0 ..] takes them in order,
+// nothing at or beyond cap.  The positions go to LDS (the wave's own kSeg ints: no workgroup barrier), then leave as
+// contiguous 256-byte stores.  Lane l holds the flag word of elements base + 32 l .. base + 32 l + 31 in `word`; a pair with
+// more than kSeg of them is written segment by segment, from `half`: the flag bits of elements 16 l .. 16 l + 15 of
+// the first segment, and of the second in the upper 16 bits.  Two full segments would not fit the LDS area, and
+// the fuller the lanes, the more of their positions share a bank: a full lane's run starts 32 words after the
+// run of the lane before it, 16 segment by segment (an 8000 x 8000 layer of which everything is kept, whole build: 94 us, and 155 with
+// two halves of 32 elements a lane; the line lies where the pair stops fitting: 640, 768 and 896 are slower or the same).
+__device__ __forceinline__ void emit_pair(uint32_t word, uint32_t half, int base, int64_t out0, int64_t cap,
+                                          int32_t *__restrict__ idx, int32_t *stage, int lane)
 {
     const int cnt = __popc(word);
     const int incl = wave_inclusive_scan(cnt, lane);
     const int total = __builtin_amdgcn_readlane(incl, 63);
-    const int lower = __builtin_amdgcn_readlane(incl, 31);
-    const bool halves = total > kSeg;
-    for (int h = 0; h < (halves ? 2 : 1); ++h) {
-        const int from = h ? lower : 0, to = (halves && !h) ? lower : total;
-        int32_t *at = stage + (incl - cnt - from);
-        uint32_t bits = (!halves || (lane >> 5) == h) ? word : 0u;
+    auto write = [&](uint32_t bits, int first, int at, int count) {
+        int32_t *to = stage + at;
         while (bits) {
-            *at++ = first + __builtin_ctz(bits);
+            *to++ = first + __builtin_ctz(bits);
             bits &= bits - 1;
         }
         __builtin_amdgcn_wave_barrier();
-        const int count = storable(cap, out0 + from, to - from);
-        int32_t *__restrict__ out = idx + out0 + from;
+        count = storable(cap, out0, count);
+        int32_t *__restrict__ out = idx + out0;
         for (int o = lane; o < count; o += 64) out[o] = stage[o];
         __builtin_amdgcn_wave_barrier();
+    };
+    if (total <= kSeg) {
+        write(word, base + lane * 32, incl - cnt, total);
+        return;
     }
+    const int c = __popc(half & 0xffffu) | (__popc(half >> 16) << 16);        // a segment's count fits 16 bits
+    const int before = wave_inclusive_scan(c, lane) - c;
+    const int first_total = __builtin_amdgcn_readlane(before + c, 63) & 0xffff;
+    write(half & 0xffffu, base + lane * 16, before & 0xffff, first_total);
+    out0 += first_total;
+    write(half >> 16, base + kSeg + lane * 16, before >> 16, total - first_total);
 }
 
 template <int PASSES>
@@ -331,7 +341,7 @@ index_kernel(const IndexBatch batch, int fill)
 #pragma unroll
         for (int j = 0; j < kPairs; ++j) {
             const int sq = p * kSegsPerPass + 2 * j;
-            emit_pair(word[j], (int)((seg0 + sq) * kSeg) + lane * 32,           // a layer's flat size fits int32
+            emit_pair(word[j], fp[p][j], (int)((seg0 + sq) * kSeg),             // a layer's flat size fits int32
                       (int64_t)base + __builtin_amdgcn_readfirstlane(sh_seg[wave * kSegsPerWave + sq]), cap, batch.idx[job], sh_stage[wave], lane);
         }
     }
@@ -354,7 +364,8 @@ fill_kernel(const IndexBatch batch)
     const int64_t nseg = (batch.n[job] + kSeg - 1) / kSeg;
     const int64_t group = (int64_t)((int)blockIdx.x - batch.wg_start[job]) * kFillWaves + wave;
     const int64_t seg0 = group * kFlagGroupSegs;
-    if (seg0 >= nseg || *batch.nnz[job] < 0) return;      // whole waves leave; nothing below is a workgroup barrier
+    if (seg0 >= nseg) return;                 // whole waves leave; nothing below is a workgroup barrier
+    const int64_t counted = *batch.nnz[job];
     const uint4 w = batch.flags[job][group * 64 + lane];
     const uint32_t halves[kPairs] = {w.x, w.y, w.z, w.w};
     uint32_t word[kPairs];
@@ -363,9 +374,10 @@ fill_kernel(const IndexBatch batch)
     int start[kPairs];
 #pragma unroll
     for (int j = 0; j < kPairs; ++j) start[j] = seg_ptr[seg0 + 2 * j < nseg ? seg0 + 2 * j : nseg];
+    if (counted < 0) return;
 #pragma unroll
     for (int j = 0; j < kPairs; ++j)
-        emit_pair(word[j], (int)((seg0 + 2 * j) * kSeg) + lane * 32, start[j], batch.cap[job], batch.idx[job], sh_stage[wave], lane);
+        emit_pair(word[j], halves[j], (int)((seg0 + 2 * j) * kSeg), start[j], batch.cap[job], batch.idx[job], sh_stage[wave], lane);
 }
 
 __global__ void __launch_bounds__(kThreads)

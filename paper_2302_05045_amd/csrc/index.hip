@@ -193,21 +193,34 @@ __device__ __forceinline__ int kept_before_block(const int32_t *seg_ptr, int64_t
     return prefix;
 }
 
+// Between one lane's LDS stores and another lane's loads, both of one wave: they execute in order, this keeps the
+// compiler to it (a fence of wavefront scope is no instruction).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Views of the wave's LDS area, an array of int32_t, that may alias it.
+typedef uint16_t __attribute__((may_alias)) AliasU16;
+typedef uint32_t __attribute__((ext_vector_type(4), may_alias)) AliasU32x4;
+
 // From 16 elements of either segment of every pair (as the mask is loaded: 1 KiB of one segment per
 // instruction; lanes that load 32 bytes apart read 17 % slower) to 32 consecutive elements of the pair, by
 // way of the wave's LDS area.
 __device__ __forceinline__ void pair_words(const uint32_t (&halves)[kPairs], uint32_t (&word)[kPairs], int32_t *stage, int lane)
 {
-    uint16_t *to = reinterpret_cast<uint16_t *>(stage) + (lane >> 1) * 2 * kPairs + (lane & 1);
+    AliasU16 *to = reinterpret_cast<AliasU16 *>(stage) + (lane >> 1) * 2 * kPairs + (lane & 1);
 #pragma unroll
     for (int j = 0; j < kPairs; ++j) {
         to[2 * j] = (uint16_t)halves[j];                                 // word (lane / 2) of the pair's first segment
         to[32 * 2 * kPairs + 2 * j] = (uint16_t)(halves[j] >> 16);       // ... of its second
     }
-    __builtin_amdgcn_wave_barrier();
-    const uint4 w = reinterpret_cast<const uint4 *>(stage)[lane];
+    wave_lds_order();
+    const AliasU32x4 w = reinterpret_cast<const AliasU32x4 *>(stage)[lane];
     word[0] = w.x; word[1] = w.y; word[2] = w.z; word[3] = w.w;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
 }
 
 // Writes the positions of one pair of segments, base the pair's first element; idx[out0 ..] takes them in order,
@@ -230,11 +243,11 @@ __device__ __forceinline__ void emit_pair(uint32_t word, uint32_t half, int base
             *to++ = first + __builtin_ctz(bits);
             bits &= bits - 1;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         count = storable(cap, out0, count);
         int32_t *__restrict__ out = idx + out0;
         for (int o = lane; o < count; o += 64) out[o] = stage[o];
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
     };
     if (total <= kSeg) {
         write(word, base + lane * 32, incl - cnt, total);
@@ -368,13 +381,13 @@ fill_kernel(const IndexBatch batch)
     const int64_t counted = *batch.nnz[job];
     const uint4 w = batch.flags[job][group * 64 + lane];
     const uint32_t halves[kPairs] = {w.x, w.y, w.z, w.w};
-    uint32_t word[kPairs];
-    pair_words(halves, word, sh_stage[wave], lane);
     const int32_t *__restrict__ seg_ptr = batch.seg_ptr[job];
     int start[kPairs];
 #pragma unroll
     for (int j = 0; j < kPairs; ++j) start[j] = seg_ptr[seg0 + 2 * j < nseg ? seg0 + 2 * j : nseg];
     if (counted < 0) return;
+    uint32_t word[kPairs];
+    pair_words(halves, word, sh_stage[wave], lane);
 #pragma unroll
     for (int j = 0; j < kPairs; ++j)
         emit_pair(word[j], halves[j], (int)((seg0 + 2 * j) * kSeg), start[j], batch.cap[job], batch.idx[job], sh_stage[wave], lane);

@@ -773,54 +773,6 @@ hipError_t launch_mfma_rate(int64_t iters, float *sink, int workgroups, hipStrea
 
 namespace {
 
-// Whether, and how, the tiles of a call are shared by several workgroups each: `splits` workgroups per tile
-// of the shape `small` says; splits == 1: not at all.
-struct SplitPlan {
-    int splits;
-    bool small;
-};
-
-// A call whose large tiles would fill less than half of the compute units has its tokens split over
-// workgroups.  Times in us (measured, one MI355X): a 32-token stage of a large tile 0.62 and 8 around it, a
-// 64-token stage of a small tile 0.50 and 6 around it; the splits' sums are written and read at 4.5 TB/s, by
-// one more launch (3).  A split is taken where it saves a tenth of the call.  Unsplit and split, 10 % kept, us:
-// 512 x 512, 2048 tokens 22.0 -> 16.1, 8192 tokens 63.5 -> 19.6; 1024 x 1024, 8192 tokens 61.4 -> 31.1;
-// 2560 x 2560, 2048 tokens 44.6 -> 37.4, 8192 tokens 138 -> 107; 1024 x 4096, 8192 tokens 78.2 -> 64.9, and
-// 24.7 unsplit at 2048 tokens, where four splits of the large shape take 28.7.
-SplitPlan plan_split(const WgradBatch &b, int cus)
-{
-    SplitPlan best = {1, true};
-    const int tiles = b.first_tile[b.jobs];
-    if (tiles * 2 > cus) return best;
-    const int forced = knob(SAMO_KNOB_WGRAD_SPLIT, 0), shape = knob(SAMO_KNOB_WGRAD_TILE, 0);
-    int64_t stages = 0, nnz = 0, quarters = 0;
-    for (int j = 0; j < b.jobs; ++j) {
-        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
-        stages = s > stages ? s : stages;
-        nnz += b.job[j].nnz;
-        quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
-    }
-    if (forced > 1) return {stages > 0 ? (int)(forced < stages ? forced : stages) : 1, shape != kBigTile};
-    if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || knob(SAMO_KNOB_WGRAD_COLS, 0) > 0 || stages < 8)
-        return best;
-    double least = 1e30;
-    for (int small = 1; small >= 0; --small) {
-        const int64_t units = small ? quarters : tiles;
-        const double stage_us = small ? 0.25 : 0.62, around = small ? 6.0 : 8.0;
-        for (int s = 1; s <= 16 && s * 4 <= stages; ++s) {
-            if (s == 1 && !small) continue;                      // the rule without splits takes the small shape here
-            const double rounds = (double)ceil_div(units * s, (int64_t)cus);
-            double us = rounds * ((double)ceil_div(stages, (int64_t)s) * stage_us + around);
-            if (s > 1) us = (us + 3.0 + 8.0 * s * (double)nnz / 4.5e6) / 0.9;
-            if (us < least) {
-                least = us;
-                best = {s, small != 0};
-            }
-        }
-    }
-    return best;
-}
-
 uint32_t per_group_of(int tiles_in) { return (uint32_t)((1ull << 32) / (4u * (uint32_t)tiles_in) + 1u); }
 
 // The call's job list with its tiles; false if there is nothing to write.
@@ -846,6 +798,135 @@ bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate
     return true;
 }
 
+void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
+{
+    const dim3 grid((blocks + 7) / 8 * 8), threads(kWgThreads);  // whole rounds of the 8 XCDs; the surplus exits at once
+    int64_t tokens = 0;
+    for (int j = 0; j < b.jobs; ++j) tokens = b.job[j].tokens > tokens ? b.job[j].tokens : tokens;
+    tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small))<<<grid, threads, kLdsBytes, s>>>(b);
+}
+
+// What the tile rules price: the longest job's 32-token stages and the kept fraction of all jobs together.
+struct CallSize {
+    int64_t stages;
+    double keep, nnz;
+};
+CallSize size_of(const WgradBatch &b)
+{
+    CallSize c = {0, 0.0, 0.0};
+    double elements = 0.0;
+    for (int j = 0; j < b.jobs; ++j) {
+        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
+        c.stages = s > c.stages ? s : c.stages;
+        c.nnz += (double)b.job[j].nnz;
+        elements += (double)b.job[j].out * b.job[j].in;
+    }
+    c.keep = c.nnz / elements;
+    return c;
+}
+
+// Time in us of a launch of that many workgroups of one shape (columns of a 256-row tile, or 128 x 128 with `small`), each
+// of them `stages` stages long: what is around a tile's loop, the loop, and the gather of what the tile keeps, per
+// round of the compute units.  A stage costs less while part of the chip is idle (the clock is higher and the memory
+// less busy): 256 columns 0.56 us up to half of the compute units, 0.70 with all of them.  Fitted to 636
+// calls (sides 512 .. 12000, 200 .. 8192 tokens, 3 to 25 % kept) in every shape and split: 3 to 5 % rms.
+double launch_us(bool small, int cols, int64_t workgroups, int64_t stages, double keep, int cus)
+{
+    const double rounds = (double)ceil_div(workgroups, (int64_t)cus), full = (double)workgroups / (rounds * cus);
+    const double busy = full < 0.5 ? 0.0 : full > 0.9 ? 1.0 : (full - 0.5) / 0.4;
+    double around = 7.0, stage = 0.70, idle_stage = 0.56, area = 256.0 * cols;
+    if (small) around = 5.2, stage = 0.24, idle_stage = 0.228, area = 128.0 * 128.0;
+    else if (cols < 256) {
+        stage = cols == 128 ? 0.47 : cols == 160 ? 0.515 : 0.56;
+        idle_stage = 0.88 * stage;
+    }
+    return 1.5 + rounds * (around + (idle_stage + busy * (stage - idle_stage)) * (double)stages + 0.38e-3 * keep * area);
+}
+
+// How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the
+// last `quarters` large tiles of the list as small ones (blocks is 8 then).  us: what a call of less than a round takes
+// by the prices above.
+struct TilePlan {
+    int wide, quarters, blocks;
+    double us;
+};
+
+// Large tiles in whole rounds of the compute units; what is left over after the last whole
+// round goes to the small shape when that is the quicker way to finish it: up to half a round
+// of large tiles is at most two rounds of small ones, and a small round takes 0.4 of a large.
+// A call of less than a round leaves compute units idle: it takes the shape that is priced lowest.  3072 x 3072 (144 large
+// tiles, 228 of 160 columns): 2048 tokens 47.5 -> 43.8 us, 512 tokens 21.5 -> 18.9; 2560 x 2560 without a workspace (100, or
+// 200 of 128 columns) 42.1 -> 38.4.  (224 columns are not built: they would be the best shape where 192 columns
+// overflow the round and 224 do not, by these prices for at most 6 %.)  Behind whole rounds the same (the last columns of the
+// largest layer in narrower tiles that make one full round) gains nothing: with all compute units busy the
+// chip is at its power limit, and idle ones let the others run faster (400 tiles 107.1 -> 103.6 us, but 102.4 -> 106.1
+// for the transposed layer and 104.1 -> 110.0 for 432 tiles).
+TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
+{
+    const int tiles = b.first_tile[b.jobs];
+    const int shape = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
+    if (shape == kSmallTile) return {0, tiles, 8, 0.0};
+    if (shape == kBigTile || cus <= 0) return {tiles, 0, 8, 0.0};
+    const int forced_cols = knob(SAMO_KNOB_WGRAD_COLS, 0);     // test aid: narrow tiles whatever they cost
+    if (forced_cols == 0 && (tiles >= cus || round_forced)) {
+        const int left = tiles % cus;
+        if (left != 0 && left <= cus / 2) return {tiles - left, left, 8, 0.0};
+        return {tiles, 0, 8, 0.0};
+    }
+    const CallSize c = size_of(b);
+    TilePlan plan = {tiles, 0, 8, launch_us(false, 256, tiles, c.stages, c.keep, cus)};
+    int64_t quarters = 0;
+    for (int j = 0; j < b.jobs; ++j) quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
+    const double small_us = launch_us(true, 128, quarters, c.stages, c.keep, cus);
+    if (small_us < plan.us) plan = {0, tiles, 8, small_us};
+    if (forced_cols) plan.us = 1e30;
+    for (int blocks = 4; blocks <= 6; ++blocks) {
+        if (forced_cols && forced_cols != 32 * blocks) continue;
+        int64_t narrow = 0;
+        for (int j = 0; j < b.jobs; ++j) narrow += b.tiles_out[j] * ceil_div((int64_t)b.job[j].in, (int64_t)(32 * blocks));
+        const double us = launch_us(false, 32 * blocks, narrow, c.stages, c.keep, cus);
+        if (narrow <= kMaxGrid && us < plan.us) plan = {(int)narrow, 0, blocks, us};
+    }
+    return plan;
+}
+
+// Whether, and how, the tiles of a call are shared by several workgroups each: `splits` workgroups per tile
+// of the shape `small` says; splits == 1: not at all.
+struct SplitPlan {
+    int splits;
+    bool small;
+};
+
+// A call whose large tiles would fill less than half of the compute units may have its tokens split over workgroups.
+// The splits' sums are written and read at 6.5 TB/s (in part in the caches) by one more launch (2.8 us and 0.2 per split).  A split is taken where
+// it is priced below the call as plan_tiles would run it.  Unsplit and split, 10 % kept, us: 512 x 512,
+// 2048 tokens 21.5 -> 14.6, 8192 tokens 62.6 -> 17.6; 1024 x 1024, 8192 tokens 59.7 -> 27.5; 2560 x 2560, 2048 tokens
+// 38.4 -> 36.1, but 1024 tokens 24.4 and 26.1, 300 tokens 13.9 and 17.5: not split.
+SplitPlan plan_split(const WgradBatch &b, int cus)
+{
+    SplitPlan best = {1, true};
+    const int tiles = b.first_tile[b.jobs];
+    if (tiles * 2 > cus) return best;
+    const int forced = knob(SAMO_KNOB_WGRAD_SPLIT, 0), shape = knob(SAMO_KNOB_WGRAD_TILE, 0);
+    const CallSize c = size_of(b);
+    if (forced > 1) return {c.stages > 0 ? (int)(forced < c.stages ? forced : c.stages) : 1, shape != kBigTile};
+    if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || knob(SAMO_KNOB_WGRAD_COLS, 0) > 0 || c.stages < 8)
+        return best;
+    int64_t quarters = 0;
+    for (int j = 0; j < b.jobs; ++j) quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
+    double least = plan_tiles(b, cus, false).us;
+    for (int s = 2; s <= 16 && s * 4 <= c.stages; ++s)
+        for (int small = 0; small <= 1; ++small) {
+            const double us = launch_us(small != 0, kBigTile, (small ? quarters : tiles) * s, ceil_div(c.stages, (int64_t)s), c.keep, cus) +
+                              2.8 + 0.2 * s + 8.0 * s * c.nnz / 6.5e6;
+            if (us < least) {
+                least = us;
+                best = {s, small != 0};
+            }
+        }
+    return best;
+}
+
 // Places the splits' sums in the workspace (or only adds up its size, with ws == NULL); returns the bytes.
 size_t place_partials(WgradBatch *b, const SplitPlan &plan, unsigned char *ws)
 {
@@ -860,64 +941,6 @@ size_t place_partials(WgradBatch *b, const SplitPlan &plan, unsigned char *ws)
         if (j < b->jobs) at += (size_t)b->partial_stride[j] * plan.splits * sizeof(float);
     }
     return at;
-}
-
-void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks, hipStream_t s)
-{
-    const dim3 grid((blocks + 7) / 8 * 8), threads(kWgThreads);  // whole rounds of the 8 XCDs; the surplus exits at once
-    int64_t tokens = 0;
-    for (int j = 0; j < b.jobs; ++j) tokens = b.job[j].tokens > tokens ? b.job[j].tokens : tokens;
-    tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small))<<<grid, threads, kLdsBytes, s>>>(b);
-}
-
-// How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the
-// last `quarters` large tiles of the list as small ones (blocks is 8 then).
-struct TilePlan {
-    int wide, quarters, blocks;
-};
-
-// Large tiles in whole rounds of the compute units; what is left over after the last whole
-// round goes to the small shape when that is the quicker way to finish it: up to half a round
-// of large tiles is at most two rounds of small ones, and a small round takes 0.4 of a large.
-// A call of less than a round leaves compute units idle, and narrower tiles that fill the round
-// better are quicker: by the times (us, one MI355X) of a 32-token stage of a tile and of what is around it,
-// 0.70 and 9 for 256 columns, 0.70 * (IB + 1) / 9 and 8 for 32 IB (a narrower tile brings fewer results per byte
-// copied), against 0.25 and 6 for a round of small ones.  3072 x 3072 (144 large tiles, 228 of 160
-// columns): 2048 tokens 47.5 -> 43.8 us, 512 tokens 21.5 -> 18.9; 2560 x 2560 without a workspace (100, or 200 of 128
-// columns) 42.1 -> 38.4.  Behind whole rounds the same (the last columns of the largest layer in narrower tiles
-// that make one full round) gains nothing: with all compute units busy the chip is at its power limit, and
-// idle ones let the others run faster (400 tiles 107.1 -> 103.6 us, but 102.4 -> 106.1 for the
-// transposed layer and 104.1 -> 110.0 for 432 tiles).
-TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
-{
-    const int tiles = b.first_tile[b.jobs];
-    const int shape = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
-    if (shape == kSmallTile) return {0, tiles, 8};
-    if (shape == kBigTile || cus <= 0) return {tiles, 0, 8};
-    const int forced_cols = knob(SAMO_KNOB_WGRAD_COLS, 0);     // test aid: narrow tiles whatever they cost
-    const int left = tiles % cus;
-    TilePlan plan = {tiles, 0, 8};
-    if (left != 0 && left <= cus / 2) plan = {tiles - left, left, 8};
-    if (forced_cols == 0 && (tiles >= cus || round_forced)) return plan;
-    int64_t stages = 0;
-    for (int j = 0; j < b.jobs; ++j) {
-        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
-        stages = s > stages ? s : stages;
-    }
-    const double n = (double)stages;
-    double least = plan.quarters ? (double)ceil_div((int64_t)left * 4, (int64_t)cus) * (0.25 * n + 6.0) : 0.70 * n + 9.0;
-    if (forced_cols) least = 1e30;
-    for (int blocks = 4; blocks <= 6; ++blocks) {
-        if (forced_cols && forced_cols != 32 * blocks) continue;
-        int64_t narrow = 0;
-        for (int j = 0; j < b.jobs; ++j) narrow += b.tiles_out[j] * ceil_div((int64_t)b.job[j].in, (int64_t)(32 * blocks));
-        const double us = (double)ceil_div(narrow, (int64_t)cus) * (0.70 * (blocks + 1) / 9.0 * n + 8.0);
-        if (narrow <= kMaxGrid && us < least) {
-            least = us;
-            plan = {(int)narrow, 0, blocks};
-        }
-    }
-    return plan;
 }
 
 }  // namespace

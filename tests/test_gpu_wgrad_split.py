@@ -78,6 +78,10 @@ def test_the_rule_splits_small_layers_and_a_short_workspace_does_not():
     assert need(2048, 1024, 4096, 419430) == 0                     # 256 small tiles: the device is full
     assert need(2048, 2560, 10240, 2621440) == 0                   # more than half a round of large tiles
     assert need(100, 512, 512, 26214) == 0                         # too short to share
+    # a split has to beat the tiles that the call would take without it, narrow ones here
+    for tokens, out_f, in_f in ((512, 2560, 2240), (300, 2560, 2560), (1024, 2048, 4096), (700, 12000, 512), (512, 512, 9000)):
+        assert need(tokens, out_f, in_f, out_f * in_f // 10) == 0, (tokens, out_f, in_f)
+    assert need(4096, 2560, 2560, 655360) >= 2 * 4 * 655360
     tokens, out_f, in_f = 1024, 512, 512
     dy, x, idx, d_dy, d_x, d_idx, d_seg = _problem(tokens, out_f, in_f, "bernoulli10", 9)
     nnz = idx.shape[0]

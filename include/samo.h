@@ -485,7 +485,7 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *                        or narrower tiles of 256 rows, whichever fills the device better).
  *   SAMO_KNOB_WGRAD_ROUND  test aid: the number of tiles taken as one round in that rule, in
  *                        place of the device's compute-unit count.
- *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace; 1: never split.  Applies to
+ *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace (at most 64); 1: never split.  Applies to
  *                        calls of at most half a round of large tiles, with the tile shape SAMO_KNOB_WGRAD_TILE names
  *                        (default there: 128 x 128).
  *   SAMO_KNOB_WGRAD_COLS   test aid: 128, 160 or 192 columns of a 256-row tile, whatever the rule says (the default

@@ -110,6 +110,7 @@ struct WgradBatch {
     int64_t partial_stride[kWgradMaxJobs];
 };
 constexpr int kOutPartial = 3;
+constexpr int kMaxSplits = 64;              // what SAMO_KNOB_WGRAD_SPLIT may ask for; the rule takes up to 16
 constexpr int64_t kMaxGrid = 1 << 24;       // far above any call: the tile lists stay 32-bit
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
@@ -909,7 +910,10 @@ SplitPlan plan_split(const WgradBatch &b, int cus)
     if (tiles * 2 > cus) return best;
     const int forced = knob(SAMO_KNOB_WGRAD_SPLIT, 0), shape = knob(SAMO_KNOB_WGRAD_TILE, 0);
     const CallSize c = size_of(b);
-    if (forced > 1) return {c.stages > 0 ? (int)(forced < c.stages ? forced : c.stages) : 1, shape != kBigTile};
+    if (forced > 1) {                                          // bounded: the workgroups of a launch are counted in 32 bits
+        const int64_t most = c.stages < kMaxSplits ? c.stages : kMaxSplits;
+        return {forced < most ? forced : most > 0 ? (int)most : 1, shape != kBigTile};
+    }
     if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || knob(SAMO_KNOB_WGRAD_COLS, 0) > 0 || c.stages < 8)
         return best;
     int64_t quarters = 0;

@@ -82,6 +82,12 @@ def test_the_rule_splits_small_layers_and_a_short_workspace_does_not():
     for tokens, out_f, in_f in ((512, 2560, 2240), (300, 2560, 2560), (1024, 2048, 4096), (700, 12000, 512), (512, 512, 9000)):
         assert need(tokens, out_f, in_f, out_f * in_f // 10) == 0, (tokens, out_f, in_f)
     assert need(4096, 2560, 2560, 655360) >= 2 * 4 * 655360
+    for forced, tokens, splits in ((1 << 30, 1 << 30, 64), (65, 1 << 20, 64), (63, 1 << 20, 63), (1 << 30, 100, 4)):
+        samo.samo_debug_set(samo.KNOB_WGRAD_SPLIT, forced)
+        try:
+            assert need(tokens, 512, 512, 26240) == splits * 26240 * 4
+        finally:
+            samo.samo_debug_set(samo.KNOB_WGRAD_SPLIT)
     tokens, out_f, in_f = 1024, 512, 512
     dy, x, idx, d_dy, d_x, d_idx, d_seg = _problem(tokens, out_f, in_f, "bernoulli10", 9)
     nnz = idx.shape[0]

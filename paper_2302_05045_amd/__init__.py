@@ -271,7 +271,7 @@ else:
     _dev, _dev_matrix = _marshal.vector, _marshal.matrix
 
 
-def _stream() -> int:
+def _public_stream() -> int:
     """Handle of the current device's current stream.  The first call goes through torch's public function, which
     initialises the runtime; the raw query that serves the later ones makes no Python object per call."""
     global _stream
@@ -281,6 +281,18 @@ def _stream() -> int:
         def _stream() -> int:
             return raw(device())
     return handle
+
+
+_stream = _public_stream
+
+
+def _after_fork() -> None:
+    """In a forked child the runtime cannot be used again; torch's public function says so, the raw query does not."""
+    global _stream
+    _stream = _public_stream
+
+
+os.register_at_fork(after_in_child=_after_fork)
 
 
 _F16 = torch.float16

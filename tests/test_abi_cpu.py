@@ -399,3 +399,17 @@ def test_python_weight_gradient_entries_take_a_workspace():
         p = inspect.signature(f).parameters
         assert list(p)[-1] == "workspace" and p["workspace"].default is None
     assert samo.samo_wgrad_workspace_bytes([]) == 0
+
+
+def test_a_forked_child_asks_for_its_stream_through_torch(monkeypatch):
+    """The raw stream query of a parent that has used the GPU would hand a forked child a stream it cannot use."""
+    monkeypatch.setattr(samo, "_stream", lambda: 4096)
+    pid = os.fork()
+    if pid == 0:
+        try:
+            samo._stream()
+        except Exception:                    # no GPU here, or "cannot re-initialize": torch's refusal
+            os._exit(0)
+        os._exit(1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert samo._stream() == 4096

@@ -332,6 +332,11 @@ def samo_build_index(mask: torch.Tensor) -> Index:
     return _build_indices([mask], "samo_build_index")[0]
 
 
+def _flag_bytes(n: int) -> int:
+    """samo_index_flags_bytes of the library without the call: 1 KiB per eight segments."""
+    return (n + 8 * SEG_ELEMS - 1) // (8 * SEG_ELEMS) * 1024
+
+
 def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     """Index of every mask: one batched count that reads the masks and leaves their flag bits, one read-back
     of the counts to size the indices, one batched fill from the flag bits.  Without memory for those
@@ -339,7 +344,7 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     dev, k = masks[0].device, len(masks)
     sizes = [m.numel() for m in masks]
     seg_lens = [samo_seg_ptr_len(n) for n in sizes]
-    flag_bytes = [(s + 6) // 8 * 1024 for s in seg_lens]                 # samo_index_flags_bytes: 1 KiB per eight segments
+    flag_bytes = [_flag_bytes(n) for n in sizes]
     flag_buf = _scratch(max(sum(flag_bytes), 1))
     nnz_out = torch.empty(k, dtype=torch.int64, device=dev)
     jobs, flags = (IndexJob * k)(), (ctypes.c_void_p * k)()
@@ -521,14 +526,18 @@ def _wgrad_need(jobs, count: int) -> int:
     return need.value
 
 
+# The library splits no call of more large tiles than half of the device's compute units (128 of 256); above this many
+# it is not asked, which a call of that size would pay 1 us for.
+_MOST_SPLIT_TILES = 160
+
+
 def _wgrad_workspace(jobs, count: int, tiles: int, given: Optional[torch.Tensor]):
     """(workspace, bytes) of a call: what the caller gave, or, for layers too small to occupy the device, scratch memory
-    for the length of the call; (None, 0) where the library would not split the call (it never does above half a
-    round of large tiles: no need to ask)."""
+    for the length of the call; (None, 0) where the library would not split the call."""
     if given is not None:
         _dev(given, torch.uint8, "workspace")
         return given, given.numel()
-    if tiles > 160:
+    if tiles > _MOST_SPLIT_TILES:
         return None, 0
     need = _wgrad_need(jobs, count)
     ws = _scratch(need) if need else None

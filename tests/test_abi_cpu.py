@@ -290,6 +290,9 @@ def test_two_call_index_build_rejects_bad_arguments():
     size = ctypes.c_size_t()
     for n, want in ((0, 0), (1, 1024), (8192, 1024), (8193, 2048), (2 ** 31 - 1, 262144 * 1024)):
         assert L.samo_index_flags_bytes(n, ctypes.byref(size)) == samo.SAMO_OK and size.value == want
+    for n in [0, 1, 8191, 8192, 8193, 65536, 2 ** 31 - 1] + [977 * k * k for k in range(1, 1400, 13)]:
+        assert L.samo_index_flags_bytes(n, ctypes.byref(size)) == samo.SAMO_OK
+        assert samo._flag_bytes(n) == size.value == samo.samo_index_flags_bytes(n), n
     assert L.samo_index_flags_bytes(-1, ctypes.byref(size)) == samo.SAMO_ERR_SIZE
     assert L.samo_index_flags_bytes(8, None) == samo.SAMO_ERR_NULL
     for entry in (L.samo_count_flags_batched, L.samo_fill_index_batched):

@@ -82,6 +82,9 @@ def test_the_rule_splits_small_layers_and_a_short_workspace_does_not():
     for tokens, out_f, in_f in ((512, 2560, 2240), (300, 2560, 2560), (1024, 2048, 4096), (700, 12000, 512), (512, 512, 9000)):
         assert need(tokens, out_f, in_f, out_f * in_f // 10) == 0, (tokens, out_f, in_f)
     assert need(4096, 2560, 2560, 655360) >= 2 * 4 * 655360
+    assert 2 * samo._MOST_SPLIT_TILES >= torch.cuda.get_device_properties(0).multi_processor_count   # the binding's shortcut loses no split
+    for tokens in (300, 2048, 8192, 1 << 20):
+        assert need(tokens, 256, 256 * (samo._MOST_SPLIT_TILES + 1), 1000) == 0
     for forced, tokens, splits in ((1 << 30, 1 << 30, 64), (65, 1 << 20, 64), (63, 1 << 20, 63), (1 << 30, 100, 4)):
         samo.samo_debug_set(samo.KNOB_WGRAD_SPLIT, forced)
         try:

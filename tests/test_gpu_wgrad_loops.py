@@ -36,3 +36,22 @@ def test_both_loops_match_the_oracle(tile, tokens, out_f, in_f, kind):
     _check_f16(host_bits(gc16[:nnz]), lo, hi, want, "gc16")
     assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"
     assert np.array_equal(gc[:nnz].cpu().numpy(), gc16[:nnz].float().cpu().numpy())
+
+
+@pytest.mark.parametrize("tile,tokens", [(128, (770, 0, 70, 1)), (128, (704, 0, 63, 640)), (256, (257, 0, 31, 97)), (256, (192, 0, 33, 1))])
+def test_layers_of_different_length_share_a_loop(tile, tokens):
+    """The longest layer of a call picks the loop; the others go through it with few stages or none."""
+    jobs, wants = [], []
+    for t, (out_f, in_f, kind) in zip(tokens, ((136, 264, "bernoulli10"), (16, 24, "bernoulli50"), (24, 520, "dense_idx"), (264, 40, "rows"))):
+        dy, x, idx, d_dy, d_x, d_idx, d_seg = _problem(max(t, 1), out_f, in_f, kind, 5 + t)
+        dy, x, d_dy, d_x = dy[:t * out_f], x[:t * in_f], d_dy[:t], d_x[:t]
+        jobs.append((d_dy, d_x, d_idx, d_seg, torch.full((idx.shape[0],), float("nan"), dtype=torch.float16, device=DEV)))
+        wants.append((oracle.wgrad_compress(dy, x, t, out_f, in_f, idx), *_bracket(dy, x, t, out_f, in_f, idx)))
+    samo.samo_debug_set(samo.KNOB_WGRAD_TILE, tile)
+    try:
+        samo.samo_wgrad_gather_fp16_batched(jobs, workspace=torch.empty(0, dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+    finally:
+        samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+    for k, (job, (want, lo, hi)) in enumerate(zip(jobs, wants)):
+        _check_f16(host_bits(job[4]), lo, hi, want, "job %d" % k)

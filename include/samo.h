@@ -457,8 +457,8 @@ samo_status samo_memory_model(int64_t n_total, int64_t nnz_total, int64_t *paper
  * launch shape as the pipeline's kernels: measures the achievable HBM stream
  * rate and calibrates hardware byte counters.  Not part of the method. */
 samo_status samo_stream_copy(void *d_dst, const void *d_src, int64_t bytes, void *stream);
-/* Issues `iters` rounds of eight independent 32x32x16 fp16 matrix instructions per wave from
- * registers, 8 waves per workgroup, `workgroups` workgroups (one per compute unit fills the
+/* Issues `iters` rounds of sixteen independent 16x16x32 fp16 matrix instructions per wave (the weight-gradient
+ * kernels' instruction, in their order) from registers, 8 waves per workgroup, `workgroups` workgroups (one per compute unit fills the
  * device): measures the matrix rate the device sustains, its clock under that load included,
  * before any operand is fetched -- the ceiling beside which the weight-gradient kernels are read.
  * d_sink (device, float[workgroups]) receives one value per workgroup; *flops (host, may be NULL)

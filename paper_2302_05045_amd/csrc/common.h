@@ -200,7 +200,7 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
 hipError_t wgrad_workspace(const WgradJob *jobs, int count, size_t *bytes);
 // Function attributes of the weight-gradient kernels and the compute-unit count of the current device (once per device).
 hipError_t wgrad_configure(int *cus);
-constexpr int kMfmaRateWaves = 8;          // waves per workgroup of launch_mfma_rate, 8 MFMAs of 32 x 32 x 16 each per iteration
+constexpr int kMfmaRateWaves = 8;          // waves per workgroup of launch_mfma_rate, 16 MFMAs of 16 x 16 x 32 each per iteration
 hipError_t launch_mfma_rate(int64_t iters, float *sink, int workgroups, hipStream_t s);
 
 hipError_t launch_copy(void *dst, const void *src, int64_t bytes, hipStream_t s);

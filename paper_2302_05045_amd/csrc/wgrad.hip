@@ -56,7 +56,6 @@ namespace {
 #define LDS_AS __attribute__((address_space(3)))
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
@@ -680,33 +679,42 @@ __global__ void __launch_bounds__(kSumThreads) wgrad_sum_kernel(const WgradBatch
     }
 }
 
-// What the matrix units sustain with nothing to fetch: every wave issues eight independent
-// 32x32x16 fp16 MFMAs per iteration from registers (128 accumulators, the large tile's share), two
-// waves to a SIMD as in the kernels above.  The operands are ordinary fp16 values (a few set
-// mantissa and exponent bits, varying by lane), because the clock the chip holds under this load,
-// and with it the rate, depends on how many bits toggle.  Each workgroup leaves one float.
+// What the matrix units sustain with nothing to fetch: every wave issues sixteen independent 16x16x32 fp16 MFMAs per
+// iteration from registers, 4 x 4 blocks in the order of the kernels above, two waves to a SIMD as there.  The operands are
+// ordinary fp16 values (a few set mantissa and exponent bits, varying by lane and block), because the clock
+// the chip holds under this load, and with it the rate, depends on how many bits toggle.  Each workgroup
+// leaves one float.
 __global__ void __launch_bounds__(kWgThreads, 2) mfma_rate_kernel(int64_t iters, float *__restrict__ sink)
 {
-    f32x16 acc[8];
+    f32x4 acc[4][4];
+    half8 xa[4], yb[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-    half8 a, b;
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        a[i] = (_Float16)(0.37f * (float)((int)(threadIdx.x % 7) + i) - 1.f);
-        b[i] = (_Float16)(0.011f * (float)((int)(threadIdx.x % 5) + 2 * i) - 0.03f);
-    }
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            xa[b][i] = (_Float16)(0.37f * (float)((int)((threadIdx.x + 3 * b) % 7) + i) - 1.f);
+            yb[b][i] = (_Float16)(0.011f * (float)((int)((threadIdx.x + 2 * b) % 5) + 2 * i) - 0.03f);
+        }
     for (int64_t it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc[i], 0, 0, 0);
+        for (int q = 0; q < 16; ++q) {
+            const int bi = q / 4, bo = (bi & 1) ? 3 - q % 4 : q % 4;
+            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        }
     }
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum += acc[i][r];
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum += acc[i][j][r];
     sum += __shfl_xor(sum, 32, 64);
     if (threadIdx.x == 0) sink[blockIdx.x] = sum;
 }

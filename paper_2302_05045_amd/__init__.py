@@ -540,23 +540,32 @@ def _wgrad_workspace(jobs, count: int, tiles: int, given: Optional[torch.Tensor]
     if tiles > _MOST_SPLIT_TILES:
         return None, 0
     need = _wgrad_need(jobs, count)
-    ws = _scratch(need) if need else None
+    ws = _capture_scratch(need) if need else None
     return ws, (need if ws is not None else 0)
 
 
 def _scratch(nbytes: int) -> Optional[torch.Tensor]:
     """Scratch memory for the kernels that the current call enqueues, given back in stream order when the call returns.
     It belongs to the device and the stream that the launches go to, wherever the arguments live.  None where there is
-    no memory for it, and where the memory would have to outlive the call: a capture replays the kernels later, so
-    while one is under way only memory of the graph's own pool will do.  torch's captures allocate from
-    such a pool; in a capture begun any other way the allocator's ordinary blocks would be handed to somebody else."""
+    no memory for it."""
     try:
-        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        return torch.empty(nbytes, dtype=torch.uint8, device=_CURRENT_DEVICE)
     except torch.OutOfMemoryError:
         return None
-    if torch.cuda.is_current_stream_capturing() and not _in_private_pool(t):
+
+
+def _capture_scratch(nbytes: int) -> Optional[torch.Tensor]:
+    """The same for calls that may be captured.  A capture replays the kernels after the call has returned, so while one
+    is under way only memory of the graph's own pool will do: torch's captures allocate from such a pool; in a
+    capture begun any other way the allocator's ordinary blocks would be handed to somebody else (None there)."""
+    t = _scratch(nbytes)
+    if t is not None and _is_capturing() and not _in_private_pool(t):
         return None
     return t
+
+
+_CURRENT_DEVICE = torch.device("cuda")
+_is_capturing = getattr(torch._C, "_cuda_isCurrentStreamCapturing", torch.cuda.is_current_stream_capturing)
 
 
 def _in_private_pool(t: torch.Tensor) -> bool:

@@ -110,7 +110,6 @@ struct WgradBatch {
 };
 constexpr int kOutPartial = 3;
 constexpr int kMaxSplits = 64;              // what SAMO_KNOB_WGRAD_SPLIT may ask for; the rule takes up to 16
-constexpr int64_t kMaxGrid = 1 << 24;       // far above any call: the tile lists stay 32-bit
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
 
@@ -817,7 +816,7 @@ void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks
 
 // What the tile rules price: the longest job's 32-token stages and the kept fraction of all jobs together.
 struct CallSize {
-    int64_t stages;
+    int stages;
     double keep, nnz;
 };
 CallSize size_of(const WgradBatch &b)
@@ -825,7 +824,7 @@ CallSize size_of(const WgradBatch &b)
     CallSize c = {0, 0.0, 0.0};
     double elements = 0.0;
     for (int j = 0; j < b.jobs; ++j) {
-        const int64_t s = ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));
+        const int s = (int)ceil_div(b.job[j].tokens, (int64_t)stage_tokens(kBigTile));       // tokens fit 31 bits
         c.stages = s > c.stages ? s : c.stages;
         c.nnz += (double)b.job[j].nnz;
         elements += (double)b.job[j].out * b.job[j].in;
@@ -834,14 +833,22 @@ CallSize size_of(const WgradBatch &b)
     return c;
 }
 
+// Tiles of all jobs in a shape: less than 2^22 (8 layers of less than 2^31 elements, sides up to 2^24).
+int count_tiles(const WgradBatch &b, int rows, int cols)
+{
+    int n = 0;
+    for (int j = 0; j < b.jobs; ++j) n += ((b.job[j].out + rows - 1) / rows) * ((b.job[j].in + cols - 1) / cols);
+    return n;
+}
+
 // Time in us of a launch of that many workgroups of one shape (columns of a 256-row tile, or 128 x 128 with `small`), each
 // of them `stages` stages long: what is around a tile's loop, the loop, and the gather of what the tile keeps, per
 // round of the compute units.  A stage costs less while part of the chip is idle (the clock is higher and the memory
 // less busy): 256 columns 0.56 us up to half of the compute units, 0.70 with all of them.  Fitted to 636
 // calls (sides 512 .. 12000, 200 .. 8192 tokens, 3 to 25 % kept) in every shape and split: 3 to 5 % rms.
-double launch_us(bool small, int cols, int64_t workgroups, int64_t stages, double keep, int cus)
+double launch_us(bool small, int cols, int workgroups, int stages, double keep, int cus)
 {
-    const double rounds = (double)ceil_div(workgroups, (int64_t)cus), full = (double)workgroups / (rounds * cus);
+    const double rounds = (workgroups + cus - 1) / cus, full = workgroups / (rounds * cus);
     const double busy = full < 0.5 ? 0.0 : full > 0.9 ? 1.0 : (full - 0.5) / 0.4;
     double around = 7.0, stage = 0.70, idle_stage = 0.56, area = 256.0 * cols;
     if (small) around = 5.2, stage = 0.24, idle_stage = 0.228, area = 128.0 * 128.0;
@@ -849,7 +856,7 @@ double launch_us(bool small, int cols, int64_t workgroups, int64_t stages, doubl
         stage = cols == 128 ? 0.47 : cols == 160 ? 0.515 : 0.56;
         idle_stage = 0.88 * stage;
     }
-    return 1.5 + rounds * (around + (idle_stage + busy * (stage - idle_stage)) * (double)stages + 0.38e-3 * keep * area);
+    return 1.5 + rounds * (around + (idle_stage + busy * (stage - idle_stage)) * stages + 0.38e-3 * keep * area);
 }
 
 // How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the
@@ -884,17 +891,15 @@ TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
     }
     const CallSize c = size_of(b);
     TilePlan plan = {tiles, 0, 8, launch_us(false, 256, tiles, c.stages, c.keep, cus)};
-    int64_t quarters = 0;
-    for (int j = 0; j < b.jobs; ++j) quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
+    const int quarters = count_tiles(b, kSmallTile, kSmallTile);
     const double small_us = launch_us(true, 128, quarters, c.stages, c.keep, cus);
     if (small_us < plan.us) plan = {0, tiles, 8, small_us};
     if (forced_cols) plan.us = 1e30;
     for (int blocks = 4; blocks <= 6; ++blocks) {
         if (forced_cols && forced_cols != 32 * blocks) continue;
-        int64_t narrow = 0;
-        for (int j = 0; j < b.jobs; ++j) narrow += b.tiles_out[j] * ceil_div((int64_t)b.job[j].in, (int64_t)(32 * blocks));
+        const int narrow = count_tiles(b, kBigTile, 32 * blocks);
         const double us = launch_us(false, 32 * blocks, narrow, c.stages, c.keep, cus);
-        if (narrow <= kMaxGrid && us < plan.us) plan = {(int)narrow, 0, blocks, us};
+        if (us < plan.us) plan = {narrow, 0, blocks, us};
     }
     return plan;
 }
@@ -919,17 +924,16 @@ SplitPlan plan_split(const WgradBatch &b, int cus)
     const int forced = knob(SAMO_KNOB_WGRAD_SPLIT, 0), shape = knob(SAMO_KNOB_WGRAD_TILE, 0);
     const CallSize c = size_of(b);
     if (forced > 1) {                                          // bounded: the workgroups of a launch are counted in 32 bits
-        const int64_t most = c.stages < kMaxSplits ? c.stages : kMaxSplits;
-        return {forced < most ? forced : most > 0 ? (int)most : 1, shape != kBigTile};
+        const int most = c.stages < kMaxSplits ? c.stages : kMaxSplits;
+        return {forced < most ? forced : most > 0 ? most : 1, shape != kBigTile};
     }
     if (forced == 1 || shape != 0 || knob(SAMO_KNOB_WGRAD_ROUND, 0) > 0 || knob(SAMO_KNOB_WGRAD_COLS, 0) > 0 || c.stages < 8)
         return best;
-    int64_t quarters = 0;
-    for (int j = 0; j < b.jobs; ++j) quarters += ceil_div(b.job[j].out, (int64_t)kSmallTile) * ceil_div(b.job[j].in, (int64_t)kSmallTile);
+    const int quarters = count_tiles(b, kSmallTile, kSmallTile);
     double least = plan_tiles(b, cus, false).us;
     for (int s = 2; s <= 16 && s * 4 <= c.stages; ++s)
         for (int small = 0; small <= 1; ++small) {
-            const double us = launch_us(small != 0, kBigTile, (small ? quarters : tiles) * s, ceil_div(c.stages, (int64_t)s), c.keep, cus) +
+            const double us = launch_us(small != 0, kBigTile, (small ? quarters : tiles) * s, (c.stages + s - 1) / s, c.keep, cus) +
                               2.8 + 0.2 * s + 8.0 * s * c.nnz / 6.5e6;
             if (us < least) {
                 least = us;

@@ -66,7 +66,7 @@ def test_torch_graph_replays_the_eager_bits(problem):
     gc, eager = torch.empty_like(gather()), gather()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        assert samo._scratch(4096) is not None              # the graph's own pool
+        assert samo._capture_scratch(4096) is not None              # the graph's own pool
         samo.samo_wgrad_gather(d_dy, *args[1:], 1.0, gc)
     for step in range(4):
         d_dy.copy_(dev_f16_bits(si.output_grads_fp16(TOKENS, OUT, 90 + step)).view(TOKENS, OUT))

@@ -176,8 +176,8 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
  * in between.  samo_index_flags_bytes: the size of a device buffer (16-byte aligned) that holds one flag
  * bit per element of a layer, rounded up to whole groups of segments.
  * samo_count_flags_batched: what samo_build_index_batched does for jobs that only count (idx and
- * idx_capacity are ignored), and every job's flag bits are left in h_flags[j], a HOST array of
- * DEVICE pointers.
+ * idx_capacity are not used), and every job's flag bits are left in h_flags[j], a HOST array of
+ * DEVICE pointers.  Both calls refuse the jobs that samo_build_index_batched refuses.
  * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
  * flag bits, the seg_ptr and the nnz such a call left, later on the same stream; the mask is not read.
  * A job whose count gave up (*nnz = -1) is left without positions. */

@@ -16,7 +16,7 @@
 // A caller that has to know the count before it can allocate the index makes two calls.  The second
 // need not read the mask again: the first can leave its flag words (an eighth of the mask's size) in a
 // buffer of the caller, and fill_kernel makes the positions from those and from seg_ptr.  Seven layers of the
-// 2.7B shape (550 M mask bytes, 10 % kept): counting 117 us and a whole second build 160 before, 133 and 63 now.
+// 2.7B shape (550 M mask bytes, 10 % kept): counting 117 us and a whole second build 160 before, 128 and 62 now.
 //
 // The chain lives in seg_ptr itself: seg_ptr[e], e the end of a workgroup's block of segments, is
 // the number of kept elements up to there — exactly the running total the next workgroup needs.
@@ -301,7 +301,7 @@ index_kernel(const IndexBatch batch, int fill)
             fp[p][j] = f[2 * j] | (f[2 * j + 1] << 16);
         }
         // the lane's flag bits of the pass, one vector: what fill_kernel reads instead of the mask (past the
-        // caches: a whole 2.7B model is counted in 0.56 instead of 0.59 ms, 0.47 without the bits)
+        // caches, which was 5 % faster; a whole 2.7B model is counted in 0.54 ms, 0.46 without the bits)
         if (batch.flags[job] != nullptr && seg0 + p * kSegsPerPass < nseg) {
             typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
             __builtin_nontemporal_store((u32x4){fp[p][0], fp[p][1], fp[p][2], fp[p][3]},
@@ -443,8 +443,9 @@ hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
     if (wgs > 0) {
         const dim3 grid((unsigned)wgs), block(kIndexThreads);
         // A launch that only counts reads as fast as the memory lets it and runs best with two workgroups per
-        // compute unit, not four (with the flag bits of 32 and 7 layers of the 2.7B shape 537 and 128 us against
-        // 558 and 133, without them 462 against 466); one that fills as well needs the waves (765 against 757).
+        // compute unit, not the three (four passes: 70 registers) or four (LDS) that fit (with the flag bits of 32 and 7
+        // layers of the 2.7B shape 537 and 128 us against 558 and 133, without them 462 against 466); one that fills as
+        // well needs the waves (765 against 757).
         const int pad = fill ? 0 : kCountLdsPad;
         if (batch.passes == 4) index_kernel<4><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
         else if (batch.passes == 2) index_kernel<2><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
@@ -464,11 +465,13 @@ int64_t index_fill_workgroups(int64_t n) { return ceil_div(ceil_div(n, kSeg), kF
 
 int64_t index_job_workgroups(int64_t n, int passes) { return ceil_div(ceil_div(n, kSeg), segs_per_wg(passes)); }
 
-// Passes per workgroup for a launch over `mask_bytes` bytes of mask: the most for which the launch
-// still has four rounds of workgroups (three of them fit a compute unit at a time).
+// Passes per workgroup for a launch over `mask_bytes` bytes of mask: the most for which the launch still has a dozen
+// blocks per compute unit.  With 1, 2 and 4 passes, 10 % kept, us: 7 layers of the 2.7B shape (550 MB of mask: 33, 16
+// and 8 blocks per compute unit) build 174, 160, 163, counting with the flag bits 152, 127, 122; 32 layers
+// 794, 753, 751 and 669, 555, 531.  The line is the build's; a launch that only counts would take four passes earlier.
 int index_passes_for(int64_t mask_bytes, int compute_units)
 {
-    const int64_t wanted = (int64_t)compute_units * 3 * 4;
+    const int64_t wanted = (int64_t)compute_units * 12;
     for (int passes = kMaxPasses; passes > 1; passes /= 2)
         if (mask_bytes / ((int64_t)segs_per_wg(passes) * kSeg) >= wanted) return passes;
     return 1;

@@ -147,8 +147,8 @@ typedef struct {
  *   *d_nnz still holds the true count, so the caller can detect it.
  *   d_idx may be NULL only if idx_capacity == 0.
  * Typical use: count, read *d_nnz, allocate idx, build; or build with capacity n.
- * The mask is read once: workgroups pass the running count along a chain kept in
- * d_seg_ptr, waiting for their predecessors for a bounded time.  Should that wait
+ * The mask is read once.  A call that writes positions passes the running count along a chain of
+ * workgroups kept in d_seg_ptr, waiting for predecessors for a bounded time.  Should that wait
  * ever run out (it cannot unless the device stops scheduling running workgroups)
  * *d_nnz is set to -1 and d_seg_ptr / d_idx are incomplete.  While the call is in
  * flight d_seg_ptr and *d_nnz hold intermediate values; the outputs of different
@@ -475,7 +475,8 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *   SAMO_KNOB_OCC_FLAT_GATHER, _OCC_FLAT_STATS, _OCC_FLAT_STEP (waves)
  *                        resident per compute unit that a launch of that kind aims at; 0 = no cap.
  *   SAMO_KNOB_INDEX_SPIN_LIMIT  polls an index-build workgroup spends on a predecessor before it
- *                        gives up (default 2^20); 0 makes the give-up path reachable in tests.
+ *                        gives up (default 2^20); 0 makes the give-up path reachable in tests.  While it is set,
+ *                        calls that only count wait along the chain too.
  *   SAMO_KNOB_INDEX_PASSES  1, 2 or 4: forces the block size of the index build (64 KiB of mask per pass and
  *                        workgroup; default: 4 for launches with at least a dozen blocks of that size per
  *                        compute unit, else 2 or 1).

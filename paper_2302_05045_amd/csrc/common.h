@@ -112,7 +112,7 @@ struct IndexBatch {
     int32_t *seg_ptr[kIndexBatchJobs];
     int64_t *nnz[kIndexBatchJobs];
     uint4 *flags[kIndexBatchJobs];       // NULL, or where a counting launch leaves the flag words and the fill launch reads them
-    int passes;                          // 64 KiB passes a workgroup makes over its block: 1, 2 or 4
+    int passes;                          // 64 KiB passes a workgroup of the chained kernel makes over its block: 1, 2 or 4
     int spin_limit;                      // polls of a missing predecessor before a workgroup gives up
     int64_t *ticket;                     // the nnz of the job that owns the last workgroup: zero before the
                                          // launch, counts the workgroups as they start, final once that one ends
@@ -131,6 +131,8 @@ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) -----------------------
 hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s);
+// Counting without a chain (rewrites batch.wg_start for its own kernels); flags: leaves the flag words as well.
+hipError_t launch_index_count(IndexBatch &batch, bool flags, hipStream_t s);
 hipError_t launch_index_fill(const IndexBatch &batch, hipStream_t s);
 int64_t index_job_workgroups(int64_t n, int passes);
 int64_t index_fill_workgroups(int64_t n);

@@ -13,10 +13,12 @@
 // collected per pair of segments in LDS and stored as contiguous runs.  All integer work: one read of the
 // mask plus the write of the index.
 //
-// A caller that has to know the count before it can allocate the index makes two calls.  The second
-// need not read the mask again: the first can leave its flag words (an eighth of the mask's size) in a
-// buffer of the caller, and fill_kernel makes the positions from those and from seg_ptr.  Seven layers of the
-// 2.7B shape (550 M mask bytes, 10 % kept): counting 117 us and a whole second build 160 before, 128 and 62 now.
+// A caller that has to know the count before it can allocate the index makes two calls.  Counting needs no chain: the
+// counts within blocks of 64 segments and the blocks' offsets are two launches, neither of which waits for anything
+// (count_kernel, offsets_kernel).  The second call need not read the mask again: the first can leave its flag words (an eighth of the
+// mask's size) in a buffer of the caller, and fill_kernel makes the positions from those and from seg_ptr.  Seven layers of
+// the 2.7B shape (550 M mask bytes, 10 % kept): 101 + 6.5 us and 56 us.  (The chained kernel counted them in 125 + 3 us: a workgroup
+// that waits for its predecessors reads nothing meanwhile.)
 //
 // The chain lives in seg_ptr itself: seg_ptr[e], e the end of a workgroup's block of segments, is
 // the number of kept elements up to there — exactly the running total the next workgroup needs.
@@ -115,7 +117,6 @@ __device__ __forceinline__ int find_job(const IndexBatch &batch, int wg)
 // fullest lane of the wave has kept elements, about 8 times for a pair at 10 % kept, where two words of 16
 // took 5 to 6 each.
 constexpr int kSegsPerPass = 8;           // per wave
-constexpr int kCountLdsPad = 22000;       // beside the kernel's 33 KB: two workgroups to a compute unit's 160 KB
 constexpr int kPairs = kSegsPerPass / 2;
 static_assert(kFlagGroupSegs == kSegsPerPass && kPairs == 4, "a lane's flag words of a pass are one 16-byte vector");
 constexpr int kMaxPasses = 4;
@@ -223,6 +224,24 @@ __device__ __forceinline__ void pair_words(const uint32_t (&halves)[kPairs], uin
     wave_lds_order();
 }
 
+// The other way round: 16 elements of either segment of every pair from 32 consecutive ones.
+__device__ __forceinline__ void word_halves(const uint32_t (&word)[kPairs], uint32_t (&halves)[kPairs], int32_t *stage, int lane)
+{
+    reinterpret_cast<AliasU32x4 *>(stage)[lane] = (AliasU32x4){word[0], word[1], word[2], word[3]};
+    wave_lds_order();
+    const AliasU16 *from = reinterpret_cast<const AliasU16 *>(stage) + (lane >> 1) * 2 * kPairs + (lane & 1);
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) halves[j] = from[2 * j] | ((uint32_t)from[32 * 2 * kPairs + 2 * j] << 16);
+    wave_lds_order();
+}
+
+// A lane's flag words of a group of eight segments, one vector, past the caches.
+__device__ __forceinline__ void store_flags(uint4 *to, const uint32_t (&word)[kPairs])
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store((u32x4){word[0], word[1], word[2], word[3]}, reinterpret_cast<u32x4 *>(to));
+}
+
 // Writes the positions of one pair of segments, base the pair's first element; idx[out0 ..] takes them in order,
 // nothing at or beyond cap.  The positions go to LDS (the wave's own kSeg ints: no workgroup barrier), then leave as
 // contiguous 256-byte stores.  Lane l holds the flag word of elements base + 32 l .. base + 32 l + 31 in `word`; a pair with
@@ -300,12 +319,10 @@ index_kernel(const IndexBatch batch, int fill)
             }
             fp[p][j] = f[2 * j] | (f[2 * j + 1] << 16);
         }
-        // the lane's flag bits of the pass, one vector: what fill_kernel reads instead of the mask (past the
-        // caches, which was 5 % faster; a whole 2.7B model is counted in 0.54 ms, 0.46 without the bits)
-        if (batch.flags[job] != nullptr && seg0 + p * kSegsPerPass < nseg) {
-            typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-            __builtin_nontemporal_store((u32x4){fp[p][0], fp[p][1], fp[p][2], fp[p][3]},
-                                        reinterpret_cast<u32x4 *>(batch.flags[job] + (seg0 / kSegsPerPass + p) * 64 + lane));
+        if (batch.flags[job] != nullptr && seg0 + p * kSegsPerPass < nseg) {      // only where the testing aid sends a counting call here
+            uint32_t word[kPairs];
+            pair_words(fp[p], word, sh_stage[wave], lane);
+            store_flags(batch.flags[job] + (seg0 / kSegsPerPass + p) * 64 + lane, word);
         }
         asm volatile("" ::: "memory");        // the next pass's loads are requested after this pass's flag words exist
     }
@@ -360,18 +377,224 @@ index_kernel(const IndexBatch batch, int fill)
     }
 }
 
+// Counting without a chain, in two launches.  count_kernel streams the mask: a wave takes a group of eight segments, a
+// workgroup a block of kCountWaves groups, and leaves in seg_ptr the number of kept elements from the block's start to the
+// end of each of its segments; the block's own total, in its last entry, is encoded as in the chain.  No workgroup waits for another.
+// offsets_kernel adds what lies in front of each block: a workgroup sums the totals of all the blocks before its own (back to one
+// that another workgroup has already replaced by the running total), so nothing waits there either.
+// What bounds it: the mask read at HBM rate, and the flag words written beside it, an eighth of that: 550 MB of mask in 101 us, 6.1 TB/s
+// read and written; a kernel that only reads them takes 82.  Blocks of 16 or 32 segments (two or four waves) count as fast
+// but leave offsets_kernel two or four times the totals to sum (8.5 us instead of 6.5 with 32).
+constexpr int kCountWaves = 8;
+constexpr int kBlockSegs = kCountWaves * kSegsPerPass;
+constexpr int kOffsetBlocks = 32;          // blocks of a workgroup of offsets_kernel
+static_assert(kBlockSegs <= 64 && kOffsetBlocks <= 64, "a wave scans a block's segments, and a workgroup's blocks");
+// LDS a counting workgroup asks for beside its own 8 KB, so that two and not four share a compute unit's 160 KB, and the number
+// of workgroups from which on it does: a long launch reads faster with 16 waves in flight per compute unit, a short one is over sooner
+// with all it can hold (us without and with, masks of 64 / 128 / 192 / 256 / 400 MB: 19.9 / 34.3 / 46.0 / 59.1 / 89.5 and
+// 20.9 / 34.4 / 44.9 / 57.7 / 84.1).
+constexpr int kCountLdsPad = 48000;
+constexpr int64_t kCountPadFrom = 2048;
+
+template <bool FLAGS>
+__global__ void __launch_bounds__(kCountWaves * 64)
+count_kernel(const IndexBatch batch)
+{
+    __shared__ __attribute__((aligned(16))) int32_t sh_stage[FLAGS ? kCountWaves : 1][kPairs * 64];
+    __shared__ int sh_seg[kBlockSegs];
+    const int job = find_job(batch, (int)blockIdx.x);
+    const int64_t n = batch.n[job];
+    const int64_t nseg = (n + kSeg - 1) / kSeg;
+    const int64_t block = (int)blockIdx.x - batch.wg_start[job];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t group = block * kCountWaves + wave, seg0 = group * kSegsPerPass;
+    if (seg0 < nseg) {
+        uint32_t f[2 * kPairs], half[kPairs];
+        const uint8_t *__restrict__ mask = batch.mask[job];
+#pragma unroll
+        for (int q = 0; q < 2 * kPairs; ++q) f[q] = lane_flags(mask, n, (seg0 + q) * kSeg + lane * 16);
+#pragma unroll
+        for (int j = 0; j < kPairs; ++j) {
+            const int incl = wave_inclusive_scan(__popc(f[2 * j]) | (__popc(f[2 * j + 1]) << 16), lane);
+            if (lane == 63) {                  // the last lane's inclusive prefixes are the segment totals
+                sh_seg[wave * kSegsPerPass + 2 * j] = incl & 0xffff;
+                sh_seg[wave * kSegsPerPass + 2 * j + 1] = incl >> 16;
+            }
+            half[j] = f[2 * j] | (f[2 * j + 1] << 16);
+        }
+        if (FLAGS) {
+            uint32_t word[kPairs];
+            pair_words(half, word, sh_stage[wave], lane);
+            store_flags(batch.flags[job] + group * 64 + lane, word);
+        }
+    } else if (lane < kSegsPerPass) {
+        sh_seg[wave * kSegsPerPass + lane] = 0;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int incl = wave_inclusive_scan(lane < kBlockSegs ? sh_seg[lane] : 0, lane);
+        const int64_t at = block * kBlockSegs + lane + 1, end = chain_slot(block, nseg, kBlockSegs);
+        if (at <= end) batch.seg_ptr[job][at] = at == end ? encode_count(incl) : incl;
+    }
+}
+
+// An entry that another workgroup may be replacing: a reader takes the old or the new value, whichever its caches hold.
+__device__ __forceinline__ int either_load(const int32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+__device__ __forceinline__ void either_store(int32_t *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
+// The sum of the totals of the blocks in front of `block0` (all threads of the workgroup; every thread gets it).  A look takes
+// kLooks entries per thread, the nearest first; entries that another workgroup replaces meanwhile read as either value.
+__device__ __forceinline__ int kept_before(const int32_t *seg_ptr, int64_t nseg, int64_t block0, int *sh_nearest, int *sh_sum)
+{
+    constexpr int kLooks = 4;
+    const int tid = threadIdx.x;
+    int before = 0;
+    for (int64_t back = block0 - 1; back >= 0; back -= kLooks * kThreads) {
+        int v[kLooks];
+#pragma unroll
+        for (int k = 0; k < kLooks; ++k) {
+            const int64_t b = back - (k * kThreads + tid);
+            v[k] = b >= 0 ? either_load(seg_ptr + chain_slot(b, nseg, kBlockSegs)) : 0;      // in front of the first block: a total of 0
+        }
+        int nearest = kLooks * kThreads;
+#pragma unroll
+        for (int k = kLooks - 1; k >= 0; --k) {
+            const unsigned long long totals = __ballot(v[k] >= 0);
+            if (totals) nearest = k * kThreads + (tid & ~63) + __ffsll((long long)totals) - 1;
+        }
+        if ((tid & 63) == 0) sh_nearest[tid >> 6] = nearest;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) nearest = sh_nearest[w] < nearest ? sh_nearest[w] : nearest;
+        int part = 0;
+#pragma unroll
+        for (int k = 0; k < kLooks; ++k) {
+            const int i = k * kThreads + tid;
+            part += i < nearest ? decode_count(v[k]) : i == nearest ? v[k] : 0;
+        }
+        part = wave_sum(part);
+        if ((tid & 63) == 0) sh_sum[tid >> 6] = part;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) before += sh_sum[w];
+        if (nearest < kLooks * kThreads) break;
+    }
+    return before;
+}
+
+__global__ void __launch_bounds__(kThreads)
+offsets_kernel(const IndexBatch batch)
+{
+    __shared__ int sh_base[kOffsetBlocks], sh_nearest[kThreads / 64], sh_sum[kThreads / 64];
+    const int job = find_job(batch, (int)blockIdx.x);
+    const int64_t nseg = (batch.n[job] + kSeg - 1) / kSeg;
+    const int64_t blocks = (nseg + kBlockSegs - 1) / kBlockSegs;
+    const int wg = (int)blockIdx.x - batch.wg_start[job];
+    const int64_t block0 = (int64_t)wg * kOffsetBlocks;
+    int32_t *seg_ptr = batch.seg_ptr[job];
+    const int tid = threadIdx.x;
+    constexpr int kEach = kOffsetBlocks * kBlockSegs / kThreads;
+    const int64_t first = block0 * kBlockSegs + 1;
+    int in_block[kEach], own = 0;
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) {
+        const int64_t at = first + i * kThreads + tid;
+        in_block[i] = at <= nseg ? seg_ptr[at] : 0;
+    }
+    if (tid < kOffsetBlocks && block0 + tid < blocks) own = decode_count(seg_ptr[chain_slot(block0 + tid, nseg, kBlockSegs)]);
+    const int before = kept_before(seg_ptr, nseg, block0, sh_nearest, sh_sum);
+    if (tid < 64) {
+        const int incl = wave_inclusive_scan(own, tid);
+        if (tid < kOffsetBlocks) sh_base[tid] = before + incl - own;
+        if (tid == 0 && wg == 0) seg_ptr[0] = 0;
+        if (tid == 63 && block0 + kOffsetBlocks >= blocks) *batch.nnz[job] = (int64_t)before + incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) {
+        const int slot = i * kThreads + tid;
+        const int64_t at = first + slot;
+        if (at > nseg) continue;
+        const bool end = slot % kBlockSegs == kBlockSegs - 1 || at == nseg;
+        either_store(seg_ptr + at, sh_base[slot / kBlockSegs] + (end ? decode_count(in_block[i]) : in_block[i]));
+    }
+}
+
+
 // The positions from the flag words and the seg_ptr a counting launch left: a wave takes a group of eight
 // segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
 // A count that gave up left *nnz = -1 and a seg_ptr that is no table of offsets (chain states, entries never
 // written): nothing is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
 // What bounds it: the loop over a lane's kept elements (7 vector instructions and an LDS store a trip, 8 trips
 // a pair at 10 % kept) beside the index written, 4 bytes per kept element: 4.6 TB/s at 10 % kept.
+// The positions from the flag words and the seg_ptr a counting call left: a wave takes a group of eight
+// segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
+// A count that gave up left *nnz = -1 and a seg_ptr that is no table of offsets (chain states, entries never
+// written): nothing is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
+// A lane holds 32 consecutive elements of each of the group's four pairs of segments.  Where a group keeps at most kStage
+// elements its four pairs go through the loop over kept elements side by side (about 9 trips at 10 % kept, which share the
+// loop's overhead, where one pair after the other took 8 each) and leave as one run; up to twice that, two pairs at a time.
+// What bounds it: HBM, with the vector ALU close behind: 69 MB of flag words and 220 MB of idx in 56 us, 5.2 TB/s; 69 us with one
+// pair at a time, 4-byte stores and idx through the caches.  A larger stage costs more in occupancy than it saves (58 us with 1280
+// positions, 74 with 2048).
 constexpr int kFillWaves = 4;
+constexpr int kStage = kSeg;               // positions a wave collects before they leave
+
+// Writes the positions of K pairs of segments that hold `total` <= kStage kept elements together.  word[k]: the lane's 32 elements
+// of pair k; at[k]: how many of these pairs' kept elements come before them; base: the first pair's first element.
+// The stage is shifted so that its 16-byte vectors are those of idx: whole ones leave as such, past the caches, and the
+// ends, shared with the neighbouring runs, element by element.
+template <int K>
+__device__ __forceinline__ void emit_pairs(const uint32_t *word, const int *at, int total, int base, int64_t out0, int64_t cap,
+                                           int32_t *__restrict__ idx, int32_t *stage, int lane)
+{
+    const int shift = (int)(out0 & 3);
+    uint32_t bits[K];
+    int32_t *to[K];
+    int first[K];
+    uint32_t left = 0u;
+    constexpr int kTrips = 2;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        bits[k] = word[k];
+        to[k] = stage + shift + at[k];
+        first[k] = base + 2 * kSeg * k + 32 * lane;
+        left |= bits[k];
+    }
+    while (__any(left != 0u)) {
+        left = 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int u = 0; u < kTrips; ++u) {
+                if (bits[k] != 0u) to[k][u] = first[k] + __builtin_ctz(bits[k]);
+                bits[k] &= bits[k] - 1u;
+            }
+            to[k] += kTrips;
+            left |= bits[k];
+        }
+    }
+    wave_lds_order();
+    const int end = shift + storable(cap, out0, total);
+    int32_t *__restrict__ out = idx + (out0 - shift);
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    for (int e = 4 * lane; e < end; e += 256) {
+        const i32x4 q = *reinterpret_cast<const i32x4 *>(stage + e);
+        if (e >= shift && e + 4 <= end) {
+            __builtin_nontemporal_store(q, reinterpret_cast<i32x4 *>(out + e));
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (e + u >= shift && e + u < end) out[e + u] = q[u];
+        }
+    }
+    wave_lds_order();
+}
 
 __global__ void __launch_bounds__(kFillWaves * 64)
 fill_kernel(const IndexBatch batch)
 {
-    __shared__ __attribute__((aligned(16))) int32_t sh_stage[kFillWaves][kSeg];
+    __shared__ __attribute__((aligned(16))) int32_t sh_stage[kFillWaves][kStage + 4];
     const int job = find_job(batch, (int)blockIdx.x);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nseg = (batch.n[job] + kSeg - 1) / kSeg;
@@ -380,17 +603,48 @@ fill_kernel(const IndexBatch batch)
     if (seg0 >= nseg) return;                 // whole waves leave; nothing below is a workgroup barrier
     const int64_t counted = *batch.nnz[job];
     const uint4 w = batch.flags[job][group * 64 + lane];
-    const uint32_t halves[kPairs] = {w.x, w.y, w.z, w.w};
-    const int32_t *__restrict__ seg_ptr = batch.seg_ptr[job];
-    int start[kPairs];
-#pragma unroll
-    for (int j = 0; j < kPairs; ++j) start[j] = seg_ptr[seg0 + 2 * j < nseg ? seg0 + 2 * j : nseg];
+    const int64_t out0 = batch.seg_ptr[job][seg0];
     if (counted < 0) return;
-    uint32_t word[kPairs];
-    pair_words(halves, word, sh_stage[wave], lane);
+    const uint32_t word[kPairs] = {w.x, w.y, w.z, w.w};
+    const int64_t cap = batch.cap[job];
+    int32_t *__restrict__ idx = batch.idx[job];
+    int32_t *stage = sh_stage[wave];
+    const int base = (int)(seg0 * kSeg);
+    int at[kPairs], total[kPairs];
 #pragma unroll
-    for (int j = 0; j < kPairs; ++j)
-        emit_pair(word[j], halves[j], (int)((seg0 + 2 * j) * kSeg), start[j], batch.cap[job], batch.idx[job], sh_stage[wave], lane);
+    for (int j = 0; j < kPairs; j += 2) {     // a pair's count fits 16 bits
+        const int c = __popc(word[j]) | (__popc(word[j + 1]) << 16);
+        const int incl = wave_inclusive_scan(c, lane);
+        const int all = __builtin_amdgcn_readlane(incl, 63);
+        const int before = incl - c;
+        at[j] = before & 0xffff;
+        at[j + 1] = before >> 16;
+        total[j] = all & 0xffff;
+        total[j + 1] = all >> 16;
+    }
+    const int half = total[0] + total[1];
+    if (half + total[2] + total[3] <= kStage) {
+        at[1] += total[0];
+        at[2] += half;
+        at[3] += half + total[2];
+        emit_pairs<4>(word, at, half + total[2] + total[3], base, out0, cap, idx, stage, lane);
+        return;
+    }
+    if (half <= kStage && total[2] + total[3] <= kStage) {
+        at[1] += total[0];
+        at[3] += total[2];
+        emit_pairs<2>(word, at, half, base, out0, cap, idx, stage, lane);
+        emit_pairs<2>(word + 2, at + 2, total[2] + total[3], base + 4 * kSeg, out0 + half, cap, idx, stage, lane);
+        return;
+    }
+    uint32_t halves[kPairs];
+    word_halves(word, halves, stage, lane);
+    int64_t out = out0;
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        emit_pair(word[j], halves[j], base + 2 * kSeg * j, out, cap, idx, stage, lane);
+        out += total[j];
+    }
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -442,15 +696,36 @@ hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
     index_init_kernel<<<dim3((unsigned)ceil_div(init_threads, kThreads)), dim3(kThreads), 0, s>>>(batch);
     if (wgs > 0) {
         const dim3 grid((unsigned)wgs), block(kIndexThreads);
-        // A launch that only counts reads as fast as the memory lets it and runs best with two workgroups per
-        // compute unit, not the three (four passes: 70 registers) or four (LDS) that fit (with the flag bits of 32 and 7
-        // layers of the 2.7B shape 537 and 128 us against 558 and 133, without them 462 against 466); one that fills as
-        // well needs the waves (765 against 757).
-        const int pad = fill ? 0 : kCountLdsPad;
-        if (batch.passes == 4) index_kernel<4><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
-        else if (batch.passes == 2) index_kernel<2><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
-        else index_kernel<1><<<grid, block, pad, s>>>(batch, fill ? 1 : 0);
+        if (batch.passes == 4) index_kernel<4><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
+        else if (batch.passes == 2) index_kernel<2><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
+        else index_kernel<1><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_index_count(IndexBatch &batch, bool flags, hipStream_t s)
+{
+    if (batch.num <= 0) return hipSuccess;
+    int64_t wgs = 0;
+    for (int j = 0; j < batch.num; ++j) {
+        batch.wg_start[j] = (int)wgs;
+        wgs += ceil_div(ceil_div(batch.n[j], kSeg), kBlockSegs);
+    }
+    batch.wg_start[batch.num] = (int)wgs;
+    if (wgs > 0) {
+        const dim3 grid((unsigned)wgs), block(kCountWaves * 64);
+        const int pad = wgs >= kCountPadFrom ? kCountLdsPad : 0;
+        if (flags) count_kernel<true><<<grid, block, pad, s>>>(batch);
+        else count_kernel<false><<<grid, block, pad, s>>>(batch);
+    }
+    wgs = 0;
+    for (int j = 0; j < batch.num; ++j) {
+        batch.wg_start[j] = (int)wgs;
+        const int64_t w = ceil_div(ceil_div(batch.n[j], kSeg), kBlockSegs * kOffsetBlocks);
+        wgs += w > 0 ? w : 1;                 // an empty job has a seg_ptr and a count as well
+    }
+    batch.wg_start[batch.num] = (int)wgs;
+    offsets_kernel<<<dim3((unsigned)wgs), dim3(kThreads), 0, s>>>(batch);
     return hipGetLastError();
 }
 
@@ -465,10 +740,9 @@ int64_t index_fill_workgroups(int64_t n) { return ceil_div(ceil_div(n, kSeg), kF
 
 int64_t index_job_workgroups(int64_t n, int passes) { return ceil_div(ceil_div(n, kSeg), segs_per_wg(passes)); }
 
-// Passes per workgroup for a launch over `mask_bytes` bytes of mask: the most for which the launch still has a dozen
+// Passes per workgroup for a chained launch over `mask_bytes` bytes of mask: the most for which the launch still has a dozen
 // blocks per compute unit.  With 1, 2 and 4 passes, 10 % kept, us: 7 layers of the 2.7B shape (550 MB of mask: 33, 16
-// and 8 blocks per compute unit) build 174, 160, 163, counting with the flag bits 152, 127, 122; 32 layers
-// 794, 753, 751 and 669, 555, 531.  The line is the build's; a launch that only counts would take four passes earlier.
+// and 8 blocks per compute unit) 174, 160, 163; 32 layers 794, 753, 751.
 int index_passes_for(int64_t mask_bytes, int compute_units)
 {
     const int64_t wanted = (int64_t)compute_units * 12;

@@ -266,6 +266,7 @@ try:
     from . import _marshal
 except ImportError:                          # not built: the Python checks serve every call
     _dev, _dev_matrix = _dev_python, _dev_matrix_python
+    _marshal = None
 else:
     _marshal.use(_dev_python, _dev_matrix_python)
     _dev, _dev_matrix = _marshal.vector, _marshal.matrix
@@ -332,6 +333,17 @@ def samo_build_index(mask: torch.Tensor) -> Index:
     return _build_indices([mask], "samo_build_index")[0]
 
 
+_addresses: dict = {}
+
+
+def _entry_address(name: str) -> int:
+    """Address of a library entry, for native code that calls it."""
+    at = _addresses.get(name)
+    if at is None:
+        at = _addresses[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+    return at
+
+
 def _flag_bytes(n: int) -> int:
     """samo_index_flags_bytes of the library without the call: 1 KiB per eight segments."""
     return (n + 8 * SEG_ELEMS - 1) // (8 * SEG_ELEMS) * 1024
@@ -339,8 +351,22 @@ def _flag_bytes(n: int) -> int:
 
 def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     """Index of every mask: one batched count that reads the masks and leaves their flag bits, one read-back
-    of the counts to size the indices, one batched fill from the flag bits.  Without memory for those
-    (an eighth of the masks) the second call reads the masks again."""
+    of the counts to size the indices, a batched fill from the flag bits.  Without memory for those
+    (an eighth of the masks) the second call reads the masks again.
+
+    The same in native code where that is built, for plain tensors and with memory for the flag bits (_marshal.build_indices:
+    28 matrices, 550 M elements: 243 us with the loops below, 194 with those)."""
+    if _marshal is not None:
+        count, fill = _entry_address("samo_count_flags_batched"), _entry_address("samo_fill_index_batched")
+        built = _marshal.build_indices(list(masks), _stream, _scratch, count, fill)
+        if isinstance(built, list):
+            return [Index(*parts) for parts in built]
+        if built == SAMO_ERR_SIZE:
+            raise SamoError(SAMO_ERR_SIZE, "samo_seg_ptr_len")
+        if built == SAMO_ERR_INDEX:
+            raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
+        if built is not None:
+            raise SamoError(built, where)
     dev, k = masks[0].device, len(masks)
     sizes = [m.numel() for m in masks]
     seg_lens = [samo_seg_ptr_len(n) for n in sizes]

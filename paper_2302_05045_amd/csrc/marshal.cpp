@@ -1,12 +1,21 @@
 // Argument marshalling of the Python binding in native code: a tensor argument's checks and its device
 // pointer in one call.  In Python the same checks are eight attribute reads, about 1 us per tensor, and an
 // entry point takes up to seven tensors: more host time than the kernel of a small layer runs.
-// Nothing but reads of tensor metadata happens here.  Whatever is not a plain torch.Tensor or Parameter (subclasses
-// may override attributes, other objects have to be refused) goes to the Python function that makes the
+// Nothing but reads of tensor metadata happens in vector() and matrix().  Whatever is not a plain torch.Tensor or Parameter
+// (subclasses may override attributes, other objects have to be refused) goes to the Python function that makes the
 // same checks, given once by use().
+//
+// build_indices() is the index build of a list of masks with its loops over them in native code, for the same reason:
+// while the device waits for the host between the count and the fill, a mask costs 0.8 us here and 3 in Python.
+#include <ATen/ops/empty.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
+
+#include <vector>
+
+#include "samo.h"
 
 namespace {
 
@@ -69,6 +78,99 @@ PyObject *matrix(PyObject *, PyObject *const *args, Py_ssize_t count)
     END_HANDLE_TH_ERRORS
 }
 
+// The GIL given up for as long as this lives.
+struct WithoutGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
+// Elements of masks from which on build_indices launches the fill of those that have their index allocated while it goes on
+// with the others; twice as many for every further launch.  28 matrices of 550 M elements: five launches.  A launch costs the host
+// 5 us and fills 32 M elements in 3, so the first one starts the device early and the last ones keep it busy.
+constexpr int64_t kFirstFill = 32 << 20;
+
+// build_indices(masks, stream, scratch, count, fill): indices of byte masks (a list) by the entries samo_count_flags_batched and
+// samo_fill_index_batched at the addresses `count` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
+// uint8 tensor for the flag bits or None.
+// A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int (SAMO_ERR_INDEX: a count gave up); None where the
+// caller has to go another way: a mask is no plain tensor, or there is no scratch memory.
+PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
+{
+    HANDLE_TH_ERRORS
+    typedef samo_status (*Entry)(const samo_index_job *, void *const *, int32_t, void *);
+    if (nargs != 5 || !PyList_Check(args[0]) || PyList_GET_SIZE(args[0]) == 0) {
+        PyErr_SetString(PyExc_TypeError, "build_indices(masks, stream, scratch, count, fill)");
+        return nullptr;
+    }
+    const Entry count = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[3])), fill = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[4]));
+    if (PyErr_Occurred()) return nullptr;
+    const size_t k = (size_t)PyList_GET_SIZE(args[0]);
+    std::vector<at::Tensor> masks(k), seg_ptrs(k), idxs(k);              // they hold the masks whatever happens to the list
+    std::vector<samo_index_job> jobs(k);
+    std::vector<void *> flags(k);
+    int64_t flag_bytes = 0;
+    for (size_t i = 0; i < k; ++i) {
+        PyObject *m = PyList_GET_ITEM(args[0], (Py_ssize_t)i);
+        if (!THPVariable_CheckExact(m)) Py_RETURN_NONE;
+        masks[i] = THPVariable_Unpack(m);
+        if (!masks[i].is_cuda() || masks[i].scalar_type() != at::kByte || masks[i].dim() != 1 || !masks[i].is_contiguous()) Py_RETURN_NONE;
+        const int64_t n = masks[i].numel();
+        if (n > INT32_MAX) return PyLong_FromLong(SAMO_ERR_SIZE);
+        flag_bytes += (n + 8 * SAMO_SEG_ELEMS - 1) / (8 * SAMO_SEG_ELEMS) * 1024;
+    }
+    THPObjectPtr handle(PyObject_CallNoArgs(args[1]));
+    if (!handle) return nullptr;
+    void *stream = PyLong_AsVoidPtr(handle.get());
+    if (PyErr_Occurred()) return nullptr;
+    THPObjectPtr bytes(PyLong_FromLongLong(flag_bytes > 0 ? flag_bytes : 1));
+    THPObjectPtr scratch(bytes ? PyObject_CallOneArg(args[2], bytes) : nullptr);
+    if (!scratch) return nullptr;
+    if (!THPVariable_Check(scratch.get())) Py_RETURN_NONE;
+    char *flags_at = static_cast<char *>(THPVariable_Unpack(scratch.get()).data_ptr());
+    const at::TensorOptions ints = masks[0].options().dtype(at::kInt).requires_grad(false);
+    at::Tensor counts;
+    samo_status status;
+    {
+        WithoutGil gil;
+        at::Tensor nnz = at::empty({(int64_t)k}, ints.dtype(at::kLong));
+        for (size_t i = 0; i < k; ++i) {
+            const int64_t n = masks[i].numel();
+            seg_ptrs[i] = at::empty({(n + SAMO_SEG_ELEMS - 1) / SAMO_SEG_ELEMS + 1}, ints);
+            jobs[i] = {n ? static_cast<const uint8_t *>(masks[i].data_ptr()) : nullptr, n, nullptr, 0,
+                       static_cast<int32_t *>(seg_ptrs[i].data_ptr()), static_cast<int64_t *>(nnz.data_ptr()) + i};
+            flags[i] = flags_at;
+            flags_at += (n + 8 * SAMO_SEG_ELEMS - 1) / (8 * SAMO_SEG_ELEMS) * 1024;
+        }
+        status = count(jobs.data(), flags.data(), (int32_t)k, stream);
+        if (status == SAMO_OK) counts = nnz.cpu();
+        for (size_t i = 0; status == SAMO_OK && i < k; ++i)
+            if (counts.data_ptr<int64_t>()[i] < 0) status = SAMO_ERR_INDEX;
+        int64_t waiting = 0, enough = kFirstFill;
+        for (size_t i = 0, first = 0; status == SAMO_OK && i < k; ++i) {
+            const int64_t found = counts.data_ptr<int64_t>()[i];
+            idxs[i] = at::empty({found}, ints);
+            jobs[i].idx = found ? static_cast<int32_t *>(idxs[i].data_ptr()) : nullptr;
+            jobs[i].idx_capacity = found;
+            waiting += jobs[i].n;
+            if (waiting < enough && i + 1 < k) continue;
+            status = fill(jobs.data() + first, flags.data() + first, (int32_t)(i + 1 - first), stream);
+            first = i + 1;
+            waiting = 0;
+            enough *= 2;
+        }
+    }
+    if (status != SAMO_OK) return PyLong_FromLong(status);
+    THPObjectPtr out(PyList_New((Py_ssize_t)k));
+    if (!out) return nullptr;
+    for (size_t i = 0; i < k; ++i) {
+        PyObject *item = Py_BuildValue("NNLL", THPVariable_Wrap(idxs[i]), THPVariable_Wrap(seg_ptrs[i]), (long long)jobs[i].idx_capacity, (long long)jobs[i].n);
+        if (!item) return nullptr;
+        PyList_SET_ITEM(out.get(), (Py_ssize_t)i, item);
+    }
+    return out.release();
+    END_HANDLE_TH_ERRORS
+}
+
 // use(vector, matrix): the Python functions for everything that is no plain tensor.
 PyObject *use(PyObject *, PyObject *const *args, Py_ssize_t count)
 {
@@ -88,6 +190,7 @@ PyObject *use(PyObject *, PyObject *const *args, Py_ssize_t count)
 PyMethodDef methods[] = {
     {"vector", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(vector)), METH_FASTCALL, nullptr},
     {"matrix", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(matrix)), METH_FASTCALL, nullptr},
+    {"build_indices", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(build_indices)), METH_FASTCALL, nullptr},
     {"use", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(use)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -39,3 +39,37 @@ def test_the_stream_is_the_current_one():
     with torch.cuda.stream(side):
         assert samo._stream() == side.cuda_stream
     assert samo._stream() == torch.cuda.current_stream().cuda_stream
+
+
+def test_native_and_python_index_builds_agree(monkeypatch):
+    """The loops over the masks exist twice; the native ones launch the fill in several parts (the first from 32 M elements on)."""
+    from paper_2302_05045_amd import _marshal
+
+    class Sub(torch.Tensor):
+        pass
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    bern = lambda n, keep: (torch.rand(n, generator=gen, device=DEV) < keep).to(torch.uint8)
+    small = [bern(n, 0.3) for n in (1, 0, 1024, 70001)]
+    large = [bern(n, 0.05) for n in (20_000_003, 1000, 20_000_001, 0, 40_000_000, 17, 50_000_000, 3000)]
+    wide = bern(4096, 0.5)
+    calls = [small, large, [wide[1:]], [wide[::2]], [wide.view(64, 64)], [wide.float()], small + [wide.as_subclass(Sub)],
+             [wide.cpu()], small + [None], tuple(small), [torch.nn.Parameter(wide, requires_grad=False)]]
+
+    def outcome(masks):
+        try:
+            return samo.samo_build_index_many(masks)
+        except (TypeError, ValueError, AttributeError, samo.SamoError) as e:
+            return type(e), str(e)
+    native = [outcome(c) for c in calls]
+    assert isinstance(_marshal.build_indices(small, samo._stream, samo._scratch, samo._entry_address("samo_count_flags_batched"),
+                                             samo._entry_address("samo_fill_index_batched")), list)
+    monkeypatch.setattr(samo, "_marshal", None)
+    for masks, got in zip(calls, native):
+        want = outcome(masks)
+        if isinstance(want, tuple):
+            assert got == want
+            continue
+        for a, b in zip(got, want):
+            assert type(a) is samo.Index and a.nnz == b.nnz and a.n == b.n
+            assert torch.equal(a.idx, b.idx) and torch.equal(a.seg_ptr, b.seg_ptr)
+            assert a.idx.dtype == b.idx.dtype and a.seg_ptr.dtype == b.seg_ptr.dtype

@@ -494,6 +494,8 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *   SAMO_KNOB_TILE_COST    the weight of a plan's tiles in units of 1024 (6 .. 96; default 32, or 48 for a
  *                        model that keeps under 7 % of its elements; 48 there with an fp32 dense side).
  *                        Read by samo_plan_workspace_bytes and samo_plan_init: set it before both.
+ *   SAMO_KNOB_STAGED_TILES  the most tiles (of the default weight) with which a fused step counts as a short launch
+ *                        and takes the kernel made for those (default 10000); 0: never.
  * Returns SAMO_ERR_ARG for an unknown knob. */
 enum {
     SAMO_KNOB_OCC_TILE_STEP = 0,
@@ -510,7 +512,8 @@ enum {
     SAMO_KNOB_TILE_COST = 11,
     SAMO_KNOB_WGRAD_SPLIT = 12,
     SAMO_KNOB_WGRAD_COLS = 13,
-    SAMO_KNOB_COUNT = 14
+    SAMO_KNOB_STAGED_TILES = 14,
+    SAMO_KNOB_COUNT = 15
 };
 #define SAMO_KNOB_DEFAULT (-1)
 samo_status samo_debug_set(int32_t knob, int32_t value);

@@ -34,7 +34,7 @@ SAMO_OK = 0
 # samo_debug_set knobs
 (KNOB_OCC_TILE_STEP, KNOB_OCC_TILE_STEP32, KNOB_OCC_TILE_DECOMP, KNOB_OCC_TILE_C16, KNOB_OCC_FLAT_GATHER,
  KNOB_OCC_FLAT_STATS, KNOB_OCC_FLAT_STEP, KNOB_INDEX_SPIN_LIMIT, KNOB_WGRAD_TILE, KNOB_WGRAD_ROUND,
- KNOB_INDEX_PASSES, KNOB_TILE_COST, KNOB_WGRAD_SPLIT, KNOB_WGRAD_COLS) = range(14)
+ KNOB_INDEX_PASSES, KNOB_TILE_COST, KNOB_WGRAD_SPLIT, KNOB_WGRAD_COLS, KNOB_STAGED_TILES) = range(15)
 KNOB_DEFAULT = -1
 
 

@@ -550,14 +550,13 @@ __device__ __forceinline__ void emit_pairs(const uint32_t *word, const int *at, 
 {
     const int shift = (int)(out0 & 3);
     uint32_t bits[K];
-    int32_t *to[K];
-    int first[K];
+    int to[K], first[K];
     uint32_t left = 0u;
     constexpr int kTrips = 2;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         bits[k] = word[k];
-        to[k] = stage + shift + at[k];
+        to[k] = shift + at[k];
         first[k] = base + 2 * kSeg * k + 32 * lane;
         left |= bits[k];
     }
@@ -567,7 +566,7 @@ __device__ __forceinline__ void emit_pairs(const uint32_t *word, const int *at, 
         for (int k = 0; k < K; ++k) {
 #pragma unroll
             for (int u = 0; u < kTrips; ++u) {
-                if (bits[k] != 0u) to[k][u] = first[k] + __builtin_ctz(bits[k]);
+                if (bits[k] != 0u) stage[to[k] + u] = first[k] + __builtin_ctz(bits[k]);
                 bits[k] &= bits[k] - 1u;
             }
             to[k] += kTrips;

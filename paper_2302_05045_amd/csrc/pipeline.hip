@@ -202,6 +202,7 @@ __device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, in
         store16_stream(reinterpret_cast<uint4 *>(L.w + base) + o, make_uint4(wq[0], wq[1], wq[2], wq[3]));
     }
     const int nvec = nvec8 * 2;           // elements handled above, in units of four
+#pragma unroll 1
     for (int e = nvec * 4 + tid; e < len; e += T) {      // ragged end of the layer
         float pe = L.p[base + e];
         if (MODE == kModeStep) {
@@ -462,6 +463,150 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
         sparse_tile_dense_grad<OPT, T>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, xj, xg);
     else
         sparse_tile<MODE, GSRC, OPT, T>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w);
+}
+
+// ------------------------------------------------------------------ the fused step of a short launch
+// A launch of few tiles per compute unit is over before its traffic is a stream: its time is the chain of dependent trips to memory
+// (record, layer, bounds, positions, gradient at the positions) and the starting of workgroups.  Here the whole gradient of the
+// tile is requested as 16-byte vectors as soon as the layer is known, beside the bounds, and waits in LDS for the positions:
+// one trip less; compressed elements go one to a lane, so that few of the workgroup's eight waves idle; and a workgroup takes two
+// consecutive tile records where a launch has more than kStagedRound of them.  Four workgroups share a compute unit (64
+// registers, up to 40 KB of LDS).  In us, tile_kernel and this one: one layer of 1024 x 1024 (10 % kept) 4.5 and 3.4, 2048 x 2048 8.1
+// and 6.2, 4096 x 2048 13.1 and 10.4; 18 convolutions (11.5 M elements, SGD) 16.1 and 14.3; a 12.6 M element GPT at 15 % kept
+// 21.0 and 19.7.  Tried instead: persistent workgroups that request the next tile while they step one (16.3 to 22 us for the
+// convolutions, whatever the number of workgroups), workgroups of 128 and 256 threads (15.4, 14.8), two elements per
+// lane requested ahead (15.4).
+constexpr int kStagedThreads = 512;
+constexpr int kStagedSlots = 1024;            // workgroups of that size the device holds at a time
+constexpr int kStagedSegs = 10;               // segments of a tile with which four workgroups still share a compute unit's LDS
+constexpr int kStagedLdsSegs = 13;            // ... and with which three do
+
+// A layer of a plan by way of constant memory: whose pointers the compiler takes for pointers to global memory (loads of
+// them are global, not flat, instructions, which would also be waited for by every LDS access).
+#define SAMO_CONSTANT __attribute__((address_space(4)))
+__device__ __forceinline__ samo_layer constant_layer(const samo_layer *layer)
+{
+    const SAMO_CONSTANT samo_layer *C = (const SAMO_CONSTANT samo_layer *)layer;
+    samo_layer L;
+    L.n = C->n; L.nnz = C->nnz; L.idx = C->idx; L.seg_ptr = C->seg_ptr; L.p = C->p; L.m = C->m; L.v = C->v; L.w = C->w; L.g = C->g;
+    L.gc = nullptr; L.gc16 = nullptr; L.w32 = nullptr; L.g32 = nullptr;
+    return L;
+}
+
+__device__ __forceinline__ WgRec constant_rec(const WgRec *rec)
+{
+    const uint64_t q = *(const SAMO_CONSTANT uint64_t *)rec;
+    WgRec r;
+    r.layer = (int32_t)(uint32_t)q;
+    r.local = (uint32_t)(q >> 32);
+    return r;
+}
+
+template <int OPT>
+__device__ __forceinline__ void staged_tile(const samo_layer &L, int s0, int nsegs, int64_t base, int len, float inv_scale, float coef,
+                                            const OptK &k, uint16_t *lds_w, uint16_t *lds_g)
+{
+    constexpr int T = kStagedThreads, kHeld = 2, kElems = 1;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));             // what follows from it is formed anew for every tile, not kept in registers
+    const uint16_t *__restrict__ G = L.g + base;
+    const int nvec = len / 8;
+    u32x4 held[kHeld];                        // loads at clamped places, none under a condition: nothing waits for them before their use
+    if (nvec > 0) {
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) {
+            const int o = tid + u * T < nvec ? tid + u * T : nvec - 1;
+            held[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(G) + o);
+        }
+    }
+    const SAMO_CONSTANT int32_t *bounds = (const SAMO_CONSTANT int32_t *)L.seg_ptr;
+    const int nnz = (int)L.nnz, b0 = bounds[s0], b1 = bounds[s0 + nsegs];
+    const int c0 = b0 < 0 ? 0 : (b0 > nnz ? nnz : b0);       // as slice_bound
+    const int c1 = b1 < 0 ? 0 : (b1 > nnz ? nnz : b1);
+    const int ibase = (int)base;
+    int j[kElems];
+    float p[kElems], m[kElems], v[kElems];
+    if (c1 > c0) {
+#pragma unroll
+        for (int u = 0; u < kElems; ++u) {
+            const int r = c0 + tid + u * T < c1 ? c0 + tid + u * T : c1 - 1;
+            j[u] = L.idx[r];
+            p[u] = L.p[r];
+            m[u] = L.m[r];
+            v[u] = OPT == kOptAdam ? L.v[r] : 0.f;
+        }
+    }
+    uint4 *w4 = reinterpret_cast<uint4 *>(lds_w);
+#pragma unroll 1
+    for (int o = tid; o < (len + 7) / 8; o += T) w4[o] = make_uint4(0u, 0u, 0u, 0u);
+    u32x4 *g4 = reinterpret_cast<u32x4 *>(lds_g);
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (tid + u * T < nvec) g4[tid + u * T] = held[u];
+#pragma unroll 1
+    for (int o = tid + kHeld * T; o < nvec; o += T) g4[o] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(G) + o);
+#pragma unroll 1
+    for (int e = nvec * 8 + tid; e < len; e += T) lds_g[e] = G[e];
+    __syncthreads();
+    auto update = [&](int r, int jr, float pr, float mr, float vr) {
+        opt_update<OPT>(pr, mr, vr, (half_bits_to_float(lds_g[jr - ibase]) * inv_scale) * coef, k);
+        L.p[r] = pr;
+        L.m[r] = mr;
+        if (OPT == kOptAdam) L.v[r] = vr;
+        lds_w[jr - ibase] = float_to_half_bits(pr);
+    };
+#pragma unroll
+    for (int u = 0; u < kElems; ++u)
+        if (c0 + tid + u * T < c1) update(c0 + tid + u * T, j[u], p[u], m[u], v[u]);
+#pragma unroll 1
+    for (int r = c0 + tid + kElems * T; r < c1; r += T) update(r, L.idx[r], L.p[r], L.m[r], OPT == kOptAdam ? L.v[r] : 0.f);
+    __syncthreads();
+    uint16_t *__restrict__ W = L.w + base;
+#pragma unroll 1
+    for (int o = tid; o < nvec; o += T) store16_stream(reinterpret_cast<uint4 *>(W) + o, w4[o]);
+#pragma unroll 1
+    for (int e = nvec * 8 + tid; e < len; e += T) W[e] = lds_w[e];
+}
+
+// `merge` consecutive records to a workgroup; those of one layer that follow each other are one tile of at most
+// merge * ls.max_segs segments.  A single layer: merge is 1, segs_per_tile says how large its tiles are.
+template <int OPT, bool PLAN>
+__global__ void __launch_bounds__(kStagedThreads, 8)
+staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, const GuardK guard)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_image[];
+    const int most = merge * ls.max_segs;
+    uint16_t *lds_w = reinterpret_cast<uint16_t *>(lds_image);       // the tile's new weights, and its gradient
+    uint16_t *lds_g = lds_w + most * kSeg;
+    bool skip;
+    const float coef = guard_coef(guard, &skip);
+    if (skip) return;
+    auto tile = [&](const samo_layer &L, int s0, int nsegs) {
+        if (nsegs > most) nsegs = most;           // records never hold more; the images must not be overrun whatever they say
+        const int64_t base = (int64_t)s0 * kSeg, rest = L.n - base;
+        const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
+        if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads>(L, base, len, inv_scale, coef, k);
+        else staged_tile<OPT>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
+    };
+    const int64_t first = (int64_t)blockIdx.x * merge;
+    if (!PLAN) {
+        const int64_t nseg = (ls.one.n + kSeg - 1) / kSeg, s0 = first * ls.segs_per_tile;
+        tile(ls.one, (int)s0, nseg - s0 < ls.segs_per_tile ? (int)(nseg - s0) : ls.segs_per_tile);
+        return;
+    }
+    const int64_t end = first + merge < ls.wgs ? first + merge : ls.wgs;
+    for (int64_t t = first; t < end;) {
+        const WgRec r = constant_rec(ls.recs + t);
+        const int s0 = (int)(r.local & ((1u << kRecSegShift) - 1u));
+        int nsegs = (int)(r.local >> kRecSegShift);
+        for (++t; t < end; ++t) {
+            const WgRec q = constant_rec(ls.recs + t);
+            if (q.layer != r.layer || (int)(q.local & ((1u << kRecSegShift) - 1u)) != s0 + nsegs) break;
+            nsegs += (int)(q.local >> kRecSegShift);
+        }
+        if (nsegs > 0) tile(constant_layer(ls.layers + r.layer), s0, nsegs);
+        if (t < end) __syncthreads();             // the images are free
+    }
 }
 
 // ------------------------------------------------------------------ single-precision tile kernel
@@ -1159,6 +1304,54 @@ static int occ_flat_step()
     return knob(SAMO_KNOB_OCC_FLAT_STEP, 13);     // a narrow optimum: 12-15 waves per CU by size of the arrays, 16 loses 7 %
 }
 
+// Whether a fused step that reads the dense gradient goes to staged_kernel, and how it is launched there.
+// Up to kStagedMost tiles of the default weight, about 40 M elements at 10 % kept: beyond, tile_kernel's smaller footprint per tile
+// lets the stream run as fast or faster (us, tile_kernel and staged: 5800 x 5800, 11000 tiles at 20 % kept, 56.7 and 56.8; 8000 x 8000 at 20 %
+// 107 and 110; 72 M elements of convolutions, SGD, 67.5 and 68.0).  Up to kStagedRound tiles one record a workgroup: the launch is
+// one round, and smaller tiles are over sooner (1448 x 1448, 540 tiles: 4.37 us, 4.67 with twice the weight); above it two
+// (2048 x 2048, 1081 tiles: 6.97 and 6.15).  A single layer, whose tiles are cut here, takes what makes it one round of the
+// device, or, where that needs more than kStagedSegs segments, twice the default weight (2896 x 2896 in tiles of
+// 4, 8 and 11 segments: 12.6, 12.3 and 10.4 us, the last one round).
+constexpr int64_t kStagedMost = 10000;
+constexpr int kStagedRound = 700;
+
+struct StagedLaunch {
+    LaunchSet ls;
+    int merge;
+    int64_t wgs;
+};
+
+static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
+{
+    const int64_t limit = knob(SAMO_KNOB_STAGED_TILES, (int)kStagedMost);
+    const bool sparse = ls.keep < (float)kSparseKeep;            // a plan's tiles have twice the weight there
+    out->ls = ls;
+    out->merge = 1;
+    if (ls.layers) {
+        if (ls.wgs > (sparse ? limit / 2 : limit)) return false;
+        if (ls.wgs > kStagedRound && !sparse && 2 * ls.max_segs <= kStagedLdsSegs) out->merge = 2;
+    } else {
+        if (!ls.one.seg_ptr || ls.one.n <= 0 || knob(SAMO_KNOB_TILE_COST, 0) > 0) return false;
+        const int64_t nseg = ceil_div(ls.one.n, (int64_t)kSeg);
+        const double per_seg = (double)kSegCost + (double)kNnzCost * (double)kSeg * ((double)ls.one.nnz / (double)ls.one.n);
+        if ((double)nseg * per_seg > (double)limit * (double)kTileCost) return false;
+        int segs = (int)((double)kTileCost / per_seg + 0.5);
+        if (segs < 1) segs = 1;
+        if (nseg > (int64_t)segs * kStagedRound) {
+            const int64_t one_round = ceil_div(nseg, (int64_t)kStagedSlots);
+            const int heavy = (int)(2.0 * (double)kTileCost / per_seg + 0.5);
+            if (one_round > kStagedSegs) segs = heavy < kStagedSegs ? heavy : kStagedSegs;
+            else if (one_round > segs) segs = (int)one_round;
+        }
+        out->ls.segs_per_tile = out->ls.max_segs = segs;
+        out->ls.wgs = ceil_div(nseg, (int64_t)segs);
+    }
+    out->wgs = ceil_div(out->ls.wgs, (int64_t)out->merge);
+    return out->ls.max_segs * out->merge <= kStagedLdsSegs;
+}
+
+#define SAMO_LAUNCH_STAGED(O)                                                                                     \
+    (ls.layers ? staged_kernel<O, true> : staged_kernel<O, false>)<<<dim3((unsigned)st.wgs), dim3(kStagedThreads), st.ls.max_segs * st.merge * kSeg * 4, s>>>(st.ls, st.merge, inv_scale, k, guard)
 #define SAMO_LAUNCH_TILE(M, G, O)                                                                          \
     tile_kernel<M, G, O, kTileThreads><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)
 
@@ -1172,7 +1365,11 @@ hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls, float i
     const int static_lds = mode == kModeStep && gsrc == kGradDense ? kTileThreads * 4 * 6 : 32;
     const int pad = tile_lds_request(mode == kModeDecompress ? occ_tile_decompress(ls.keep) : occ_tile_step(gsrc, opt, ls.keep),
                                      static_lds, ls.max_segs * kSeg * 2);
-    if (mode == kModeDecompress) {
+    StagedLaunch st;
+    if (mode == kModeStep && gsrc == kGradDense && staged_launch(ls, &st)) {
+        if (opt == kOptAdam) SAMO_LAUNCH_STAGED(kOptAdam);
+        else SAMO_LAUNCH_STAGED(kOptSgd);
+    } else if (mode == kModeDecompress) {
         tile_kernel<kModeDecompress, kGradDense, kOptAdam, kExpandThreads><<<dim3((unsigned)ls.wgs), dim3(kExpandThreads), pad, s>>>(ls, inv_scale, k,
                                                                                                                           guard);
     } else if (opt == kOptAdam) {

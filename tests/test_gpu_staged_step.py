@@ -1,0 +1,108 @@
+"""The fused step of short launches (staged_kernel) against the kernel of the others (SAMO_KNOB_STAGED_TILES = 0), which the
+full-size tests hold to the oracle: the same arithmetic in both, so the same bits.  At the edges of its dispatch: one and two tile
+records to a workgroup, records that end a layer, a single layer cut for one round of the device and beyond; tiles whose kept
+elements exceed a workgroup's 512 lanes, ragged ends, layers with nothing and with everything kept, unpruned layers."""
+import pytest
+import torch
+
+import paper_2302_05045_amd as samo
+import samo_inputs as si
+from gpu_util import DEV, INV
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(n, keep, seed, dense=False):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rand = lambda k: torch.rand(k, generator=gen, device=DEV)
+    mask = (rand(n) < keep).to(torch.uint8)
+    if keep > 0 and n > 40000:                       # a stretch ten times denser than the rest
+        mask[20000:30000] = (rand(10000) < min(1.0, 10 * keep)).to(torch.uint8)
+    ix = samo.samo_build_index(mask) if not dense else None
+    nnz = n if dense else ix.nnz
+    s = dict(n=n, idx=None if dense else ix.idx, seg_ptr=None if dense else ix.seg_ptr, p=rand(nnz) - 0.5, m=rand(nnz) - 0.5,
+             v=rand(nnz), w=torch.full((n,), float("nan"), dtype=torch.float16, device=DEV), g=((rand(n) - 0.5) * 1024).half())
+    return s
+
+
+def _copy(s):
+    return {k: x.clone() if isinstance(x, torch.Tensor) and k in "pmvw" else x for k, x in s.items()}
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        for name in "pmvw":
+            assert torch.equal(x[name].view(torch.int16 if name == "w" else torch.int32),
+                               y[name].view(torch.int16 if name == "w" else torch.int32)), (x["n"], name)
+
+
+def _run_plan(layers, opt, guard_from=None):
+    plan = samo.Plan([samo.Layer(s["n"], s["idx"], s["seg_ptr"], s["p"], s["m"], s["v"], s["w"], s["g"], None, None) for s in layers])
+    guard = None
+    if guard_from is not None:
+        stats = samo.GradStats(plan)
+        plan.samo_grad_stats_batched(0, INV, stats)
+        guard = stats.guard(guard_from, True)
+    if opt == "adam":
+        plan.samo_fused_step_batched(INV, samo.adam_cfg(3, **si.ADAM), guard)
+    else:
+        plan.samo_fused_sgd_step_batched(INV, samo.sgd_cfg(1e-3, 0.9), guard)
+
+
+MODELS = {
+    # under 700 records: one to a workgroup
+    "few": [(5, .5, False), (7, 0., False), (1024 * 5 + 3, .1, False), (70001, .3, False), (40960, 1., False), (3000, 1., True)],
+    # more: two to a workgroup, odd counts of records in a layer, so that workgroups straddle layers
+    "many": [(1_500_007, .1, False), (1024 * 4, .1, False), (1024 * 13 + 8, .5, False), (6000, 1., True), (900_001, .2, False),
+             (33333, 0., False), (1_300_003, .12, False), (17, 1., False)],
+    # tiles of twice the weight
+    "sparse": [(2_000_003, .03, False), (500_000, .05, False), (9, 1., False)],
+}
+
+
+@pytest.mark.parametrize("opt", ["adam", "sgd"])
+@pytest.mark.parametrize("model", list(MODELS))
+def test_plan_step_has_the_bits_of_the_long_launches_kernel(model, opt):
+    layers = [_layer(n, keep, 7 * i + len(model), dense) for i, (n, keep, dense) in enumerate(MODELS[model])]
+    other = [_copy(s) for s in layers]
+    _run_plan(layers, opt)
+    samo.samo_debug_set(samo.KNOB_STAGED_TILES, 0)
+    try:
+        _run_plan(other, opt)
+    finally:
+        samo.samo_debug_set(samo.KNOB_STAGED_TILES)
+    _same(layers, other)
+
+
+def test_guarded_step():
+    layers = [_layer(200_003, .1, 3), _layer(5000, 1., 4, dense=True)]
+    other, before = [_copy(s) for s in layers], [_copy(s) for s in layers]
+    _run_plan(layers, "adam", guard_from=0.5)        # clipped
+    samo.samo_debug_set(samo.KNOB_STAGED_TILES, 0)
+    try:
+        _run_plan(other, "adam", guard_from=0.5)
+    finally:
+        samo.samo_debug_set(samo.KNOB_STAGED_TILES)
+    _same(layers, other)
+    bad = [_copy(s) for s in before]
+    bad[0]["g"] = before[0]["g"].clone()
+    bad[0]["g"][int(bad[0]["idx"][17])] = float("inf")
+    _run_plan(bad, "adam", guard_from=0.5)           # skipped: nothing is written
+    _same(bad, before)
+
+
+@pytest.mark.parametrize("n,keep", [(1, 1.), (1023, .5), (300 * 500, .1), (1024 * 4 * 700 - 1, .1), (1024 * 4 * 700 + 5, .1), (2048 * 2048, .2),
+                                    (10 * 1024 * 1024 - 7, .1), (10 * 1024 * 1024 + 9, .1), (2900 * 2904, .03), (600 * 1024, 1.)])
+def test_single_layer_step_has_the_bits_of_the_long_launches_kernel(n, keep):
+    s = _layer(n, keep, n % 1000)
+    o = _copy(s)
+    step = lambda x: samo.samo_fused_step(x["g"], x["w"], x["idx"], x["seg_ptr"], x["p"], x["m"], x["v"], INV, samo.adam_cfg(2, **si.ADAM))
+    sgd = lambda x: samo.samo_fused_sgd_step(x["g"], x["w"], x["idx"], x["seg_ptr"], x["p"], x["m"], INV, samo.sgd_cfg(1e-3, 0.9))
+    for f in (step, sgd):
+        f(s)
+        samo.samo_debug_set(samo.KNOB_STAGED_TILES, 0)
+        try:
+            f(o)
+        finally:
+            samo.samo_debug_set(samo.KNOB_STAGED_TILES)
+        _same([s], [o])

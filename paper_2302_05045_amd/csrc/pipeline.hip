@@ -107,6 +107,28 @@ __device__ __forceinline__ float guard_coef(const GuardK &gd, bool *skip)
     return coef;
 }
 
+// A layer of a plan, and a record, by way of constant memory: pointers read from there the compiler takes for pointers to
+// global memory.  Read from the table as it is they are generic, every access through them is a flat instruction, and
+// whoever waits for LDS waits for all of those as well.
+#define SAMO_CONSTANT __attribute__((address_space(4)))
+__device__ __forceinline__ samo_layer constant_layer(const samo_layer *layer)
+{
+    const SAMO_CONSTANT samo_layer *C = (const SAMO_CONSTANT samo_layer *)layer;
+    samo_layer L;
+    L.n = C->n; L.nnz = C->nnz; L.idx = C->idx; L.seg_ptr = C->seg_ptr; L.p = C->p; L.m = C->m; L.v = C->v; L.w = C->w; L.g = C->g;
+    L.gc = C->gc; L.gc16 = C->gc16; L.w32 = C->w32; L.g32 = C->g32;
+    return L;
+}
+
+__device__ __forceinline__ WgRec constant_rec(const WgRec *rec)
+{
+    const uint64_t q = *(const SAMO_CONSTANT uint64_t *)rec;
+    WgRec r;
+    r.layer = (int32_t)(uint32_t)q;
+    r.local = (uint32_t)(q >> 32);
+    return r;
+}
+
 __device__ __forceinline__ void pick_work(const LaunchSet &ls, samo_layer *L, int64_t *local)
 {
     if (ls.layers) {
@@ -119,12 +141,17 @@ __device__ __forceinline__ void pick_work(const LaunchSet &ls, samo_layer *L, in
     }
 }
 
-// The tile of this workgroup: segments [*s0, *s0 + *nsegs) of *L; *nsegs may be 0 (nothing to do).
+// The tile of this workgroup: segments [*s0, *s0 + *nsegs) of *L; *nsegs may be 0 (nothing to do).  GLOBAL: through constant_layer.
+// The kernels that gain by that take it: the step on the dense gradient (2.7B model 2712 -> 2680 us, the 6.7B layers with the embedding
+// 1711 -> 1703; without the bound of 64 registers at tile_kernel 1735), the single-precision step (1226 -> 1219), the expansion
+// (0.7 % on an 85 M element model).  The step on the fp16 message lost 0.4 to 2 %, the flat kernels gained nothing.
+template <bool GLOBAL>
 __device__ __forceinline__ void pick_tile(const LaunchSet &ls, samo_layer *L, int *s0, int *nsegs)
 {
     if (ls.layers) {
-        const WgRec r = ls.recs[blockIdx.x];
-        *L = ls.layers[r.layer];
+        const WgRec r = GLOBAL ? constant_rec(ls.recs + blockIdx.x) : ls.recs[blockIdx.x];
+        if (GLOBAL) *L = constant_layer(ls.layers + r.layer);
+        else *L = ls.layers[r.layer];
         *s0 = (int)(r.local & ((1u << kRecSegShift) - 1u));
         *nsegs = (int)(r.local >> kRecSegShift);
     } else {
@@ -438,7 +465,7 @@ __device__ __forceinline__ void sparse_tile_dense_grad(const samo_layer &L, int 
 }
 
 template <int MODE, int GSRC, int OPT, int T>
-__global__ void __launch_bounds__(T)
+__global__ void __launch_bounds__(T, 8)
 tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guard)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_image[];      // ls.max_segs segments of fp16 (and the occupancy padding)
@@ -451,7 +478,7 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
     if (skip) return;                         // uniform: every workgroup of the launch takes it
     samo_layer L;
     int s0, nsegs;
-    pick_tile(ls, &L, &s0, &nsegs);
+    pick_tile<kExchange || MODE == kModeDecompress>(ls, &L, &s0, &nsegs);
     if (nsegs > ls.max_segs) nsegs = ls.max_segs;   // a record never holds more; the image must not be overrun whatever it says
     if (nsegs <= 0) return;                   // uniform per workgroup: a record without segments
     const int64_t base = (int64_t)s0 * kSeg;
@@ -480,27 +507,6 @@ constexpr int kStagedThreads = 512;
 constexpr int kStagedSlots = 1024;            // workgroups of that size the device holds at a time
 constexpr int kStagedSegs = 10;               // segments of a tile with which four workgroups still share a compute unit's LDS
 constexpr int kStagedLdsSegs = 13;            // ... and with which three do
-
-// A layer of a plan by way of constant memory: whose pointers the compiler takes for pointers to global memory (loads of
-// them are global, not flat, instructions, which would also be waited for by every LDS access).
-#define SAMO_CONSTANT __attribute__((address_space(4)))
-__device__ __forceinline__ samo_layer constant_layer(const samo_layer *layer)
-{
-    const SAMO_CONSTANT samo_layer *C = (const SAMO_CONSTANT samo_layer *)layer;
-    samo_layer L;
-    L.n = C->n; L.nnz = C->nnz; L.idx = C->idx; L.seg_ptr = C->seg_ptr; L.p = C->p; L.m = C->m; L.v = C->v; L.w = C->w; L.g = C->g;
-    L.gc = nullptr; L.gc16 = nullptr; L.w32 = nullptr; L.g32 = nullptr;
-    return L;
-}
-
-__device__ __forceinline__ WgRec constant_rec(const WgRec *rec)
-{
-    const uint64_t q = *(const SAMO_CONSTANT uint64_t *)rec;
-    WgRec r;
-    r.layer = (int32_t)(uint32_t)q;
-    r.local = (uint32_t)(q >> 32);
-    return r;
-}
 
 template <int OPT>
 __device__ __forceinline__ void staged_tile(const samo_layer &L, int s0, int nsegs, int64_t base, int len, float inv_scale, float coef,
@@ -714,7 +720,7 @@ tile_fp32_kernel(const LaunchSet ls, float factor, const OptK k, const GuardK gu
     if (skip) return;
     samo_layer L;
     int s0, nsegs;
-    pick_tile(ls, &L, &s0, &nsegs);
+    pick_tile<true>(ls, &L, &s0, &nsegs);
     if (nsegs > ls.max_segs) nsegs = ls.max_segs;
     if (nsegs <= 0) return;
     const int64_t base = (int64_t)s0 * kSeg;

@@ -1297,11 +1297,12 @@ static int occ_flat_gather(int out, int src, float keep, bool with_stats)
     // masks are narrow (10 at 5 % kept, 14-15 at 10 %, 22-24 at 20 %: two waves off cost 5-8 %).
     float t = 5.7f + 87.f * keep;
     if (t < 10.f) t = 10.f;
-    // the statistics add an arithmetic tail during which a wave has no memory traffic in flight:
-    // more waves have to be resident for the same traffic in flight, most when the wave also
-    // has a store to retire (optima: 15 / 24 / 28 with the fp16 store, 11 / 16 / 27 without; 24 on the row-clustered 6.7B model, whose
-    // dense embedding lifts its kept fraction to 0.13)
-    if (with_stats) t *= (out == kOutNone) ? 1.3f : 1.4f;
+    // the statistics add an arithmetic tail during which a wave has no memory traffic in flight: more waves have to be
+    // resident for the same traffic in flight, most when the wave also has an fp16 store to retire (optima there 15 / 24 / 28).
+    // With the fp32 store, or none, 9-11 / 14-16 / 26, followed by whatever else a step does (us with 1.4 and 1.12 times the above: three
+    // passes over the 1.3B model 1643 and 1615, 16 of its layers at 95 / 80 % pruning 854 and 839, 1670 and 1633; the clipped step, 1.3
+    // and 1.12: 963 and 956, 1665 and 1658)
+    if (with_stats) t *= (out == kOutF16) ? 1.4f : 1.12f;
     return t > 30.f ? 0 : (int)(t + 0.5f);
 }
 

@@ -810,6 +810,15 @@ gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, Stat
     const int cnt = (nnz - i >= 4) ? 4 : (nnz - i > 0 ? (int)(nnz - i) : 0);
     uint16_t hb[4] = {0, 0, 0, 0};
     float fv[4] = {0.f, 0.f, 0.f, 0.f};
+    uint16_t old[4] = {0, 0, 0, 0};                       // requested first: they travel beside the positions and the gather
+    if (OUT == kOutF16 && accumulate) {
+        if (cnt == 4) {
+            const uint2 q = *reinterpret_cast<const uint2 *>(L.gc16 + i);
+            old[0] = (uint16_t)q.x; old[1] = (uint16_t)(q.x >> 16); old[2] = (uint16_t)q.y; old[3] = (uint16_t)(q.y >> 16);
+        } else {
+            for (int e = 0; e < cnt; ++e) old[e] = L.gc16[i + e];
+        }
+    }
     if (src == kGradC32 || (src == kGradDense32 && identity)) {
         const float *S = (src == kGradC32) ? L.gc : L.g32;
         if (cnt == 4) {
@@ -869,13 +878,6 @@ gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, Stat
     }
     if (OUT == kOutF16) {
         if (accumulate) {                                  // one correctly rounded half addition
-            uint16_t old[4] = {0, 0, 0, 0};
-            if (cnt == 4) {
-                const uint2 q = *reinterpret_cast<const uint2 *>(L.gc16 + i);
-                old[0] = (uint16_t)q.x; old[1] = (uint16_t)(q.x >> 16); old[2] = (uint16_t)q.y; old[3] = (uint16_t)(q.y >> 16);
-            } else {
-                for (int e = 0; e < cnt; ++e) old[e] = L.gc16[i + e];
-            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const _Float16 sum = __builtin_bit_cast(_Float16, old[e]) + __builtin_bit_cast(_Float16, hb[e]);

@@ -924,12 +924,35 @@ gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, Stat
 constexpr int kStatRun = 8;
 constexpr int kStatAhead = 8;        // records whose loads are in flight together
 
+// The value of lane l ^ MASK.
+template <int MASK>
+__device__ __forceinline__ double xor_f64(double x)
+{
+    return __hiloint2double(__shfl_xor(__double2hiint(x), MASK, 64), __shfl_xor(__double2loint(x), MASK, 64));
+}
+
+// One level of eight sums over the lanes at once: of 2 K records a lane holds, it keeps the K whose numbers have the bit that
+// its own lane number has, and adds its partner's.  After three levels lane l holds record l % 8; three more sum over the wave.  Every
+// record's additions are those of wave_sum_f64, a balanced tree over neighbouring lanes, in 60 instructions for the eight
+// of them where eight separate sums took 160 (16 layers of the 2.7B model at 80 % pruning, 0.5 GB: 113 -> 108 us).
+template <int K, int MASK>
+__device__ __forceinline__ void sum_records(double *part, int lane)
+{
+    const bool upper = (lane & MASK) != 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double keep = upper ? part[2 * k + 1] : part[2 * k], give = upper ? part[2 * k] : part[2 * k + 1];
+        part[k] = keep + xor_f64<MASK>(give);
+    }
+}
+
 template <int SRC>
 __global__ void __launch_bounds__(kFlatThreads)
 stats_compressed_kernel(const LaunchSet ls, float inv_scale, StatPartial *__restrict__ partials)
 {
     static_assert(SRC == kGradC16 || SRC == kGradC32, "compressed sources only");
     static_assert(kStatRun <= kFlatThreads && kStatRun % kStatAhead == 0, "lane k keeps partial k");
+    static_assert(kStatAhead == 8, "sum_records takes eight records together");
     constexpr int kWords = (SRC == kGradC32) ? 4 : 2;     // 32-bit words of a lane's four elements
     const unsigned total = (unsigned)ls.wgs;              // records, and workgroups of the launch this one stands for
     const unsigned per_xcd = (total + 7u) / 8u;
@@ -937,7 +960,6 @@ stats_compressed_kernel(const LaunchSet ls, float inv_scale, StatPartial *__rest
     const unsigned base = (blockIdx.x >> 3) * kStatRun;   // first slot of the wave within that eighth
     double mine_ss = 0.0;
     int mine_bad = 0;
-    bool have = false;
     typedef const __attribute__((address_space(1))) uint32_t *GlobalWords;     // the arrays live in device memory
     typedef const __attribute__((address_space(1))) uint16_t *GlobalHalves;
     typedef unsigned int Words2 __attribute__((ext_vector_type(2)));
@@ -994,6 +1016,8 @@ stats_compressed_kernel(const LaunchSet ls, float inv_scale, StatPartial *__rest
                 }
             }
         }
+        double part[kStatAhead];
+        unsigned bads = 0u;
 #pragma unroll
         for (int u = 0; u < kStatAhead; ++u) {
             double ss = 0.0;
@@ -1008,12 +1032,20 @@ stats_compressed_kernel(const LaunchSet ls, float inv_scale, StatPartial *__rest
                     bad |= is_nonfinite(x) ? 1 : 0;
                 }
             }
-            ss = wave_sum_f64(ss);
-            bad = __any(bad) ? 1 : 0;
-            if ((int)threadIdx.x == r0 + u) { mine_ss = ss; mine_bad = bad; have = live[u]; }
+            part[u] = ss;
+            if (__any(bad)) bads |= 1u << u;
         }
+        const int lane = threadIdx.x;
+        sum_records<4, 1>(part, lane);
+        sum_records<2, 2>(part, lane);
+        sum_records<1, 4>(part, lane);
+        double ss = part[0];
+        ss += xor_f64<8>(ss);
+        ss += xor_f64<16>(ss);
+        ss += xor_f64<32>(ss);
+        if (lane / kStatAhead * kStatAhead == r0) { mine_ss = ss; mine_bad = (bads >> (lane & 7)) & 1; }
     }
-    if (have) {
+    if (threadIdx.x < kStatRun && base + threadIdx.x < per_xcd && run + 8u * (base + threadIdx.x) < total) {
         const unsigned slot = run * per_xcd + base + threadIdx.x;
         partials[slot].sum_squares = mine_ss;
         partials[slot].nonfinite = mine_bad;

@@ -502,7 +502,10 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
 // (record, layer, bounds, positions, gradient at the positions) and the starting of workgroups.  Here the whole gradient of the
 // tile is requested as 16-byte vectors as soon as the layer is known, beside the bounds, and waits in LDS for the positions:
 // one trip less; compressed elements go one to a lane, so that few of the workgroup's eight waves idle; and a workgroup takes two
-// consecutive tile records where a launch has more than kStagedRound of them.  Four workgroups share a compute unit (64
+// consecutive tile records where a launch has more than kStagedRound of them.  Where under 7 % are kept (WHOLE = false) the gradient
+// is read at the kept positions after all, two elements to a lane: the whole of it would be the larger part of the traffic (20 layers
+// of 1 M elements, 0.5 / 3 / 6 % kept: 16.9, 20.2 and 22.7 us with it, 10.0, 15.3 and 18.9 without; tile_kernel 14.0, 19.1, 23.4).
+// Through the caches, several kept positions share a line (past them: 13.3, 17.8, 22.4).  Four workgroups share a compute unit (64
 // registers, up to 40 KB of LDS).  In us, tile_kernel and this one: one layer of 1024 x 1024 (10 % kept) 4.5 and 3.4, 2048 x 2048 8.1
 // and 6.2, 4096 x 2048 13.1 and 10.4; 18 convolutions (11.5 M elements, SGD) 16.1 and 14.3; a 12.6 M element GPT at 15 % kept
 // 21.0 and 19.7.  Tried instead: persistent workgroups that request the next tile while they step one (16.3 to 22 us for the
@@ -513,17 +516,17 @@ constexpr int kStagedSlots = 1024;            // workgroups of that size the dev
 constexpr int kStagedSegs = 10;               // segments of a tile with which four workgroups still share a compute unit's LDS
 constexpr int kStagedLdsSegs = 13;            // ... and with which three do
 
-template <int OPT>
+template <int OPT, bool WHOLE>
 __device__ __forceinline__ void staged_tile(const samo_layer &L, int s0, int nsegs, int64_t base, int len, float inv_scale, float coef,
                                             const OptK &k, uint16_t *lds_w, uint16_t *lds_g)
 {
-    constexpr int T = kStagedThreads, kHeld = 2, kElems = 1;
+    constexpr int T = kStagedThreads, kHeld = 2, kElems = WHOLE ? 1 : 2;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));             // what follows from it is formed anew for every tile, not kept in registers
     const uint16_t *__restrict__ G = L.g + base;
     const int nvec = len / 8;
     u32x4 held[kHeld];                        // loads at clamped places, none under a condition: nothing waits for them before their use
-    if (nvec > 0) {
+    if (WHOLE && nvec > 0) {
 #pragma unroll
         for (int u = 0; u < kHeld; ++u) {
             const int o = tid + u * T < nvec ? tid + u * T : nvec - 1;
@@ -550,17 +553,19 @@ __device__ __forceinline__ void staged_tile(const samo_layer &L, int s0, int nse
     uint4 *w4 = reinterpret_cast<uint4 *>(lds_w);
 #pragma unroll 1
     for (int o = tid; o < (len + 7) / 8; o += T) w4[o] = make_uint4(0u, 0u, 0u, 0u);
-    u32x4 *g4 = reinterpret_cast<u32x4 *>(lds_g);
+    if (WHOLE) {
+        u32x4 *g4 = reinterpret_cast<u32x4 *>(lds_g);
 #pragma unroll
-    for (int u = 0; u < kHeld; ++u)
-        if (tid + u * T < nvec) g4[tid + u * T] = held[u];
+        for (int u = 0; u < kHeld; ++u)
+            if (tid + u * T < nvec) g4[tid + u * T] = held[u];
 #pragma unroll 1
-    for (int o = tid + kHeld * T; o < nvec; o += T) g4[o] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(G) + o);
+        for (int o = tid + kHeld * T; o < nvec; o += T) g4[o] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(G) + o);
 #pragma unroll 1
-    for (int e = nvec * 8 + tid; e < len; e += T) lds_g[e] = G[e];
+        for (int e = nvec * 8 + tid; e < len; e += T) lds_g[e] = G[e];
+    }
     __syncthreads();
     auto update = [&](int r, int jr, float pr, float mr, float vr) {
-        opt_update<OPT>(pr, mr, vr, (half_bits_to_float(lds_g[jr - ibase]) * inv_scale) * coef, k);
+        opt_update<OPT>(pr, mr, vr, (half_bits_to_float(WHOLE ? lds_g[jr - ibase] : G[jr - ibase]) * inv_scale) * coef, k);
         L.p[r] = pr;
         L.m[r] = mr;
         if (OPT == kOptAdam) L.v[r] = vr;
@@ -581,7 +586,7 @@ __device__ __forceinline__ void staged_tile(const samo_layer &L, int s0, int nse
 
 // `merge` consecutive records to a workgroup; those of one layer that follow each other are one tile of at most
 // merge * ls.max_segs segments.  A single layer: merge is 1, segs_per_tile says how large its tiles are.
-template <int OPT, bool PLAN>
+template <int OPT, bool PLAN, bool WHOLE>
 __global__ void __launch_bounds__(kStagedThreads, 8)
 staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, const GuardK guard)
 {
@@ -596,7 +601,7 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
         first_rec = *(const SAMO_CONSTANT uint64_t *)(ls.recs + first);       // the grid has no workgroup without a record
         asm volatile("" ::"s"(first_rec));
     }
-    uint16_t *lds_w = reinterpret_cast<uint16_t *>(lds_image);       // the tile's new weights, and its gradient
+    uint16_t *lds_w = reinterpret_cast<uint16_t *>(lds_image);       // the tile's new weights, and with WHOLE its gradient
     uint16_t *lds_g = lds_w + most * kSeg;
     bool skip;
     const float coef = guard_coef(guard, &skip);
@@ -606,7 +611,7 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
         const int64_t base = (int64_t)s0 * kSeg, rest = L.n - base;
         const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
         if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads>(L, base, len, inv_scale, coef, k);
-        else staged_tile<OPT>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
+        else staged_tile<OPT, WHOLE>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
     };
     if (!PLAN) {
         const int64_t nseg = (ls.one.n + kSeg - 1) / kSeg, s0 = first * ls.segs_per_tile;
@@ -1373,6 +1378,7 @@ struct StagedLaunch {
     LaunchSet ls;
     int merge;
     int64_t wgs;
+    bool whole;      // the tile's gradient is read whole
 };
 
 static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
@@ -1381,6 +1387,7 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
     const bool sparse = ls.keep < (float)kSparseKeep;            // a plan's tiles have twice the weight there
     out->ls = ls;
     out->merge = 1;
+    out->whole = !sparse;
     if (ls.layers) {
         if (ls.wgs > (sparse ? limit / 2 : limit)) return false;
         if (ls.wgs > kStagedRound && !sparse && 2 * ls.max_segs <= kStagedLdsSegs) out->merge = 2;
@@ -1405,7 +1412,9 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
 }
 
 #define SAMO_LAUNCH_STAGED(O)                                                                                     \
-    (ls.layers ? staged_kernel<O, true> : staged_kernel<O, false>)<<<dim3((unsigned)st.wgs), dim3(kStagedThreads), st.ls.max_segs * st.merge * kSeg * 4, s>>>(st.ls, st.merge, inv_scale, k, guard)
+    (st.whole ? (ls.layers ? staged_kernel<O, true, true> : staged_kernel<O, false, true>)                        \
+              : (ls.layers ? staged_kernel<O, true, false> : staged_kernel<O, false, false>))                     \
+        <<<dim3((unsigned)st.wgs), dim3(kStagedThreads), st.ls.max_segs * st.merge * kSeg * (st.whole ? 4 : 2), s>>>(st.ls, st.merge, inv_scale, k, guard)
 #define SAMO_LAUNCH_TILE(M, G, O)                                                                          \
     tile_kernel<M, G, O, kTileThreads><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)
 

@@ -55,8 +55,9 @@ MODELS = {
     # more: two to a workgroup, odd counts of records in a layer, so that workgroups straddle layers
     "many": [(1_500_007, .1, False), (1024 * 4, .1, False), (1024 * 13 + 8, .5, False), (6000, 1., True), (900_001, .2, False),
              (33333, 0., False), (1_300_003, .12, False), (17, 1., False)],
-    # tiles of twice the weight
+    # tiles of twice the weight, the gradient read at the kept positions
     "sparse": [(2_000_003, .03, False), (500_000, .05, False), (9, 1., False)],
+    "sparser": [(300_005, .0005, False), (70_000, 0., False), (700_001, .065, False), (5000, 1., True)],
 }
 
 
@@ -92,7 +93,8 @@ def test_guarded_step():
 
 
 @pytest.mark.parametrize("n,keep", [(1, 1.), (1023, .5), (300 * 500, .1), (1024 * 4 * 700 - 1, .1), (1024 * 4 * 700 + 5, .1), (2048 * 2048, .2),
-                                    (10 * 1024 * 1024 - 7, .1), (10 * 1024 * 1024 + 9, .1), (2900 * 2904, .03), (600 * 1024, 1.)])
+                                    (10 * 1024 * 1024 - 7, .1), (10 * 1024 * 1024 + 9, .1), (2900 * 2904, .03), (600 * 1024, 1.),
+                                    (40_003, .06), (3_000_001, .001), (12_000_007, .069), (1_000_000, 0.)])
 def test_single_layer_step_has_the_bits_of_the_long_launches_kernel(n, keep):
     s = _layer(n, keep, n % 1000)
     o = _copy(s)
@@ -106,3 +108,39 @@ def test_single_layer_step_has_the_bits_of_the_long_launches_kernel(n, keep):
         finally:
             samo.samo_debug_set(samo.KNOB_STAGED_TILES)
         _same([s], [o])
+
+
+def _passes(fn, count):
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
+    for _ in range(count):
+        fn()
+    end.record()
+    torch.cuda.synchronize()
+    return start.elapsed_time(end) / count
+
+
+def test_a_sparse_model_is_stepped_no_slower_than_by_the_long_launches_kernel():
+    """40 M elements, 0.5 % kept: with the whole gradient read the short launches' kernel took 1.25 times the other's time; reading
+    it at the kept positions 0.66 times.  Medians of both in turn."""
+    layers = [_layer(1 << 20, .005, i) for i in range(40)]
+    plan = samo.Plan([samo.Layer(s["n"], s["idx"], s["seg_ptr"], s["p"], s["m"], s["v"], s["w"], s["g"], None, None) for s in layers])
+    cfg = samo.adam_cfg(3, **si.ADAM)
+    graphs = []
+    for tiles in (samo.KNOB_DEFAULT, 0):                # captured: the host's part is the same in both
+        samo.samo_debug_set(samo.KNOB_STAGED_TILES, tiles)
+        try:
+            plan.samo_fused_step_batched(INV, cfg)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                for _ in range(10):
+                    plan.samo_fused_step_batched(INV, cfg)
+        finally:
+            samo.samo_debug_set(samo.KNOB_STAGED_TILES)
+        graphs.append(graph)
+    times = [[], []]
+    for _ in range(9):
+        for got, graph in zip(times, graphs):
+            got.append(_passes(graph.replay, 10))
+    short, long = (sorted(t)[4] for t in times)
+    assert short <= 1.05 * long, (short, long)

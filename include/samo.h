@@ -314,7 +314,8 @@ typedef struct {
     int64_t n_total, nnz_total;   /* sums over the descriptors as given */
     int32_t num_layers;
     uint32_t buffers;       /* bits 0-8: which arrays every layer of the plan provides; bits 16-23: the most
-                               segments one tile of the plan holds (sizes the tile kernels' LDS request) */
+                               segments one tile of the plan holds (sizes the tile kernels' LDS request);
+                               bits 24-31: what its pruned layers keep (chooses between kernels) */
 } samo_plan;
 
 samo_status samo_plan_workspace_bytes(const samo_layer *h_layers, int32_t num_layers, size_t *bytes);

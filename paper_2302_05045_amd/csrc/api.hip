@@ -26,7 +26,8 @@ namespace {
 enum : uint32_t {
     kHasP = 1u << 0, kHasM = 1u << 1, kHasV = 1u << 2, kHasW = 1u << 3, kHasG = 1u << 4, kHasGc = 1u << 5,
     kHasGc16 = 1u << 6, kHasW32 = 1u << 7, kHasG32 = 1u << 8, kHasAll = (1u << 9) - 1u,
-    kPlanSegsShift = 16      // bits 16-23 of samo_plan::buffers: the most segments a tile of the plan holds
+    kPlanSegsShift = 16,     // bits 16-23 of samo_plan::buffers: the most segments a tile of the plan holds
+    kPlanKeptShift = 24      // bits 24-31: 0 for a plan without pruned layers, else 1 + 254 times what those keep
 };
 inline bool has(const samo_plan *plan, uint32_t bits) { return (plan->buffers & bits) == bits; }
 
@@ -348,6 +349,8 @@ LaunchSet single(const samo_layer &L, int64_t wgs)
     ls.wgs = wgs;
     ls.segs_per_tile = 1;
     ls.keep = L.n > 0 ? (float)((double)L.nnz / (double)L.n) : 1.f;
+    ls.kept = L.seg_ptr ? ls.keep : -1.f;
+    ls.num_layers = 1;
     ls.max_segs = 1;
     return ls;
 }
@@ -622,7 +625,7 @@ inline size_t round_up_256(size_t x) { return (x + 255u) & ~(size_t)255u; }
 
 // Sizes of a plan's tables; validates the descriptors when `check` is set.
 struct PlanSizes {
-    int64_t ntiles = 0, nchunks = 0, n_total = 0, nnz_total = 0, tile_cost = kTileCost;
+    int64_t ntiles = 0, nchunks = 0, n_total = 0, nnz_total = 0, n_pruned = 0, nnz_pruned = 0, tile_cost = kTileCost;
     uint32_t buffers = kHasAll;
     size_t off_tile_start = 0, off_chunk_start = 0, off_tiles = 0, off_chunks = 0, bytes = 0;
 };
@@ -657,6 +660,10 @@ samo_status plan_sizes(const samo_layer *h_layers, int32_t num_layers, bool chec
         }
         z.n_total += L.n;
         z.nnz_total += L.nnz;
+        if (L.seg_ptr && L.n > 0) {
+            z.n_pruned += L.n;
+            z.nnz_pruned += L.nnz;
+        }
         z.nchunks += ceil_div(L.nnz, kChunk);
     }
     // one tile weight for the whole plan, by its kept fraction and the width of its dense side; when only
@@ -743,7 +750,8 @@ samo_status samo_plan_init(const samo_layer *h_layers, int32_t num_layers, void 
     plan->n_total = z.n_total;
     plan->nnz_total = z.nnz_total;
     plan->num_layers = num_layers;
-    plan->buffers = z.buffers | ((uint32_t)tile_cost_segs(z.tile_cost) << kPlanSegsShift);
+    const uint32_t kept = z.n_pruned > 0 ? 1u + (uint32_t)(254.0 * (double)z.nnz_pruned / (double)z.n_pruned + 0.5) : 0u;
+    plan->buffers = z.buffers | ((uint32_t)tile_cost_segs(z.tile_cost) << kPlanSegsShift) | (kept << kPlanKeptShift);
     return SAMO_OK;
 }
 
@@ -767,6 +775,9 @@ LaunchSet tiles_of(const samo_plan *plan)
     ls.wgs = plan->num_tiles;
     ls.segs_per_tile = 1;
     ls.keep = plan->n_total > 0 ? (float)((double)plan->nnz_total / (double)plan->n_total) : 1.f;
+    const uint32_t kept = plan->buffers >> kPlanKeptShift;
+    ls.kept = kept > 0 ? (float)(kept - 1u) * (1.f / 254.f) : -1.f;
+    ls.num_layers = plan->num_layers;
     ls.max_segs = (int)((plan->buffers >> kPlanSegsShift) & 0xffu);     // as samo_plan_init cut the tiles (checked at launch)
     return ls;
 }

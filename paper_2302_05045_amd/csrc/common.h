@@ -150,6 +150,8 @@ struct LaunchSet {
     int64_t wgs;
     int segs_per_tile;   // single-layer tile launches: workgroup b owns segments [b * this, (b + 1) * this)
     float keep;          // kept fraction nnz / n of the work (plan average); steers the flat kernels' occupancy target
+    float kept;          // the same of its pruned layers alone; negative: it has none
+    int num_layers;      // layers of the plan
     int max_segs;        // tile launches: segments the workgroups' LDS image holds (no tile of the launch has more)
 };
 // Segments per tile of a single-layer launch, from the layer's average density.

@@ -1373,6 +1373,11 @@ static int occ_flat_step()
 // 4, 8 and 11 segments: 12.6, 12.3 and 10.4 us, the last one round).
 constexpr int64_t kStagedMost = 10000;
 constexpr int kStagedRound = 700;
+// A plan of unpruned layers alone comes here from this many records on and with four or more to a layer, so that a workgroup's two are
+// one tile; two short layers in one workgroup are stepped one after the other (us, tile_kernel and staged: 2000 vectors of 768
+// 10.7 and 13.0, 9000 of them 36.6 and 45.1, 300 of 2560 6.0 and 7.2, 2000 of 4096 40.6 and 38.4, one layer of 1 M elements, SGD,
+// 4.49 and 4.63, of 3 M 13.5 and 13.2, of 8 M 29.9 and 29.0).
+constexpr int64_t kStagedUnpruned = 2900;
 
 struct StagedLaunch {
     LaunchSet ls;
@@ -1390,6 +1395,8 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
     out->whole = !sparse;
     if (ls.layers) {
         if (ls.wgs > (sparse ? limit / 2 : limit)) return false;
+        // unpruned layers alone: nothing to wait for in LDS, one segment a record
+        if (ls.kept < 0.f && (ls.wgs < kStagedUnpruned || ls.wgs < 4 * (int64_t)ls.num_layers)) return false;
         if (ls.wgs > kStagedRound && !sparse && 2 * ls.max_segs <= kStagedLdsSegs) out->merge = 2;
     } else {
         if (!ls.one.seg_ptr || ls.one.n <= 0 || knob(SAMO_KNOB_TILE_COST, 0) > 0) return false;

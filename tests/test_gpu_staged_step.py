@@ -58,6 +58,10 @@ MODELS = {
     # tiles of twice the weight, the gradient read at the kept positions
     "sparse": [(2_000_003, .03, False), (500_000, .05, False), (9, 1., False)],
     "sparser": [(300_005, .0005, False), (70_000, 0., False), (700_001, .065, False), (5000, 1., True)],
+    # unpruned layers alone: too few records, too many layers for their records, neither
+    "vectors": [(768, 1., True)] * 5,
+    "short": [(1025, 1., True), (768, 1., True), (3000, 1., True)] * 500,
+    "unpruned": [(1_000_003, 1., True), (2_000_000, 1., True)],
 }
 
 
@@ -123,7 +127,15 @@ def _passes(fn, count):
 def test_a_sparse_model_is_stepped_no_slower_than_by_the_long_launches_kernel():
     """40 M elements, 0.5 % kept: with the whole gradient read the short launches' kernel took 1.25 times the other's time; reading
     it at the kept positions 0.66 times.  Medians of both in turn."""
-    layers = [_layer(1 << 20, .005, i) for i in range(40)]
+    _not_slower([_layer(1 << 20, .005, i) for i in range(40)])
+
+
+def test_unpruned_vectors_are_stepped_no_slower_than_by_the_long_launches_kernel():
+    """Biases and norm weights in a plan of their own: two records to a workgroup of 512 threads took 1.2 times the other's time."""
+    _not_slower([_layer(768, 1., i, dense=True) for i in range(2000)])
+
+
+def _not_slower(layers):
     plan = samo.Plan([samo.Layer(s["n"], s["idx"], s["seg_ptr"], s["p"], s["m"], s["v"], s["w"], s["g"], None, None) for s in layers])
     cfg = samo.adam_cfg(3, **si.ADAM)
     graphs = []

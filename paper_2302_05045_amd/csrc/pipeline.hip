@@ -147,9 +147,8 @@ __device__ __forceinline__ void pick_work(const LaunchSet &ls, samo_layer *L, in
 }
 
 // The tile of this workgroup: segments [*s0, *s0 + *nsegs) of *L; *nsegs may be 0 (nothing to do).  GLOBAL: through constant_layer.
-// The kernels that gain by that take it: the step on the dense gradient (2.7B model 2712 -> 2680 us, the 6.7B layers with the embedding
-// 1711 -> 1703; without the bound of 64 registers at tile_kernel 1735), the single-precision step (1226 -> 1219), the expansion
-// (0.7 % on an 85 M element model).  The step on the fp16 message lost 0.4 to 2 %, the flat kernels gained nothing.
+// The single-precision step takes it always (1226 -> 1219 us, 5 % where half or everything is kept), the step on the dense gradient and
+// the expansion in plans where it gains (global_access).  The step on the fp16 message lost 0.4 to 2 %, the flat kernels gained nothing.
 template <bool GLOBAL>
 __device__ __forceinline__ void pick_tile(const LaunchSet &ls, samo_layer *L, int *s0, int *nsegs)
 {
@@ -469,7 +468,7 @@ __device__ __forceinline__ void sparse_tile_dense_grad(const samo_layer &L, int 
     for (int e = nvecw * 8 + tid; e < len; e += T) W[e] = lds_w[e];
 }
 
-template <int MODE, int GSRC, int OPT, int T>
+template <int MODE, int GSRC, int OPT, int T, bool GLOBAL>
 __global__ void __launch_bounds__(T, 8)
 tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guard)
 {
@@ -483,7 +482,7 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
     if (skip) return;                         // uniform: every workgroup of the launch takes it
     samo_layer L;
     int s0, nsegs;
-    pick_tile<kExchange || MODE == kModeDecompress>(ls, &L, &s0, &nsegs);
+    pick_tile<GLOBAL>(ls, &L, &s0, &nsegs);
     if (nsegs > ls.max_segs) nsegs = ls.max_segs;   // a record never holds more; the image must not be overrun whatever it says
     if (nsegs <= 0) return;                   // uniform per workgroup: a record without segments
     const int64_t base = (int64_t)s0 * kSeg;
@@ -1318,7 +1317,7 @@ static int tile_lds_request(int target_wgs, int static_bytes, int image_bytes)
     return pad > image_bytes ? pad : image_bytes;
 }
 
-static int occ_tile_step(int gsrc, int opt, float keep)
+static int occ_tile_step(int gsrc, int opt, float keep, float kept)
 {
     // a step that reads the dense gradient keeps whole dense lines in flight: 6 workgroups per CU;
     // with a compressed gradient (half the bytes per workgroup) every wave slot is worth filling at
@@ -1326,7 +1325,11 @@ static int occ_tile_step(int gsrc, int opt, float keep)
     // in-place streams are over half the traffic and 6 is the optimum again (0.74 against 0.68 with 8)
     // (where the model keeps so little that its tiles have twice the weight: 4, and 6 with the compressed gradient)
     const bool sparse = keep < (float)kSparseKeep;
-    if (gsrc == kGradDense) return knob(SAMO_KNOB_OCC_TILE_STEP, sparse ? (opt == kOptSgd ? 3 : 4) : 6);
+    // Adam where the pruned layers keep a fifth and more: 5 (400 M elements, 20 / 25 / 50 / 80 % kept, 5 and 6 workgroups: 642 and 667 us,
+    // 735 and 782, 1239 and 1255, 1842 and 2068; 10 and 15 % 452 and 444, 545 and 543; SGD 533 and 524 at 20 %, 1390 and 1365 at 80 %).  What an unpruned
+    // embedding adds does not count: three 6.7B layers at 11.5 % with theirs 1756 and 1691
+    const int most = opt == kOptAdam && kept >= 0.19f ? 5 : 6;
+    if (gsrc == kGradDense) return knob(SAMO_KNOB_OCC_TILE_STEP, sparse ? (opt == kOptSgd ? 3 : 4) : most);
     return knob(SAMO_KNOB_OCC_TILE_C16, (sparse || keep > 0.15f) ? 6 : 0);
 }
 
@@ -1422,8 +1425,18 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
     (st.whole ? (ls.layers ? staged_kernel<O, true, true> : staged_kernel<O, false, true>)                        \
               : (ls.layers ? staged_kernel<O, true, false> : staged_kernel<O, false, false>))                     \
         <<<dim3((unsigned)st.wgs), dim3(kStagedThreads), st.ls.max_segs * st.merge * kSeg * (st.whole ? 4 : 2), s>>>(st.ls, st.merge, inv_scale, k, guard)
-#define SAMO_LAUNCH_TILE(M, G, O)                                                                          \
-    tile_kernel<M, G, O, kTileThreads><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)
+// Whether a launch of tile_kernel reaches its layers through global instead of flat accesses (pick_tile).  Fewer waits: faster
+// where a workgroup's own chain bounds the launch, level or slower where it only changes what is in flight together.  Adam on the dense
+// gradient, us without and with: 400 M elements at 1 / 2 / 10 % kept 222 and 208, 244 and 241, 448 and 444, the 2.7B model 2712 and 2680; 85 M
+// elements at 3 / 5 / 6.9 % 60.5 and 62.7, 69.4 and 70.1, 78.3 and 78.7, and nothing gained there at 400 M.  SGD 254 and 223 at 1 %, 389 and 386 at 10 %.
+// A layer by itself, whose pointers come with the launch, loses 1 to 3.5 % (8192 x 8192 at 20 % 113.1 and 115.8).
+static bool global_access(const LaunchSet &ls, int opt)
+{
+    return ls.layers && (opt == kOptSgd || ls.keep < 0.025f || ls.keep >= (float)kSparseKeep);
+}
+
+#define SAMO_LAUNCH_TILE(M, G, O, A)                                                                       \
+    tile_kernel<M, G, O, kTileThreads, A><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)
 
 hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls, float inv_scale, const OptK &k,
                        const GuardK &guard, hipStream_t s)
@@ -1433,23 +1446,25 @@ hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls, float i
     // static LDS of the kernel: for the step that gathers the dense gradient the waves' exchange areas;
     // dynamic: the tile's fp16 image
     const int static_lds = mode == kModeStep && gsrc == kGradDense ? kTileThreads * 4 * 6 : 32;
-    const int pad = tile_lds_request(mode == kModeDecompress ? occ_tile_decompress(ls.keep) : occ_tile_step(gsrc, opt, ls.keep),
+    const int pad = tile_lds_request(mode == kModeDecompress ? occ_tile_decompress(ls.keep) : occ_tile_step(gsrc, opt, ls.keep, ls.layers ? ls.kept : -1.f),
                                      static_lds, ls.max_segs * kSeg * 2);
     StagedLaunch st;
     if (mode == kModeStep && gsrc == kGradDense && staged_launch(ls, &st)) {
         if (opt == kOptAdam) SAMO_LAUNCH_STAGED(kOptAdam);
         else SAMO_LAUNCH_STAGED(kOptSgd);
     } else if (mode == kModeDecompress) {
-        tile_kernel<kModeDecompress, kGradDense, kOptAdam, kExpandThreads><<<dim3((unsigned)ls.wgs), dim3(kExpandThreads), pad, s>>>(ls, inv_scale, k,
+        tile_kernel<kModeDecompress, kGradDense, kOptAdam, kExpandThreads, true><<<dim3((unsigned)ls.wgs), dim3(kExpandThreads), pad, s>>>(ls, inv_scale, k,
                                                                                                                           guard);
     } else if (opt == kOptAdam) {
-        if (gsrc == kGradDense) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptAdam);
-        else if (gsrc == kGradC16) SAMO_LAUNCH_TILE(kModeStep, kGradC16, kOptAdam);
-        else SAMO_LAUNCH_TILE(kModeStep, kGradC32, kOptAdam);
+        if (gsrc == kGradDense && global_access(ls, opt)) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptAdam, true);
+        else if (gsrc == kGradDense) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptAdam, false);
+        else if (gsrc == kGradC16) SAMO_LAUNCH_TILE(kModeStep, kGradC16, kOptAdam, false);
+        else SAMO_LAUNCH_TILE(kModeStep, kGradC32, kOptAdam, false);
     } else {
-        if (gsrc == kGradDense) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptSgd);
-        else if (gsrc == kGradC16) SAMO_LAUNCH_TILE(kModeStep, kGradC16, kOptSgd);
-        else SAMO_LAUNCH_TILE(kModeStep, kGradC32, kOptSgd);
+        if (gsrc == kGradDense && global_access(ls, opt)) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptSgd, true);
+        else if (gsrc == kGradDense) SAMO_LAUNCH_TILE(kModeStep, kGradDense, kOptSgd, false);
+        else if (gsrc == kGradC16) SAMO_LAUNCH_TILE(kModeStep, kGradC16, kOptSgd, false);
+        else SAMO_LAUNCH_TILE(kModeStep, kGradC32, kOptSgd, false);
     }
     return hipGetLastError();
 }

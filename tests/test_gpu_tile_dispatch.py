@@ -57,3 +57,15 @@ def test_a_plans_step_has_the_bits_of_the_layers(keep, opt):
     finally:
         samo.samo_debug_set(samo.KNOB_STAGED_TILES)
     _same(a, b, "pmvw")
+
+
+@pytest.mark.parametrize("keep", KEEPS)
+def test_a_plans_expansion_has_the_bits_of_the_layers(keep):
+    a = _layer(200_003, keep)
+    b = _copy(a)
+    _plan(a).samo_decompress_batched()
+    samo.samo_decompress(b["p"], b["idx"], b["seg_ptr"], b["w"])
+    _same(a, b, "w")
+    want = torch.zeros(a["n"], dtype=torch.float16, device=DEV)
+    want[a["idx"].long()] = a["p"].half()
+    assert torch.equal(a["w"].view(torch.int16), want.view(torch.int16))

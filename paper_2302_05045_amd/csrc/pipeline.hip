@@ -811,7 +811,8 @@ __device__ __forceinline__ void write_partial(double ss, int bad, StatPartial *_
 // One workgroup (a single wave) per chunk record; with statistics it leaves one partial, which
 // stats_reduce_kernel / stats_finalize_kernel sum afterwards (a grid of padded slots: see
 // launch_gather).
-template <int OUT>
+// OLD_FIRST: an accumulating gather requests the old message before it gathers (old_message_first).
+template <int OUT, bool OLD_FIRST>
 __global__ void __launch_bounds__(kFlatThreads)
 gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, StatPartial *__restrict__ partials)
 {
@@ -827,8 +828,8 @@ gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, Stat
     const int cnt = (nnz - i >= 4) ? 4 : (nnz - i > 0 ? (int)(nnz - i) : 0);
     uint16_t hb[4] = {0, 0, 0, 0};
     float fv[4] = {0.f, 0.f, 0.f, 0.f};
-    uint16_t old[4] = {0, 0, 0, 0};                       // requested first: they travel beside the positions and the gather
-    if (OUT == kOutF16 && accumulate) {
+    uint16_t old[4] = {0, 0, 0, 0};
+    if (OUT == kOutF16 && OLD_FIRST && accumulate) {      // they travel beside the positions and the gather
         if (cnt == 4) {
             const uint2 q = *reinterpret_cast<const uint2 *>(L.gc16 + i);
             old[0] = (uint16_t)q.x; old[1] = (uint16_t)(q.x >> 16); old[2] = (uint16_t)q.y; old[3] = (uint16_t)(q.y >> 16);
@@ -895,6 +896,14 @@ gather_kernel(const LaunchSet ls, int src, float inv_scale, int accumulate, Stat
     }
     if (OUT == kOutF16) {
         if (accumulate) {                                  // one correctly rounded half addition
+            if (!OLD_FIRST) {
+                if (cnt == 4) {
+                    const uint2 q = *reinterpret_cast<const uint2 *>(L.gc16 + i);
+                    old[0] = (uint16_t)q.x; old[1] = (uint16_t)(q.x >> 16); old[2] = (uint16_t)q.y; old[3] = (uint16_t)(q.y >> 16);
+                } else {
+                    for (int e = 0; e < cnt; ++e) old[e] = L.gc16[i + e];
+                }
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const _Float16 sum = __builtin_bit_cast(_Float16, old[e]) + __builtin_bit_cast(_Float16, hb[e]);
@@ -1340,7 +1349,7 @@ static int occ_tile_decompress(float keep)
 
 // Flat gather: one wave holds 1 KiB of indices and about 512 / keep bytes of dense lines in
 // flight; aim at ~75 KiB per CU.
-static int occ_flat_gather(int out, int src, float keep, bool with_stats)
+static int occ_flat_gather(int out, int src, float keep, bool with_stats, bool long_sum)
 {
     const int forced = knob(SAMO_KNOB_OCC_FLAT_GATHER, -1);
     const int forced_stats = knob(SAMO_KNOB_OCC_FLAT_STATS, -1);
@@ -1358,8 +1367,22 @@ static int occ_flat_gather(int out, int src, float keep, bool with_stats)
     // passes over the 1.3B model 1643 and 1615, 16 of its layers at 95 / 80 % pruning 854 and 839, 1670 and 1633; the clipped step, 1.3
     // and 1.12: 963 and 956, 1665 and 1658)
     if (with_stats) t *= (out == kOutF16) ? 1.4f : 1.12f;
+    // A long accumulating gather has the old message in flight as well (us of 800 M elements, by that formula alone and as here: 18 / 20 / 25 /
+    // 30 / 35 % kept 497 and 460, 509 and 485, 572 and 541, 719 and 615, 747 and 654; at 16 % of 400 M 221 and 234, hence the line)
+    else if (long_sum && keep >= 0.17f) {
+        t *= 0.87f;
+        if (t > 28.f && keep < 0.47f) t = 28.f;
+    }
     return t > 30.f ? 0 : (int)(t + 0.5f);
 }
+
+// An accumulating gather is long when what it moves (dense gradient, positions, message in and out) is well beyond the 256 MB of the
+// last-level cache.
+constexpr double kLongSum = 400e6;
+// The old message is requested first: one trip less at the end of every wave (42 / 85 / 400 M elements at 10 % kept 22.7 and 21.1 us, 46.9 and
+// 44.3, 192.3 and 190.0).  A long one that keeps under 7 % reads it last: there HBM is the bound and the order only splits its stream
+// (800 M elements at 3 and 5 % 276 and 278, 323 and 333; 1.2 G at 5 % 482 and 499).
+static bool old_message_first(float keep, bool long_sum) { return !long_sum || keep >= (float)kSparseKeep; }
 
 static int occ_flat_step()
 {
@@ -1530,10 +1553,13 @@ hipError_t launch_gather(int out, int src, const LaunchSet &ls, float inv_scale,
         return hipGetLastError();
     }
     const dim3 grid((unsigned)ls.wgs), block(kFlatThreads);
-    const int pad = lds_pad_for(occ_flat_gather(out, src, ls.keep, partials != nullptr), 2 * kChunk * 4);   // static: the exchange areas
-    if (out == kOutF32) gather_kernel<kOutF32><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
-    else if (out == kOutF16) gather_kernel<kOutF16><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
-    else gather_kernel<kOutNone><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
+    const double nnz = (double)ls.wgs * kChunk;
+    const bool long_sum = accumulate && ls.keep > 0.f && 8.0 * nnz + 2.0 * nnz / (double)ls.keep > kLongSum;
+    const int pad = lds_pad_for(occ_flat_gather(out, src, ls.keep, partials != nullptr, long_sum), 2 * kChunk * 4);   // static: the exchange areas
+    if (out == kOutF32) gather_kernel<kOutF32, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
+    else if (out == kOutF16 && old_message_first(ls.keep, long_sum)) gather_kernel<kOutF16, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
+    else if (out == kOutF16) gather_kernel<kOutF16, false><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
+    else gather_kernel<kOutNone, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
     return hipGetLastError();
 }
 

@@ -69,3 +69,17 @@ def test_a_plans_expansion_has_the_bits_of_the_layers(keep):
     want = torch.zeros(a["n"], dtype=torch.float16, device=DEV)
     want[a["idx"].long()] = a["p"].half()
     assert torch.equal(a["w"].view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("n,keep", [(200_000_003, .03), (200_000_003, .2), (1003, .03), (1_000_001, .5)])
+def test_long_accumulating_gathers_have_the_bits_of_short_ones(n, keep):
+    """Beyond the last-level cache the old message is read before or after the gather, by what is kept: the same one
+    rounded addition."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    ix = samo.samo_build_index((torch.rand(n, generator=gen, device=DEV) < keep).to(torch.uint8))
+    g = torch.randn(n, generator=gen, device=DEV).half()
+    old = torch.randn(ix.nnz, generator=gen, device=DEV).half()
+    got = old.clone()
+    samo.samo_gather_grads_fp16(g, ix.idx, got, accumulate=True)
+    want = old + g[ix.idx.long()]
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))

@@ -150,17 +150,18 @@ __device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, int &row0, int &col0)
 {
     // The workgroup's first copies wait for this function, and what it reads comes from the kernel arguments by way of
-    // cold caches: a single job's descriptor is read at fixed places, and everything at once (left alone, the compiler loads each
-    // value in front of its use, one trip more: two calls of 1003 tokens, 4096 x 1024, 31.3 -> 30.8 us, FC1 of the
-    // 2.7B model 102.2 -> 101.5); only a list of several is searched.
+    // cold caches: a single job's descriptor is read at fixed places, and what the way to the first copies needs at once (left alone,
+    // the compiler loads each value in front of its use, one trip more: the kernel of 1003 tokens, 4096 x 1024, 16.80 -> 16.47 us, 200 tokens,
+    // 2560 x 7680, 28.65 -> 27.80; FC1 of the 2.7B model level).  The scale and `accumulate`, wanted at the end only,
+    // are not among it: with them launches of a few workgroups took 0.2 us longer (512 x 512, 20 / 100 / 300 tokens 6.25, 7.04, 9.00 us
+    // left alone, 6.51, 7.28, 9.22 with them, 6.33, 7.05, 9.02 without).  Only a list of several is searched.
     const int quadrants = B.quadrants, tiles = B.tiles, splits = B.splits, jobs = B.jobs, first_listed = B.first, tile_cols = B.tile_cols;
     const float inv_scale = B.inv_scale;
     const int accumulate = B.accumulate;
     WgradJob J = B.job[0];
     int j = 0, first = 0, tiles_out = B.tiles_out[0], tiles_in = B.tiles_in[0];
     uint32_t per_group = B.per_group[0];
-    asm volatile("" ::"s"(quadrants), "s"(tiles), "s"(splits), "s"(jobs), "s"(first_listed), "s"(tile_cols), "s"(inv_scale), "s"(accumulate),
-                 "s"(J.dy), "s"(J.x), "s"(J.tokens), "s"(J.out), "s"(J.in), "s"(J.idx), "s"(J.seg_ptr), "s"(J.nnz), "s"(J.gc), "s"(tiles_out),
+    asm volatile("" ::"s"(quadrants), "s"(tiles), "s"(splits), "s"(jobs), "s"(first_listed), "s"(tile_cols), "s"(J.dy), "s"(J.x), "s"(J.tokens), "s"(J.out), "s"(J.in), "s"(J.idx), "s"(J.seg_ptr), "s"(J.nnz), "s"(J.gc), "s"(tiles_out),
                  "s"(tiles_in), "s"(per_group));
     const int shares = quadrants ? tiles * 4 : tiles;            // workgroups of one split
     const int blocks = shares * splits;

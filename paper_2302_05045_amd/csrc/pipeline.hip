@@ -592,7 +592,7 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_image[];
     // what the workgroup needs of the kernel arguments, requested at once (the caches are cold, a line at a time is a trip each), and
     // the first record beside the guard (18 convolutions 14.25 -> 14.0 us)
-    const int64_t first = (int64_t)blockIdx.x * merge;
+    const int first = (int)blockIdx.x * merge;          // a short launch: at most kStagedMost records
     const int most = merge * ls.max_segs;
     asm volatile("" ::"s"(ls.layers), "s"(ls.recs), "s"(ls.wgs), "s"(most), "s"(ls.one.n), "s"(ls.one.seg_ptr), "s"(guard.stats), "s"(inv_scale), "s"(k.adam.lr));
     uint64_t first_rec = 0;
@@ -613,12 +613,12 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
         else staged_tile<OPT, WHOLE>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
     };
     if (!PLAN) {
-        const int64_t nseg = (ls.one.n + kSeg - 1) / kSeg, s0 = first * ls.segs_per_tile;
-        tile(ls.one, (int)s0, nseg - s0 < ls.segs_per_tile ? (int)(nseg - s0) : ls.segs_per_tile);
+        const int nseg = (int)((ls.one.n + kSeg - 1) / kSeg), s0 = first * ls.segs_per_tile;
+        tile(ls.one, s0, nseg - s0 < ls.segs_per_tile ? nseg - s0 : ls.segs_per_tile);
         return;
     }
-    const int64_t end = first + merge < ls.wgs ? first + merge : ls.wgs;
-    for (int64_t t = first; t < end;) {
+    const int records = (int)ls.wgs, end = first + merge < records ? first + merge : records;
+    for (int t = first; t < end;) {
         const WgRec r = t == first ? rec_of(first_rec) : constant_rec(ls.recs + t);
         const int s0 = (int)(r.local & ((1u << kRecSegShift) - 1u));
         int nsegs = (int)(r.local >> kRecSegShift);

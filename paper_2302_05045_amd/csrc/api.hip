@@ -18,6 +18,21 @@ int knob(int which, int dflt)
     const int v = g_knobs[which].load(std::memory_order_relaxed);
     return v > 0 ? v - 1 : dflt;
 }
+
+constexpr int kMaxDevices = 64;
+
+int compute_units()
+{
+    static std::atomic<int> cached[kMaxDevices] = {};
+    int device = 0, n = 0;
+    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) return 256;
+    n = cached[device].load(std::memory_order_relaxed);
+    if (n <= 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n <= 0) n = 256;
+        cached[device].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
 }  // namespace samo
 
 namespace {
@@ -36,22 +51,7 @@ inline bool has(const samo_plan *plan, uint32_t bits) { return (plan->buffers & 
 // is only a handle for hipGetSymbolAddress; kernels get the resolved address as an argument.
 constexpr size_t kStaticScratchBytes = 16u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
-constexpr int kMaxDevices = 64;
 std::atomic<void *> g_scratch_ptr[kMaxDevices] = {};
-
-// Number of compute units of the current device (looked up once per device; 256 if the query fails).
-int compute_units()
-{
-    static std::atomic<int> cached[kMaxDevices] = {};
-    int device = 0, n = 0;
-    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) return 256;
-    n = cached[device].load(std::memory_order_relaxed);
-    if (n <= 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n <= 0) n = 256;
-        cached[device].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
 
 // Device address of `scratch` on the current device (looked up once per device, then cached).
 hipError_t static_scratch(void **ptr)

@@ -127,6 +127,9 @@ __host__ __device__ inline int storable(int64_t cap, int64_t at, int count)
     return cap - at < count ? (int)(cap - at) : count;
 }
 
+// Compute units of the current device (looked up once per device; 256 if the query fails).
+int compute_units();
+
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) -----------------------

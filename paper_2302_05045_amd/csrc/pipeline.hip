@@ -505,14 +505,14 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
 // is read at the kept positions after all, two elements to a lane: the whole of it would be the larger part of the traffic (20 layers
 // of 1 M elements, 0.5 / 3 / 6 % kept: 16.9, 20.2 and 22.7 us with it, 10.0, 15.3 and 18.9 without; tile_kernel 14.0, 19.1, 23.4).
 // Through the caches, several kept positions share a line (past them: 13.3, 17.8, 22.4).  Four workgroups share a compute unit (64
-// registers, up to 40 KB of LDS).  In us, tile_kernel and this one: one layer of 1024 x 1024 (10 % kept) 4.5 and 3.4, 2048 x 2048 8.1
+// registers, up to 40 KB of LDS; three where two records of default weight are merged, 48 KB).  In us, tile_kernel and this one: one layer of 1024 x 1024 (10 % kept) 4.5 and 3.4, 2048 x 2048 8.1
 // and 6.2, 4096 x 2048 13.1 and 10.4; 18 convolutions (11.5 M elements, SGD) 16.1 and 14.3; a 12.6 M element GPT at 15 % kept
 // 21.0 and 19.7.  Tried instead: persistent workgroups that request the next tile while they step one (16.3 to 22 us for the
 // convolutions, whatever the number of workgroups), workgroups of 128 and 256 threads (15.4, 14.8), two elements per
 // lane requested ahead (15.4).
 constexpr int kStagedThreads = 512;
-constexpr int kStagedSlots = 1024;            // workgroups of that size the device holds at a time
-constexpr int kStagedSegs = 10;               // segments of a tile with which four workgroups still share a compute unit's LDS
+constexpr int kStagedPerUnit = 4;             // workgroups of that size a compute unit holds at a time
+constexpr int kStagedSegs = 10;               // segments of a tile with which that many share its LDS
 constexpr int kStagedLdsSegs = 13;            // ... and with which three do
 
 template <int OPT, bool WHOLE>
@@ -1432,7 +1432,7 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
         int segs = (int)((double)kTileCost / per_seg + 0.5);
         if (segs < 1) segs = 1;
         if (nseg > (int64_t)segs * kStagedRound) {
-            const int64_t one_round = ceil_div(nseg, (int64_t)kStagedSlots);
+            const int64_t one_round = ceil_div(nseg, (int64_t)kStagedPerUnit * compute_units());
             const int heavy = (int)(2.0 * (double)kTileCost / per_seg + 0.5);
             if (one_round > kStagedSegs) segs = heavy < kStagedSegs ? heavy : kStagedSegs;
             else if (one_round > segs) segs = (int)one_round;

@@ -180,7 +180,7 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
  * DEVICE pointers.  Both calls refuse the jobs that samo_build_index_batched refuses.
  * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
  * flag bits, the seg_ptr and the nnz such a call left, later on the same stream; the mask is not read.
- * A job whose count gave up (*nnz = -1) is left without positions. */
+ * A job with *nnz < 0 (as a build in one call reports that it gave up) is left without positions. */
 samo_status samo_index_flags_bytes(int64_t n, size_t *bytes);
 samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,
                                      void *stream);
@@ -476,8 +476,8 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *   SAMO_KNOB_OCC_FLAT_GATHER, _OCC_FLAT_STATS, _OCC_FLAT_STEP (waves)
  *                        resident per compute unit that a launch of that kind aims at; 0 = no cap.
  *   SAMO_KNOB_INDEX_SPIN_LIMIT  polls an index-build workgroup spends on a predecessor before it
- *                        gives up (default 2^20); 0 makes the give-up path reachable in tests.  While it is set,
- *                        calls that only count wait along the chain too.
+ *                        gives up (default 2^20); 0 makes the give-up path reachable in tests.  Builds that count
+ *                        and write positions in one call only: nothing else waits.
  *   SAMO_KNOB_INDEX_PASSES  1, 2 or 4: forces the block size of the index build (64 KiB of mask per pass and
  *                        workgroup; default: 4 for launches with at least a dozen blocks of that size per
  *                        compute unit, else 2 or 1).

@@ -363,8 +363,6 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
             return [Index(*parts) for parts in built]
         if built == SAMO_ERR_SIZE:
             raise SamoError(SAMO_ERR_SIZE, "samo_seg_ptr_len")
-        if built == SAMO_ERR_INDEX:
-            raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
         if built is not None:
             raise SamoError(built, where)
     dev, k = masks[0].device, len(masks)
@@ -387,8 +385,6 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     else:
         _check(lib().samo_build_index_batched(jobs, k, _stream()), where)                # no room for positions: counts only
     counts = nnz_out.cpu().tolist()
-    if any(c < 0 for c in counts):
-        raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
     out = []
     for i, c in enumerate(counts):
         idx = torch.empty(c, dtype=torch.int32, device=dev)
@@ -399,6 +395,8 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
         _check(lib().samo_fill_index_batched(jobs, flags, k, _stream()), where)
     else:
         _check(lib().samo_build_index_batched(jobs, k, _stream()), where)
+        if bool((nnz_out < 0).any()):                    # of the builds only this one waits for other workgroups
+            raise SamoError(SAMO_ERR_INDEX, where + " (the device-side scan gave up)")
     return out
 
 

@@ -244,10 +244,8 @@ samo_status run_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, i
             wgs += w;
         }
         batch.wg_start[k] = (int)wgs;
-        // a launch that only counts waits for nothing; with the testing aid set it takes the kernel that can give up
-        const bool chained = fill || knob(SAMO_KNOB_INDEX_SPIN_LIMIT, -1) >= 0;
-        if ((chained ? launch_index_batch(batch, fill, as_stream(stream)) : launch_index_count(batch, h_flags != nullptr, as_stream(stream))) !=
-            hipSuccess)
+        // a launch that only counts has no use for the chain
+        if ((fill ? launch_index_batch(batch, as_stream(stream)) : launch_index_count(batch, h_flags != nullptr, as_stream(stream))) != hipSuccess)
             return SAMO_ERR_HIP;
         j0 += k;
     }

@@ -133,7 +133,7 @@ int compute_units();
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) -----------------------
-hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s);
+hipError_t launch_index_batch(const IndexBatch &batch, hipStream_t s);
 // Counting without a chain (rewrites batch.wg_start for its own kernels); flags: leaves the flag words as well.
 hipError_t launch_index_count(IndexBatch &batch, bool flags, hipStream_t s);
 hipError_t launch_index_fill(const IndexBatch &batch, hipStream_t s);

@@ -286,7 +286,7 @@ __device__ __forceinline__ void emit_pair(uint32_t word, uint32_t half, int base
 
 template <int PASSES>
 __global__ void __launch_bounds__(kIndexThreads)
-index_kernel(const IndexBatch batch, int fill)
+index_kernel(const IndexBatch batch)
 {
     constexpr int kSegsPerWave = kSegsPerPass * PASSES;
     constexpr int kSegsPerWg = segs_per_wg(PASSES);
@@ -322,11 +322,6 @@ index_kernel(const IndexBatch batch, int fill)
                 dst[1] = incl >> 16;
             }
             fp[p][j] = f[2 * j] | (f[2 * j + 1] << 16);
-        }
-        if (batch.flags[job] != nullptr && seg0 + p * kSegsPerPass < nseg) {      // only where the testing aid sends a counting call here
-            uint32_t word[kPairs];
-            pair_words(fp[p], word, sh_stage[wave], lane);
-            store_flags(batch.flags[job] + (seg0 / kSegsPerPass + p) * 64 + lane, word);
         }
         asm volatile("" ::: "memory");        // the next pass's loads are requested after this pass's flag words exist
     }
@@ -367,7 +362,7 @@ index_kernel(const IndexBatch batch, int fill)
         if (t >= 1 && first_seg + t < slot) seg_ptr[first_seg + t] = base + sh_seg[t];
 
     const int64_t cap = batch.cap[job];
-    if (!fill || cap <= 0 || seg0 >= nseg) return;
+    if (cap <= 0 || seg0 >= nseg) return;      // no room: this job only counts
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         uint32_t word[kPairs];
@@ -693,7 +688,7 @@ validate_kernel(const int32_t *__restrict__ idx, int64_t nnz, int64_t n, int64_t
 
 }  // namespace
 
-hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
+hipError_t launch_index_batch(const IndexBatch &batch, hipStream_t s)
 {
     if (batch.num <= 0) return hipSuccess;
     const int wgs = batch.wg_start[batch.num];
@@ -701,9 +696,9 @@ hipError_t launch_index_batch(const IndexBatch &batch, bool fill, hipStream_t s)
     index_init_kernel<<<dim3((unsigned)ceil_div(init_threads, kThreads)), dim3(kThreads), 0, s>>>(batch);
     if (wgs > 0) {
         const dim3 grid((unsigned)wgs), block(kIndexThreads);
-        if (batch.passes == 4) index_kernel<4><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
-        else if (batch.passes == 2) index_kernel<2><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
-        else index_kernel<1><<<grid, block, 0, s>>>(batch, fill ? 1 : 0);
+        if (batch.passes == 4) index_kernel<4><<<grid, block, 0, s>>>(batch);
+        else if (batch.passes == 2) index_kernel<2><<<grid, block, 0, s>>>(batch);
+        else index_kernel<1><<<grid, block, 0, s>>>(batch);
     }
     return hipGetLastError();
 }

@@ -85,14 +85,14 @@ struct WithoutGil {
 };
 
 // Elements of masks from which on build_indices launches the fill of those that have their index allocated while it goes on
-// with the others; twice as many for every further launch.  28 matrices of 550 M elements: five launches.  A launch costs the host
+// with the others; twice as many for every further launch.  28 matrices of 550 M elements: four launches.  A launch costs the host
 // 5 us and fills 32 M elements in 3, so the first one starts the device early and the last ones keep it busy.
 constexpr int64_t kFirstFill = 32 << 20;
 
 // build_indices(masks, stream, scratch, count, fill): indices of byte masks (a list) by the entries samo_count_flags_batched and
 // samo_fill_index_batched at the addresses `count` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
 // uint8 tensor for the flag bits or None.
-// A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int (SAMO_ERR_INDEX: a count gave up); None where the
+// A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int; None where the
 // caller has to go another way: a mask is no plain tensor, or there is no scratch memory.
 PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
@@ -143,8 +143,6 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         }
         status = count(jobs.data(), flags.data(), (int32_t)k, stream);
         if (status == SAMO_OK) counts = nnz.cpu();
-        for (size_t i = 0; status == SAMO_OK && i < k; ++i)
-            if (counts.data_ptr<int64_t>()[i] < 0) status = SAMO_ERR_INDEX;
         int64_t waiting = 0, enough = kFirstFill;
         for (size_t i = 0, first = 0; status == SAMO_OK && i < k; ++i) {
             const int64_t found = counts.data_ptr<int64_t>()[i];

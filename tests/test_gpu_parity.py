@@ -106,31 +106,49 @@ def test_build_index_batched_many_jobs():
     assert samo.samo_build_index_many([]) == []
 
 
-def test_build_index_gives_up_cleanly_when_the_wait_is_cut_short():
+def test_build_index_gives_up_cleanly_when_the_wait_is_cut_short(monkeypatch):
     """With no patience at all for a predecessor, a workgroup gives up instead of waiting: the
     call must still end, and report either the right index or the failure — never a wrong one.
     The layer is 611 blocks, more than two per compute unit: the workgroups that start together
     cannot all find their predecessor's count published at their first look, so the give-up path
-    is taken in at least one of the three builds."""
+    is taken in at least one of the three builds.  Only a build that counts and writes positions in one call waits; one in two
+    calls is right whatever the limit, and without memory for the flag bits, whose second call is of the first kind, it says so."""
     n = 40_000_003
     mask = si.bernoulli_mask(n, 0.1, 31)
+    ref = oracle.build_index(mask)
     d_mask = dev_u8(mask)
-    outcomes = set()
+    room = ref.shape[0]
+    idx = torch.empty(room + 64, dtype=torch.int32, device=DEV)
+    seg = torch.empty(samo.samo_seg_ptr_len(n), dtype=torch.int32, device=DEV)
+    nnz = torch.zeros(1, dtype=torch.int64, device=DEV)
+    outcomes, fallback = set(), set()
     samo.samo_debug_set(samo.KNOB_INDEX_SPIN_LIMIT, 0)
     try:
         for _ in range(3):
-            try:
-                ix = samo.samo_build_index(d_mask)
-                assert np.array_equal(ix.idx.cpu().numpy(), oracle.build_index(mask))
-                outcomes.add("ok")
-            except samo.SamoError as e:
-                assert e.status == samo.SAMO_ERR_INDEX
+            idx.fill_(-5)
+            samo.samo_build_index_into(d_mask, idx[:room], seg, nnz)
+            count = int(nnz.item())
+            assert bool((idx[room:] == -5).all()), "stored past the capacity"
+            if count == -1:
                 outcomes.add("gave up")
+            else:
+                assert count == room and np.array_equal(idx[:room].cpu().numpy(), ref)
+                outcomes.add("ok")
+            ix = samo.samo_build_index(d_mask)
+            assert ix.nnz == room and np.array_equal(ix.idx.cpu().numpy(), ref)
+            with monkeypatch.context() as m:
+                m.setattr(samo, "_scratch", lambda nbytes: None)
+                try:
+                    assert np.array_equal(samo.samo_build_index(d_mask).idx.cpu().numpy(), ref)
+                    fallback.add("ok")
+                except samo.SamoError as e:
+                    assert e.status == samo.SAMO_ERR_INDEX
+                    fallback.add("gave up")
     finally:
         samo.samo_debug_set(samo.KNOB_INDEX_SPIN_LIMIT)
-    assert "gave up" in outcomes
-    ix = samo.samo_build_index(d_mask)                  # and the library is fine afterwards
-    assert np.array_equal(ix.idx.cpu().numpy(), oracle.build_index(mask))
+    assert "gave up" in outcomes and "gave up" in fallback
+    samo.samo_build_index_into(d_mask, idx[:room], seg, nnz)        # and the library is fine afterwards
+    assert int(nnz.item()) == room and np.array_equal(idx[:room].cpu().numpy(), ref)
 
 
 def test_build_index_empty_layer():

@@ -73,3 +73,24 @@ def test_native_and_python_index_builds_agree(monkeypatch):
             assert type(a) is samo.Index and a.nnz == b.nnz and a.n == b.n
             assert torch.equal(a.idx, b.idx) and torch.equal(a.seg_ptr, b.seg_ptr)
             assert a.idx.dtype == b.idx.dtype and a.seg_ptr.dtype == b.seg_ptr.dtype
+
+
+def test_index_builds_on_a_side_stream_beside_work_on_the_current_one():
+    """The fill is launched in parts and the flag words are given back while it still reads them, in stream order: scratch memory, counts
+    and indices belong to the stream that is current, and what other streams allocate meanwhile is not theirs."""
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    sizes = (20_000_003, 1000, 20_000_001, 0, 40_000_000, 17, 50_000_000, 3000)
+    masks = [(torch.rand(n, generator=gen, device=DEV) < 0.05).to(torch.uint8) for n in sizes]
+    want = samo.samo_build_index_many(masks)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    flag_bytes = sum(samo._flag_bytes(n) for n in sizes)
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            got = samo.samo_build_index_many(masks)
+            torch.full((flag_bytes,), 0xff, dtype=torch.uint8, device=DEV)      # the flag words' memory, next in the stream
+        for _ in range(4):
+            torch.full((flag_bytes,), 0xff, dtype=torch.uint8, device=DEV)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert a.nnz == b.nnz and torch.equal(a.idx, b.idx) and torch.equal(a.seg_ptr, b.seg_ptr)

@@ -91,6 +91,42 @@ def test_build_index_every_block_size(passes):
         samo.samo_debug_set(samo.KNOB_INDEX_PASSES)
 
 
+@pytest.mark.parametrize("passes", [1, 2, 4])
+def test_one_call_build_at_the_block_edges_of_every_block_size(passes):
+    """The chained kernel, which the forced block size concerns (a build in two calls has blocks of its own): less than a block,
+    one block, one element more, and more than 64 blocks, so that a workgroup looks back twice; with room for every position, each by
+    itself and as one batched call, jobs without room among them."""
+    block = 65536 * passes
+    sizes = [1, block - 1, block, block + 1, 2 * block, 3 * block + 17 * 1024 + 5, 70 * block + 123457]
+    masks = [si.bernoulli_mask(n, keep, 60 + i) for i, (n, keep) in enumerate(zip(sizes, [1.0, 0.1, 0.4, 0.03, 0.9, 0.2, 0.1]))]
+    refs = [oracle.build_index(m) for m in masks]
+    dev = [dev_u8(m) for m in masks]
+    tables = lambda: [torch.full((samo.samo_seg_ptr_len(len(m)),), -9, dtype=torch.int32, device=DEV) for m in masks]
+    idxs = lambda: [torch.full((r.shape[0] + 8,), -5, dtype=torch.int32, device=DEV) for r in refs]
+
+    def check(idx, seg, count, mask, ref):
+        assert count == ref.shape[0]
+        assert np.array_equal(seg.cpu().numpy(), ref_seg_ptr(ref, mask.shape[0]))
+        assert np.array_equal(idx[:count].cpu().numpy(), ref) and bool((idx[count:] == -5).all())
+    samo.samo_debug_set(samo.KNOB_INDEX_PASSES, passes)
+    try:
+        nnz = torch.zeros(len(masks), dtype=torch.int64, device=DEV)
+        for d, idx, seg, mask, ref in zip(dev, idxs(), tables(), masks, refs):
+            samo.samo_build_index_into(d, idx[:ref.shape[0]], seg, nnz[:1])
+            check(idx, seg, int(nnz[0].item()), mask, ref)
+        idx, seg = idxs(), tables()
+        room = [None if j == 2 else x[:r.shape[0]] for j, (x, r) in enumerate(zip(idx, refs))]
+        samo.samo_build_index_batched(dev, room, seg, nnz)
+        for j, count in enumerate(nnz.cpu().tolist()):
+            if room[j] is None:
+                assert count == refs[j].shape[0] and bool((idx[j] == -5).all())
+                assert np.array_equal(seg[j].cpu().numpy(), ref_seg_ptr(refs[j], masks[j].shape[0]))
+            else:
+                check(idx[j], seg[j], count, masks[j], refs[j])
+    finally:
+        samo.samo_debug_set(samo.KNOB_INDEX_PASSES)
+
+
 def test_build_index_batched_many_jobs():
     # more jobs than one launch group holds (48), with empty, tiny, ragged and multi-segment layers
     rng = np.random.default_rng(7)

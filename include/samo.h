@@ -474,13 +474,15 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  * choice.  Not needed for normal use: the defaults are the measured optima.
  *   SAMO_KNOB_OCC_TILE_STEP, _OCC_TILE_STEP32, _OCC_TILE_DECOMP, _OCC_TILE_C16 (workgroups) and
  *   SAMO_KNOB_OCC_FLAT_GATHER, _OCC_FLAT_STATS, _OCC_FLAT_STEP (waves)
- *                        resident per compute unit that a launch of that kind aims at; 0 = no cap.
+ *                        resident per compute unit that a launch of that kind aims at; 0 = no cap.  _OCC_TILE_STEP has
+ *                        no effect on a step that counts as a short launch (SAMO_KNOB_STAGED_TILES).
  *   SAMO_KNOB_INDEX_SPIN_LIMIT  polls an index-build workgroup spends on a predecessor before it
  *                        gives up (default 2^20); 0 makes the give-up path reachable in tests.  Builds that count
  *                        and write positions in one call only: nothing else waits.
- *   SAMO_KNOB_INDEX_PASSES  1, 2 or 4: forces the block size of the index build (64 KiB of mask per pass and
- *                        workgroup; default: 4 for launches with at least a dozen blocks of that size per
- *                        compute unit, else 2 or 1).
+ *   SAMO_KNOB_INDEX_PASSES  1, 2 or 4: forces the block size of builds that count and write positions in one call
+ *                        (64 KiB of mask per pass and workgroup; default: 4 for launches with at least a dozen blocks
+ *                        of that size per compute unit, else 2 or 1).  Calls that only count, and the fill, have blocks
+ *                        of their own.
  *   SAMO_KNOB_WGRAD_TILE   128 or 256: forces the tile shape of the weight-gradient entries
  *                        (default: 256 x 256 in whole rounds of the compute units and 128 x 128 for a
  *                        remainder of at most half a round; calls of less than a round take 128 x 128
@@ -492,9 +494,10 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *                        (default there: 128 x 128).
  *   SAMO_KNOB_WGRAD_COLS   test aid: 128, 160 or 192 columns of a 256-row tile, whatever the rule says (the default
  *                        takes such tiles for calls of less than a round of 256 x 256 ones where they fill it better).
- *   SAMO_KNOB_TILE_COST    the weight of a plan's tiles in units of 1024 (6 .. 96; default 32, or 48 for a
+ *   SAMO_KNOB_TILE_COST    the weight of a plan's tiles in units of 1024 (6 .. 96; default 32, or 64 for a
  *                        model that keeps under 7 % of its elements; 48 there with an fp32 dense side).
- *                        Read by samo_plan_workspace_bytes and samo_plan_init: set it before both.
+ *                        Read by samo_plan_init and samo_plan_workspace_bytes: set it before both.  The step of a
+ *                        layer by itself does not count as a short launch while it is set; that of a plan may.
  *   SAMO_KNOB_STAGED_TILES  the most tiles (of the default weight) with which a fused step counts as a short launch
  *                        and takes the kernel made for those (default 10000); 0: never.
  * Returns SAMO_ERR_ARG for an unknown knob. */

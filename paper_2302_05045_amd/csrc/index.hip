@@ -520,16 +520,10 @@ offsets_kernel(const IndexBatch batch)
 }
 
 
-// The positions from the flag words and the seg_ptr a counting launch left: a wave takes a group of eight
-// segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
-// A count that gave up left *nnz = -1 and a seg_ptr that is no table of offsets (chain states, entries never
-// written): nothing is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
-// What bounds it: the loop over a lane's kept elements (7 vector instructions and an LDS store a trip, 8 trips
-// a pair at 10 % kept) beside the index written, 4 bytes per kept element: 4.6 TB/s at 10 % kept.
 // The positions from the flag words and the seg_ptr a counting call left: a wave takes a group of eight
 // segments (1 KiB of flag words in one load, where the mask is 8 KiB) and nothing waits for anything.
-// A count that gave up left *nnz = -1 and a seg_ptr that is no table of offsets (chain states, entries never
-// written): nothing is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
+// A negative *nnz is no count: a build in one call leaves it, with a seg_ptr that is no table of offsets, where it gave up.  Nothing
+// is stored then, and whatever seg_ptr holds no store leaves idx[0 .. cap) (storable).
 // A lane holds 32 consecutive elements of each of the group's four pairs of segments.  Where a group keeps at most kStage
 // elements its four pairs go through the loop over kept elements side by side (about 9 trips at 10 % kept, which share the
 // loop's overhead, where one pair after the other took 8 each) and leave as one run; up to twice that, two pairs at a time.

@@ -93,7 +93,8 @@ __device__ __forceinline__ void opt_update(float &p, float &m, float &v, float g
 #define SAMO_CONSTANT __attribute__((address_space(4)))       // memory that no launch writes while it reads it through this
 
 // Clipping coefficient from the device-resident statistics; *skip says the step must do nothing.  One scalar load of both: as
-// two, the second after the test of the first, every workgroup began with two trips (clipped steps, 12.6 M and 85 M elements: 31.35 -> 31.15, 146.3 -> 145.9 us).
+// two, the second after the test of the first, every workgroup began with two trips (with staged_kernel's arguments requested at once a clipped
+// step of 12.6 M elements 31.0 -> 30.6 us; longer ones do not show it).
 __device__ __forceinline__ float guard_coef(const GuardK &gd, bool *skip)
 {
     *skip = false;

@@ -147,22 +147,29 @@ __device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 // at a time then share about 4 + 8 operand panels rather than 1 + 32.
 // Returns false for a workgroup with nothing to do: the surplus of the last round, or a quarter
 // that lies outside the matrix.
+// JOB_FIRST: the job's descriptor is requested with the launch's fields.
+template <bool JOB_FIRST>
 __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, int &row0, int &col0)
 {
     // The workgroup's first copies wait for this function, and what it reads comes from the kernel arguments by way of
-    // cold caches: a single job's descriptor is read at fixed places, and what the way to the first copies needs at once (left alone,
-    // the compiler loads each value in front of its use, one trip more: the kernel of 1003 tokens, 4096 x 1024, 16.80 -> 16.47 us, 200 tokens,
-    // 2560 x 7680, 28.65 -> 27.80; FC1 of the 2.7B model level).  The scale and `accumulate`, wanted at the end only,
-    // are not among it: with them launches of a few workgroups took 0.2 us longer (512 x 512, 20 / 100 / 300 tokens 6.25, 7.04, 9.00 us
-    // left alone, 6.51, 7.28, 9.22 with them, 6.33, 7.05, 9.02 without).  Only a list of several is searched.
+    // cold caches: a single job's descriptor is read at fixed places, and everything at once (left alone, the compiler loads each
+    // value in front of its use, one trip more: the kernel of 1003 tokens, 4096 x 1024, 15.8 -> 15.4 us, 200 tokens, 2560 x 7680,
+    // 27.8 -> 27.0; FC1 of the 2.7B model 101.0 -> 100.4).  Launches of few workgroups (kFewBlocks) take the descriptor after the
+    // launch's fields: 512 x 512, 20 / 100 / 300 tokens, left alone, everything at once, so: 6.23, 7.01, 8.97 us; 6.49, 7.26, 9.20;
+    // 6.10, 6.88, 8.86.  Only a list of several jobs is searched.
     const int quadrants = B.quadrants, tiles = B.tiles, splits = B.splits, jobs = B.jobs, first_listed = B.first, tile_cols = B.tile_cols;
     const float inv_scale = B.inv_scale;
     const int accumulate = B.accumulate;
     WgradJob J = B.job[0];
     int j = 0, first = 0, tiles_out = B.tiles_out[0], tiles_in = B.tiles_in[0];
     uint32_t per_group = B.per_group[0];
-    asm volatile("" ::"s"(quadrants), "s"(tiles), "s"(splits), "s"(jobs), "s"(first_listed), "s"(tile_cols), "s"(J.dy), "s"(J.x), "s"(J.tokens), "s"(J.out), "s"(J.in), "s"(J.idx), "s"(J.seg_ptr), "s"(J.nnz), "s"(J.gc), "s"(tiles_out),
-                 "s"(tiles_in), "s"(per_group));
+    if (JOB_FIRST)
+        asm volatile("" ::"s"(quadrants), "s"(tiles), "s"(splits), "s"(jobs), "s"(first_listed), "s"(tile_cols), "s"(inv_scale), "s"(accumulate),
+                     "s"(J.dy), "s"(J.x), "s"(J.tokens), "s"(J.out), "s"(J.in), "s"(J.idx), "s"(J.seg_ptr), "s"(J.nnz), "s"(J.gc), "s"(tiles_out),
+                     "s"(tiles_in), "s"(per_group));
+    else
+        asm volatile("" ::"s"(quadrants), "s"(tiles), "s"(splits), "s"(jobs), "s"(first_listed), "s"(tile_cols), "s"(inv_scale), "s"(accumulate),
+                     "s"(tiles_out), "s"(tiles_in), "s"(per_group));
     const int shares = quadrants ? tiles * 4 : tiles;            // workgroups of one split
     const int blocks = shares * splits;
     const int per_xcd = (blocks + 7) / 8;
@@ -544,7 +551,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
     __shared__ int bounds[2 * kTile];
     WgradArgs A;
     int row0, col0;
-    if (!tile_origin(B, A, row0, col0)) return;
+    if (!tile_origin<true>(B, A, row0, col0)) return;
 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
@@ -598,7 +605,10 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
 }
 
 // 128 x 128 tile: 64 x 64 per wave, the waves of a group as 2 x 2; group g multiplies tokens 2g and 2g + 1 of every row.
-template <int OUT, bool APART>
+// FEW: for launches of fewer than kFewBlocks workgroups (768 x 768, 36 of them, 300 tokens: 9.22 us without and 8.93 with; 1024 x 1024, 64, 200
+// tokens 8.30 and 8.32; 4096 x 1024, 256, 700 tokens 12.73 and 12.84).
+constexpr unsigned kFewBlocks = 64;
+template <int OUT, bool APART, bool FEW>
 __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradBatch B)
 {
     constexpr int kTile = kSmallTile, kEpiPitch = kTile + 8, kSumPitch = kTile + 4;
@@ -607,7 +617,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     __shared__ int bounds[2 * kTile];
     WgradArgs A;
     int row0, col0;
-    if (!tile_origin(B, A, row0, col0)) return;
+    if (!tile_origin<!FEW>(B, A, row0, col0)) return;
 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
@@ -736,9 +746,10 @@ bool loop_apart(int64_t tokens, bool small) { return tokens > (small ? 11 * stag
 // The kernel of a tile shape: 32 * blocks columns of a 256-row tile, or the small one.
 typedef void (*TileKernel)(const WgradBatch);
 template <int OUT>
-TileKernel tile_kernel_of(bool small, int blocks, bool apart)
+TileKernel tile_kernel_of(bool small, int blocks, bool apart, bool few)
 {
-    if (small) return apart ? &wgrad_small_kernel<OUT, true> : &wgrad_small_kernel<OUT, false>;
+    if (small && apart) return &wgrad_small_kernel<OUT, true, false>;         // long enough for the difference not to show
+    if (small) return few ? &wgrad_small_kernel<OUT, false, true> : &wgrad_small_kernel<OUT, false, false>;
     switch (blocks) {
     case 4: return &wgrad_big_kernel<OUT, 4, true>;
     case 5: return &wgrad_big_kernel<OUT, 5, true>;
@@ -746,10 +757,10 @@ TileKernel tile_kernel_of(bool small, int blocks, bool apart)
     default: return apart ? &wgrad_big_kernel<OUT, 8, true> : &wgrad_big_kernel<OUT, 8, false>;
     }
 }
-TileKernel tile_kernel(int out, bool small, int blocks, bool apart)
+TileKernel tile_kernel(int out, bool small, int blocks, bool apart, bool few)
 {
-    if (out == kOutPartial) return small ? &wgrad_small_kernel<kOutPartial, true> : &wgrad_big_kernel<kOutPartial, 8, true>;
-    return out == kOutF32 ? tile_kernel_of<kOutF32>(small, blocks, apart) : tile_kernel_of<kOutF16>(small, blocks, apart);
+    if (out == kOutPartial) return small ? &wgrad_small_kernel<kOutPartial, true, false> : &wgrad_big_kernel<kOutPartial, 8, true>;
+    return out == kOutF32 ? tile_kernel_of<kOutF32>(small, blocks, apart, few) : tile_kernel_of<kOutF16>(small, blocks, apart, few);
 }
 
 // The LDS size above 64 KiB is a per-device attribute of a kernel: set once per device, where the
@@ -764,10 +775,11 @@ hipError_t configure_once(int *cus)
     if (!(configured.load(std::memory_order_acquire) & bit)) {
         for (int out : {(int)kOutF32, (int)kOutF16, kOutPartial})
             for (int shape = 3; shape <= 8; ++shape)                             // 3: the small tile
-                for (bool apart : {false, true}) {
-                    const void *k = reinterpret_cast<const void *>(tile_kernel(out, shape == 3, shape, apart));
-                    if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes)) return e;
-                }
+                for (bool apart : {false, true})
+                    for (bool few : {false, true}) {
+                        const void *k = reinterpret_cast<const void *>(tile_kernel(out, shape == 3, shape, apart, few));
+                        if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes)) return e;
+                    }
         int n = 0;
         if (hipError_t e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device)) return e;
         cus_of[device & 63] = n;
@@ -819,7 +831,7 @@ void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks
     const dim3 grid((blocks + 7) / 8 * 8), threads(kWgThreads);  // whole rounds of the 8 XCDs; the surplus exits at once
     int64_t tokens = 0;
     for (int j = 0; j < b.jobs; ++j) tokens = b.job[j].tokens > tokens ? b.job[j].tokens : tokens;
-    tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small))<<<grid, threads, kLdsBytes, s>>>(b);
+    tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small), blocks < kFewBlocks)<<<grid, threads, kLdsBytes, s>>>(b);
 }
 
 // What the tile rules price: the longest job's 32-token stages and the kept fraction of all jobs together.

@@ -1451,17 +1451,26 @@ static bool staged_launch(const LaunchSet &ls, StagedLaunch *out)
         <<<dim3((unsigned)st.wgs), dim3(kStagedThreads), st.ls.max_segs * st.merge * kSeg * (st.whole ? 4 : 2), s>>>(st.ls, st.merge, inv_scale, k, guard)
 // Whether a launch of tile_kernel reaches its layers through global instead of flat accesses (pick_tile).  Fewer waits: faster
 // where a workgroup's own chain bounds the launch, level or slower where it only changes what is in flight together.  Adam on the dense
-// gradient, us without and with: 400 M elements at 1 / 2 / 10 % kept 222 and 208, 244 and 241, 448 and 444, the 2.7B model 2712 and 2680; 85 M
-// elements at 3 / 5 / 6.9 % 60.5 and 62.7, 69.4 and 70.1, 78.3 and 78.7, and nothing gained there at 400 M.  SGD 254 and 223 at 1 %, 389 and 386 at 10 %.
+// gradient, us without and with: 400 M elements at 1 / 2 / 10 % kept 222 and 208, 244 and 241, 448 and 444, the 2.7B model 2712 and 2680, at 6 %
+// 2258 and 2209; but 85 / 130 / 200 / 250 M elements at 3 % 60.8 and 62.0, 88.2 and 90.4, 131.6 and 134.8, 165.2 and 168.1, at 6.8 % 76.7 and
+// 77.5, 116.4 and 118.1, 190.1 and 192.1, 241.1 and 241.1.  SGD 254 and 223 at 1 %, 389 and 386 at 10 %.
 // A layer by itself, whose pointers come with the launch, loses 1 to 3.5 % (8192 x 8192 at 20 % 113.1 and 115.8).
 static bool global_access(const LaunchSet &ls, int opt)
 {
-    return ls.layers && (opt == kOptSgd || ls.keep < 0.025f || ls.keep >= (float)kSparseKeep);
+    constexpr int64_t kLongSparse = 30000;       // tiles of 260 to 290 M elements at 3 to 7 % kept
+    return ls.layers && (opt == kOptSgd || ls.keep < 0.025f || ls.keep >= (float)kSparseKeep || ls.wgs >= kLongSparse);
 }
 
-// The same for the expansion of a plan, us without and with: 400 M elements at 3 / 4.5 / 5.5 / 6.8 / 10 / 30 / 80 % kept 152 and 156, 153 and 158, 162 and 156,
-// 178 and 174, 182 and 180, 284 and 283, 544 and 539, everything kept 651 and 680; 85 M elements at 3 % 31.3 and 32.3, at 10 % 37.1 and 36.9.
-static bool expand_global_access(const LaunchSet &ls) { return ls.layers && ls.keep >= 0.055f && ls.keep < 0.9f; }
+// The same for the expansion of a plan, us without and with: 400 M elements at 5.5 / 6.8 / 10 / 30 / 80 % kept 162 and 156, 178 and 174, 182 and
+// 180, 284 and 283, 544 and 539, everything kept 651 and 680.  Below 5.5 % the long ones gain: at 3 % 400 / 600 / 800 M and 2.5 G elements 155 and 157, 219
+// and 226, 311 and 299, 989 and 947, at 4 % 147 and 153, 231 and 226, 317 and 315, 981 and 953, at 2 % 153 and 155, 224 and 225, 285 and 294,
+// 985 and 941; under 2 % none does.
+static bool expand_global_access(const LaunchSet &ls)
+{
+    constexpr int64_t kLong4 = 63000, kLong2 = 80000;        // tiles of 600 M elements at 4 %, of 800 M at 2.5 %
+    if (!ls.layers || ls.keep >= 0.9f) return false;
+    return ls.keep >= 0.055f || (ls.keep >= 0.035f && ls.wgs >= kLong4) || (ls.keep >= 0.02f && ls.wgs >= kLong2);
+}
 
 #define SAMO_LAUNCH_TILE(M, G, O, A)                                                                       \
     tile_kernel<M, G, O, kTileThreads, A><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)

@@ -1378,12 +1378,13 @@ static int occ_flat_gather(int out, int src, float keep, bool with_stats, bool l
 }
 
 // An accumulating gather is long when what it moves (dense gradient, positions, message in and out) is well beyond the 256 MB of the
-// last-level cache.
-constexpr double kLongSum = 400e6;
-// The old message is requested first: one trip less at the end of every wave (42 / 85 / 400 M elements at 10 % kept 22.7 and 21.1 us, 46.9 and
-// 44.3, 192.3 and 190.0).  A long one that keeps under 7 % reads it last: there HBM is the bound and the order only splits its stream
-// (800 M elements at 3 and 5 % 276 and 278, 323 and 333; 1.2 G at 5 % 482 and 499).
-static bool old_message_first(float keep, bool long_sum) { return !long_sum || keep >= (float)kSparseKeep; }
+// last-level cache; very long ones are those of about 800 M elements and more.
+constexpr double kLongSum = 400e6, kVeryLongSum = 2e9;
+// The old message is requested first: one trip less at the end of every wave (us of 42 / 85 / 400 M elements at 10 % kept, last and first: 22.7 and
+// 21.1, 46.9 and 44.3, 192.3 and 190.0).  A long one that keeps little reads it last, there HBM is the bound and the order only splits its
+// stream: under 7 % (800 M elements at 3 and 5 % 276 and 278, 323 and 333; 1.2 G at 5 % 482 and 499), a very long one under 17 % (1.2 G
+// at 9 / 10 / 11 / 12 / 15 % 546 and 570, 564 and 571, 591 and 576, 593 and 612, 646 and 659; 2.5 G at 10 and 15 % 1172 and 1207, 1346 and 1402).
+static bool old_message_first(float keep, double bytes) { return bytes < kLongSum || keep >= (bytes < kVeryLongSum ? (float)kSparseKeep : 0.17f); }
 
 static int occ_flat_step()
 {
@@ -1564,10 +1565,10 @@ hipError_t launch_gather(int out, int src, const LaunchSet &ls, float inv_scale,
     }
     const dim3 grid((unsigned)ls.wgs), block(kFlatThreads);
     const double nnz = (double)ls.wgs * kChunk;
-    const bool long_sum = accumulate && ls.keep > 0.f && 8.0 * nnz + 2.0 * nnz / (double)ls.keep > kLongSum;
-    const int pad = lds_pad_for(occ_flat_gather(out, src, ls.keep, partials != nullptr, long_sum), 2 * kChunk * 4);   // static: the exchange areas
+    const double sum_bytes = accumulate && ls.keep > 0.f ? 8.0 * nnz + 2.0 * nnz / (double)ls.keep : 0.0;
+    const int pad = lds_pad_for(occ_flat_gather(out, src, ls.keep, partials != nullptr, sum_bytes >= kLongSum), 2 * kChunk * 4);   // static: the exchange areas
     if (out == kOutF32) gather_kernel<kOutF32, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
-    else if (out == kOutF16 && old_message_first(ls.keep, long_sum)) gather_kernel<kOutF16, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
+    else if (out == kOutF16 && old_message_first(ls.keep, sum_bytes)) gather_kernel<kOutF16, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
     else if (out == kOutF16) gather_kernel<kOutF16, false><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
     else gather_kernel<kOutNone, true><<<grid, block, pad, s>>>(ls, src, inv_scale, accumulate, partials);
     return hipGetLastError();

@@ -1335,10 +1335,11 @@ static int occ_tile_step(int gsrc, int opt, float keep, float kept)
     // in-place streams are over half the traffic and 6 is the optimum again (0.74 against 0.68 with 8)
     // (where the model keeps so little that its tiles have twice the weight: 4, and 6 with the compressed gradient)
     const bool sparse = keep < (float)kSparseKeep;
-    // Adam where the pruned layers keep a fifth and more: 5 (400 M elements, 20 / 25 / 50 / 80 % kept, 5 and 6 workgroups: 642 and 667 us,
-    // 735 and 782, 1239 and 1255, 1842 and 2068; 10 and 15 % 452 and 444, 545 and 543; SGD 533 and 524 at 20 %, 1390 and 1365 at 80 %).  What an unpruned
+    // Adam where the pruned layers keep nearly a fifth and more: 5 (400 M elements, 20 / 25 / 50 / 80 % kept, 5 and 6 workgroups: 642 and 667 us,
+    // 735 and 782, 1239 and 1255, 1842 and 2068; 10 and 15 % 452 and 444, 545 and 543; at the line, 18.9 % of 435 M 676 and 680-686, of 1.7 G 2519 and 2671,
+    // 18 % 653 and 652, 2481 and 2467; SGD 533 and 524 at 20 %, 1390 and 1365 at 80 %).  What an unpruned
     // embedding adds does not count: three 6.7B layers at 11.5 % with theirs 1756 and 1691
-    const int most = opt == kOptAdam && kept >= 0.19f ? 5 : 6;
+    const int most = opt == kOptAdam && kept >= 0.185f ? 5 : 6;
     if (gsrc == kGradDense) return knob(SAMO_KNOB_OCC_TILE_STEP, sparse ? (opt == kOptSgd ? 3 : 4) : most);
     return knob(SAMO_KNOB_OCC_TILE_C16, (sparse || keep > 0.15f) ? 6 : 0);
 }

@@ -212,87 +212,234 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
     return row0 < A.out && col0 < A.in;
 }
 
-// The kept entries of a tile row are a run of idx between two bounds: the first kept position at
-// or after the row's first column in the tile, and the first one at or after the column where the
-// tile ends.  A bound is searched in three steps with the tile's other work between them:
-// bound_open reads the segment's range from seg_ptr, bound_window requests the entries of idx around
-// where the bound should be, bound_settle decides.
-struct Bound {
-    int lo, hi, key;
-};
-
-__device__ __forceinline__ Bound bound_open(const WgradArgs &A, int row, int col)
-{
-    Bound b = {0, 0, 0};
-    if (row >= A.out) return b;                                   // no such row: an empty run
-    const int64_t p = (int64_t)row * A.in + (col < A.in ? col : A.in);
-    if (p >= (int64_t)A.out * A.in) b.lo = b.hi = (int)A.nnz;
-    else if (!A.idx) b.lo = b.hi = (int)p;                        // nothing pruned: position = entry
-    else {
-        b.lo = A.seg_ptr[p / kSeg];
-        b.hi = A.seg_ptr[p / kSeg + 1];
-        b.key = (int)p;
-    }
-    return b;
-}
-
-// The guess is an interpolation inside the segment (kept elements spread evenly over it would put the
-// bound at lo + (hi - lo) * offset / 1024), the look takes the 32 entries around it as eight vectors:
-// on masks without structure the bound of a segment with k kept of 1024 is within sqrt(k (1 - k / 1024)) / 2
-// of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %), so a look of 32 misses hardly
-// ever, where one of 8 left a third of the bounds of a 10 % mask to a bisection of six dependent loads
-// (2.2 us per tile).  What is left after a miss is bisected.
-// The look is requested by bound_window near the end of the main loop and used by bound_settle after it.
-constexpr int kLook = 32;
+// Epilogue of one wave over ROWS rows of a tile held as an image in LDS (fp16; fp32 sums for kOutPartial).  The kept entries
+// of a row in the tile are a run of idx: from its first entry at or after the row's first column to the last one before
+// the tile's end.  Each half-wave takes every other row, all of them at once, 32 entries of every row a step:
+// idx is read and the compressed gradient written coalesced, the values are picked from the image.
+//
+// Where a run begins is searched in steps with the tile's other work between them.  open() reads the segment's range from seg_ptr;
+// look() reads 32 entries around the place where interpolation inside the segment puts the beginning; settle() decides.
+// Eight lanes, 16 bytes each, look for one row together, so that an instruction reads eight pieces of 128 bytes, and the
+// entries below the row's first column are counted across them.  (What it replaces: a lane by itself read 32 entries for a bound
+// of its own, two bounds to a row, 64 places with every instruction: 3 to 5 us of a workgroup's time where all of a launch's
+// search together.)  Kept elements spread evenly over a segment of k put the beginning within sqrt(k (1 - k / 1024)) / 2
+// of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %).  A look of 32 misses one row in hundreds, but one
+// in most tiles at 20 % kept; a miss is a near one on masks without structure, so a second look beside the first comes before any
+// bisection (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it).  Where a run ends shows when it is read.
+// begin() requests the first AHEAD steps' idx, which travels while the image is written; request_old() the values that are
+// added to, when the accumulators' registers are free.  Before and now, 10 % kept unless said, us: 512 x 512, 100 tokens 6.75 and
+// 6.17; 4096 x 1024, 1003 tokens 15.2 and 14.3; 4096 x 4096, 500 tokens 22.6 and 20.0; 7856 x 4632, 106 tokens, 20 % 50.3 and 43.7;
+// FC1 of the 2.7B model 98.7 and 96.1 (20 %: 105.3 and 102.1).  Rows of very different density (a tenth of them ten times denser) gain
+// less, and up to 8 % is lost on a small layer whose segments straddle rows (512 x 520, 100 tokens 8.6 and 9.3).
 typedef int Look __attribute__((ext_vector_type(4), aligned(4)));
-struct Window {
-    int w0, wn;              // entries w0 .. w0 + wn - 1; wn = 0: nothing was requested
-    Look v[kLook / 4];
+
+// The sum over aligned groups of eight lanes, in every lane.
+__device__ __forceinline__ int sum_of_eight(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);        // quad_perm 1 0 3 2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);        // quad_perm 2 3 0 1
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true); // row_half_mirror
+}
+
+template <int OUT, int ROWS, int AHEAD>
+struct RunPass {
+    static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = 32;
+    static constexpr unsigned kNone = ~0u;   // no entry: further from every row of a layer than a tile is wide
+    int first_row, rows, col0, cols;
+    int lo[kLooks], hi[kLooks];              // row 8 i + lane / 8: the entries between which its run begins; from settle() on lo is where
+    int seen_at[kLooks];                     // -1: nothing was looked at
+    Look seen[kLooks];
+    unsigned from[kRows];                    // row 2 it + half-wave: the step's first entry; unsigned: may pass 2^31 behind a layer's last
+    unsigned pos[AHEAD][kRows];
+    _Float16 old[AHEAD][kRows];
+
+    // The row's first position in the tile (a layer's positions fit 32 bits).
+    __device__ __forceinline__ int key(const WgradArgs &A, int row) const { return (first_row + row) * A.in + col0; }
+    __device__ __forceinline__ int look_row(int i) const { return 8 * i + (int)((threadIdx.x & 63) >> 3); }
+
+    __device__ __forceinline__ void open(const WgradArgs &A, int row0, int column0, int tile_cols)
+    {
+        first_row = row0;
+        col0 = column0;
+        rows = A.out - row0 < ROWS ? A.out - row0 : ROWS;            // not positive: none
+        cols = A.in - col0 < tile_cols ? A.in - col0 : tile_cols;
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            lo[i] = hi[i] = (int)A.nnz;                              // no such row: an empty run
+            if (look_row(i) >= rows) continue;
+            const int p = key(A, look_row(i));
+            lo[i] = hi[i] = p;                                       // nothing pruned: position = entry
+            if (A.idx) {
+                lo[i] = A.seg_ptr[p / kSeg];
+                hi[i] = A.seg_ptr[p / kSeg + 1];
+            }
+        }
+    }
+    __device__ __forceinline__ void look(const WgradArgs &A)
+    {
+        const int last = (int)A.nnz - kLook;                         // the last place a look may start at
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            seen[i] = Look{0, 0, 0, 0};
+            seen_at[i] = -1;
+            if (hi[i] > lo[i] && last >= 0) {
+                const int offset = key(A, look_row(i)) & (kSeg - 1);
+                int at = lo[i] + (((hi[i] - lo[i]) * offset) >> 10) - kLook / 2;
+                at = at > lo[i] ? at : lo[i];
+                seen_at[i] = at < last ? at : last;
+                seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
+            }
+        }
+    }
+    __device__ __forceinline__ void settle(const WgradArgs &A)
+    {
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            const int want = key(A, look_row(i));
+            int below = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
+            below = sum_of_eight(below);
+            // before, inside or behind the look (both ends are written whatever the case: stores to either of two arrays keep them in memory)
+            const bool looked = seen_at[i] >= 0, early = looked && below == 0, late = looked && below == kLook, found = looked && !early && !late;
+            const int at = seen_at[i] + below, l = lo[i], h = hi[i];
+            lo[i] = found || late ? at : l;
+            hi[i] = found ? at : early ? (seen_at[i] > l ? seen_at[i] : l) : h;
+        }
+        bool left = false;
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) left |= lo[i] < hi[i];
+        if (!__ballot(left)) return;
+        // A miss on a mask without structure is a near one: the 32 entries beside the look, on the side it points to.
+        left = false;
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            const int last = (int)A.nnz - kLook;
+            if (lo[i] < hi[i] && last >= 0) {
+                const int beside = lo[i] == seen_at[i] + kLook ? lo[i] : hi[i] - kLook;
+                seen_at[i] = beside < last ? (beside > 0 ? beside : 0) : last;
+                seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            const int l = lo[i], h = hi[i], want = key(A, look_row(i));
+            int below = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
+            below = sum_of_eight(below);
+            const bool looked = l < h && seen_at[i] >= 0;
+            const int at = seen_at[i] + below;                       // the first entry of the look that is not below
+            lo[i] = looked && below > 0 ? (at > l ? at : l) : l;
+            hi[i] = looked && below < kLook ? (at < h ? at : h) : h;
+            if (looked && below == 0 && hi[i] < l) hi[i] = l;
+            left |= lo[i] < hi[i];
+        }
+        while (left) {                                               // all the searches a step at a time
+            int there[kLooks];
+#pragma unroll
+            for (int i = 0; i < kLooks; ++i) there[i] = lo[i] < hi[i] ? A.idx[(lo[i] + hi[i]) >> 1] : 0;
+            left = false;
+#pragma unroll
+            for (int i = 0; i < kLooks; ++i) {
+                const int l = lo[i], h = hi[i], mid = (l + h) >> 1;
+                const bool open = l < h, before = there[i] < key(A, look_row(i));
+                lo[i] = open && before ? mid + 1 : l;
+                hi[i] = open && !before ? mid : h;
+                left |= lo[i] < hi[i];
+            }
+        }
+    }
+    __device__ __forceinline__ void request(const WgradArgs &A)
+    {
+        const unsigned l32 = threadIdx.x & 31, nnz = (unsigned)A.nnz;
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a)
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) {
+                const unsigned k = from[it] + a * 32 + l32;
+                pos[a][it] = k < nnz ? (A.idx ? (unsigned)A.idx[k] : k) : kNone;
+            }
+    }
+    // Column in the tile of the lane's entry of row 2 it + half-wave; not below cols: it isn't in the row's run.
+    __device__ __forceinline__ unsigned column(const WgradArgs &A, int a, int it) const
+    {
+        return pos[a][it] - (unsigned)key(A, 2 * it + (int)((threadIdx.x & 63) >> 5));
+    }
+    // Whether any row of the wave has entries in step a of those requested (all of the first, and all of passes of
+    // many rows, are taken to have).
+    __device__ __forceinline__ bool wanted(const WgradArgs &A, int a) const
+    {
+        if (a == 0 || kRows > 8) return true;
+        bool in = false;
+#pragma unroll
+        for (int it = 0; it < kRows; ++it) in |= column(A, a, it) < (unsigned)cols;
+        return __ballot(in) != 0;
+    }
+    __device__ __forceinline__ void request_old(const WgradArgs &A)
+    {
+        if (OUT != kOutF16 || !A.accumulate) return;
+        asm volatile("" ::: "memory");                               // not before the image is written
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            if (!wanted(A, a)) break;
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) {
+                const bool in = column(A, a, it) < (unsigned)cols;
+                old[a][it] = in ? reinterpret_cast<const _Float16 *>(A.gc)[from[it] + a * 32 + (threadIdx.x & 31)] : (_Float16)0.f;
+            }
+        }
+    }
+    __device__ __forceinline__ void begin(const WgradArgs &A)
+    {
+        const int h = (threadIdx.x & 63) >> 5;
+#pragma unroll
+        for (int it = 0; it < kRows; ++it) from[it] = (unsigned)__shfl(lo[it / 4], 8 * ((2 * it & 7) + h), 64);
+        request(A);
+    }
+    // The entries requested; returns, in lanes 31 and 63, whether a row's run may go on behind the last of them.
+    // img: the image's row of the pass's first row.
+    template <typename Pixel>
+    __device__ __forceinline__ bool step(const WgradArgs &A, const Pixel *img, int pitch)
+    {
+        const int h = (threadIdx.x & 63) >> 5;
+        bool on = false;
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            if (!wanted(A, a)) return false;
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) {
+                const unsigned at = column(A, a, it), k = from[it] + a * 32 + (threadIdx.x & 31);
+                const bool in = at < (unsigned)cols;
+                if (a == AHEAD - 1) on |= at < (unsigned)cols - 1;
+                const Pixel v = img[(2 * it + h) * pitch + (in ? at : 0)];        // all rows' reads in flight together
+                if (!in) continue;
+                if (OUT == kOutPartial) reinterpret_cast<float *>(A.gc)[k] = (float)v;
+                else if (OUT == kOutF32) reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
+                else reinterpret_cast<_Float16 *>(A.gc)[k] = A.accumulate ? (_Float16)(old[a][it] + v) : v;
+            }
+        }
+        return on;
+    }
+    template <typename Pixel>
+    __device__ __forceinline__ void finish(const WgradArgs &A, const Pixel *img, int pitch)
+    {
+        while (__ballot(step(A, img, pitch)) & 0x8000000080000000ull) {
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) from[it] += 32 * AHEAD;
+            request(A);
+            request_old(A);
+        }
+    }
 };
 
-// First entry of vector i of a window: the last ones of a short range overlap, every vector lies inside it.
-__device__ __forceinline__ int look_start(const Window &w, int i)
-{
-    return w.w0 + (4 * i + 4 <= w.wn ? 4 * i : w.wn - 4);
-}
-
-__device__ __forceinline__ Window bound_window(const WgradArgs &A, const Bound &b)
-{
-    Window w;
-    w.w0 = 0; w.wn = 0;
-#pragma unroll
-    for (int i = 0; i < kLook / 4; ++i) w.v[i] = Look{0, 0, 0, 0};
-    if (b.hi - b.lo >= 4) {
-        const int guess = b.lo + (int)(((int64_t)(b.hi - b.lo) * (b.key & (kSeg - 1))) >> 10);
-        w.w0 = guess - kLook / 2 > b.lo ? guess - kLook / 2 : b.lo;
-        if (w.w0 + kLook > b.hi) w.w0 = b.hi - kLook > b.lo ? b.hi - kLook : b.lo;
-        w.wn = b.hi - w.w0 < kLook ? b.hi - w.w0 : kLook;
-#pragma unroll
-        for (int i = 0; i < kLook / 4; ++i) w.v[i] = *reinterpret_cast<const Look *>(A.idx + look_start(w, i));
-    }
-    return w;
-}
-
-__device__ __forceinline__ int bound_settle(const WgradArgs &A, Bound b, const Window &w)
-{
-    if (w.wn > 0) {
-        int at = w.w0;                                           // after the last entry of the look that is below the key
-#pragma unroll
-        for (int i = 0; i < kLook / 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (w.v[i][e] < b.key) at = look_start(w, i) + e + 1;
-        if (at == w.w0) b.hi = w.w0;                             // the bound is at or before the look
-        else if (at == w.w0 + w.wn) b.lo = at;                   // at or after its end
-        else b.lo = b.hi = at;                                   // inside
-    }
-    while (b.lo < b.hi) {
-        const int mid = (b.lo + b.hi) >> 1;
-        if (A.idx[mid] < b.key) b.lo = mid + 1;
-        else b.hi = mid;
-    }
-    return b.lo;
-}
+// The two passes of a wave over a tile whose sums are held in LDS half of the rows at a time.
+template <typename Pass>
+struct TwoPasses {
+    Pass half[2];
+    __device__ __forceinline__ void look(const WgradArgs &A) { half[0].look(A); half[1].look(A); }
+    __device__ __forceinline__ void settle(const WgradArgs &A) { half[0].settle(A); half[1].settle(A); }
+};
 
 // Waits until at most `younger` stages' copies of this wave are outstanding (and every LDS read has returned).
 __device__ __forceinline__ void wait_copies(int64_t younger)
@@ -313,8 +460,8 @@ __device__ __forceinline__ void meet()
 // LDS rows, row j < 16 row_tokens(TILE) consecutive tokens of X (room for TILE features each), row 16 + j
 // the same tokens of dY.
 // Waves 0-3 (group 0) copy X, waves 4-7 (group 1) dY.  x_at / y_at: byte offset, within a row, of the
-// wave's first feature of the first of the two tokens it multiplies per row.  Returns the thread's bound;
-// the ring is free after the next __syncthreads.
+// wave's first feature of the first of the two tokens it multiplies per row.  The epilogue's look
+// and its outcome come with the last stages; the ring is free after the next __syncthreads.
 //
 // The groups' half stages, b(i) the barriers all eight waves meet at:
 //   group 0:  b(0) fetch 0  b(1) multiply 0  b(2) fetch 1  b(3) multiply 1 ...
@@ -323,20 +470,20 @@ __device__ __forceinline__ void meet()
 // slot of stage s - 1: group 1, the later one, has finished reading that slot before b(2s).  Stage
 // s + 1 is read from b(2s + 2) on, so every wave waits for its own copies of it before that barrier —
 // group 0 at the end of multiply s, group 1 at the end of fetch s — when the copies of stages s + 2
-// and s + 3 are the only younger ones.  The loads of bound_open are older than every copy.  Those of
-// bound_window are requested when the last full stage is on its way: the wait for bound_open's results
+// and s + 3 are the only younger ones.  The loads of run.open are older than every copy.  Those of
+// run.look are requested when the last full stage is on its way: the wait for run.open's results
 // is a wait for every copy in flight, once, where only one or two stages are; after it they can only make
 // the waits of the last stages longer than needed, never shorter.
 //
 // Not APART, all waves take a stage together, one barrier each: fetch s and multiply s are one step, the copies of stage
 // s + 3 go into the slot of stage s - 1, which every wave has finished reading before the barrier of step s.  That
 // saves the half stage at either end and the second barrier, and is quicker where a call has few stages
-// (loop_apart).  bound_window comes first in the small tile, whose registers allow it, and travels under the whole
+// (loop_apart).  run.look comes first in the small tile, whose registers allow it, and travels under the whole
 // loop; the large tile requests it where the other loop does.  Its wait for every copy in flight is
 // made explicit and remembered.
-template <int TILE, int COLS, bool APART, int OB, int IB>
-__device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
-                                                const Bound &open, f32x4 (&acc)[OB][IB])
+template <int TILE, int COLS, bool APART, typename Run, int OB, int IB>
+__device__ __forceinline__ void multiply_tile(const WgradArgs &A, int row0, int col0, int x_at, int y_at, unsigned char *lds,
+                                                Run &run, f32x4 (&acc)[OB][IB])
 {
     constexpr int kRowTokens = row_tokens(TILE), kTokens = stage_tokens(TILE), kTokenLanes = 64 / kRowTokens;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -388,14 +535,12 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
         slot = slot == (kStages - 1) * kStageBytes ? 0 : slot + kStageBytes;
     };
     if constexpr (!APART) {
-        Window window;
-        window.w0 = 0; window.wn = 0;
         const int64_t look = TILE == kSmallTile || full <= 3 ? 0 : full - 3;
         int64_t arrived = 0;                                 // stages whose copies are known to be there
         for (int64_t s = 0; s < stages; ++s) {
             if (s == look) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                window = bound_window(A, open);
+                run.look(A);
                 arrived = s + 3;
             }
             if (s < arrived) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -416,8 +561,10 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             advance();
         }
+        if (stages == 0) run.look(A);
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        return bound_settle(A, open, window);
+        run.settle(A);
+        return;
     }
     wait_copies(stages - 1);
     meet();                                                  // b(0)
@@ -459,87 +606,12 @@ __device__ __forceinline__ int multiply_tile(const WgradArgs &A, int row0, int c
     };
     int64_t s = 0;
     for (; s + 3 < full; ++s) stage(s, std::true_type{});
-    const Window window = bound_window(A, open);
+    run.look(A);
     for (; s < stages; ++s) stage(s, std::false_type{});
     if (group == 0) meet();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    return bound_settle(A, open, window);
+    run.settle(A);
 }
-
-// Epilogue over the ROWS rows of a tile held as an image in LDS (fp16; fp32 sums for kOutPartial): each of the 16 half-waves
-// takes every 16th row, all of them at once; per row, idx between the row's two bounds is read
-// coalesced, the values are picked from the image and the compressed gradient is written
-// coalesced, 32 entries of every row a step.  What a step needs from memory (idx, and the old values where it
-// accumulates) is requested for kAhead steps together; the first kAhead steps' idx is requested by
-// begin(), before the image exists, and travels while it is written; the old values by request_old(), when
-// the accumulators' registers are free.
-template <int OUT, int ROWS>
-struct GatherPass {
-    static constexpr int kRows = ROWS / (kWgThreads / 32), kAhead = 2;
-    int lo[kRows], hi[kRows], longest;
-    int pos[kAhead][kRows];                  // -1: past the end of the row's run
-    _Float16 old[kAhead][kRows];
-
-    __device__ __forceinline__ void request_idx(const WgradArgs &A, int step)
-    {
-        const int l32 = threadIdx.x & 31;
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-#pragma unroll
-            for (int it = 0; it < kRows; ++it) {
-                const int k = lo[it] + (step + a) * 32 + l32;
-                pos[a][it] = k < hi[it] ? (A.idx ? A.idx[k] : k) : -1;
-            }
-    }
-    __device__ __forceinline__ void request_old(const WgradArgs &A, int step)
-    {
-        if (OUT != kOutF16 || !A.accumulate) return;
-        const int l32 = threadIdx.x & 31;
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-#pragma unroll
-            for (int it = 0; it < kRows; ++it) {
-                const int k = lo[it] + (step + a) * 32 + l32;
-                old[a][it] = k < hi[it] ? reinterpret_cast<const _Float16 *>(A.gc)[k] : (_Float16)0.f;
-            }
-    }
-    __device__ __forceinline__ void begin(const WgradArgs &A, const int *first, const int *last)
-    {
-        const int hw = threadIdx.x >> 5;
-        longest = 0;
-#pragma unroll
-        for (int it = 0; it < kRows; ++it) {
-            lo[it] = first[it * 16 + hw];
-            hi[it] = last[it * 16 + hw];
-            longest = hi[it] - lo[it] > longest ? hi[it] - lo[it] : longest;
-        }
-        request_idx(A, 0);
-    }
-    template <typename Pixel>
-    __device__ __forceinline__ void finish(const WgradArgs &A, const Pixel *img, int pitch, int first_row, int col0)
-    {
-        const int hw = threadIdx.x >> 5, l32 = threadIdx.x & 31;
-        for (int step = 0; step * 32 < longest; step += kAhead) {
-            if (step > 0) {
-                request_idx(A, step);
-                request_old(A, step);
-            }
-#pragma unroll
-            for (int a = 0; a < kAhead; ++a)
-#pragma unroll
-                for (int it = 0; it < kRows; ++it) {
-                    if (pos[a][it] < 0) continue;
-                    const int k = lo[it] + (step + a) * 32 + l32;
-                    const int rl = it * 16 + hw;
-                    // positions of a layer fit 32 bits
-                    const Pixel v = img[rl * pitch + (pos[a][it] - ((first_row + rl) * A.in + col0))];
-                    if (OUT == kOutPartial) reinterpret_cast<float *>(A.gc)[k] = (float)v;
-                    else if (OUT == kOutF32) reinterpret_cast<float *>(A.gc)[k] = (float)v * A.inv_scale;
-                    else reinterpret_cast<_Float16 *>(A.gc)[k] = A.accumulate ? (_Float16)(old[a][it] + v) : v;
-                }
-        }
-    }
-};
 
 // 256 x (32 IB) tile, IB = 8 or fewer for calls of less than a round: 64 (out) x 16 IB (in) per wave, waves as 4 x 2;
 // both groups multiply every token.
@@ -548,26 +620,25 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
 {
     constexpr int kTile = kBigTile, kCols = 32 * IB, kEpiPitch = kCols + 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ int bounds[2 * kTile];
     WgradArgs A;
     int row0, col0;
     if (!tile_origin<true>(B, A, row0, col0)) return;
 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    // thread t < 256: the first bound of tile row t; thread 256 + t: its second
-    const Bound open = bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kCols);
     const int wo = wave & 3, wi = wave >> 2;
     f32x4 acc[4][IB];
-    bounds[t] = multiply_tile<kTile, kCols, APART>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, open, acc);
-    __syncthreads();
     if constexpr (OUT == kOutPartial) {                      // fp32 sums: the ring holds half of the rows at a time
-        constexpr int kHalf = kTile / 2, kSumPitch = kCols + 4;
+        constexpr int kHalf = kTile / 2, kSumPitch = kCols + 4, kRows = kHalf / 8;
         static_assert(kHalf * kSumPitch * 4 <= kLdsBytes, "half of the tile's sums fit in the stages");
+        TwoPasses<RunPass<OUT, kRows, 2>> run;               // of each half wave w gathers rows 16 w ..
+        for (int half = 0; half < 2; ++half) run.half[half].open(A, row0 + half * kHalf + wave * kRows, col0, kCols);
+        multiply_tile<kTile, kCols, APART>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, run, acc);
         float *sums = reinterpret_cast<float *>(lds);
+#pragma unroll
         for (int half = 0; half < 2; ++half) {
-            GatherPass<OUT, kHalf> gather;
-            gather.begin(A, bounds + half * kHalf, bounds + kTile + half * kHalf);
+            __syncthreads();
+            run.half[half].begin(A);
             if (wo >> 1 == half) {
 #pragma unroll
                 for (int bo = 0; bo < 4; ++bo)
@@ -578,13 +649,15 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
                     }
             }
             __syncthreads();
-            gather.finish(A, sums, kSumPitch, row0 + half * kHalf, col0);
-            __syncthreads();
+            run.half[half].finish(A, sums + wave * kRows * kSumPitch, kSumPitch);
         }
         return;
     }
-    GatherPass<OUT, kTile> gather;
-    gather.begin(A, bounds, bounds + kTile);
+    RunPass<OUT, kTile / 8, 2> run;                          // wave w gathers rows 32 w ..
+    run.open(A, row0 + wave * 32, col0, kCols);
+    multiply_tile<kTile, kCols, APART>(A, row0, col0, wi * (kCols / 2) * 2, wo * 64 * 2, lds, run, acc);
+    __syncthreads();
+    run.begin(A);
 
     // accumulator layout: lane l holds dW[.. + (l & 15)][.. + 4 * (l >> 4) + r], r = 0..3
     _Float16 *img = reinterpret_cast<_Float16 *>(lds);
@@ -599,9 +672,9 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
             const int col = wi * (kCols / 2) + bi * 16 + (lane >> 4) * 4;
             *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
         }
-    gather.request_old(A, 0);
+    run.request_old(A);
     __syncthreads();
-    gather.finish(A, img, kEpiPitch, row0, col0);
+    run.finish(A, img + wave * 32 * kEpiPitch, kEpiPitch);
 }
 
 // 128 x 128 tile: 64 x 64 per wave, the waves of a group as 2 x 2; group g multiplies tokens 2g and 2g + 1 of every row.
@@ -614,24 +687,21 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
     constexpr int kTile = kSmallTile, kEpiPitch = kTile + 8, kSumPitch = kTile + 4;
     static_assert(kTile * kSumPitch * 4 + kTile * kEpiPitch * 2 <= kLdsBytes, "group 1's sums and the image reuse the stages");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ int bounds[2 * kTile];
     WgradArgs A;
     int row0, col0;
     if (!tile_origin<!FEW>(B, A, row0, col0)) return;
 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    // thread t < 128: the first bound of tile row t; thread 128 + t: its second; the rest: none
-    const Bound open = t < 2 * kTile ? bound_open(A, row0 + (t & (kTile - 1)), t < kTile ? col0 : col0 + kTile) : Bound{0, 0, 0};
+    RunPass<OUT, kTile / 8, 2> run;                          // wave w gathers rows 16 w ..
+    run.open(A, row0 + wave * 16, col0, kTile);
     const int half = wave >> 2;
     const int wo = wave & 1, wi = (wave >> 1) & 1;
     f32x4 acc[4][4];
     const int tokens_at = half * 2 * kTile * 2;
-    const int closed = multiply_tile<kTile, kTile, APART>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, open, acc);
-    if (t < 2 * kTile) bounds[t] = closed;
+    multiply_tile<kTile, kTile, APART>(A, row0, col0, tokens_at + wi * 64 * 2, tokens_at + wo * 64 * 2, lds, run, acc);
     __syncthreads();
-    GatherPass<OUT, kTile> gather;
-    gather.begin(A, bounds, bounds + kTile);
+    run.begin(A);
 
     // group 1's sums -> LDS as fp32; group 0 adds them to its own, rounds once to fp16 and writes
     // the image behind them
@@ -668,10 +738,10 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
                 *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
             }
     }
-    gather.request_old(A, 0);
+    run.request_old(A);
     __syncthreads();
-    if constexpr (OUT == kOutPartial) gather.finish(A, sums, kSumPitch, row0, col0);
-    else gather.finish(A, img, kEpiPitch, row0, col0);
+    if constexpr (OUT == kOutPartial) run.finish(A, sums + wave * 16 * kSumPitch, kSumPitch);
+    else run.finish(A, img + wave * 16 * kEpiPitch, kEpiPitch);
 }
 
 // Adds the splits' sums of every kept element in split order, rounds once to fp16 and stores as the

@@ -1,0 +1,72 @@
+"""The weight gradient's epilogue where the search for a tile row's run of kept entries can go wrong: layers with fewer entries than
+a look reads, segments whose kept elements sit at one end (the guess misses on either side), runs longer than the entries requested ahead,
+runs that end with a tile, a segment or the index."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2302_05045_amd as samo
+import samo_inputs as si
+from gpu_util import DEV, dev_f16_bits, dev_i32, host_bits, ref_seg_ptr
+from test_gpu_wgrad import _bracket, _check_f16
+
+pytestmark = pytest.mark.gpu
+
+
+def _kept(kind, out_f, in_f):
+    m = np.zeros((out_f, in_f), np.uint8)
+    flat = m.reshape(-1)
+    if kind.startswith("first"):                       # the first k elements of the layer alone
+        flat[:int(kind[5:])] = 1
+    elif kind.startswith("last"):
+        flat[flat.size - int(kind[4:]):] = 1
+    elif kind == "heads":                              # the first 200 of every segment: guesses too early
+        flat[np.arange(flat.size) % 1024 < 200] = 1
+    elif kind == "tails":                              # the last 200: guesses too late
+        flat[np.arange(flat.size) % 1024 >= 824] = 1
+    elif kind == "full_rows":                          # every third row whole, the others two elements at tile edges
+        m[::3] = 1
+        m[1::3, ::128] = 1
+    elif kind == "columns":                            # whole columns around the tiles' edges
+        for c in (0, 127, 128, 255, 256, in_f - 1):
+            if c < in_f:
+                m[:, c] = 1
+    elif kind == "runs33":                             # 33 and 65 entries in a row of a tile: one past a step, one past two
+        m[::2, 10:43] = 1
+        m[1::2, 20:85] = 1
+    else:
+        raise KeyError(kind)
+    return flat
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("out_f,in_f", [(16, 136), (264, 520), (40, 1032)])
+@pytest.mark.parametrize("kind", ["first1", "first31", "first32", "first33", "last1", "last31", "last33", "heads", "tails",
+                                  "full_rows", "columns", "runs33"])
+def test_runs_are_found(kind, out_f, in_f, tile):
+    tokens, seed = 37, 4
+    dy, x = si.output_grads_fp16(tokens, out_f, seed), si.activations_fp16(tokens, in_f, seed)
+    idx = oracle.build_index(_kept(kind, out_f, in_f))
+    nnz = idx.shape[0]
+    d_dy, d_x = dev_f16_bits(dy).view(tokens, out_f), dev_f16_bits(x).view(tokens, in_f)
+    d_idx, d_seg = dev_i32(idx), dev_i32(ref_seg_ptr(idx, out_f * in_f))
+    want = oracle.wgrad_compress(dy, x, tokens, out_f, in_f, idx)
+    lo, hi = _bracket(dy, x, tokens, out_f, in_f, idx)
+    gc16 = torch.full((nnz + 8,), float("nan"), dtype=torch.float16, device=DEV)
+    gc = torch.full((nnz + 8,), float("nan"), device=DEV)
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)
+    samo.samo_debug_set(samo.KNOB_WGRAD_TILE, tile)
+    try:
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], workspace=none)
+        samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0, gc[:nnz], workspace=none)
+        torch.cuda.synchronize()
+        bits = host_bits(gc16[:nnz])
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], accumulate=True, workspace=none)
+        torch.cuda.synchronize()
+    finally:
+        samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+    _check_f16(bits, lo, hi, want, kind)
+    assert np.array_equal(gc[:nnz].cpu().numpy(), bits.view(np.float16).astype(np.float32))
+    assert np.array_equal(host_bits(gc16[:nnz]), (bits.view(np.float16) + bits.view(np.float16)).astype(np.float16).view(np.uint16))
+    assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"

@@ -483,10 +483,12 @@ samo_status samo_mfma_rate_probe(int64_t iters, float *d_sink, int32_t workgroup
  *                        (64 KiB of mask per pass and workgroup; default: 4 for launches with at least a dozen blocks
  *                        of that size per compute unit, else 2 or 1).  Calls that only count, and the fill, have blocks
  *                        of their own.
- *   SAMO_KNOB_WGRAD_TILE   128 or 256: forces the tile shape of the weight-gradient entries
+ *   SAMO_KNOB_WGRAD_TILE   128 or 256: forces the tile shape of the weight-gradient entries; 512: 128 x 128
+ *                        tiles, four workgroups to a compute unit
  *                        (default: 256 x 256 in whole rounds of the compute units and 128 x 128 for a
  *                        remainder of at most half a round; calls of less than a round take 128 x 128
- *                        or narrower tiles of 256 rows, whichever fills the device better).
+ *                        or narrower tiles of 256 rows, whichever fills the device better; short calls of
+ *                        more 128 x 128 tiles than compute units take four of those to a unit).
  *   SAMO_KNOB_WGRAD_ROUND  test aid: the number of tiles taken as one round in that rule, in
  *                        place of the device's compute-unit count.
  *   SAMO_KNOB_WGRAD_SPLIT  workgroups that share a tile of a weight gradient with a workspace (at most 64); 1: never split.  Applies to

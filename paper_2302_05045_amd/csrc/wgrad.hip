@@ -27,7 +27,9 @@
 //   128 x 128 for smaller calls, and for what is left of a call after whole rounds of large tiles where
 //   that is at most half a round: each group covers the whole tile with 64 x 64 per wave (64
 //   accumulators) and multiplies half of the tokens of every 64-token stage; group 1 hands its sums to
-//   group 0 through LDS at the end.
+//   group 0 through LDS at the end;
+//   128 x 128 by four waves, four workgroups to a compute unit, for short calls of more tiles than compute units
+//   (wgrad_resident_kernel: a kernel of its own; what is said here of rings and groups is of the others).
 // Calls of few tiles may have their tokens split over several workgroups per tile (plan_split).
 // Short calls go through the stages with all waves in step (loop_apart).
 //
@@ -68,6 +70,7 @@ constexpr int kStageBytes = kStageRows * kRowPitch;  // 33792
 constexpr int kStages = 4;
 constexpr int kLdsBytes = kStages * kStageBytes;     // 135168: one workgroup per CU
 constexpr int kBigTile = 256, kSmallTile = 128;
+constexpr int kGroupDepth = 4;                       // tile rows of a group of tiles that share operand panels
 // Tokens of one operand in an LDS row, and in a stage (16 rows of each operand).
 constexpr int row_tokens(int tile) { return 512 / tile; }
 constexpr int stage_tokens(int tile) { return 16 * row_tokens(tile); }       // 32, 64
@@ -93,14 +96,14 @@ struct WgradArgs {
 struct WgradBatch {
     WgradJob job[kWgradMaxJobs];
     int tiles_out[kWgradMaxJobs], tiles_in[kWgradMaxJobs];
-    uint32_t per_group[kWgradMaxJobs];       // 2^32 / (4 * tiles_in), rounded up
+    uint32_t per_group[kWgradMaxJobs];       // 2^32 / (tile rows of a group * tiles_in), rounded up
     int first_tile[kWgradMaxJobs + 1];       // 32 bits: a layer of less than 2^31 elements, sides up to 2^24, has about 10^5 tiles at most
     int jobs;
     float inv_scale;
     int accumulate;
     int quadrants;
     int first, tiles;
-    int tile_cols;                           // columns of a tile that is not quartered: 256, or 128, 160 or 192
+    int tile_cols;                           // columns of a tile that is not quartered: 256, or 128, 160 or 192; 128 of the resident shape
     // splits > 1: that many workgroups share a tile, each multiplies split_tokens[j] tokens and leaves its fp32
     // sums at the kept positions in partial[j] + split * partial_stride[j]; wgrad_sum_kernel adds them up.
     int splits;
@@ -109,6 +112,7 @@ struct WgradBatch {
     int64_t partial_stride[kWgradMaxJobs];
 };
 constexpr int kOutPartial = 3;
+constexpr int kResidentShape = 512;         // SAMO_KNOB_WGRAD_TILE: 128 x 128 tiles, four workgroups to a compute unit
 constexpr int kMaxSplits = 64;              // what SAMO_KNOB_WGRAD_SPLIT may ask for; the rule takes up to 16
 
 __device__ __attribute__((aligned(16))) const unsigned char wgrad_zero_row[16] = {0};
@@ -147,8 +151,8 @@ __device__ __forceinline__ half8 read_fragment(const unsigned char *p, int step)
 // at a time then share about 4 + 8 operand panels rather than 1 + 32.
 // Returns false for a workgroup with nothing to do: the surplus of the last round, or a quarter
 // that lies outside the matrix.
-// JOB_FIRST: the job's descriptor is requested with the launch's fields.
-template <bool JOB_FIRST>
+// JOB_FIRST: the job's descriptor is requested with the launch's fields.  The list's tiles have TILE_ROWS rows.
+template <bool JOB_FIRST, int TILE_ROWS = kBigTile>
 __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, int &row0, int &col0)
 {
     // The workgroup's first copies wait for this function, and what it reads comes from the kernel arguments by way of
@@ -197,13 +201,13 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
         A.gc = B.partial[j] + split * B.partial_stride[j];
     }
     const int tile = listed - first;
-    // tile / (4 * tiles_in) by the reciprocal the host prepared (2^32 over it, rounded up: one too many at most)
+    // tile / (kGroupDepth * tiles_in) by the reciprocal the host prepared (2^32 over it, rounded up: one too many at most)
     int group = (int)(((uint64_t)(uint32_t)tile * per_group) >> 32);
-    if (group * 4 * tiles_in > tile) --group;
-    const int in_group = tile - group * 4 * tiles_in;
-    const int group_rows = tiles_out - group * 4 < 4 ? tiles_out - group * 4 : 4;
-    const int across = group_rows == 4 ? in_group >> 2 : in_group / group_rows;
-    row0 = (group * 4 + in_group - across * group_rows) * kBigTile;   // first row of dW (feature of dY)
+    if (group * kGroupDepth * tiles_in > tile) --group;
+    const int in_group = tile - group * kGroupDepth * tiles_in;
+    const int group_rows = tiles_out - group * kGroupDepth < kGroupDepth ? tiles_out - group * kGroupDepth : kGroupDepth;
+    const int across = group_rows == kGroupDepth ? in_group / kGroupDepth : in_group / group_rows;
+    row0 = (group * kGroupDepth + in_group - across * group_rows) * TILE_ROWS;   // first row of dW (feature of dY)
     col0 = across * tile_cols;                             // first column of dW (feature of X)
     if (quadrants) {
         row0 += (local & 1) * kSmallTile;
@@ -226,8 +230,10 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
 // of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %).  A look of 32 misses one row in hundreds, but one
 // in most tiles at 20 % kept; a miss is a near one on masks without structure, so a second look beside the first comes before any
 // bisection (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it).  Where a run ends shows when it is read.
-// begin() requests the first AHEAD steps' idx, which travels while the image is written; request_old() the values that are
-// added to, when the accumulators' registers are free.  Before and now, 10 % kept unless said, us: 512 x 512, 100 tokens 6.75 and
+// begin() requests the first AHEAD steps' idx, which travels while the image is written, and the values that are added to:
+// with EARLY at once, else when their positions are known and the image is written (the 128 x 128 tile of the longer calls, 4096 x 1024, 1003
+// tokens, accumulating 15.6 against 15.85 us; FC1 of the 2.7B model 102.9 against 102.1 the other way, four workgroups to a compute unit
+// 3 to 5 %).  Before and now, 10 % kept unless said, us: 512 x 512, 100 tokens 6.75 and
 // 6.17; 4096 x 1024, 1003 tokens 15.2 and 14.3; 4096 x 4096, 500 tokens 22.6 and 20.0; 7856 x 4632, 106 tokens, 20 % 50.3 and 43.7;
 // FC1 of the 2.7B model 98.7 and 96.1 (20 %: 105.3 and 102.1).  Rows of very different density (a tenth of them ten times denser) gain
 // less, and up to 8 % is lost on a small layer whose segments straddle rows (512 x 520, 100 tokens 8.6 and 9.3).
@@ -241,7 +247,7 @@ __device__ __forceinline__ int sum_of_eight(int v)
     return v + __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true); // row_half_mirror
 }
 
-template <int OUT, int ROWS, int AHEAD>
+template <int OUT, int ROWS, int AHEAD, bool EARLY = true>
 struct RunPass {
     static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = 32;
     static constexpr unsigned kNone = ~0u;   // no entry: further from every row of a layer than a tile is wide
@@ -350,6 +356,7 @@ struct RunPass {
             }
         }
     }
+    // A step's positions; with EARLY also the values that are added to.
     __device__ __forceinline__ void request(const WgradArgs &A)
     {
         const unsigned l32 = threadIdx.x & 31, nnz = (unsigned)A.nnz;
@@ -360,35 +367,39 @@ struct RunPass {
                 const unsigned k = from[it] + a * 32 + l32;
                 pos[a][it] = k < nnz ? (A.idx ? (unsigned)A.idx[k] : k) : kNone;
             }
+        if (EARLY) request_old(A);
+    }
+    // The values that are added to.  Those of entries behind the run belong to other tiles, whose workgroups may be writing
+    // them: they are read to have all of them on their way at once, and not used.
+    __device__ __forceinline__ void request_old(const WgradArgs &A)
+    {
+        if (OUT != kOutF16 || !A.accumulate) return;
+        if (!EARLY) asm volatile("" ::: "memory");                   // not before the image is written
+        const unsigned l32 = threadIdx.x & 31, nnz = (unsigned)A.nnz;
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            if (!EARLY && !wanted(A, a)) break;
+#pragma unroll
+            for (int it = 0; it < kRows; ++it) {
+                const unsigned k = from[it] + a * 32 + l32;
+                const bool there = EARLY ? k < nnz : column(A, a, it) < (unsigned)cols;
+                old[a][it] = there ? reinterpret_cast<const _Float16 *>(A.gc)[k] : (_Float16)0.f;
+            }
+        }
     }
     // Column in the tile of the lane's entry of row 2 it + half-wave; not below cols: it isn't in the row's run.
     __device__ __forceinline__ unsigned column(const WgradArgs &A, int a, int it) const
     {
         return pos[a][it] - (unsigned)key(A, 2 * it + (int)((threadIdx.x & 63) >> 5));
     }
-    // Whether any row of the wave has entries in step a of those requested (all of the first, and all of passes of
-    // many rows, are taken to have).
+    // Whether any row of the wave has entries in step a of those requested (of the first, some row is taken to have).
     __device__ __forceinline__ bool wanted(const WgradArgs &A, int a) const
     {
-        if (a == 0 || kRows > 8) return true;
+        if (a == 0) return true;
         bool in = false;
 #pragma unroll
         for (int it = 0; it < kRows; ++it) in |= column(A, a, it) < (unsigned)cols;
         return __ballot(in) != 0;
-    }
-    __device__ __forceinline__ void request_old(const WgradArgs &A)
-    {
-        if (OUT != kOutF16 || !A.accumulate) return;
-        asm volatile("" ::: "memory");                               // not before the image is written
-#pragma unroll
-        for (int a = 0; a < AHEAD; ++a) {
-            if (!wanted(A, a)) break;
-#pragma unroll
-            for (int it = 0; it < kRows; ++it) {
-                const bool in = column(A, a, it) < (unsigned)cols;
-                old[a][it] = in ? reinterpret_cast<const _Float16 *>(A.gc)[from[it] + a * 32 + (threadIdx.x & 31)] : (_Float16)0.f;
-            }
-        }
     }
     __device__ __forceinline__ void begin(const WgradArgs &A)
     {
@@ -428,7 +439,7 @@ struct RunPass {
 #pragma unroll
             for (int it = 0; it < kRows; ++it) from[it] += 32 * AHEAD;
             request(A);
-            request_old(A);
+            if (!EARLY) request_old(A);
         }
     }
 };
@@ -672,7 +683,6 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_big_kernel(const WgradBat
             const int col = wi * (kCols / 2) + bi * 16 + (lane >> 4) * 4;
             *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
         }
-    run.request_old(A);
     __syncthreads();
     run.finish(A, img + wave * 32 * kEpiPitch, kEpiPitch);
 }
@@ -693,7 +703,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    RunPass<OUT, kTile / 8, 2> run;                          // wave w gathers rows 16 w ..
+    RunPass<OUT, kTile / 8, 2, !APART> run;                  // wave w gathers rows 16 w ..
     run.open(A, row0 + wave * 16, col0, kTile);
     const int half = wave >> 2;
     const int wo = wave & 1, wi = (wave >> 1) & 1;
@@ -738,10 +748,134 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_small_kernel(const WgradB
                 *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kEpiPitch + col) = h;
             }
     }
-    run.request_old(A);
+    if (APART) run.request_old(A);
     __syncthreads();
     if constexpr (OUT == kOutPartial) run.finish(A, sums + wave * 16 * kSumPitch, kSumPitch);
     else run.finish(A, img + wave * 16 * kEpiPitch, kEpiPitch);
+}
+
+// 128 x 128 tile by a workgroup of four waves, of which a compute unit holds four (128 registers, 34 KB of LDS): 64 x 64 per wave,
+// the waves as 2 x 2, a ring of two 32-token stages of 16 LDS rows (8 of X, 8 of dY).  For calls whose time is not the main loop but what
+// is around it: with one workgroup to a compute unit the start of a tile (arguments, first copies), the search for its runs, the image and
+// the gather are waited for one after the other, 7 us and more a round; here other tiles' steps run meanwhile.  Nothing in a workgroup
+// overlaps anything else, which is why the code is plain: all waves take a stage together, its look comes after the loop.
+// Rings of three and four stages (three and two workgroups to a unit) are slower (7856 x 4632, 106 tokens, 20 % kept 32.5 us and more
+// against 29.3; one workgroup of 256 x 256: 43.5), and so are 128 x 256 tiles, two to a unit, by 0 to 15 % where this shape is the best.
+// The copies set the pace of the loop, twice the bytes per flop of the large tile, so long calls are not for it (plan_tiles).
+constexpr int kResidentThreads = 256, kResidentRows = 16, kResidentStage = kResidentRows * kRowPitch, kResidentPitch = kSmallTile + 8;
+constexpr int kResidentLds = kSmallTile * kResidentPitch * 2;
+static_assert(2 * kResidentStage <= kResidentLds, "the ring of two stages fits in the image's place");
+static_assert(4 * (kResidentLds + 1024) <= 160 * 1024, "four workgroups to a compute unit");
+
+// A pointer all lanes of a wave agree on, told to the compiler.
+__device__ __forceinline__ const unsigned char *uniform(const unsigned char *p)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<const unsigned char *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a) |
+                                                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) << 32);
+}
+
+template <int OUT>
+__global__ void __launch_bounds__(kResidentThreads, 4) wgrad_resident_kernel(const WgradBatch B)
+{
+    constexpr int kTokens = 32, kRowTokens = row_tokens(kSmallTile);
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    WgradArgs A;
+    int row0, col0;
+    if (!tile_origin<true, kSmallTile>(B, A, row0, col0)) return;
+    const int t = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int wo = wave & 1, wi = wave >> 1;
+
+    // Copies: wave w owns rows 2w, 2w + 1 of either operand, a row holds four tokens: 4 row + lane / 16.
+    const int64_t x_bytes = (int64_t)A.in * 2, y_bytes = (int64_t)A.out * 2;
+    const int sub = lane >> 4, f = (lane & 15) * 8;
+    const unsigned xf = (unsigned)(col0 + f < A.in ? f : 0) * 2, yf = (unsigned)(row0 + f < A.out ? f : 0) * 2;    // else: the first feature again
+    const unsigned x_lane = (unsigned)sub * (unsigned)x_bytes + xf, y_lane = (unsigned)sub * (unsigned)y_bytes + yf;   // below 2^27
+    const unsigned char *xbase = reinterpret_cast<const unsigned char *>(A.x) + (int64_t)col0 * 2;
+    const unsigned char *ybase = reinterpret_cast<const unsigned char *>(A.dy) + (int64_t)row0 * 2;
+    const int first_token = 2 * kRowTokens * wave;
+    const unsigned x_rows = (unsigned)(size_t)(LDS_AS unsigned char *)lds + (unsigned)(wave * 2) * kRowPitch;
+    const unsigned y_rows = x_rows + kResidentRows / 2 * kRowPitch;
+    const int stages = (int)((A.tokens + kTokens - 1) / kTokens), full = (int)(A.tokens / kTokens);   // tokens fit 31 bits
+    const unsigned char *xnext = xbase + first_token * x_bytes, *ynext = ybase + first_token * y_bytes;
+    auto issue = [&](int s) {                                // stages in order, from 0
+        const unsigned slot = (s & 1) * kResidentStage;
+        if (s < full) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                dma16_from(uniform(xnext + kRowTokens * i * x_bytes), x_lane, x_rows + slot + i * kRowPitch);
+                dma16_from(uniform(ynext + kRowTokens * i * y_bytes), y_lane, y_rows + slot + i * kRowPitch);
+            }
+            xnext += kTokens * x_bytes;
+            ynext += kTokens * y_bytes;
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int64_t token = (int64_t)s * kTokens + first_token + kRowTokens * i + sub;
+            const bool there = token < A.tokens;
+            dma16(there ? xbase + token * x_bytes + xf : wgrad_zero_row, x_rows + slot + i * kRowPitch);
+            dma16(there ? ybase + token * y_bytes + yf : wgrad_zero_row, y_rows + slot + i * kRowPitch);
+        }
+    };
+    // Wave w gathers rows 32 w .. 32 w + 31; in two parts where old values take registers too.
+    constexpr int kParts = OUT == kOutF16 ? 2 : 1, kPartRows = kSmallTile / 4 / kParts;
+    RunPass<OUT, kPartRows, 1> run[kParts];
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) run[i].open(A, row0 + wave * 32 + i * kPartRows, col0, kSmallTile);
+    if (stages > 0) issue(0);
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int bo = 0; bo < 4; ++bo)
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[bo][bi][r] = 0.f;
+    // 16 lanes read four rows, 16 features: the lane groups take rows 0-3 and 4-7, tokens 0 and 1, then 2 and 3 of each
+    const int lane_read = ((lane >> 2) & 7) * kRowPitch + (lane >> 5) * 2 * kSmallTile * 2 + (lane & 3) * 8;
+    const int x_off = lane_read + wi * 64 * 2, y_off = lane_read + kResidentRows / 2 * kRowPitch + wo * 64 * 2;
+    for (int s = 0; s < stages; ++s) {
+        // stage s is there, and every wave has read stage s - 1, whose place the next copies take
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        meet();
+        if (s + 1 < stages) issue(s + 1);
+        const unsigned char *cur = lds + (s & 1) * kResidentStage;
+        half8 xa[4], yb[4];
+#pragma unroll
+        for (int bo = 0; bo < 4; ++bo) yb[bo] = read_fragment(cur + y_off + bo * 32, kSmallTile * 2);
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi) xa[bi] = read_fragment(cur + x_off + bi * 32, kSmallTile * 2);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int bi = q / 4, bo = (bi & 1) ? 3 - q % 4 : q % 4;
+            acc[bo][bi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[bi], yb[bo], acc[bo][bi], 0, 0, 0);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) run[i].look(A);
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) run[i].settle(A);
+    run[0].begin(A);
+    _Float16 *img = reinterpret_cast<_Float16 *>(lds);
+#pragma unroll
+    for (int bo = 0; bo < 4; ++bo)
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi) {
+            half4 h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[bo][bi][e];           // round to nearest even
+            const int col = wi * 64 + bi * 16 + (lane >> 4) * 4;
+            *reinterpret_cast<half4 *>(img + (wo * 64 + bo * 16 + (lane & 15)) * kResidentPitch + col) = h;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) {
+        if (i + 1 < kParts) run[i + 1].begin(A);
+        run[i].finish(A, img + (wave * 32 + i * kPartRows) * kResidentPitch, kResidentPitch);
+    }
 }
 
 // Adds the splits' sums of every kept element in split order, rounds once to fp16 and stores as the
@@ -871,24 +1005,33 @@ hipError_t launch_mfma_rate(int64_t iters, float *sink, int workgroups, hipStrea
 
 namespace {
 
-uint32_t per_group_of(int tiles_in) { return (uint32_t)((1ull << 32) / (4u * (uint32_t)tiles_in) + 1u); }
+uint32_t per_group_of(int tiles_in) { return (uint32_t)((1ull << 32) / ((uint32_t)kGroupDepth * (uint32_t)tiles_in) + 1u); }
 
-// The call's job list with its tiles; false if there is nothing to write.
+// The jobs' tiles of a shape, layer after layer.
+void cut_tiles(WgradBatch *b, int rows, int cols)
+{
+    b->tile_cols = cols;
+    b->first_tile[0] = 0;
+    for (int k = 0; k < b->jobs; ++k) {
+        b->tiles_out[k] = (int)ceil_div(b->job[k].out, rows);
+        b->tiles_in[k] = (int)ceil_div(b->job[k].in, cols);
+        b->first_tile[k + 1] = b->first_tile[k] + b->tiles_out[k] * b->tiles_in[k];
+        b->per_group[k] = per_group_of(b->tiles_in[k]);
+    }
+}
+
+// The call's job list with its large tiles; false if there is nothing to write.
 bool list_tiles(const WgradJob *jobs, int count, float inv_scale, int accumulate, WgradBatch *out)
 {
     WgradBatch &b = *out;
-    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate; b.splits = 1; b.tile_cols = kBigTile;
-    b.first_tile[0] = 0;
+    b.jobs = 0; b.inv_scale = inv_scale; b.accumulate = accumulate; b.splits = 1;
     for (int j = 0; j < count && b.jobs < kWgradMaxJobs; ++j) {
         if (jobs[j].out <= 0 || jobs[j].in <= 0 || jobs[j].nnz <= 0) continue;     // nothing to write
         const int k = b.jobs++;
         b.job[k] = jobs[j];
-        b.tiles_out[k] = (int)ceil_div(jobs[j].out, kBigTile);
-        b.tiles_in[k] = (int)ceil_div(jobs[j].in, kBigTile);
-        b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
-        b.per_group[k] = per_group_of(b.tiles_in[k]);
     }
     if (b.jobs == 0) return false;
+    cut_tiles(&b, kBigTile, kBigTile);
     for (int k = b.jobs; k < kWgradMaxJobs; ++k) {
         b.job[k] = b.job[0]; b.tiles_out[k] = b.tiles_in[k] = 1; b.first_tile[k + 1] = b.first_tile[b.jobs];
         b.per_group[k] = per_group_of(1);
@@ -902,6 +1045,14 @@ void launch_tiles(int out_kind, const WgradBatch &b, bool small, unsigned blocks
     int64_t tokens = 0;
     for (int j = 0; j < b.jobs; ++j) tokens = b.job[j].tokens > tokens ? b.job[j].tokens : tokens;
     tile_kernel(out_kind, small, b.tile_cols / 32, loop_apart(tokens, small), blocks < kFewBlocks)<<<grid, threads, kLdsBytes, s>>>(b);
+}
+
+void launch_resident(int out_kind, WgradBatch &b, hipStream_t s)
+{
+    b.quadrants = 0; b.first = 0; b.tiles = b.first_tile[b.jobs];
+    const dim3 grid((unsigned)((b.tiles + 7) / 8 * 8)), threads(kResidentThreads);
+    if (out_kind == kOutF32) wgrad_resident_kernel<kOutF32><<<grid, threads, kResidentLds, s>>>(b);
+    else wgrad_resident_kernel<kOutF16><<<grid, threads, kResidentLds, s>>>(b);
 }
 
 // What the tile rules price: the longest job's 32-token stages and the kept fraction of all jobs together.
@@ -934,28 +1085,50 @@ int count_tiles(const WgradBatch &b, int rows, int cols)
 // Time in us of a launch of that many workgroups of one shape (columns of a 256-row tile, or 128 x 128 with `small`), each
 // of them `stages` stages long: what is around a tile's loop, the loop, and the gather of what the tile keeps, per
 // round of the compute units.  A stage costs less while part of the chip is idle (the clock is higher and the memory
-// less busy): 256 columns 0.56 us up to half of the compute units, 0.70 with all of them.  Fitted to 636
-// calls (sides 512 .. 12000, 200 .. 8192 tokens, 3 to 25 % kept) in every shape and split: 3 to 5 % rms.
+// less busy): 256 columns 0.545 us up to half of the compute units, 0.73 with all of them.  Fitted to 1000 calls (sides 512 ..
+// 12000, 100 .. 8192 tokens, 3 to 25 % kept) in every shape: 2 to 3.5 % rms in the tiles of 256 rows, 10 % in 128 x 128 up to four rounds.
 double launch_us(bool small, int cols, int workgroups, int stages, double keep, int cus)
 {
     const double rounds = (workgroups + cus - 1) / cus, full = workgroups / (rounds * cus);
     const double busy = full < 0.5 ? 0.0 : full > 0.9 ? 1.0 : (full - 0.5) / 0.4;
-    double around = 7.0, stage = 0.70, idle_stage = 0.56, area = 256.0 * cols;
-    if (small) around = 5.2, stage = 0.24, idle_stage = 0.228, area = 128.0 * 128.0;
-    else if (cols < 256) {
-        stage = cols == 128 ? 0.47 : cols == 160 ? 0.515 : 0.56;
-        idle_stage = 0.88 * stage;
-    }
-    return 1.5 + rounds * (around + (idle_stage + busy * (stage - idle_stage)) * stages + 0.38e-3 * keep * area);
+    double around = 6.0, stage = 0.73, idle_stage = 0.545, gather = 0.36e-3, area = 256.0 * cols;
+    if (small) around = 4.2, stage = 0.26, idle_stage = 0.231, gather = 0.34e-3, area = 128.0 * 128.0;
+    else if (cols == 128) around = 5.9, stage = 0.473, idle_stage = 0.43, gather = 0.235e-3;
+    else if (cols == 160) stage = 0.538, idle_stage = 0.448, gather = 0.24e-3;
+    else if (cols == 192) around = 5.9, stage = 0.615, idle_stage = 0.49, gather = 0.30e-3;
+    return 1.5 + rounds * (around + (idle_stage + busy * (stage - idle_stage)) * stages + gather * keep * area);
+}
+
+// The same of the resident shape: whole rounds of four workgroups to every compute unit, and a last one with `most` of them on the
+// busiest.  Fitted to 411 calls of up to 2048 tokens: 6 % rms.
+double resident_us(int workgroups, int stages, double keep, int cus)
+{
+    const int rounds = workgroups / (4 * cus), most = (workgroups - rounds * 4 * cus + cus - 1) / cus;
+    const double kept = keep * 16.384;                         // thousand entries a tile
+    double us = 1.4 + rounds * (3.85 + 0.986 * stages + 0.98 * kept);
+    if (most > 0) us += 3.2 + (0.1 + 0.2 * most) * stages + 0.444 * kept * most;
+    return us;
 }
 
 // How the tiles of an unsplit call are launched: `wide` of the list, in tiles of 32 * blocks columns, and the
-// last `quarters` large tiles of the list as small ones (blocks is 8 then).  us: what a call of less than a round takes
-// by the prices above.
+// last `quarters` large tiles of the list as small ones (blocks is 8 then); blocks == 0: all in the resident shape.  us: what
+// it takes by the prices above.
 struct TilePlan {
     int wide, quarters, blocks;
     double us;
 };
+
+// Short calls of more tiles than compute units go to four workgroups to a unit.  Us, as the rules below would run it and so, 10 % kept
+// unless said: 2320 x 2624, 112 tokens, 5 % 9.8 and 7.2; 4096 x 4096, 200 and 300 tokens 14.4 and 13.1, 16.9 and 16.8; 2376 x 7080, 235
+// tokens, 5 % 22.8 and 19.1; 7856 x 4632, 106 tokens, 20 % 43.3 and 28.6; 10760 x 5200, 408 tokens, 12 % 65.8 and 62.8; past about 600
+// tokens the copies of the smaller tiles cost more than is gained (4096 x 4096, 500 tokens 20.1 and 21.3, 1000 33.3 and 37.5), and with a
+// tile to a compute unit or less there is nothing to share one.  2 % below the other price, because that of this shape is the rougher one.
+TilePlan resident_if_quicker(const TilePlan &plan, int small_tiles, const CallSize &c, int cus)
+{
+    if (small_tiles <= cus) return plan;
+    const double us = resident_us(small_tiles, c.stages, c.keep, cus);
+    return us * 1.02 < plan.us ? TilePlan{0, small_tiles, 0, us} : plan;
+}
 
 // Large tiles in whole rounds of the compute units; what is left over after the last whole
 // round goes to the small shape when that is the quicker way to finish it: up to half a round
@@ -970,18 +1143,21 @@ struct TilePlan {
 TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
 {
     const int tiles = b.first_tile[b.jobs];
-    const int shape = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128 or 256
+    const int shape = knob(SAMO_KNOB_WGRAD_TILE, 0);           // tuning and test aid: 128, 256 or 512 (the resident shape)
     if (shape == kSmallTile) return {0, tiles, 8, 0.0};
+    if (shape == kResidentShape) return {0, tiles, 0, 0.0};
     if (shape == kBigTile || cus <= 0) return {tiles, 0, 8, 0.0};
     const int forced_cols = knob(SAMO_KNOB_WGRAD_COLS, 0);     // test aid: narrow tiles whatever they cost
-    if (forced_cols == 0 && (tiles >= cus || round_forced)) {
-        const int left = tiles % cus;
-        if (left != 0 && left <= cus / 2) return {tiles - left, left, 8, 0.0};
-        return {tiles, 0, 8, 0.0};
-    }
     const CallSize c = size_of(b);
     TilePlan plan = {tiles, 0, 8, launch_us(false, 256, tiles, c.stages, c.keep, cus)};
     const int quarters = count_tiles(b, kSmallTile, kSmallTile);
+    if (forced_cols == 0 && (tiles >= cus || round_forced)) {
+        const int left = tiles % cus;
+        if (left != 0 && left <= cus / 2)
+            plan = {tiles - left, left, 8,
+                    launch_us(false, 256, tiles - left, c.stages, c.keep, cus) + launch_us(true, 128, left * 4, c.stages, c.keep, cus)};
+        return round_forced ? plan : resident_if_quicker(plan, quarters, c, cus);
+    }
     const double small_us = launch_us(true, 128, quarters, c.stages, c.keep, cus);
     if (small_us < plan.us) plan = {0, tiles, 8, small_us};
     if (forced_cols) plan.us = 1e30;
@@ -991,7 +1167,7 @@ TilePlan plan_tiles(const WgradBatch &b, int cus, bool round_forced)
         const double us = launch_us(false, 32 * blocks, narrow, c.stages, c.keep, cus);
         if (us < plan.us) plan = {narrow, 0, blocks, us};
     }
-    return plan;
+    return forced_cols ? plan : resident_if_quicker(plan, quarters, c, cus);
 }
 
 // Whether, and how, the tiles of a call are shared by several workgroups each: `splits` workgroups per tile
@@ -1089,16 +1265,14 @@ hipError_t launch_wgrad(int out_kind, const WgradJob *jobs, int count, float inv
     }
     const int round = knob(SAMO_KNOB_WGRAD_ROUND, 0);          // test aid: tiles per round in place of the CU count
     const TilePlan plan = plan_tiles(b, round > 0 ? round : cus, round > 0);
+    if (plan.blocks == 0) {
+        cut_tiles(&b, kSmallTile, kSmallTile);
+        launch_resident(out_kind, b, s);
+        return hipGetLastError();
+    }
     if (plan.wide > 0) {
         b.quadrants = 0; b.first = 0; b.tiles = plan.wide;
-        if (plan.blocks != 8) {
-            b.tile_cols = 32 * plan.blocks;
-            for (int k = 0; k < b.jobs; ++k) {
-                b.tiles_in[k] = (int)ceil_div(b.job[k].in, b.tile_cols);
-                b.first_tile[k + 1] = b.first_tile[k] + b.tiles_out[k] * b.tiles_in[k];
-                b.per_group[k] = per_group_of(b.tiles_in[k]);
-            }
-        }
+        if (plan.blocks != 8) cut_tiles(&b, kBigTile, 32 * plan.blocks);
         launch_tiles(out_kind, b, false, (unsigned)plan.wide, s);
     }
     if (plan.quarters > 0) {

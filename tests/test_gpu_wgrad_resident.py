@@ -1,0 +1,86 @@
+"""Weight gradients in 128 x 128 tiles with four workgroups to a compute unit, against the oracle's rounding bracket: no token,
+the ring of two stages at its start, wrap and partial last stage, ragged tiles in both directions, both outputs, several layers, and
+the calls that the rule gives it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2302_05045_amd as samo
+import samo_inputs as si
+from gpu_util import DEV, dev_f16_bits, dev_i32, host_bits, ref_seg_ptr
+from test_gpu_wgrad import _bracket, _check_f16, _problem
+
+pytestmark = pytest.mark.gpu
+RESIDENT = 512                  # SAMO_KNOB_WGRAD_TILE
+
+
+@pytest.fixture
+def resident():
+    samo.samo_debug_set(samo.KNOB_WGRAD_TILE, RESIDENT)
+    yield
+    samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+
+
+def _run(problem, gc16, gc):
+    dy, x, idx, d_dy, d_x, d_idx, d_seg = problem
+    nnz = idx.shape[0]
+    samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], workspace=torch.empty(0, dtype=torch.uint8, device=DEV))
+    samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0 / si.LOSS_SCALE, gc[:nnz], workspace=torch.empty(0, dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.parametrize("kind", ["bernoulli10", "bernoulli50", "rows", "edges", "dense_idx"])
+@pytest.mark.parametrize("tokens,out_f,in_f", [(1, 8, 8), (31, 128, 136), (32, 136, 128), (33, 264, 264), (63, 16, 392), (64, 392, 24),
+                                               (65, 120, 520), (96, 520, 248), (161, 648, 136)])
+def test_resident_tiles_match_the_oracle(tokens, out_f, in_f, kind, resident):
+    problem = _problem(tokens, out_f, in_f, kind, 21 + tokens)
+    dy, x, idx = problem[:3]
+    nnz = idx.shape[0]
+    gc16 = torch.full((nnz + 8,), float("nan"), dtype=torch.float16, device=DEV)
+    gc = torch.full((nnz + 8,), float("nan"), device=DEV)
+    _run(problem, gc16, gc)
+    torch.cuda.synchronize()
+    bits = host_bits(gc16[:nnz])
+    lo, hi = _bracket(dy, x, tokens, out_f, in_f, idx)
+    _check_f16(bits, lo, hi, oracle.wgrad_compress(dy, x, tokens, out_f, in_f, idx), "gc16")
+    inv = np.float32(1.0 / si.LOSS_SCALE)
+    assert np.array_equal(gc[:nnz].cpu().numpy().view(np.uint32), (bits.view(np.float16).astype(np.float32) * inv).view(np.uint32))
+    samo.samo_wgrad_gather_fp16(problem[3], problem[4], problem[5], problem[6], gc16[:nnz], accumulate=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bits(gc16[:nnz]), (bits.view(np.float16) + bits.view(np.float16)).astype(np.float16).view(np.uint16))
+    assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"
+
+
+def test_several_layers_one_of_them_without_tokens_or_index(resident):
+    jobs, wants = [], []
+    for tokens, out_f, in_f, kind in ((70, 264, 200, "bernoulli10"), (0, 24, 136, "bernoulli50"), (33, 136, 264, None)):
+        dy, x = si.output_grads_fp16(max(tokens, 1), out_f, 3)[:tokens * out_f], si.activations_fp16(max(tokens, 1), in_f, 3)[:tokens * in_f]
+        idx = np.arange(out_f * in_f, dtype=np.int32) if kind is None else oracle.build_index(si.bernoulli_mask(out_f * in_f, 0.1, 5))
+        ptrs = (None, None) if kind is None else (dev_i32(idx), dev_i32(ref_seg_ptr(idx, out_f * in_f)))
+        gc16 = torch.full((idx.shape[0],), float("nan"), dtype=torch.float16, device=DEV)
+        jobs.append((dev_f16_bits(dy).view(tokens, out_f), dev_f16_bits(x).view(tokens, in_f), *ptrs, gc16))
+        wants.append((oracle.wgrad_compress(dy, x, tokens, out_f, in_f, idx), *_bracket(dy, x, tokens, out_f, in_f, idx)))
+    samo.samo_wgrad_gather_fp16_batched(jobs, workspace=torch.empty(0, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    for k, (job, (want, lo, hi)) in enumerate(zip(jobs, wants)):
+        _check_f16(host_bits(job[4]), lo, hi, want, "job %d" % k)
+
+
+@pytest.mark.parametrize("tokens,out_f,in_f", [(70, 2600, 2248), (33, 4104, 4104), (1000, 3000, 3080)])
+def test_layers_on_either_side_of_the_rule(tokens, out_f, in_f):
+    """Short calls of more tiles than compute units (four to a unit, two rounds of them), and one long enough for tiles of 256 rows: in 64
+    bits on the GPU, within the bound of tokens fp32 additions."""
+    gen = torch.Generator(device=DEV).manual_seed(tokens)
+    dy = torch.randn(tokens, out_f, generator=gen, device=DEV).half()
+    x = torch.randn(tokens, in_f, generator=gen, device=DEV).half()
+    ix = samo.samo_build_index((torch.rand(out_f * in_f, generator=gen, device=DEV) < 0.1).to(torch.uint8))
+    at = ix.idx.long()
+    exact = (dy.double().t().contiguous() @ x.double()).view(-1)[at]
+    slack = (tokens + 2) * 2.0 ** -23 * (dy.double().abs().t().contiguous() @ x.double().abs()).view(-1)[at]
+    got = torch.full((ix.nnz,), float("nan"), dtype=torch.float16, device=DEV)
+    samo.samo_wgrad_gather_fp16(dy, x, ix.idx, ix.seg_ptr, got)
+    as_half = lambda v: torch.from_numpy(v.cpu().numpy().astype(np.float16)).to(DEV)          # one rounding
+    assert bool(((got >= as_half(exact - slack)) & (got <= as_half(exact + slack))).all())
+    first = got.clone()
+    samo.samo_wgrad_gather_fp16(dy, x, ix.idx, ix.seg_ptr, got, accumulate=True)
+    assert torch.equal(got, first + first)

@@ -178,10 +178,16 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
  * samo_count_flags_batched: what samo_build_index_batched does for jobs that only count (idx and
  * idx_capacity are not used), and every job's flag bits are left in h_flags[j], a HOST array of
  * DEVICE pointers.  Both calls refuse the jobs that samo_build_index_batched refuses.
+ * samo_count_flags_mirrored_batched: the same, and the count of job j is stored in h_counts[j] too, page-locked host
+ * memory that the device can write (hipHostMalloc); a count there is final as soon as it is seen, which
+ * may be before the launch has ended.  The memory has to stay until all counts have been seen or the
+ * stream has been waited for.
  * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
  * flag bits, the seg_ptr and the nnz such a call left, later on the same stream; the mask is not read.
  * A job with *nnz < 0 (as a build in one call reports that it gave up) is left without positions. */
 samo_status samo_index_flags_bytes(int64_t n, size_t *bytes);
+samo_status samo_count_flags_mirrored_batched(const samo_index_job *h_jobs, void *const *h_flags, int64_t *h_counts,
+                                              int32_t num_jobs, void *stream);
 samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,
                                      void *stream);
 samo_status samo_fill_index_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs,

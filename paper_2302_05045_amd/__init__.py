@@ -111,6 +111,8 @@ _SIGNATURES = {
     "samo_index_flags_bytes": (ctypes.c_int32, [ctypes.c_int64, ctypes.POINTER(ctypes.c_size_t)]),
     "samo_count_flags_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.POINTER(ctypes.c_void_p),
                                                   ctypes.c_int32, ctypes.c_void_p]),
+    "samo_count_flags_mirrored_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p,
+                                                           ctypes.c_int32, ctypes.c_void_p]),
     "samo_fill_index_batched": (ctypes.c_int32, [ctypes.POINTER(IndexJob), ctypes.POINTER(ctypes.c_void_p),
                                                  ctypes.c_int32, ctypes.c_void_p]),
     "samo_build_seg_ptr": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
@@ -358,7 +360,8 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     28 matrices, 550 M elements: 243 us with the loops below, 194 with those)."""
     if _marshal is not None:
         count, fill = _entry_address("samo_count_flags_batched"), _entry_address("samo_fill_index_batched")
-        built = _marshal.build_indices(list(masks), _stream, _scratch, count, fill)
+        mirrored = _entry_address("samo_count_flags_mirrored_batched")
+        built = _marshal.build_indices(list(masks), _stream, _scratch, count, fill, mirrored)
         if isinstance(built, list):
             return [Index(*parts) for parts in built]
         if built == SAMO_ERR_SIZE:

@@ -205,7 +205,7 @@ samo_status check_index_jobs(const samo_index_job *h_jobs, void *const *h_flags,
 
 // Launches the jobs in groups of up to kIndexBatchJobs: counting (and filling, where a job has room for
 // positions), leaving the flag words where h_flags says so.
-samo_status run_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)
+samo_status run_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, int64_t *mirror, int32_t num_jobs, void *stream)
 {
     const int cus = compute_units();
     for (int32_t j0 = 0; j0 < num_jobs;) {
@@ -226,6 +226,7 @@ samo_status run_index_jobs(const samo_index_job *h_jobs, void *const *h_flags, i
         const int forced = knob(SAMO_KNOB_INDEX_PASSES, 0);
         batch.passes = (forced == 1 || forced == 2 || forced == 4) ? forced : index_passes_for(bytes, cus);
         batch.num = k;
+        batch.mirror = mirror ? mirror + j0 : nullptr;
         bool fill = false;
         int64_t wgs = 0;
         for (int i = 0; i < k; ++i) {
@@ -259,7 +260,7 @@ extern "C" {
 samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_jobs, void *stream)
 {
     if (samo_status s = check_index_jobs(h_jobs, nullptr, false, num_jobs)) return s;     // everything before any launch
-    return run_index_jobs(h_jobs, nullptr, num_jobs, stream);
+    return run_index_jobs(h_jobs, nullptr, nullptr, num_jobs, stream);
 }
 
 samo_status samo_index_flags_bytes(int64_t n, size_t *bytes)
@@ -273,7 +274,16 @@ samo_status samo_index_flags_bytes(int64_t n, size_t *bytes)
 samo_status samo_count_flags_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)
 {
     if (samo_status s = check_index_jobs(h_jobs, h_flags, true, num_jobs)) return s;
-    return run_index_jobs(h_jobs, h_flags, num_jobs, stream);
+    return run_index_jobs(h_jobs, h_flags, nullptr, num_jobs, stream);
+}
+
+samo_status samo_count_flags_mirrored_batched(const samo_index_job *h_jobs, void *const *h_flags, int64_t *h_counts, int32_t num_jobs,
+                                              void *stream)
+{
+    if (samo_status s = check_index_jobs(h_jobs, h_flags, true, num_jobs)) return s;
+    if (!h_counts && num_jobs > 0) return SAMO_ERR_NULL;
+    if (reinterpret_cast<uintptr_t>(h_counts) & 7u) return SAMO_ERR_ALIGN;
+    return run_index_jobs(h_jobs, h_flags, h_counts, num_jobs, stream);
 }
 
 samo_status samo_fill_index_batched(const samo_index_job *h_jobs, void *const *h_flags, int32_t num_jobs, void *stream)

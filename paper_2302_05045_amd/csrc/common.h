@@ -112,6 +112,7 @@ struct IndexBatch {
     int32_t *seg_ptr[kIndexBatchJobs];
     int64_t *nnz[kIndexBatchJobs];
     uint4 *flags[kIndexBatchJobs];       // NULL, or where a counting launch leaves the flag words and the fill launch reads them
+    int64_t *mirror;                     // NULL, or page-locked host memory: where a counting launch puts the jobs' counts besides *nnz
     int passes;                          // 64 KiB passes a workgroup of the chained kernel makes over its block: 1, 2 or 4
     int spin_limit;                      // polls of a missing predecessor before a workgroup gives up
     int64_t *ticket;                     // the nnz of the job that owns the last workgroup: zero before the

@@ -506,7 +506,11 @@ offsets_kernel(const IndexBatch batch)
         const int incl = wave_inclusive_scan(own, tid);
         if (tid < kOffsetBlocks) sh_base[tid] = before + incl - own;
         if (tid == 0 && wg == 0) seg_ptr[0] = 0;
-        if (tid == 63 && block0 + kOffsetBlocks >= blocks) *batch.nnz[job] = (int64_t)before + incl;
+        if (tid == 63 && block0 + kOffsetBlocks >= blocks) {
+            *batch.nnz[job] = (int64_t)before + incl;
+            // past the caches: a host that polls it has the count before the launch has ended
+            if (batch.mirror) __hip_atomic_store(batch.mirror + job, (int64_t)before + incl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
     __syncthreads();
 #pragma unroll

@@ -13,6 +13,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/utils/object_ptr.h>
 
+#include <chrono>
 #include <vector>
 
 #include "samo.h"
@@ -89,8 +90,47 @@ struct WithoutGil {
 // 5 us and fills 32 M elements in 3, so the first one starts the device early and the last ones keep it busy.
 constexpr int64_t kFirstFill = 32 << 20;
 
-// build_indices(masks, stream, scratch, count, fill): indices of byte masks (a list) by the entries samo_count_flags_batched and
-// samo_fill_index_batched at the addresses `count` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
+// Waits until a count has appeared in page-locked memory; false if that takes longer than kPatience: other work ahead on the
+// stream, or a stream under capture, where nothing runs.  The caller then reads the counts back, which waits for the stream or refuses.
+constexpr int64_t kNoCount = -1;
+constexpr std::chrono::microseconds kPatience(2000);
+bool seen(const int64_t *count)
+{
+    if (__atomic_load_n(count, __ATOMIC_ACQUIRE) != kNoCount) return true;
+    const auto until = std::chrono::steady_clock::now() + kPatience;
+    for (int spins = 1; __atomic_load_n(count, __ATOMIC_ACQUIRE) == kNoCount; ++spins) {
+        __builtin_ia32_pause();
+        if (spins % 64 == 0 && std::chrono::steady_clock::now() > until) return false;
+    }
+    return true;
+}
+
+// Page-locked memory goes back to torch's cache when the build leaves it, also by an exception (no memory for an index): not before
+// the last count was stored in it.
+struct CountsAwaited {
+    const at::Tensor &nnz;
+    const int64_t *counts = nullptr;
+    size_t k = 0;
+    ~CountsAwaited()
+    {
+        for (size_t i = 0; i < k; ++i) {
+            if (seen(counts + i)) continue;
+            try {
+                nnz.cpu();
+            } catch (...) {
+            }
+            return;
+        }
+    }
+};
+
+// Elements of masks from which on they are counted in two launches: the counts of the first half are there, and the
+// fill of its masks is launched, while the second half is counted.
+constexpr int64_t kCountInParts = 64 << 20;
+
+// build_indices(masks, stream, scratch, count, fill[, mirrored]): indices of byte masks (a list) by the entries samo_count_flags_batched (or,
+// where it is given, samo_count_flags_mirrored_batched, whose counts are polled instead of read back: a stream synchronisation
+// and a copy between the two launches are 10 to 15 us) and samo_fill_index_batched at the addresses `count`, `mirrored` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
 // uint8 tensor for the flag bits or None.
 // A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int; None where the
 // caller has to go another way: a mask is no plain tensor, or there is no scratch memory.
@@ -98,17 +138,19 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     HANDLE_TH_ERRORS
     typedef samo_status (*Entry)(const samo_index_job *, void *const *, int32_t, void *);
-    if (nargs != 5 || !PyList_Check(args[0]) || PyList_GET_SIZE(args[0]) == 0) {
-        PyErr_SetString(PyExc_TypeError, "build_indices(masks, stream, scratch, count, fill)");
+    typedef samo_status (*Mirrored)(const samo_index_job *, void *const *, int64_t *, int32_t, void *);
+    if (nargs < 5 || nargs > 6 || !PyList_Check(args[0]) || PyList_GET_SIZE(args[0]) == 0) {
+        PyErr_SetString(PyExc_TypeError, "build_indices(masks, stream, scratch, count, fill[, mirrored])");
         return nullptr;
     }
     const Entry count = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[3])), fill = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[4]));
+    const Mirrored mirrored = reinterpret_cast<Mirrored>(nargs > 5 ? PyLong_AsVoidPtr(args[5]) : nullptr);
     if (PyErr_Occurred()) return nullptr;
     const size_t k = (size_t)PyList_GET_SIZE(args[0]);
     std::vector<at::Tensor> masks(k), seg_ptrs(k), idxs(k);              // they hold the masks whatever happens to the list
     std::vector<samo_index_job> jobs(k);
     std::vector<void *> flags(k);
-    int64_t flag_bytes = 0;
+    int64_t flag_bytes = 0, elements = 0;
     for (size_t i = 0; i < k; ++i) {
         PyObject *m = PyList_GET_ITEM(args[0], (Py_ssize_t)i);
         if (!THPVariable_CheckExact(m)) Py_RETURN_NONE;
@@ -117,6 +159,7 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         const int64_t n = masks[i].numel();
         if (n > INT32_MAX) return PyLong_FromLong(SAMO_ERR_SIZE);
         flag_bytes += (n + 8 * SAMO_SEG_ELEMS - 1) / (8 * SAMO_SEG_ELEMS) * 1024;
+        elements += n;
     }
     THPObjectPtr handle(PyObject_CallNoArgs(args[1]));
     if (!handle) return nullptr;
@@ -128,11 +171,12 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     if (!THPVariable_Check(scratch.get())) Py_RETURN_NONE;
     char *flags_at = static_cast<char *>(THPVariable_Unpack(scratch.get()).data_ptr());
     const at::TensorOptions ints = masks[0].options().dtype(at::kInt).requires_grad(false);
-    at::Tensor counts;
+    at::Tensor counts;                       // in host memory
     samo_status status;
     {
         WithoutGil gil;
         at::Tensor nnz = at::empty({(int64_t)k}, ints.dtype(at::kLong));
+        CountsAwaited awaited{nnz};
         for (size_t i = 0; i < k; ++i) {
             const int64_t n = masks[i].numel();
             seg_ptrs[i] = at::empty({(n + SAMO_SEG_ELEMS - 1) / SAMO_SEG_ELEMS + 1}, ints);
@@ -141,10 +185,33 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             flags[i] = flags_at;
             flags_at += (n + 8 * SAMO_SEG_ELEMS - 1) / (8 * SAMO_SEG_ELEMS) * 1024;
         }
-        status = count(jobs.data(), flags.data(), (int32_t)k, stream);
-        if (status == SAMO_OK) counts = nnz.cpu();
+        if (mirrored) {
+            counts = at::empty({(int64_t)k}, at::TensorOptions().dtype(at::kLong).pinned_memory(true));
+            int64_t *there = counts.data_ptr<int64_t>();
+            for (size_t i = 0; i < k; ++i) there[i] = kNoCount;
+            size_t part = k;
+            if (elements >= kCountInParts)
+                for (int64_t sum = part = 0; 2 * sum < elements; ++part) sum += jobs[part].n;
+            status = mirrored(jobs.data(), flags.data(), there, (int32_t)part, stream);
+            awaited.counts = there;
+            if (status == SAMO_OK) awaited.k = part;
+            if (status == SAMO_OK && part < k) {
+                status = mirrored(jobs.data() + part, flags.data() + part, there + part, (int32_t)(k - part), stream);
+                if (status == SAMO_OK) awaited.k = k;
+            }
+        } else {
+            status = count(jobs.data(), flags.data(), (int32_t)k, stream);
+            if (status == SAMO_OK) counts = nnz.cpu();
+        }
+        bool polled = mirrored != nullptr;
         int64_t waiting = 0, enough = kFirstFill;
         for (size_t i = 0, first = 0; status == SAMO_OK && i < k; ++i) {
+            if (polled && !seen(counts.data_ptr<int64_t>() + i)) {
+                at::Tensor read = nnz.cpu();     // waits for the stream
+                awaited.k = 0;
+                counts = std::move(read);
+                polled = false;
+            }
             const int64_t found = counts.data_ptr<int64_t>()[i];
             idxs[i] = at::empty({found}, ints);
             jobs[i].idx = found ? static_cast<int32_t *>(idxs[i].data_ptr()) : nullptr;

@@ -416,3 +416,15 @@ def test_a_forked_child_asks_for_its_stream_through_torch(monkeypatch):
         os._exit(1)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
     assert samo._stream() == 4096
+
+
+def test_mirrored_count_rejects_bad_arguments():
+    L = samo.lib()
+    jobs, flags = (samo.IndexJob * 1)(), (ctypes.c_void_p * 1)(FAKE)
+    jobs[0].mask, jobs[0].n, jobs[0].seg_ptr, jobs[0].nnz = FAKE, 8, FAKE, FAKE
+    assert L.samo_count_flags_mirrored_batched(jobs, flags, None, 1, None) == samo.SAMO_ERR_NULL
+    assert L.samo_count_flags_mirrored_batched(jobs, flags, FAKE + 4, 1, None) == samo.SAMO_ERR_ALIGN
+    assert L.samo_count_flags_mirrored_batched(None, flags, FAKE, 1, None) == samo.SAMO_ERR_NULL
+    assert L.samo_count_flags_mirrored_batched(None, None, None, 0, None) == samo.SAMO_OK
+    jobs[0].n = 2**31
+    assert L.samo_count_flags_mirrored_batched(jobs, flags, FAKE, 1, None) == samo.SAMO_ERR_SIZE

@@ -24,6 +24,7 @@ namespace samo {
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
@@ -53,7 +54,6 @@ __device__ __forceinline__ void store16_stream(void *dst, const uint4 &v)
 
 __device__ __forceinline__ void store8_stream(void *dst, const uint2 &v)
 {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_nontemporal_store((u32x2){v.x, v.y}, reinterpret_cast<u32x2 *>(dst));
 }
 
@@ -177,63 +177,77 @@ __device__ __forceinline__ int slice_bound(const samo_layer &L, int s)
 }
 
 // ------------------------------------------------------------------ tile kernels
-// Dense (unpruned) layer: identity index, plain elementwise pass over the tile (one segment, so
-// one trip).  A thread takes four consecutive elements — one 16-byte vector of each fp32 array,
-// one 8-byte vector of each fp16 array — so every wave-level access is one contiguous run.
+// Dense (unpruned) layer: identity index, plain elementwise pass over the tile (one segment).  A thread takes eight elements a trip:
+// in a step two 16-byte vectors of each fp32 array and two 8-byte vectors of each fp16 array, the active threads' vectors next to
+// each other, so that every access of a wave is one contiguous run.  (Two vectors side by side in a thread, as it was, and 16 bytes of
+// the fp16 arrays: every line is asked for twice.)  The gradient, read exactly once, is loaded past the caches.  The expansion
+// reads one array and writes one, with 16 bytes a thread of what it writes.
+// active: how many threads take part.  What bounds a long launch is how much is in flight: one wave of a workgroup is enough, the
+// others only add to it; a short one ends sooner with two.  Us of an Adam step, as it was / 64 threads / 128: the 50304 x 4096
+// embedding 989 / 933 / 995, 60 M elements 291 / 282 / 291, 30 M 148 / 147 / 146, 12 M 57.7 / 60.1 / 54.3, 2000 vectors of 768 elements 10.6 / 10.3 / 9.0.
+constexpr int64_t kLongDense = 25000;   // workgroups of a launch (segments, where all is unpruned) from which on it is 64
 template <int MODE, int GSRC, int OPT, int T>
-__device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, int len, float inv_scale, float coef,
+__device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, int len, int active, float inv_scale, float coef,
                                            const OptK &k)
 {
+    constexpr bool kPair = MODE == kModeDecompress;          // the two vectors of a thread side by side
+    if (kPair) active = T;
     const int tid = threadIdx.x;
     float4 *__restrict__ P = reinterpret_cast<float4 *>(L.p + base);
     float4 *__restrict__ M = reinterpret_cast<float4 *>(L.m + base);
     float4 *__restrict__ V = reinterpret_cast<float4 *>(L.v + base);
-    // Eight consecutive elements per thread: two 16-byte vectors of each fp32 array, one of each
-    // fp16 array (16-byte instead of 8-byte accesses to g and w: 0.72 against 0.70 of peak on the
-    // 50304 x 4096 embedding; the gradient, read exactly once, loaded past the caches: 0.74).
-    const int nvec8 = len / 8;
-    for (int o = tid; o < nvec8; o += T) {
+    const int trips = kPair ? (len / 8 + T - 1) / T : len / (8 * active);
+#pragma unroll 1
+    for (int trip = 0; trip < trips && tid < active; ++trip) {
+        const int o = kPair ? 2 * (trip * T + tid) : trip * 2 * active + tid, o2 = kPair ? o + 1 : o + active;
+        if (kPair && o2 >= len / 8 * 2) break;
         float p[8], m[8], v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, g[8];
-        const float4 pa = P[2 * o], pb = P[2 * o + 1];
+        const float4 pa = P[o], pb = P[o2];
         p[0] = pa.x; p[1] = pa.y; p[2] = pa.z; p[3] = pa.w; p[4] = pb.x; p[5] = pb.y; p[6] = pb.z; p[7] = pb.w;
         if (MODE == kModeStep) {
-            const float4 ma = M[2 * o], mb = M[2 * o + 1];
+            const float4 ma = M[o], mb = M[o2];
             m[0] = ma.x; m[1] = ma.y; m[2] = ma.z; m[3] = ma.w; m[4] = mb.x; m[5] = mb.y; m[6] = mb.z; m[7] = mb.w;
             if (OPT == kOptAdam) {
-                const float4 va = V[2 * o], vb = V[2 * o + 1];
+                const float4 va = V[o], vb = V[o2];
                 v[0] = va.x; v[1] = va.y; v[2] = va.z; v[3] = va.w; v[4] = vb.x; v[5] = vb.y; v[6] = vb.z; v[7] = vb.w;
             }
             if (GSRC == kGradC32) {
-                const f32x4 ga = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(L.gc + base) + 2 * o);
-                const f32x4 gb = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(L.gc + base) + 2 * o + 1);
+                const f32x4 ga = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(L.gc + base) + o);
+                const f32x4 gb = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(L.gc + base) + o2);
                 g[0] = ga.x; g[1] = ga.y; g[2] = ga.z; g[3] = ga.w; g[4] = gb.x; g[5] = gb.y; g[6] = gb.z; g[7] = gb.w;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) g[u] *= coef;
             } else {
-                const u32x4 gq = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>((GSRC == kGradDense ? L.g : L.gc16) + base) + o);
-                const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w};
+                const u32x2 *gv = reinterpret_cast<const u32x2 *>((GSRC == kGradDense ? L.g : L.gc16) + base);
+                const u32x2 ga = __builtin_nontemporal_load(gv + o), gb = __builtin_nontemporal_load(gv + o2);
+                const uint32_t gw[4] = {ga.x, ga.y, gb.x, gb.y};
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     g[u] = (half_bits_to_float((uint16_t)(gw[u >> 1] >> (16 * (u & 1)))) * inv_scale) * coef;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) opt_update<OPT>(p[u], m[u], v[u], g[u], k);
-            P[2 * o] = make_float4(p[0], p[1], p[2], p[3]);
-            P[2 * o + 1] = make_float4(p[4], p[5], p[6], p[7]);
-            M[2 * o] = make_float4(m[0], m[1], m[2], m[3]);
-            M[2 * o + 1] = make_float4(m[4], m[5], m[6], m[7]);
+            P[o] = make_float4(p[0], p[1], p[2], p[3]);
+            P[o2] = make_float4(p[4], p[5], p[6], p[7]);
+            M[o] = make_float4(m[0], m[1], m[2], m[3]);
+            M[o2] = make_float4(m[4], m[5], m[6], m[7]);
             if (OPT == kOptAdam) {
-                V[2 * o] = make_float4(v[0], v[1], v[2], v[3]);
-                V[2 * o + 1] = make_float4(v[4], v[5], v[6], v[7]);
+                V[o] = make_float4(v[0], v[1], v[2], v[3]);
+                V[o2] = make_float4(v[4], v[5], v[6], v[7]);
             }
         }
         uint32_t wq[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             wq[u] = (uint32_t)float_to_half_bits(p[2 * u]) | ((uint32_t)float_to_half_bits(p[2 * u + 1]) << 16);
-        store16_stream(reinterpret_cast<uint4 *>(L.w + base) + o, make_uint4(wq[0], wq[1], wq[2], wq[3]));
+        if (kPair) store16_stream(reinterpret_cast<uint4 *>(L.w + base) + o / 2, make_uint4(wq[0], wq[1], wq[2], wq[3]));
+        else {
+            u32x2 *wv = reinterpret_cast<u32x2 *>(L.w + base);
+            __builtin_nontemporal_store(u32x2{wq[0], wq[1]}, wv + o);
+            __builtin_nontemporal_store(u32x2{wq[2], wq[3]}, wv + o2);
+        }
     }
-    const int nvec = nvec8 * 2;           // elements handled above, in units of four
+    const int nvec = kPair ? len / 8 * 2 : trips * 2 * active;    // elements handled above, in units of four
 #pragma unroll 1
     for (int e = nvec * 4 + tid; e < len; e += T) {      // ragged end of the layer
         float pe = L.p[base + e];
@@ -490,7 +504,7 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
     const int64_t rest = L.n - base;
     const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
     if (L.seg_ptr == nullptr)                 // dense (unpruned) layer
-        dense_tile<MODE, GSRC, OPT, T>(L, base, len, inv_scale, coef, k);
+        dense_tile<MODE, GSRC, OPT, T>(L, base, len, ls.wgs > kLongDense ? 64 : 128, inv_scale, coef, k);
     else if (kExchange)
         sparse_tile_dense_grad<OPT, T>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, xj, xg);
     else
@@ -610,7 +624,7 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
         if (nsegs > most) nsegs = most;           // records never hold more; the images must not be overrun whatever they say
         const int64_t base = (int64_t)s0 * kSeg, rest = L.n - base;
         const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
-        if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads>(L, base, len, inv_scale, coef, k);
+        if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads>(L, base, len, 128, inv_scale, coef, k);
         else staged_tile<OPT, WHOLE>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
     };
     if (!PLAN) {
@@ -1339,7 +1353,10 @@ static int occ_tile_step(int gsrc, int opt, float keep, float kept)
     // 735 and 782, 1239 and 1255, 1842 and 2068; 10 and 15 % 452 and 444, 545 and 543; at the line, 18.9 % of 435 M 676 and 680-686, of 1.7 G 2519 and 2671,
     // 18 % 653 and 652, 2481 and 2467; SGD 533 and 524 at 20 %, 1390 and 1365 at 80 %).  What an unpruned
     // embedding adds does not count: three 6.7B layers at 11.5 % with theirs 1756 and 1691
-    const int most = opt == kOptAdam && kept >= 0.185f ? 5 : 6;
+    // (and where unpruned layers are a fifth of the model and more, 6 whatever the pruned ones keep: their tiles want it; 20 % kept, unpruned layers
+    // 15 / 20 / 30 / 50 % of 200 M elements, 5 and 6: 419 and 419, 465 and 461, 506 and 495, 648 and 627)
+    const bool unpruned = keep - kept >= 0.18f * (1.f - kept);
+    const int most = opt == kOptAdam && kept >= 0.185f && !unpruned ? 5 : 6;
     if (gsrc == kGradDense) return knob(SAMO_KNOB_OCC_TILE_STEP, sparse ? (opt == kOptSgd ? 3 : 4) : most);
     return knob(SAMO_KNOB_OCC_TILE_C16, (sparse || keep > 0.15f) ? 6 : 0);
 }

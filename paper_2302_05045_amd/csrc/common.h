@@ -157,6 +157,7 @@ struct LaunchSet {
     float kept;          // the same of its pruned layers alone; negative: it has none
     int num_layers;      // layers of the plan
     int max_segs;        // tile launches: segments the workgroups' LDS image holds (no tile of the launch has more)
+    bool backwards = false;   // tile launches of a plan: the last record first
 };
 // Segments per tile of a single-layer launch, from the layer's average density.
 int single_layer_tile_segs(int64_t n, int64_t nnz, bool dense, bool dense_fp32);

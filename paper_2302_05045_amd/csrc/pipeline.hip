@@ -154,7 +154,8 @@ template <bool GLOBAL>
 __device__ __forceinline__ void pick_tile(const LaunchSet &ls, samo_layer *L, int *s0, int *nsegs)
 {
     if (ls.layers) {
-        const WgRec r = GLOBAL ? constant_rec(ls.recs + blockIdx.x) : ls.recs[blockIdx.x];
+        const int64_t at = ls.backwards ? ls.wgs - 1 - blockIdx.x : blockIdx.x;
+        const WgRec r = GLOBAL ? constant_rec(ls.recs + at) : ls.recs[at];
         if (GLOBAL) *L = constant_layer(ls.layers + r.layer);
         else *L = ls.layers[r.layer];
         *s0 = (int)(r.local & ((1u << kRecSegShift) - 1u));
@@ -1494,14 +1495,21 @@ static bool expand_global_access(const LaunchSet &ls)
 #define SAMO_LAUNCH_TILE(M, G, O, A)                                                                       \
     tile_kernel<M, G, O, kTileThreads, A><<<dim3((unsigned)ls.wgs), dim3(kTileThreads), pad, s>>>(ls, inv_scale, k, guard)
 
-hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls, float inv_scale, const OptK &k,
+// A step under a guard follows the statistics of the gradient that it reads again: tiles taken from the last one back find the end of
+// it still in the last-level cache.  Long plans only, where most of it no longer is (us of statistics and step, forwards and
+// backwards: 350M model, 10 and 20 % kept 483 and 477, 649 and 640; 400 M elements, 15 % 748 and 734; 1.2 G, 10 % 1779 and 1762; 800 M level); what fits
+// the cache is found in either order and was slower backwards (85 M elements, 10 % 144.6 and 147.5), and so were models under 7 %.
+constexpr int64_t kBackwardsFrom = 45000;      // tiles: about 200 M elements
+hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls_in, float inv_scale, const OptK &k,
                        const GuardK &guard, hipStream_t s)
 {
-    if (ls.wgs <= 0) return hipSuccess;
-    if (ls.max_segs < 1 || ls.max_segs > kMaxTileSegs) return hipErrorInvalidValue;
+    if (ls_in.wgs <= 0) return hipSuccess;
+    if (ls_in.max_segs < 1 || ls_in.max_segs > kMaxTileSegs) return hipErrorInvalidValue;
     // static LDS of the kernel: for the step that gathers the dense gradient the waves' exchange areas;
     // dynamic: the tile's fp16 image
     const int static_lds = mode == kModeStep && gsrc == kGradDense ? kTileThreads * 4 * 6 : 32;
+    LaunchSet ls = ls_in;
+    ls.backwards = mode == kModeStep && gsrc == kGradDense && guard.stats && ls.layers && ls.keep >= (float)kSparseKeep && ls.wgs >= kBackwardsFrom;
     const int pad = tile_lds_request(mode == kModeDecompress ? occ_tile_decompress(ls.keep) : occ_tile_step(gsrc, opt, ls.keep, ls.layers ? ls.kept : -1.f),
                                      static_lds, ls.max_segs * kSeg * 2);
     StagedLaunch st;

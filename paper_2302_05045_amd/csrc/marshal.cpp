@@ -194,10 +194,11 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                 for (int64_t sum = part = 0; 2 * sum < elements; ++part) sum += jobs[part].n;
             status = mirrored(jobs.data(), flags.data(), there, (int32_t)part, stream);
             awaited.counts = there;
-            if (status == SAMO_OK) awaited.k = part;
+            // a call that failed at a launch may have launched others before it, any other failure has launched nothing
+            if (status == SAMO_OK || status == SAMO_ERR_HIP) awaited.k = part;
             if (status == SAMO_OK && part < k) {
                 status = mirrored(jobs.data() + part, flags.data() + part, there + part, (int32_t)(k - part), stream);
-                if (status == SAMO_OK) awaited.k = k;
+                if (status == SAMO_OK || status == SAMO_ERR_HIP) awaited.k = k;
             }
         } else {
             status = count(jobs.data(), flags.data(), (int32_t)k, stream);

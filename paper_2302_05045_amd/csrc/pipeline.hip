@@ -150,11 +150,12 @@ __device__ __forceinline__ void pick_work(const LaunchSet &ls, samo_layer *L, in
 // The tile of this workgroup: segments [*s0, *s0 + *nsegs) of *L; *nsegs may be 0 (nothing to do).  GLOBAL: through constant_layer.
 // The single-precision step takes it always (1226 -> 1219 us, 5 % where half or everything is kept), the step on the dense gradient and
 // the expansion in plans where it gains (global_access).  The step on the fp16 message lost 0.4 to 2 %, the flat kernels gained nothing.
-template <bool GLOBAL>
+// EITHER_WAY: the launches whose plans may be taken from the last record back; the others don't look at ls.backwards.
+template <bool GLOBAL, bool EITHER_WAY = false>
 __device__ __forceinline__ void pick_tile(const LaunchSet &ls, samo_layer *L, int *s0, int *nsegs)
 {
     if (ls.layers) {
-        const int64_t at = ls.backwards ? ls.wgs - 1 - blockIdx.x : blockIdx.x;
+        const int64_t at = EITHER_WAY && ls.backwards ? ls.wgs - 1 - blockIdx.x : blockIdx.x;
         const WgRec r = GLOBAL ? constant_rec(ls.recs + at) : ls.recs[at];
         if (GLOBAL) *L = constant_layer(ls.layers + r.layer);
         else *L = ls.layers[r.layer];
@@ -498,7 +499,7 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
     if (skip) return;                         // uniform: every workgroup of the launch takes it
     samo_layer L;
     int s0, nsegs;
-    pick_tile<GLOBAL>(ls, &L, &s0, &nsegs);
+    pick_tile<GLOBAL, kExchange>(ls, &L, &s0, &nsegs);
     if (nsegs > ls.max_segs) nsegs = ls.max_segs;   // a record never holds more; the image must not be overrun whatever it says
     if (nsegs <= 0) return;                   // uniform per workgroup: a record without segments
     const int64_t base = (int64_t)s0 * kSeg;

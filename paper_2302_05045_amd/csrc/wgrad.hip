@@ -51,6 +51,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "runs.h"
 
 namespace samo {
 namespace {
@@ -250,7 +251,7 @@ __device__ __forceinline__ int sum_of_eight(int v)
 template <int OUT, int ROWS, int AHEAD, bool EARLY = true>
 struct RunPass {
     static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = 32;
-    static constexpr unsigned kNone = ~0u;   // no entry: further from every row of a layer than a tile is wide
+    static constexpr unsigned kNone = runs::kNone;
     int first_row, rows, col0, cols;
     int lo[kLooks], hi[kLooks];              // row 8 i + lane / 8: the entries between which its run begins; from settle() on lo is where
     int seen_at[kLooks];                     // -1: nothing was looked at
@@ -259,8 +260,7 @@ struct RunPass {
     unsigned pos[AHEAD][kRows];
     _Float16 old[AHEAD][kRows];
 
-    // The row's first position in the tile (a layer's positions fit 32 bits).
-    __device__ __forceinline__ int key(const WgradArgs &A, int row) const { return (first_row + row) * A.in + col0; }
+    __device__ __forceinline__ unsigned key(const WgradArgs &A, int row) const { return runs::row_key(first_row, row, A.in, col0); }
     __device__ __forceinline__ int look_row(int i) const { return 8 * i + (int)((threadIdx.x & 63) >> 3); }
 
     __device__ __forceinline__ void open(const WgradArgs &A, int row0, int column0, int tile_cols)
@@ -273,7 +273,7 @@ struct RunPass {
         for (int i = 0; i < kLooks; ++i) {
             lo[i] = hi[i] = (int)A.nnz;                              // no such row: an empty run
             if (look_row(i) >= rows) continue;
-            const int p = key(A, look_row(i));
+            const int p = (int)key(A, look_row(i));
             lo[i] = hi[i] = p;                                       // nothing pruned: position = entry
             if (A.idx) {
                 lo[i] = A.seg_ptr[p / kSeg];
@@ -289,7 +289,7 @@ struct RunPass {
             seen[i] = Look{0, 0, 0, 0};
             seen_at[i] = -1;
             if (hi[i] > lo[i] && last >= 0) {
-                const int offset = key(A, look_row(i)) & (kSeg - 1);
+                const int offset = (int)(key(A, look_row(i)) & (kSeg - 1));
                 int at = lo[i] + (((hi[i] - lo[i]) * offset) >> 10) - kLook / 2;
                 at = at > lo[i] ? at : lo[i];
                 seen_at[i] = at < last ? at : last;
@@ -301,7 +301,7 @@ struct RunPass {
     {
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
-            const int want = key(A, look_row(i));
+            const int want = (int)key(A, look_row(i));
             int below = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
@@ -329,7 +329,7 @@ struct RunPass {
         }
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
-            const int l = lo[i], h = hi[i], want = key(A, look_row(i));
+            const int l = lo[i], h = hi[i], want = (int)key(A, look_row(i));
             int below = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
@@ -349,7 +349,7 @@ struct RunPass {
 #pragma unroll
             for (int i = 0; i < kLooks; ++i) {
                 const int l = lo[i], h = hi[i], mid = (l + h) >> 1;
-                const bool open = l < h, before = there[i] < key(A, look_row(i));
+                const bool open = l < h, before = there[i] < (int)key(A, look_row(i));
                 lo[i] = open && before ? mid + 1 : l;
                 hi[i] = open && !before ? mid : h;
                 left |= lo[i] < hi[i];
@@ -390,7 +390,7 @@ struct RunPass {
     // Column in the tile of the lane's entry of row 2 it + half-wave; not below cols: it isn't in the row's run.
     __device__ __forceinline__ unsigned column(const WgradArgs &A, int a, int it) const
     {
-        return pos[a][it] - (unsigned)key(A, 2 * it + (int)((threadIdx.x & 63) >> 5));
+        return runs::column_of(pos[a][it], runs::pair_key(first_row, 2 * it, (int)((threadIdx.x & 63) >> 5), rows, A.in, col0));
     }
     // Whether any row of the wave has entries in step a of those requested (of the first, some row is taken to have).
     __device__ __forceinline__ bool wanted(const WgradArgs &A, int a) const

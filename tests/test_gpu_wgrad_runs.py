@@ -70,3 +70,36 @@ def test_runs_are_found(kind, out_f, in_f, tile):
     assert np.array_equal(gc[:nnz].cpu().numpy(), bits.view(np.float16).astype(np.float32))
     assert np.array_equal(host_bits(gc16[:nnz]), (bits.view(np.float16) + bits.view(np.float16)).astype(np.float16).view(np.uint16))
     assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"
+
+
+@pytest.mark.parametrize("tile,cols", [(128, None), (256, None), (512, None), (None, 128), (None, 160), (None, 192)])
+def test_the_widest_layer(tile, cols):
+    """8 x 2^24, the rows of a tile behind its last one among them: nothing is stored behind the index's entries."""
+    out_f, in_f = 8, 1 << 24
+    rng = np.random.default_rng(6)
+    dy, x = rng.standard_normal((1, out_f)).astype(np.float16), rng.standard_normal((1, in_f)).astype(np.float16)
+    ends = (np.arange(out_f)[:, None] * in_f + np.concatenate([np.arange(70), in_f - 1 - np.arange(70)])[None]).reshape(-1)
+    idx = np.unique(np.concatenate([ends, rng.integers(0, out_f * in_f, 20_000)])).astype(np.int32)
+    nnz = idx.shape[0]
+    want = (dy[0].astype(np.float32)[idx // in_f] * x[0].astype(np.float32)[idx % in_f]).astype(np.float16)       # the product is exact in fp32
+    d_dy, d_x, d_idx, d_seg = torch.from_numpy(dy).to(DEV), torch.from_numpy(x).to(DEV), dev_i32(idx), dev_i32(ref_seg_ptr(idx, out_f * in_f))
+    gc16 = torch.full((nnz + 256,), float("nan"), dtype=torch.float16, device=DEV)
+    gc = torch.full((nnz + 256,), float("nan"), device=DEV)
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)
+    if tile:
+        samo.samo_debug_set(samo.KNOB_WGRAD_TILE, tile)
+    if cols:
+        samo.samo_debug_set(samo.KNOB_WGRAD_COLS, cols)
+    try:
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], workspace=none)
+        samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0, gc[:nnz], workspace=none)
+        torch.cuda.synchronize()
+        bits = host_bits(gc16[:nnz])
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], accumulate=True, workspace=none)
+        torch.cuda.synchronize()
+    finally:
+        samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+        samo.samo_debug_set(samo.KNOB_WGRAD_COLS)
+    assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"
+    assert np.array_equal(bits, want.view(np.uint16)) and np.array_equal(gc[:nnz].cpu().numpy(), want.astype(np.float32))
+    assert np.array_equal(host_bits(gc16[:nnz]), (want + want).view(np.uint16))

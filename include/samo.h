@@ -402,6 +402,9 @@ samo_status samo_fused_step_fp32_batched(const samo_plan *plan, float grad_facto
  * describe the layer of n = out * in elements as everywhere else; d_idx may be
  * NULL only when nnz == out * in (unpruned layer), d_seg_ptr is required
  * whenever d_idx is given.  Nothing is written when nnz == 0.
+ * nnz may be larger than the count in seg_ptr's last entry (the capacity of arrays whose
+ * index was rebuilt with fewer kept elements): entries of idx behind that count are not looked
+ * at, and what d_gc holds behind it is undefined.
  * The first call on a device configures the kernels' LDS size (a HIP function
  * attribute): call samo_init, or make that first call, outside stream capture;
  * later calls only enqueue. */

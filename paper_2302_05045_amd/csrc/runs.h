@@ -23,6 +23,38 @@ constexpr unsigned pair_key(int first_row, int pair, int half, int rows, int in,
     return (unsigned)half * (unsigned)in + row_key(first_row, pair < rows ? pair : rows - 2, in, col0);
 }
 
+// How many entries idx has: a buffer may be longer (an index rebuilt with fewer elements kept in the place of another), and what is behind
+// the ones seg_ptr counts is no index.  counted: the last value of seg_ptr.
+constexpr int entries_of(int nnz, int counted) { return counted < nnz ? counted : nnz; }
+
+// The entries between which a row's run begins: the first one whose position is not below the row's key is at lo at least, at hi at most.
+struct Range {
+    int lo, hi;
+};
+
+// A look reads kLook entries at once.  The first one is put where the run begins if the segment's entries are spread evenly over it; offset:
+// the key's place in the segment.  It may reach beyond the range, never beyond the index (entries >= kLook).
+constexpr int kLook = 32;
+constexpr int first_look(Range r, int offset, int entries)
+{
+    const int at = r.lo + (((r.hi - r.lo) * offset) >> 10) - kLook / 2, from = at > r.lo ? at : r.lo;
+    return from < entries - kLook ? from : entries - kLook;
+}
+
+// The second one beside the first, which began at `seen`, on the side that it points to.
+constexpr int second_look(Range r, int seen, int entries)
+{
+    const int beside = r.lo == seen + kLook ? r.lo : r.hi - kLook, from = beside > 0 ? beside : 0;
+    return from < entries - kLook ? from : entries - kLook;
+}
+
+// What is left of a range after a look at `at` that found `below` entries below the key.
+constexpr Range after_look(Range r, int at, int below)
+{
+    const int first = at + below, lo = below > 0 && first > r.lo ? first : r.lo, hi = below < kLook && first < r.hi ? first : r.hi;
+    return {lo, hi > lo ? hi : lo};
+}
+
 // Column in the tile of an entry at position pos; not below the tile's columns if the entry is not in the row's run.
 constexpr unsigned column_of(unsigned pos, unsigned key) { return pos - key; }
 

@@ -250,9 +250,10 @@ __device__ __forceinline__ int sum_of_eight(int v)
 
 template <int OUT, int ROWS, int AHEAD, bool EARLY = true>
 struct RunPass {
-    static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = 32;
+    static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = runs::kLook;
     static constexpr unsigned kNone = runs::kNone;
     int first_row, rows, col0, cols;
+    int counted, entries;                    // the last value of seg_ptr; the entries of idx that may be looked at, from look() on
     int lo[kLooks], hi[kLooks];              // row 8 i + lane / 8: the entries between which its run begins; from settle() on lo is where
     int seen_at[kLooks];                     // -1: nothing was looked at
     Look seen[kLooks];
@@ -269,6 +270,10 @@ struct RunPass {
         col0 = column0;
         rows = A.out - row0 < ROWS ? A.out - row0 : ROWS;            // not positive: none
         cols = A.in - col0 < tile_cols ? A.in - col0 : tile_cols;
+        // by a scalar load without a branch, which travels with the first copies (await): a vector load of a uniform value, and a load behind a
+        // branch, are waited for at once (7856 x 4632, 106 tokens, 20 % kept 28.9 -> 29.7 us)
+        const int32_t *last = A.idx ? A.seg_ptr + ((unsigned)A.out * (unsigned)A.in + (kSeg - 1)) / kSeg : reinterpret_cast<const int32_t *>(wgrad_zero_row);
+        counted = *(const __attribute__((address_space(4))) int32_t *)last;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
             lo[i] = hi[i] = (int)A.nnz;                              // no such row: an empty run
@@ -281,37 +286,39 @@ struct RunPass {
             }
         }
     }
+    // Behind the first copies.  The compiler, which does not know of the waits in asm, has to see the scalar load used before the main loop:
+    // it would wait for all of a stage's LDS reads at once otherwise, as those and a scalar load return in any order.
+    __device__ __forceinline__ void await() const { asm volatile("" ::"s"(counted)); }
     __device__ __forceinline__ void look(const WgradArgs &A)
     {
-        const int last = (int)A.nnz - kLook;                         // the last place a look may start at
+        entries = A.idx ? runs::entries_of((int)A.nnz, counted) : (int)A.nnz;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
             seen[i] = Look{0, 0, 0, 0};
             seen_at[i] = -1;
-            if (hi[i] > lo[i] && last >= 0) {
-                const int offset = (int)(key(A, look_row(i)) & (kSeg - 1));
-                int at = lo[i] + (((hi[i] - lo[i]) * offset) >> 10) - kLook / 2;
-                at = at > lo[i] ? at : lo[i];
-                seen_at[i] = at < last ? at : last;
+            if (hi[i] > lo[i] && entries >= kLook) {
+                seen_at[i] = runs::first_look({lo[i], hi[i]}, (int)(key(A, look_row(i)) & (kSeg - 1)), entries);
                 seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
             }
         }
     }
+    // What the look of a row's eight lanes leaves of the range, if there was one.  (Both ends are written whatever the case: stores to
+    // either of two arrays keep them in memory.)
+    __device__ __forceinline__ void narrow(const WgradArgs &A, int i, bool looked)
+    {
+        const int want = (int)key(A, look_row(i));
+        int below = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
+        below = sum_of_eight(below);
+        const runs::Range was = {lo[i], hi[i]}, is = runs::after_look(was, seen_at[i], below);
+        lo[i] = looked ? is.lo : was.lo;
+        hi[i] = looked ? is.hi : was.hi;
+    }
     __device__ __forceinline__ void settle(const WgradArgs &A)
     {
 #pragma unroll
-        for (int i = 0; i < kLooks; ++i) {
-            const int want = (int)key(A, look_row(i));
-            int below = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
-            below = sum_of_eight(below);
-            // before, inside or behind the look (both ends are written whatever the case: stores to either of two arrays keep them in memory)
-            const bool looked = seen_at[i] >= 0, early = looked && below == 0, late = looked && below == kLook, found = looked && !early && !late;
-            const int at = seen_at[i] + below, l = lo[i], h = hi[i];
-            lo[i] = found || late ? at : l;
-            hi[i] = found ? at : early ? (seen_at[i] > l ? seen_at[i] : l) : h;
-        }
+        for (int i = 0; i < kLooks; ++i) narrow(A, i, seen_at[i] >= 0);
         bool left = false;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) left |= lo[i] < hi[i];
@@ -320,25 +327,14 @@ struct RunPass {
         left = false;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
-            const int last = (int)A.nnz - kLook;
-            if (lo[i] < hi[i] && last >= 0) {
-                const int beside = lo[i] == seen_at[i] + kLook ? lo[i] : hi[i] - kLook;
-                seen_at[i] = beside < last ? (beside > 0 ? beside : 0) : last;
+            if (lo[i] < hi[i] && entries >= kLook) {
+                seen_at[i] = runs::second_look({lo[i], hi[i]}, seen_at[i], entries);
                 seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
             }
         }
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) {
-            const int l = lo[i], h = hi[i], want = (int)key(A, look_row(i));
-            int below = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) below += seen[i][e] < want ? 1 : 0;
-            below = sum_of_eight(below);
-            const bool looked = l < h && seen_at[i] >= 0;
-            const int at = seen_at[i] + below;                       // the first entry of the look that is not below
-            lo[i] = looked && below > 0 ? (at > l ? at : l) : l;
-            hi[i] = looked && below < kLook ? (at < h ? at : h) : h;
-            if (looked && below == 0 && hi[i] < l) hi[i] = l;
+            narrow(A, i, lo[i] < hi[i] && seen_at[i] >= 0);
             left |= lo[i] < hi[i];
         }
         while (left) {                                               // all the searches a step at a time
@@ -359,13 +355,13 @@ struct RunPass {
     // A step's positions; with EARLY also the values that are added to.
     __device__ __forceinline__ void request(const WgradArgs &A)
     {
-        const unsigned l32 = threadIdx.x & 31, nnz = (unsigned)A.nnz;
+        const unsigned l32 = threadIdx.x & 31, end = (unsigned)entries;
 #pragma unroll
         for (int a = 0; a < AHEAD; ++a)
 #pragma unroll
             for (int it = 0; it < kRows; ++it) {
                 const unsigned k = from[it] + a * 32 + l32;
-                pos[a][it] = k < nnz ? (A.idx ? (unsigned)A.idx[k] : k) : kNone;
+                pos[a][it] = k < end ? (A.idx ? (unsigned)A.idx[k] : k) : kNone;
             }
         if (EARLY) request_old(A);
     }
@@ -375,14 +371,14 @@ struct RunPass {
     {
         if (OUT != kOutF16 || !A.accumulate) return;
         if (!EARLY) asm volatile("" ::: "memory");                   // not before the image is written
-        const unsigned l32 = threadIdx.x & 31, nnz = (unsigned)A.nnz;
+        const unsigned l32 = threadIdx.x & 31, end = (unsigned)entries;
 #pragma unroll
         for (int a = 0; a < AHEAD; ++a) {
             if (!EARLY && !wanted(A, a)) break;
 #pragma unroll
             for (int it = 0; it < kRows; ++it) {
                 const unsigned k = from[it] + a * 32 + l32;
-                const bool there = EARLY ? k < nnz : column(A, a, it) < (unsigned)cols;
+                const bool there = EARLY ? k < end : column(A, a, it) < (unsigned)cols;
                 old[a][it] = there ? reinterpret_cast<const _Float16 *>(A.gc)[k] : (_Float16)0.f;
             }
         }
@@ -448,6 +444,7 @@ struct RunPass {
 template <typename Pass>
 struct TwoPasses {
     Pass half[2];
+    __device__ __forceinline__ void await() const { half[0].await(); half[1].await(); }
     __device__ __forceinline__ void look(const WgradArgs &A) { half[0].look(A); half[1].look(A); }
     __device__ __forceinline__ void settle(const WgradArgs &A) { half[0].settle(A); half[1].settle(A); }
 };
@@ -532,6 +529,7 @@ __device__ __forceinline__ void multiply_tile(const WgradArgs &A, int row0, int 
     const int x_off = lane_read + x_at, y_off = lane_read + 16 * kRowPitch + y_at;
 
     for (int64_t s = 0; s < 3 && s < stages; ++s) issue_stage(s);
+    run.await();
     unsigned slot = 0;                                       // LDS offset of the stage being read
     const unsigned char *gnext = gbase + (3 * kTokens + first_token) * row_bytes;    // the wave's rows three stages ahead
     auto multiply = [&](const half8 (&xa)[IB], const half8 (&yb)[OB]) {
@@ -825,6 +823,8 @@ __global__ void __launch_bounds__(kResidentThreads, 4) wgrad_resident_kernel(con
 #pragma unroll
     for (int i = 0; i < kParts; ++i) run[i].open(A, row0 + wave * 32 + i * kPartRows, col0, kSmallTile);
     if (stages > 0) issue(0);
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) run[i].await();
     f32x4 acc[4][4];
 #pragma unroll
     for (int bo = 0; bo < 4; ++bo)

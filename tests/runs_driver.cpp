@@ -1,6 +1,7 @@
 // Host checks of the weight gradient's run arithmetic (csrc/runs.h), over sides that no GPU test allocates.
 #include <algorithm>
 #include <cstdio>
+#include <random>
 #include <vector>
 
 #include "runs.h"
@@ -41,10 +42,95 @@ void rows_of_tiles(long out, long in, long part0, int tile_rows, int tile_cols)
     }
 }
 
+// A layer's index as the epilogue reads it: idx of nnz entries, of which seg_ptr counts fewer where the buffer is that of an older, longer index.
+struct Layer {
+    int out, in, nnz;
+    std::vector<int> idx, seg_ptr;
+};
+
+Layer layer_of(int out, int in, const std::vector<char> &mask, const std::vector<int> &tail)
+{
+    Layer l = {out, in, 0, {}, {0}};
+    for (int p = 0; p < out * in; ++p) {
+        if (mask[p]) l.idx.push_back(p);
+        if (p % 1024 == 1023 || p + 1 == out * in) l.seg_ptr.push_back((int)l.idx.size());
+    }
+    l.idx.insert(l.idx.end(), tail.begin(), tail.end());
+    l.nnz = (int)l.idx.size();
+    return l;
+}
+
+// Where the run of a row begins that has that key, as the kernel looks for it.
+int begin_of(const Layer &l, int entries, int key)
+{
+    runs::Range r = {l.seg_ptr[key / 1024], l.seg_ptr[key / 1024 + 1]};
+    auto look = [&](int at) {
+        int below = 0;
+        for (int e = 0; e < runs::kLook; ++e) below += l.idx.at(at + e) < key;
+        r = runs::after_look(r, at, below);
+    };
+    if (r.lo < r.hi && entries >= runs::kLook) {
+        const int seen = runs::first_look(r, key & 1023, entries);
+        look(seen);
+        if (r.lo < r.hi) look(runs::second_look(r, seen, entries));
+    }
+    while (r.lo < r.hi) {
+        const int mid = (r.lo + r.hi) >> 1;
+        if (l.idx.at(mid) < key) r.lo = mid + 1;
+        else r.hi = mid;
+    }
+    return r.lo;
+}
+
+// Every row of every tile against the index itself: all its entries, in their places, and none of the tail behind the index.
+void runs_of_layer(const Layer &l, int tile_cols, const char *what)
+{
+    const int entries = runs::entries_of(l.nnz, l.seg_ptr.back()), count = l.seg_ptr.back();
+    for (int row = 0; row < l.out; ++row)
+        for (int col0 = 0; col0 < l.in; col0 += tile_cols) {
+            const int cols = std::min(tile_cols, l.in - col0), key = (int)runs::row_key(0, row, l.in, col0);
+            const int first = (int)(std::lower_bound(l.idx.begin(), l.idx.begin() + count, key) - l.idx.begin());
+            const int last = (int)(std::lower_bound(l.idx.begin(), l.idx.begin() + count, key + cols) - l.idx.begin());
+            int k = begin_of(l, entries, key);
+            expect(k == first, what, row, col0, k, first);
+            while (k < entries && runs::column_of((unsigned)l.idx[k], (unsigned)key) < (unsigned)cols) ++k;
+            expect(k == last, what, row, col0, k, last);
+        }
+}
+
+void runs_of_masks()
+{
+    std::mt19937 rng(11);
+    auto uniform = [&] { return std::uniform_real_distribution<double>(0, 1)(rng); };
+    const int sides[][2] = {{8, 8}, {16, 136}, {64, 520}, {40, 1032}, {520, 64}, {24, 2560}};
+    for (auto &side : sides)
+        for (int kind = 0; kind < 8; ++kind) {
+            const int out = side[0], in = side[1], n = out * in;
+            const double keep[] = {0.0, 0.002, 0.05, 0.1, 0.5, 1.0, 0.1, 0.1};
+            std::vector<char> mask(n);
+            for (int p = 0; p < n; ++p) {
+                double k = keep[kind];
+                if (kind == 6) k = p / in % 10 == 3 ? 0.6 : 0.05;                  // rows of very different density
+                if (kind == 7) k = p % 1024 >= 824 ? 1.0 : 0.0;                    // a segment's last elements alone
+                mask[p] = uniform() < k;
+            }
+            std::vector<int> tail;                                                // the end of an older index
+            for (int p = n - n / 5; p < n; ++p)
+                if (uniform() < 0.5) tail.push_back(p);
+            for (int cols : {128, 160, 256}) {
+                runs_of_layer(layer_of(out, in, mask, {}), cols, "run");
+                runs_of_layer(layer_of(out, in, mask, tail), cols, "run with a tail behind the index");
+                std::vector<int> zeros(50, 0);
+                runs_of_layer(layer_of(out, in, mask, zeros), cols, "run with zeros behind the index");
+            }
+        }
+}
+
 }  // namespace
 
 int main()
 {
+    runs_of_masks();
     const long most = 2147483647, side = 1 << 24;
     for (int rows : {128, 256})
         for (int cols : {128, 160, 192, 256})

@@ -103,3 +103,36 @@ def test_the_widest_layer(tile, cols):
     assert torch.isnan(gc16[nnz:]).all() and torch.isnan(gc[nnz:]).all(), "wrote past the compressed gradient"
     assert np.array_equal(bits, want.view(np.uint16)) and np.array_equal(gc[:nnz].cpu().numpy(), want.astype(np.float32))
     assert np.array_equal(host_bits(gc16[:nnz]), (want + want).view(np.uint16))
+
+
+@pytest.mark.parametrize("tile", [128, 256, 512])
+@pytest.mark.parametrize("keep", [0.002, 0.1, 0.5])
+@pytest.mark.parametrize("out_f,in_f", [(16, 136), (264, 520), (40, 1032)])
+def test_an_index_shorter_than_its_buffer(out_f, in_f, keep, tile):
+    """A layer pruned again with fewer elements kept, in the place of its old index: the entries behind the ones that seg_ptr counts are not
+    looked at, and the gradient behind them is left as it was."""
+    tokens = 37
+    dy, x = si.output_grads_fp16(tokens, out_f, 4), si.activations_fp16(tokens, in_f, 4)
+    n = out_f * in_f
+    idx = oracle.build_index(si.bernoulli_mask(n, keep, 9))
+    nnz = idx.shape[0]
+    d_dy, d_x, d_seg = dev_f16_bits(dy).view(tokens, out_f), dev_f16_bits(x).view(tokens, in_f), dev_i32(ref_seg_ptr(idx, n))
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)
+
+    def gather(d_idx):
+        gc16 = torch.full((d_idx.numel(),), float("nan"), dtype=torch.float16, device=DEV)
+        gc = torch.full((d_idx.numel(),), float("nan"), device=DEV)
+        samo.samo_debug_set(samo.KNOB_WGRAD_TILE, tile)
+        try:
+            samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16, workspace=none)
+            samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16, accumulate=True, workspace=none)
+            samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0, gc, workspace=none)
+            torch.cuda.synchronize()
+        finally:
+            samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+        return gc16, gc
+    want = gather(dev_i32(idx))
+    for tail in (np.arange(n - n // 4, n, 2), np.zeros(70), np.arange(300) * (n // 300)):
+        got = gather(dev_i32(np.concatenate([idx, tail.astype(np.int32)])))
+        for a, b in zip(got, want):
+            assert torch.equal(a[:nnz], b) and torch.isnan(a[nnz:]).all()

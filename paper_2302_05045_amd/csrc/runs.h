@@ -55,6 +55,9 @@ constexpr Range after_look(Range r, int at, int below)
     return {lo, hi > lo ? hi : lo};
 }
 
+// The entry in the middle of a range: entries go up to 2^31, their sum does not fit.
+constexpr int middle(Range r) { return r.lo + ((r.hi - r.lo) >> 1); }
+
 // Column in the tile of an entry at position pos; not below the tile's columns if the entry is not in the row's run.
 constexpr unsigned column_of(unsigned pos, unsigned key) { return pos - key; }
 

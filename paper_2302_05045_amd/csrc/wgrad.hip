@@ -340,11 +340,11 @@ struct RunPass {
         while (left) {                                               // all the searches a step at a time
             int there[kLooks];
 #pragma unroll
-            for (int i = 0; i < kLooks; ++i) there[i] = lo[i] < hi[i] ? A.idx[(lo[i] + hi[i]) >> 1] : 0;
+            for (int i = 0; i < kLooks; ++i) there[i] = lo[i] < hi[i] ? A.idx[runs::middle({lo[i], hi[i]})] : 0;
             left = false;
 #pragma unroll
             for (int i = 0; i < kLooks; ++i) {
-                const int l = lo[i], h = hi[i], mid = (l + h) >> 1;
+                const int l = lo[i], h = hi[i], mid = runs::middle({l, h});
                 const bool open = l < h, before = there[i] < (int)key(A, look_row(i));
                 lo[i] = open && before ? mid + 1 : l;
                 hi[i] = open && !before ? mid : h;

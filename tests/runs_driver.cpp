@@ -75,7 +75,7 @@ int begin_of(const Layer &l, int entries, int key)
         if (r.lo < r.hi) look(runs::second_look(r, seen, entries));
     }
     while (r.lo < r.hi) {
-        const int mid = (r.lo + r.hi) >> 1;
+        const int mid = runs::middle(r);
         if (l.idx.at(mid) < key) r.lo = mid + 1;
         else r.hi = mid;
     }
@@ -131,6 +131,9 @@ void runs_of_masks()
 int main()
 {
     runs_of_masks();
+    const int top = 2147483647;
+    for (int lo : {0, 1, 1 << 30, (1 << 30) + 1, top - 1024, top - 1})
+        for (int hi : {lo + 1, lo + std::min(top - lo, 1024)}) expect(runs::middle({lo, hi}) >= lo && runs::middle({lo, hi}) < hi, "middle", lo, hi, runs::middle({lo, hi}), 0);
     const long most = 2147483647, side = 1 << 24;
     for (int rows : {128, 256})
         for (int cols : {128, 160, 192, 256})

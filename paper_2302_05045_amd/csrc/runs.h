@@ -5,23 +5,17 @@
 namespace samo {
 namespace runs {
 
-constexpr unsigned kNone = ~0u;              // the position of an entry that is not there
-
 // First position in the tile of row `row` of a tile (or part of one) that starts at row first_row, column col0.  The positions of a layer
-// fit 31 bits.  It is for the layer's own rows: (first_row + row) * in passes 2^32 behind the last of a wide one.
+// fit 31 bits, those of the rows of its last tile behind it 32: 256 rows of 2^24, or less than twice the layer's.
 constexpr unsigned row_key(int first_row, int row, int in, int col0)
 {
     return (unsigned)(first_row + row) * (unsigned)in + (unsigned)col0;
 }
 
-// The same of row pair + half for the entries of a pair of rows, pair even.  rows: how many of the tile's rows from first_row on the layer has, not
-// positive if none; it is even, as a layer's sides are multiples of 8.  A pair behind them has no entries, only kNone, and is given the
-// layer's last pair of rows: whatever its key, kNone is a column of no tile (taken as it is, the key of row 255 of the last tile behind
-// 8 x 2^24 is 2^32 - 256, and kNone would be its column 255).
-constexpr unsigned pair_key(int first_row, int pair, int half, int rows, int in, int col0)
-{
-    return (unsigned)half * (unsigned)in + row_key(first_row, pair < rows ? pair : rows - 2, in, col0);
-}
+// The position of an entry that is not there, in a tile column: left of the first row's first position, so that it is the furthest from
+// every row, those behind the layer's last too, whose entries are all of this kind (2^32 - 1 in its place would be column 255 of
+// row 255 in the last tile of an 8 x 2^24 layer).
+constexpr unsigned no_position(int col0) { return (unsigned)col0 - 1u; }
 
 // How many entries idx has: a buffer may be longer (an index rebuilt with fewer elements kept in the place of another), and what is behind
 // the ones seg_ptr counts is no index.  counted: the last value of seg_ptr.

@@ -251,7 +251,6 @@ __device__ __forceinline__ int sum_of_eight(int v)
 template <int OUT, int ROWS, int AHEAD, bool EARLY = true>
 struct RunPass {
     static constexpr int kLooks = ROWS / 8, kRows = ROWS / 2, kLook = runs::kLook;
-    static constexpr unsigned kNone = runs::kNone;
     int first_row, rows, col0, cols;
     int counted, entries;                    // the last value of seg_ptr; the entries of idx that may be looked at, from look() on
     int lo[kLooks], hi[kLooks];              // row 8 i + lane / 8: the entries between which its run begins; from settle() on lo is where
@@ -361,7 +360,7 @@ struct RunPass {
 #pragma unroll
             for (int it = 0; it < kRows; ++it) {
                 const unsigned k = from[it] + a * 32 + l32;
-                pos[a][it] = k < end ? (A.idx ? (unsigned)A.idx[k] : k) : kNone;
+                pos[a][it] = k < end ? (A.idx ? (unsigned)A.idx[k] : k) : runs::no_position(col0);
             }
         if (EARLY) request_old(A);
     }
@@ -384,9 +383,10 @@ struct RunPass {
         }
     }
     // Column in the tile of the lane's entry of row 2 it + half-wave; not below cols: it isn't in the row's run.
+    // (The pair's key in scalar registers: the halves' keys of all rows by themselves were kept in vector registers, of which there are no more.)
     __device__ __forceinline__ unsigned column(const WgradArgs &A, int a, int it) const
     {
-        return runs::column_of(pos[a][it], runs::pair_key(first_row, 2 * it, (int)((threadIdx.x & 63) >> 5), rows, A.in, col0));
+        return runs::column_of(pos[a][it], ((threadIdx.x & 63) >> 5) * (unsigned)A.in + key(A, 2 * it));
     }
     // Whether any row of the wave has entries in step a of those requested (of the first, some row is taken to have).
     __device__ __forceinline__ bool wanted(const WgradArgs &A, int a) const

@@ -29,10 +29,9 @@ void rows_of_tiles(long out, long in, long part0, int tile_rows, int tile_cols)
         if (t >= 0 && t < tiles && std::find(at.begin(), at.end(), t) == at.end()) at.push_back(t);
     for (long t : at) {
         const int col0 = (int)(t * tile_cols), cols = (int)std::min<long>(tile_cols, in - col0);
-        const int rows = (int)std::min<long>(tile_rows, out - part0);
         for (int row = 0; row < tile_rows; ++row) {
-            const unsigned key = runs::pair_key((int)part0, row & ~1, row & 1, rows, (int)in, col0);
-            expect(runs::column_of(runs::kNone, key) >= (unsigned)cols, "no entry", out, in, part0 + row, col0);
+            const unsigned key = runs::row_key((int)part0, row, (int)in, col0);
+            expect(runs::column_of(runs::no_position(col0), key) >= (unsigned)cols, "no entry", out, in, part0 + row, col0);
             if (part0 + row >= out) continue;
             const long first = (part0 + row) * in + col0;
             for (long p : {first - 1, first, first + cols - 1, first + cols, n - 1, 0l})

@@ -49,8 +49,15 @@ constexpr Range after_look(Range r, int at, int below)
     return {lo, hi > lo ? hi : lo};
 }
 
-// The entry in the middle of a range: entries go up to 2^31, their sum does not fit.
-constexpr int middle(Range r) { return r.lo + ((r.hi - r.lo) >> 1); }
+// Where both looks missed (rows of very different density in one segment): eight entries that part what is left in nine, one to each lane.
+// Entries go up to 2^31, so no two of them are added.
+constexpr int kProbes = 8;
+constexpr int probe(Range r, int j) { return r.lo + (int)((unsigned)(j + 1) * (unsigned)(r.hi - r.lo) / (kProbes + 1)); }
+// What is left when `below` of them are below the key.
+constexpr Range after_probes(Range r, int below)
+{
+    return {below > 0 ? probe(r, below - 1) + 1 : r.lo, below < kProbes ? probe(r, below) : r.hi};
+}
 
 // Column in the tile of an entry at position pos; not below the tile's columns if the entry is not in the row's run.
 constexpr unsigned column_of(unsigned pos, unsigned key) { return pos - key; }

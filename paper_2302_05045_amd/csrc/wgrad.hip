@@ -230,14 +230,16 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
 // search together.)  Kept elements spread evenly over a segment of k put the beginning within sqrt(k (1 - k / 1024)) / 2
 // of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %).  A look of 32 misses one row in hundreds, but one
 // in most tiles at 20 % kept; a miss is a near one on masks without structure, so a second look beside the first comes before any
-// bisection (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it).  Where a run ends shows when it is read.
+// other search (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it).  Where more rows of a wave miss, rows of different density share
+// their segments: the eight lanes part what is left in nine at a time (7856 x 4632, a tenth of the rows ten times denser, 20 % kept 42.9 us by
+// bisection behind a second look, 42.0 so; 1000 x 520, 300 tokens 11.9 and 11.3).  Where a run ends shows when it is read.
 // begin() requests the first AHEAD steps' idx, which travels while the image is written, and the values that are added to:
 // with EARLY at once, else when their positions are known and the image is written (the 128 x 128 tile of the longer calls, 4096 x 1024, 1003
 // tokens, accumulating 15.6 against 15.85 us; FC1 of the 2.7B model 102.9 against 102.1 the other way, four workgroups to a compute unit
 // 3 to 5 %).  Before and now, 10 % kept unless said, us: 512 x 512, 100 tokens 6.75 and
 // 6.17; 4096 x 1024, 1003 tokens 15.2 and 14.3; 4096 x 4096, 500 tokens 22.6 and 20.0; 7856 x 4632, 106 tokens, 20 % 50.3 and 43.7;
-// FC1 of the 2.7B model 98.7 and 96.1 (20 %: 105.3 and 102.1).  Rows of very different density (a tenth of them ten times denser) gain
-// less, and up to 8 % is lost on a small layer whose segments straddle rows (512 x 520, 100 tokens 8.6 and 9.3).
+// FC1 of the 2.7B model 98.7 and 96.1 (20 %: 105.3 and 102.1).  Rows of very different density (a tenth of
+// them ten times denser): 7856 x 4632 63.7 and 42.0, FC1 113 and 111, 512 x 520, 100 tokens 9.1 and 9.2.
 typedef int Look __attribute__((ext_vector_type(4), aligned(4)));
 
 // The sum over aligned groups of eight lanes, in every lane.
@@ -321,32 +323,36 @@ struct RunPass {
         bool left = false;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) left |= lo[i] < hi[i];
-        if (!__ballot(left)) return;
-        // A miss on a mask without structure is a near one: the 32 entries beside the look, on the side it points to.
-        left = false;
-#pragma unroll
-        for (int i = 0; i < kLooks; ++i) {
-            if (lo[i] < hi[i] && entries >= kLook) {
-                seen_at[i] = runs::second_look({lo[i], hi[i]}, seen_at[i], entries);
-                seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kLooks; ++i) {
-            narrow(A, i, lo[i] < hi[i] && seen_at[i] >= 0);
-            left |= lo[i] < hi[i];
-        }
-        while (left) {                                               // all the searches a step at a time
-            int there[kLooks];
-#pragma unroll
-            for (int i = 0; i < kLooks; ++i) there[i] = lo[i] < hi[i] ? A.idx[runs::middle({lo[i], hi[i]})] : 0;
+        const uint64_t missed = __ballot(left);
+        if (!missed) return;
+        // A miss on a mask without structure is a near one: the 32 entries beside the look, on the side it points to.  Where more than a few
+        // rows miss, their densities differ and it may be anywhere.
+        if (__popcll(missed) <= 16) {
             left = false;
 #pragma unroll
             for (int i = 0; i < kLooks; ++i) {
-                const int l = lo[i], h = hi[i], mid = runs::middle({l, h});
-                const bool open = l < h, before = there[i] < (int)key(A, look_row(i));
-                lo[i] = open && before ? mid + 1 : l;
-                hi[i] = open && !before ? mid : h;
+                if (lo[i] < hi[i] && entries >= kLook) {
+                    seen_at[i] = runs::second_look({lo[i], hi[i]}, seen_at[i], entries);
+                    seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kLooks; ++i) {
+                narrow(A, i, lo[i] < hi[i] && seen_at[i] >= 0);
+                left |= lo[i] < hi[i];
+            }
+        }
+        while (__ballot(left)) {                                     // all the searches a step at a time
+            int there[kLooks];
+#pragma unroll
+            for (int i = 0; i < kLooks; ++i) there[i] = lo[i] < hi[i] ? A.idx[runs::probe({lo[i], hi[i]}, threadIdx.x & 7)] : 0;
+            left = false;
+#pragma unroll
+            for (int i = 0; i < kLooks; ++i) {
+                const runs::Range was = {lo[i], hi[i]}, is = runs::after_probes(was, sum_of_eight(there[i] < (int)key(A, look_row(i)) ? 1 : 0));
+                const bool open = was.lo < was.hi;
+                lo[i] = open ? is.lo : was.lo;
+                hi[i] = open ? is.hi : was.hi;
                 left |= lo[i] < hi[i];
             }
         }

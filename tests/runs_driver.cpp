@@ -73,10 +73,11 @@ int begin_of(const Layer &l, int entries, int key)
         look(seen);
         if (r.lo < r.hi) look(runs::second_look(r, seen, entries));
     }
-    while (r.lo < r.hi) {
-        const int mid = runs::middle(r);
-        if (l.idx.at(mid) < key) r.lo = mid + 1;
-        else r.hi = mid;
+    for (int steps = 0; r.lo < r.hi; ++steps) {
+        expect(steps < 4, "steps", steps, r.lo, r.hi, key);
+        int below = 0;
+        for (int j = 0; j < runs::kProbes; ++j) below += l.idx.at(runs::probe(r, j)) < key;
+        r = runs::after_probes(r, below);
     }
     return r.lo;
 }
@@ -125,14 +126,36 @@ void runs_of_masks()
         }
 }
 
+// The probes of what two looks left, at the ends of the range of entries: in order, never further from the beginning.
+void probes_of_ranges()
+{
+    const int top = 2147483647;
+    for (int lo : {0, 1, 1 << 30, (1 << 30) + 1, top - 1024, top - 9, top - 1})
+        for (int length = 1; length <= 1024 && length <= top - lo; ++length) {
+            const runs::Range r = {lo, lo + length};
+            for (int j = 0; j < runs::kProbes; ++j) {
+                const int k = runs::probe(r, j);
+                expect(k >= lo && k < r.hi && (j == 0 || k >= runs::probe(r, j - 1)), "probe", lo, length, j, k);
+            }
+            for (int at = 0; at <= length; ++at) {
+                int below = 0;
+                for (int j = 0; j < runs::kProbes; ++j) below += runs::probe(r, j) - lo < at;
+                const runs::Range is = runs::after_probes(r, below);
+                expect(is.lo - lo <= at && at <= is.hi - lo && is.hi - is.lo < length, "left", lo, length, at, is.hi - is.lo);
+            }
+            for (int below = 0; below <= runs::kProbes; ++below) {                // whatever idx holds, the search ends
+                const runs::Range is = runs::after_probes(r, below);
+                expect(is.lo >= r.lo && is.hi <= r.hi && is.hi - is.lo < length, "shorter", lo, length, below, is.hi - is.lo);
+            }
+        }
+}
+
 }  // namespace
 
 int main()
 {
     runs_of_masks();
-    const int top = 2147483647;
-    for (int lo : {0, 1, 1 << 30, (1 << 30) + 1, top - 1024, top - 1})
-        for (int hi : {lo + 1, lo + std::min(top - lo, 1024)}) expect(runs::middle({lo, hi}) >= lo && runs::middle({lo, hi}) < hi, "middle", lo, hi, runs::middle({lo, hi}), 0);
+    probes_of_ranges();
     const long most = 2147483647, side = 1 << 24;
     for (int rows : {128, 256})
         for (int cols : {128, 160, 192, 256})

@@ -32,6 +32,8 @@ def _kept(kind, out_f, in_f):
         for c in (0, 127, 128, 255, 256, in_f - 1):
             if c < in_f:
                 m[:, c] = 1
+    elif kind == "uneven":                             # every seventh row ten times denser, in segments of several rows
+        m[:] = np.random.default_rng(3).random(m.shape) < np.where(np.arange(out_f) % 7 == 3, 0.6, 0.06)[:, None]
     elif kind == "runs33":                             # 33 and 65 entries in a row of a tile: one past a step, one past two
         m[::2, 10:43] = 1
         m[1::2, 20:85] = 1
@@ -40,12 +42,23 @@ def _kept(kind, out_f, in_f):
     return flat
 
 
-@pytest.mark.parametrize("tile", [128, 256])
+# The epilogue's shapes, as (knob, value) pairs, and token counts: of the 128 x 128 tile both loops, the longer of which reads old values late, of the
+# 256 x 256 tile too, the tiles of 256 rows between, four workgroups to a compute unit, and the sums of a split.
+SHAPES = {
+    "128": ([("WGRAD_TILE", 128)], 37), "128 long": ([("WGRAD_TILE", 128)], 705), "256": ([("WGRAD_TILE", 256)], 37),
+    "256 long": ([("WGRAD_TILE", 256)], 257), "256x128": ([("WGRAD_COLS", 128)], 37), "256x160": ([("WGRAD_COLS", 160)], 37),
+    "256x192": ([("WGRAD_COLS", 192)], 37), "resident": ([("WGRAD_TILE", 512)], 37),
+    "split 128": ([("WGRAD_TILE", 128), ("WGRAD_SPLIT", 2)], 130), "split 256": ([("WGRAD_TILE", 256), ("WGRAD_SPLIT", 3)], 130),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(SHAPES))
 @pytest.mark.parametrize("out_f,in_f", [(16, 136), (264, 520), (40, 1032)])
 @pytest.mark.parametrize("kind", ["first1", "first31", "first32", "first33", "last1", "last31", "last33", "heads", "tails",
-                                  "full_rows", "columns", "runs33"])
-def test_runs_are_found(kind, out_f, in_f, tile):
-    tokens, seed = 37, 4
+                                  "full_rows", "columns", "uneven", "runs33"])
+def test_runs_are_found(kind, out_f, in_f, shape):
+    knobs, tokens = SHAPES[shape]
+    seed = 4
     dy, x = si.output_grads_fp16(tokens, out_f, seed), si.activations_fp16(tokens, in_f, seed)
     idx = oracle.build_index(_kept(kind, out_f, in_f))
     nnz = idx.shape[0]
@@ -55,17 +68,19 @@ def test_runs_are_found(kind, out_f, in_f, tile):
     lo, hi = _bracket(dy, x, tokens, out_f, in_f, idx)
     gc16 = torch.full((nnz + 8,), float("nan"), dtype=torch.float16, device=DEV)
     gc = torch.full((nnz + 8,), float("nan"), device=DEV)
-    none = torch.empty(0, dtype=torch.uint8, device=DEV)
-    samo.samo_debug_set(samo.KNOB_WGRAD_TILE, tile)
+    kw = {} if "split" in shape else dict(workspace=torch.empty(0, dtype=torch.uint8, device=DEV))
+    for name, value in knobs:
+        samo.samo_debug_set(getattr(samo, "KNOB_" + name), value)
     try:
-        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], workspace=none)
-        samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0, gc[:nnz], workspace=none)
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], **kw)
+        samo.samo_wgrad_gather(d_dy, d_x, d_idx, d_seg, 1.0, gc[:nnz], **kw)
         torch.cuda.synchronize()
         bits = host_bits(gc16[:nnz])
-        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], accumulate=True, workspace=none)
+        samo.samo_wgrad_gather_fp16(d_dy, d_x, d_idx, d_seg, gc16[:nnz], accumulate=True, **kw)
         torch.cuda.synchronize()
     finally:
-        samo.samo_debug_set(samo.KNOB_WGRAD_TILE)
+        for name, _ in knobs:
+            samo.samo_debug_set(getattr(samo, "KNOB_" + name))
     _check_f16(bits, lo, hi, want, kind)
     assert np.array_equal(gc[:nnz].cpu().numpy(), bits.view(np.float16).astype(np.float32))
     assert np.array_equal(host_bits(gc16[:nnz]), (bits.view(np.float16) + bits.view(np.float16)).astype(np.float16).view(np.uint16))

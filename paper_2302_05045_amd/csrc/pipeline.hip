@@ -184,24 +184,29 @@ __device__ __forceinline__ int slice_bound(const samo_layer &L, int s)
 // each other, so that every access of a wave is one contiguous run.  (Two vectors side by side in a thread, as it was, and 16 bytes of
 // the fp16 arrays: every line is asked for twice.)  The gradient, read exactly once, is loaded past the caches.  The expansion
 // reads one array and writes one, with 16 bytes a thread of what it writes.
-// active: how many threads take part.  What bounds a long launch is how much is in flight: one wave of a workgroup is enough, the
-// others only add to it; a short one ends sooner with two.  Us of an Adam step, as it was / 64 threads / 128: the 50304 x 4096
-// embedding 989 / 933 / 995, 60 M elements 291 / 282 / 291, 30 M 148 / 147 / 146, 12 M 57.7 / 60.1 / 54.3, 2000 vectors of 768 elements 10.6 / 10.3 / 9.0.
-constexpr int64_t kLongDense = 25000;   // workgroups of a launch (segments, where all is unpruned) from which on it is 64
-template <int MODE, int GSRC, int OPT, int T>
-__device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, int len, int active, float inv_scale, float coef,
-                                           const OptK &k)
+// ACTIVE: how many threads take part.  What bounds a long launch is how much is in flight: one wave of a workgroup is enough, the
+// others only add to it; a short one ends sooner with two.  Us of an Adam step, two vectors side by side / 64 threads / 128: the 50304 x 4096
+// embedding 989 / 966 / 995, 46 M elements 222 / 213 / 222, 27 M 126 / 120 / 127, 17 M 87.5 / 84.0 / 79.3, 2000 vectors of 768 elements 10.6 / 10.3 / 9.0.
+// ORDER: in the longest launches the last vector of the state is requested when the first one has come (the embedding 966 and 914, three
+// 6.7B layers with it 1686 and 1618); shorter ones lose by such a wait (for the gradient: 27 M 120 and 123, on the fp16 message 119 and 126, 38 M
+// 173 and 177).  The gradient before v alone: where all 512 threads of staged_kernel take part it gains (8 M
+// elements 41.9 and 39.3), with 64 threads it loses (27 M 120 and 129).
+// What is no whole trip is taken element by element (9000 vectors of 768 elements 30.6 us, a vector to a thread 32.0), in staged_kernel a vector
+// to a thread (two records of 1024 elements are one tile there: 128 threads made two trips, 2000 vectors of 4096 40.4 and 36.4 us).
+constexpr int64_t kLongDense = 25000, kLongestDense = 45000;   // workgroups of a launch (segments, where all is unpruned) above which it is 64, and late
+enum Order { kStateFirst, kGradientFirst, kLastLate };
+template <int MODE, int GSRC, int OPT, int T, int ACTIVE, Order ORDER, bool VECTORS = false>
+__device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, int len, float inv_scale, float coef, const OptK &k)
 {
     constexpr bool kPair = MODE == kModeDecompress;          // the two vectors of a thread side by side
-    if (kPair) active = T;
     const int tid = threadIdx.x;
     float4 *__restrict__ P = reinterpret_cast<float4 *>(L.p + base);
     float4 *__restrict__ M = reinterpret_cast<float4 *>(L.m + base);
     float4 *__restrict__ V = reinterpret_cast<float4 *>(L.v + base);
-    const int trips = kPair ? (len / 8 + T - 1) / T : len / (8 * active);
+    const int trips = kPair ? (len / 8 + T - 1) / T : len / (8 * ACTIVE);
 #pragma unroll 1
-    for (int trip = 0; trip < trips && tid < active; ++trip) {
-        const int o = kPair ? 2 * (trip * T + tid) : trip * 2 * active + tid, o2 = kPair ? o + 1 : o + active;
+    for (int trip = 0; trip < trips && (kPair || tid < ACTIVE); ++trip) {
+        const int o = kPair ? 2 * (trip * T + tid) : trip * 2 * ACTIVE + tid, o2 = kPair ? o + 1 : o + ACTIVE;
         if (kPair && o2 >= len / 8 * 2) break;
         float p[8], m[8], v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, g[8];
         const float4 pa = P[o], pb = P[o2];
@@ -209,7 +214,7 @@ __device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, in
         if (MODE == kModeStep) {
             const float4 ma = M[o], mb = M[o2];
             m[0] = ma.x; m[1] = ma.y; m[2] = ma.z; m[3] = ma.w; m[4] = mb.x; m[5] = mb.y; m[6] = mb.z; m[7] = mb.w;
-            if (OPT == kOptAdam) {
+            if (OPT == kOptAdam && ORDER == kStateFirst) {
                 const float4 va = V[o], vb = V[o2];
                 v[0] = va.x; v[1] = va.y; v[2] = va.z; v[3] = va.w; v[4] = vb.x; v[5] = vb.y; v[6] = vb.z; v[7] = vb.w;
             }
@@ -226,6 +231,13 @@ __device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, in
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     g[u] = (half_bits_to_float((uint16_t)(gw[u >> 1] >> (16 * (u & 1)))) * inv_scale) * coef;
+            }
+            if (OPT == kOptAdam && ORDER != kStateFirst) {
+                const float4 va = V[o];
+                int last = o2;
+                if (ORDER == kLastLate) asm volatile("" : "+v"(last) : "v"(pa.x));
+                const float4 vb = V[last];
+                v[0] = va.x; v[1] = va.y; v[2] = va.z; v[3] = va.w; v[4] = vb.x; v[5] = vb.y; v[6] = vb.z; v[7] = vb.w;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) opt_update<OPT>(p[u], m[u], v[u], g[u], k);
@@ -249,7 +261,36 @@ __device__ __forceinline__ void dense_tile(const samo_layer &L, int64_t base, in
             __builtin_nontemporal_store(u32x2{wq[2], wq[3]}, wv + o2);
         }
     }
-    const int nvec = kPair ? len / 8 * 2 : trips * 2 * active;    // elements handled above, in units of four
+    int nvec = kPair ? len / 8 * 2 : trips * 2 * ACTIVE;      // elements handled above, in units of four
+    if (VECTORS) {
+#pragma unroll 1
+        for (int o = nvec + tid; o < len / 4; o += T) {       // what is no whole trip, a vector to a thread
+            const float4 pa = P[o], ma = M[o];
+            float p[4] = {pa.x, pa.y, pa.z, pa.w}, m[4] = {ma.x, ma.y, ma.z, ma.w}, v[4] = {0.f, 0.f, 0.f, 0.f}, g[4];
+            if (OPT == kOptAdam) {
+                const float4 va = V[o];
+                v[0] = va.x; v[1] = va.y; v[2] = va.z; v[3] = va.w;
+            }
+            if (GSRC == kGradC32) {
+                const f32x4 ga = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(L.gc + base) + o);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) g[u] = ga[u] * coef;
+            } else {
+                const u32x2 ga = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>((GSRC == kGradDense ? L.g : L.gc16) + base) + o);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) g[u] = (half_bits_to_float((uint16_t)(ga[u >> 1] >> (16 * (u & 1)))) * inv_scale) * coef;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) opt_update<OPT>(p[u], m[u], v[u], g[u], k);
+            P[o] = make_float4(p[0], p[1], p[2], p[3]);
+            M[o] = make_float4(m[0], m[1], m[2], m[3]);
+            if (OPT == kOptAdam) V[o] = make_float4(v[0], v[1], v[2], v[3]);
+            const u32x2 wq = {(uint32_t)float_to_half_bits(p[0]) | ((uint32_t)float_to_half_bits(p[1]) << 16),
+                              (uint32_t)float_to_half_bits(p[2]) | ((uint32_t)float_to_half_bits(p[3]) << 16)};
+            __builtin_nontemporal_store(wq, reinterpret_cast<u32x2 *>(L.w + base) + o);
+        }
+        nvec = len / 4;
+    }
 #pragma unroll 1
     for (int e = nvec * 4 + tid; e < len; e += T) {      // ragged end of the layer
         float pe = L.p[base + e];
@@ -505,9 +546,11 @@ tile_kernel(const LaunchSet ls, float inv_scale, const OptK k, const GuardK guar
     const int64_t base = (int64_t)s0 * kSeg;
     const int64_t rest = L.n - base;
     const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
-    if (L.seg_ptr == nullptr)                 // dense (unpruned) layer
-        dense_tile<MODE, GSRC, OPT, T>(L, base, len, ls.wgs > kLongDense ? 64 : 128, inv_scale, coef, k);
-    else if (kExchange)
+    if (L.seg_ptr == nullptr) {               // dense (unpruned) layer
+        if (MODE == kModeStep && ls.wgs > kLongestDense) dense_tile<MODE, GSRC, OPT, T, 64, kLastLate>(L, base, len, inv_scale, coef, k);
+        else if (MODE == kModeStep && ls.wgs > kLongDense) dense_tile<MODE, GSRC, OPT, T, 64, kStateFirst>(L, base, len, inv_scale, coef, k);
+        else dense_tile<MODE, GSRC, OPT, T, 128, kStateFirst>(L, base, len, inv_scale, coef, k);
+    } else if (kExchange)
         sparse_tile_dense_grad<OPT, T>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, xj, xg);
     else
         sparse_tile<MODE, GSRC, OPT, T>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w);
@@ -626,7 +669,7 @@ staged_kernel(const LaunchSet ls, int merge, float inv_scale, const OptK k, cons
         if (nsegs > most) nsegs = most;           // records never hold more; the images must not be overrun whatever they say
         const int64_t base = (int64_t)s0 * kSeg, rest = L.n - base;
         const int len = rest < (int64_t)nsegs * kSeg ? (int)rest : nsegs * kSeg;
-        if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads>(L, base, len, 128, inv_scale, coef, k);
+        if (L.seg_ptr == nullptr) dense_tile<kModeStep, kGradDense, OPT, kStagedThreads, kStagedThreads / 2, kGradientFirst, true>(L, base, len, inv_scale, coef, k);
         else staged_tile<OPT, WHOLE>(L, s0, nsegs, base, len, inv_scale, coef, k, lds_w, lds_g);
     };
     if (!PLAN) {

@@ -1,4 +1,4 @@
-"""Unpruned layers in launches long enough for one wave a tile, against the same elements stepped in short launches (two waves a tile, or the
+"""Unpruned layers in launches long enough for one wave a tile, and for a late last request, against the same elements stepped in short launches (two waves a tile, or the
 kernel of short launches): the same bits, over the ragged end of the layer too, beside small layers and pruned ones."""
 import pytest
 import torch
@@ -7,7 +7,7 @@ import paper_2302_05045_amd as samo
 from gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
-LONG = 25_010 * 1024            # more workgroups than the line between the two, by itself
+LONG, LONGEST = 25_010 * 1024, 45_010 * 1024            # more workgroups than the lines between the three, by themselves
 
 
 def _fill(layers, seed):
@@ -36,9 +36,10 @@ def _step(plan, op):
 
 
 @pytest.mark.parametrize("op", ["adam", "sgd", "c16", "expand"])
-@pytest.mark.parametrize("extra", [0, 8, 515, 1019])
-def test_long_launches_give_the_bits_of_short_ones(extra, op):
-    sizes = [(777, 777, True), (LONG + extra, LONG + extra, True), (1024, 1024, True)]
+@pytest.mark.parametrize("n", [LONG, LONG + 8, LONG + 515, LONG + 1019, LONGEST + 4, LONGEST + 515])
+def test_long_launches_give_the_bits_of_short_ones(n, op):
+    extra = n % 1024
+    sizes = [(777, 777, True), (n, n, True), (1024, 1024, True)]
     kw = dict(bucket_gc16=True) if op == "c16" else {}
     layers = samo.alloc_model(sizes, DEV, **kw)
     _fill(layers, 3 + extra)
@@ -60,3 +61,23 @@ def test_long_launches_give_the_bits_of_short_ones(extra, op):
                 if getattr(S, k) is not None:
                     a, b = getattr(L, k)[first:first + n], getattr(S, k)[:n]
                     assert torch.equal(a.view(torch.int16 if k == "w" else torch.int32), b.view(torch.int16 if k == "w" else torch.int32)), (k, first)
+
+
+@pytest.mark.parametrize("op", ["adam", "sgd"])
+@pytest.mark.parametrize("n", [4096, 4099, 4100, 4611, 5117, 5120])
+def test_two_records_a_workgroup_give_the_bits_of_one(n, op):
+    """The kernel of short launches takes two segments of an unpruned layer as one tile, ragged ends among them."""
+    got = []
+    for tiles in (samo.KNOB_DEFAULT, 0):
+        layers = samo.alloc_model([(n, n, True)] * 750, DEV)
+        _fill(layers[:20], n)
+        samo.samo_debug_set(samo.KNOB_STAGED_TILES, tiles)
+        try:
+            _step(samo.Plan(layers), op)
+            torch.cuda.synchronize()
+        finally:
+            samo.samo_debug_set(samo.KNOB_STAGED_TILES)
+        got.append([(L.p, L.m, L.w) + (() if L.v is None else (L.v,)) for L in layers[:20]])
+    for a, b in zip(*got):
+        for x, y in zip(a, b):
+            assert torch.equal(x.view(torch.int16), y.view(torch.int16))

@@ -91,7 +91,7 @@ struct WithoutGil {
 constexpr int64_t kFirstFill = 32 << 20;
 
 // Waits until a count has appeared in page-locked memory; false if that takes longer than kPatience: other work ahead on the
-// stream, or a stream under capture, where nothing runs.  The caller then reads the counts back, which waits for the stream or refuses.
+// stream.  The caller then reads the counts back, which waits for the stream.
 constexpr int64_t kNoCount = -1;
 constexpr std::chrono::microseconds kPatience(2000);
 bool seen(const int64_t *count)
@@ -129,8 +129,8 @@ struct CountsAwaited {
 constexpr int64_t kCountInParts = 64 << 20;
 
 // build_indices(masks, stream, scratch, count, fill[, mirrored]): indices of byte masks (a list) by the entries samo_count_flags_batched (or,
-// where it is given, samo_count_flags_mirrored_batched, whose counts are polled instead of read back: a stream synchronisation
-// and a copy between the two launches are 10 to 15 us) and samo_fill_index_batched at the addresses `count`, `mirrored` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
+// where it is given and not 0, samo_count_flags_mirrored_batched, whose counts are polled instead of read back: a stream synchronisation
+// and a copy between the two launches are 10 to 15 us; not on a stream under capture, whose graph would keep the page-locked memory) and samo_fill_index_batched at the addresses `count`, `mirrored` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
 // uint8 tensor for the flag bits or None.
 // A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int; None where the
 // caller has to go another way: a mask is no plain tensor, or there is no scratch memory.

@@ -1,5 +1,5 @@
 """The index build whose counts are polled in page-locked memory: the counts there, masks counted in two launches, other work ahead of
-the build for longer than it polls, several threads on streams of their own."""
+the build for longer than it polls, several threads on streams of their own, a stream under capture, launches that fail."""
 import ctypes
 import threading
 
@@ -82,3 +82,72 @@ def test_threads_on_streams_of_their_own():
     assert not failed
     for m, ix in zip(masks, found):
         _check(m, ix)
+
+
+MIRRORED = ctypes.CFUNCTYPE(ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p)
+
+
+def _mirrored_through(entry):
+    """The address of the entry's callback, which calls entry(real entry, arguments); the callback object keeps it alive."""
+    real = ctypes.cast(samo._entry_address("samo_count_flags_mirrored_batched"), MIRRORED)
+    callback = MIRRORED(lambda *a: entry(real, a))
+    return callback, ctypes.cast(callback, ctypes.c_void_p).value
+
+
+def test_build_under_capture_is_refused_and_captures_no_page_locked_memory(monkeypatch):
+    """Nothing runs on a stream under capture, so the read-back of the counts is refused there.  The capture itself goes on, and its graph
+    can be launched: what it holds must not write to page-locked memory that has gone back to its cache."""
+    with open("/proc/self/maps") as maps:
+        path = next(line.split()[-1] for line in maps if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    calls = []
+    callback, address = _mirrored_through(lambda real, a: (calls.append(a[2]), real(*a))[1])
+    entry_address = samo._entry_address
+    monkeypatch.setattr(samo, "_entry_address", lambda name: address if name == "samo_count_flags_mirrored_batched" else entry_address(name))
+    mask = _mask(70_000, 0.2, 9)
+    side, graph = torch.cuda.Stream(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        _check(mask, samo.samo_build_index(mask))                    # the allocators hold what the next call needs
+        assert len(calls) == 1
+        torch.cuda.synchronize()
+        stream = ctypes.c_void_p(side.cuda_stream)
+        assert hip.hipStreamBeginCapture(stream, 1) == 0
+        try:
+            with pytest.raises(RuntimeError):
+                samo.samo_build_index(mask)
+        finally:
+            hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+            if graph.value:
+                hip.hipGraphDestroy(graph)
+        assert len(calls) == 1, "page-locked memory of a call that has returned is written by the captured launch"
+        hip.hipGetLastError()
+        torch.cuda.synchronize()
+        for _ in range(3):
+            _check(mask, samo.samo_build_index(mask))
+        assert len(calls) == 4
+    del callback
+
+
+@pytest.mark.parametrize("fails", [0, 1])
+def test_a_launch_that_fails(fails):
+    """The counts of the launches before it are waited for: the page-locked memory goes back to its cache with the call."""
+    seen = []
+
+    def entry(real, a):
+        seen.append((a[2], a[3]))
+        return real(*a) if len(seen) != fails + 1 else samo.SAMO_ERR_HIP
+    callback, address = _mirrored_through(entry)
+    masks = [_mask(n, 0.1, 4) for n in ((1 << 25) + 3, 5000, 1 << 25)]          # counted in two launches
+    torch.cuda.synchronize()
+    torch.cuda._sleep(50_000_000)                     # for longer than the host polls
+    status = samo._marshal.build_indices(masks, samo._stream, samo._scratch, samo._entry_address("samo_count_flags_batched"),
+                                         samo._entry_address("samo_fill_index_batched"), address)
+    assert status == samo.SAMO_ERR_HIP and len(seen) == fails + 1
+    for counts, num_jobs in seen[:fails]:
+        found = list((ctypes.c_int64 * num_jobs).from_address(counts))
+        assert found == [int(m.sum()) for m in masks[:num_jobs]]
+    torch.cuda.synchronize()
+    for m, ix in zip(masks, samo.samo_build_index_many(masks)):
+        _check(m, ix)
+    del callback

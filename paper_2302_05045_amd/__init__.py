@@ -359,12 +359,13 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     For plain tensors, with memory for the flag bits, native code does it where that is built (_marshal.build_indices): the counts are
     not read back but polled in page-locked memory, by a host that spins for at most 2 ms and then reads them back after all, and from
     64 M elements on the masks are counted in two launches.  28 matrices, 550 M elements: 243 us with the loops below, 183 so."""
+    masks = list(masks)
     if _marshal is not None:
         count, fill = _entry_address("samo_count_flags_batched"), _entry_address("samo_fill_index_batched")
         # Not under capture: the graph may be launched after the page-locked counts have gone back to their cache.
         capturing = getattr(masks[0], "is_cuda", False) and _is_capturing()
         mirrored = 0 if capturing else _entry_address("samo_count_flags_mirrored_batched")
-        built = _marshal.build_indices(list(masks), _stream, _scratch, count, fill, mirrored)
+        built = _marshal.build_indices(masks, _stream, _scratch, count, fill, mirrored)
         if isinstance(built, list):
             return [Index(*parts) for parts in built]
         if built == SAMO_ERR_SIZE:

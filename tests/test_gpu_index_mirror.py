@@ -49,7 +49,7 @@ def test_counts_in_page_locked_memory(sizes):
 @pytest.mark.parametrize("sizes", [((1 << 26) + 5,), (1 << 25, 1 << 25), (5, 1 << 26, 1000), (40_000_001, 30_000_000, 0, 77)])
 def test_masks_counted_in_two_launches(sizes):
     masks = [_mask(n, 0.1, 5 + i) for i, n in enumerate(sizes)]
-    for m, ix in zip(masks, samo.samo_build_index_many(masks)):
+    for m, ix in zip(masks, samo.samo_build_index_many(m for m in masks)):             # any iterable of masks
         _check(m, ix)
 
 

@@ -230,9 +230,10 @@ __device__ __forceinline__ bool tile_origin(const WgradBatch &B, WgradArgs &A, i
 // search together.)  Kept elements spread evenly over a segment of k put the beginning within sqrt(k (1 - k / 1024)) / 2
 // of the guess in the mean square (5 entries at 10 % kept, 8 at 50 %).  A look of 32 misses one row in hundreds, but one
 // in most tiles at 20 % kept; a miss is a near one on masks without structure, so a second look beside the first comes before any
-// other search (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it).  Where more rows of a wave miss, rows of different density share
-// their segments: the eight lanes part what is left in nine at a time (7856 x 4632, a tenth of the rows ten times denser, 20 % kept 42.9 us by
-// bisection behind a second look, 42.0 so; 1000 x 520, 300 tokens 11.9 and 11.3).  Where a run ends shows when it is read.
+// other search (2376 x 7080, 20 % kept, 235 tokens 29.4 -> 27.9 us with it; left out where more than two groups of lanes missed, layers of no
+// round width lose 3 to 7 % at 20 % kept, and gain nothing on rows of different density).  Rows of very different density that share a
+// segment miss it too: the eight lanes part what is left in nine at a time (1000 x 520, 300 tokens, 20 % kept, a tenth of the rows ten times
+// denser 12.1 us by bisection, 11.4 so; 7856 x 4632, 106 tokens 45.4 and 44.0).  Where a run ends shows when it is read.
 // begin() requests the first AHEAD steps' idx, which travels while the image is written, and the values that are added to:
 // with EARLY at once, else when their positions are known and the image is written (the 128 x 128 tile of the longer calls, 4096 x 1024, 1003
 // tokens, accumulating 15.6 against 15.85 us; FC1 of the 2.7B model 102.9 against 102.1 the other way, four workgroups to a compute unit
@@ -323,24 +324,20 @@ struct RunPass {
         bool left = false;
 #pragma unroll
         for (int i = 0; i < kLooks; ++i) left |= lo[i] < hi[i];
-        const uint64_t missed = __ballot(left);
-        if (!missed) return;
-        // A miss on a mask without structure is a near one: the 32 entries beside the look, on the side it points to.  Where more than a few
-        // rows miss, their densities differ and it may be anywhere.
-        if (__popcll(missed) <= 16) {
-            left = false;
+        if (!__ballot(left)) return;
+        // A miss on a mask without structure is a near one: the 32 entries beside the look, on the side it points to.
+        left = false;
 #pragma unroll
-            for (int i = 0; i < kLooks; ++i) {
-                if (lo[i] < hi[i] && entries >= kLook) {
-                    seen_at[i] = runs::second_look({lo[i], hi[i]}, seen_at[i], entries);
-                    seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
-                }
+        for (int i = 0; i < kLooks; ++i) {
+            if (lo[i] < hi[i] && entries >= kLook) {
+                seen_at[i] = runs::second_look({lo[i], hi[i]}, seen_at[i], entries);
+                seen[i] = *reinterpret_cast<const Look *>(A.idx + seen_at[i] + 4 * (threadIdx.x & 7));
             }
+        }
 #pragma unroll
-            for (int i = 0; i < kLooks; ++i) {
-                narrow(A, i, lo[i] < hi[i] && seen_at[i] >= 0);
-                left |= lo[i] < hi[i];
-            }
+        for (int i = 0; i < kLooks; ++i) {
+            narrow(A, i, lo[i] < hi[i] && seen_at[i] >= 0);
+            left |= lo[i] < hi[i];
         }
         while (__ballot(left)) {                                     // all the searches a step at a time
             int there[kLooks];

@@ -32,7 +32,8 @@
  *     owns every buffer, workspaces included.  The library is stateless: it
  *     allocates nothing, frees nothing and copies nothing between host and
  *     device; host tables (layer descriptors, job lists) reach the device inside
- *     kernel arguments.
+ *     kernel arguments.  (samo_count_flags_mirrored_batched alone has the device
+ *     store in host memory, the caller's page-locked counts.)
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
  *     Every call only enqueues kernels on `stream` and returns; nothing
  *     synchronises, nothing runs on another stream, so every entry point that
@@ -181,7 +182,7 @@ samo_status samo_build_index_batched(const samo_index_job *h_jobs, int32_t num_j
  * samo_count_flags_mirrored_batched: the same, and the count of job j is stored in h_counts[j] too, page-locked host
  * memory that the device can write (hipHostMalloc); a count there is final as soon as it is seen, which
  * may be before the launch has ended.  The memory has to stay until all counts have been seen or the
- * stream has been waited for.
+ * stream has been waited for; that of a captured call for as long as its graph may be launched.
  * samo_fill_index_batched: writes the first idx_capacity positions of every job from the
  * flag bits, the seg_ptr and the nnz such a call left, later on the same stream; the mask is not read.
  * A job with *nnz < 0 (as a build in one call reports that it gave up) is left without positions. */

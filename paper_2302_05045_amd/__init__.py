@@ -339,7 +339,7 @@ _addresses: dict = {}
 
 
 def _entry_address(name: str) -> int:
-    """Address of a library entry, for native code that calls it."""
+    """Address of an entry of the library, or of the runtime it is linked with, for native code that calls it."""
     at = _addresses.get(name)
     if at is None:
         at = _addresses[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
@@ -362,10 +362,8 @@ def _build_indices(masks: Sequence[torch.Tensor], where: str) -> list:
     masks = list(masks)
     if _marshal is not None:
         count, fill = _entry_address("samo_count_flags_batched"), _entry_address("samo_fill_index_batched")
-        # Not under capture: the graph may be launched after the page-locked counts have gone back to their cache.
-        capturing = getattr(masks[0], "is_cuda", False) and _is_capturing()
-        mirrored = 0 if capturing else _entry_address("samo_count_flags_mirrored_batched")
-        built = _marshal.build_indices(masks, _stream, _scratch, count, fill, mirrored)
+        mirrored, capture = _entry_address("samo_count_flags_mirrored_batched"), _entry_address("hipStreamIsCapturing")
+        built = _marshal.build_indices(masks, _stream, _scratch, count, fill, mirrored, capture)
         if isinstance(built, list):
             return [Index(*parts) for parts in built]
         if built == SAMO_ERR_SIZE:

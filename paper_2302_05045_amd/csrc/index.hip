@@ -381,8 +381,8 @@ index_kernel(const IndexBatch batch)
 // end of each of its segments; the block's own total, in its last entry, is encoded as in the chain.  No workgroup waits for another.
 // offsets_kernel adds what lies in front of each block: a workgroup sums the totals of all the blocks before its own (back to one
 // that another workgroup has already replaced by the running total), so nothing waits there either.
-// What bounds it: the mask read at HBM rate, and the flag words written beside it, an eighth of that: 550 MB of mask in 101 us, 6.1 TB/s
-// read and written; a kernel that only reads them takes 82.  Blocks of 16 or 32 segments (two or four waves) count as fast
+// What bounds it: the mask read at HBM rate, and the flag words written beside it, an eighth of that: 550 MB of mask in one launch 101 us,
+// 6.1 TB/s read and written, in the two that the binding makes of so many 54 and 49; a kernel that only reads them takes 82.  Blocks of 16 or 32 segments (two or four waves) count as fast
 // but leave offsets_kernel two or four times the totals to sum (8.5 us instead of 6.5 with 32).
 constexpr int kCountWaves = 8;
 constexpr int kBlockSegs = kCountWaves * kSegsPerPass;

@@ -128,10 +128,11 @@ struct CountsAwaited {
 // fill of its masks is launched, while the second half is counted.
 constexpr int64_t kCountInParts = 64 << 20;
 
-// build_indices(masks, stream, scratch, count, fill[, mirrored]): indices of byte masks (a list) by the entries samo_count_flags_batched (or,
-// where it is given and not 0, samo_count_flags_mirrored_batched, whose counts are polled instead of read back: a stream synchronisation
-// and a copy between the two launches are 10 to 15 us; not on a stream under capture, whose graph would keep the page-locked memory) and samo_fill_index_batched at the addresses `count`, `mirrored` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
-// uint8 tensor for the flag bits or None.
+// build_indices(masks, stream, scratch, count, fill[, mirrored, capture]): indices of byte masks (a list) by the entries samo_count_flags_batched
+// and samo_fill_index_batched at the addresses `count` and `fill`; stream() is the handle of the stream to launch on, scratch(nbytes) a
+// uint8 tensor for the flag bits or None.  With `mirrored` (samo_count_flags_mirrored_batched) and `capture` (hipStreamIsCapturing) the
+// counts are polled instead of read back: a stream synchronisation and a copy between the two launches are 10 to 15 us.  Not on a
+// stream under capture: its graph may be launched after the page-locked counts have gone back to their cache.
 // A list of (idx, seg_ptr, nnz, n); a status other than SAMO_OK as an int; None where the
 // caller has to go another way: a mask is no plain tensor, or there is no scratch memory.
 PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
@@ -139,12 +140,14 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     HANDLE_TH_ERRORS
     typedef samo_status (*Entry)(const samo_index_job *, void *const *, int32_t, void *);
     typedef samo_status (*Mirrored)(const samo_index_job *, void *const *, int64_t *, int32_t, void *);
-    if (nargs < 5 || nargs > 6 || !PyList_Check(args[0]) || PyList_GET_SIZE(args[0]) == 0) {
-        PyErr_SetString(PyExc_TypeError, "build_indices(masks, stream, scratch, count, fill[, mirrored])");
+    if ((nargs != 5 && nargs != 7) || !PyList_Check(args[0]) || PyList_GET_SIZE(args[0]) == 0) {
+        PyErr_SetString(PyExc_TypeError, "build_indices(masks, stream, scratch, count, fill[, mirrored, capture])");
         return nullptr;
     }
     const Entry count = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[3])), fill = reinterpret_cast<Entry>(PyLong_AsVoidPtr(args[4]));
-    const Mirrored mirrored = reinterpret_cast<Mirrored>(nargs > 5 ? PyLong_AsVoidPtr(args[5]) : nullptr);
+    typedef int (*Capture)(void *, int *);
+    Mirrored mirrored = reinterpret_cast<Mirrored>(nargs > 5 ? PyLong_AsVoidPtr(args[5]) : nullptr);
+    const Capture capture = reinterpret_cast<Capture>(nargs > 5 ? PyLong_AsVoidPtr(args[6]) : nullptr);
     if (PyErr_Occurred()) return nullptr;
     const size_t k = (size_t)PyList_GET_SIZE(args[0]);
     std::vector<at::Tensor> masks(k), seg_ptrs(k), idxs(k);              // they hold the masks whatever happens to the list
@@ -165,6 +168,8 @@ PyObject *build_indices(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     if (!handle) return nullptr;
     void *stream = PyLong_AsVoidPtr(handle.get());
     if (PyErr_Occurred()) return nullptr;
+    int capturing = 1;
+    if (mirrored && (!capture || capture(stream, &capturing) != 0 || capturing != 0)) mirrored = nullptr;
     THPObjectPtr bytes(PyLong_FromLongLong(flag_bytes > 0 ? flag_bytes : 1));
     THPObjectPtr scratch(bytes ? PyObject_CallOneArg(args[2], bytes) : nullptr);
     if (!scratch) return nullptr;

@@ -1541,9 +1541,10 @@ static bool expand_global_access(const LaunchSet &ls)
 
 // A step under a guard follows the statistics of the gradient that it reads again: tiles taken from the last one back find the end of
 // it still in the last-level cache.  Long plans only, where most of it no longer is (us of statistics and step, forwards and
-// backwards: 350M model, 10 and 20 % kept 483 and 477, 649 and 640; 400 M elements, 15 % 748 and 734; 1.2 G, 10 % 1779 and 1762; 800 M level); what fits
-// the cache is found in either order and was slower backwards (85 M elements, 10 % 144.6 and 147.5), and so were models under 7 %.
-constexpr int64_t kBackwardsFrom = 45000;      // tiles: about 200 M elements
+// backwards: 190 M elements at 8 / 10 / 15 / 20 / 25 % kept 282 and 280, 310 and 302, 372 and 357, 418 and 406, 474 and 462, 230, 280, 340 and 420 M at the
+// same 1 to 4 % each; 1.2 G, 10 % 1779 and 1762; 800 M level); what fits the cache is found in either order and was slower
+// backwards (85 M elements, 10 % 144.6 and 147.5), and so were models under 7 %.  Between 85 and 190 M nothing was measured.
+constexpr int64_t kBackwardsFrom = 45000;      // tiles: 190 M elements at 10 % kept
 hipError_t launch_tile(int mode, int gsrc, int opt, const LaunchSet &ls_in, float inv_scale, const OptK &k,
                        const GuardK &guard, hipStream_t s)
 {

@@ -98,7 +98,8 @@ struct WgradBatch {
     WgradJob job[kWgradMaxJobs];
     int tiles_out[kWgradMaxJobs], tiles_in[kWgradMaxJobs];
     uint32_t per_group[kWgradMaxJobs];       // 2^32 / (tile rows of a group * tiles_in), rounded up
-    int first_tile[kWgradMaxJobs + 1];       // 32 bits: a layer of less than 2^31 elements, sides up to 2^24, has about 10^5 tiles at most
+    int first_tile[kWgradMaxJobs + 1];       // 32 bits: a layer of less than 2^31 elements, sides up to 2^24, has less than 2^18 tiles of 128 x 128
+                                             // (131072 of 8 x 2^24, 246000 of 136 x 15.7 M), a call less than 2^21; tile_origin's reciprocal takes up to 2^32
     int jobs;
     float inv_scale;
     int accumulate;
@@ -1077,7 +1078,7 @@ CallSize size_of(const WgradBatch &b)
     return c;
 }
 
-// Tiles of all jobs in a shape: less than 2^22 (8 layers of less than 2^31 elements, sides up to 2^24).
+// Tiles of all jobs in a shape: less than 2^21 (8 layers of less than 2^31 elements, sides up to 2^24, of 128 x 128 at least).
 int count_tiles(const WgradBatch &b, int rows, int cols)
 {
     int n = 0;

@@ -142,7 +142,7 @@ def test_a_launch_that_fails(fails):
     torch.cuda.synchronize()
     torch.cuda._sleep(50_000_000)                     # for longer than the host polls
     status = samo._marshal.build_indices(masks, samo._stream, samo._scratch, samo._entry_address("samo_count_flags_batched"),
-                                         samo._entry_address("samo_fill_index_batched"), address)
+                                         samo._entry_address("samo_fill_index_batched"), address, samo._entry_address("hipStreamIsCapturing"))
     assert status == samo.SAMO_ERR_HIP and len(seen) == fails + 1
     for counts, num_jobs in seen[:fails]:
         found = list((ctypes.c_int64 * num_jobs).from_address(counts))

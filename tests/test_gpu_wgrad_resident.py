@@ -68,8 +68,8 @@ def test_several_layers_one_of_them_without_tokens_or_index(resident):
 
 @pytest.mark.parametrize("tokens,out_f,in_f", [(70, 2600, 2248), (33, 4104, 4104), (1000, 3000, 3080)])
 def test_layers_on_either_side_of_the_rule(tokens, out_f, in_f):
-    """Short calls of more tiles than compute units (four to a unit, two rounds of them), and one long enough for tiles of 256 rows: in 64
-    bits on the GPU, within the bound of tokens fp32 additions."""
+    """Sizes on either side of the rule that gives short calls of more tiles than compute units four of them to a unit, in whatever shape
+    they are run: against 64 bits on the GPU, within the bound of tokens fp32 additions."""
     gen = torch.Generator(device=DEV).manual_seed(tokens)
     dy = torch.randn(tokens, out_f, generator=gen, device=DEV).half()
     x = torch.randn(tokens, in_f, generator=gen, device=DEV).half()
